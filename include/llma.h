@@ -139,9 +139,9 @@ int llma_find_trigger(const int32_t *y, int32_t y_len,
  *   result_dev int32[3] receives (matched, doc, pos): (1, doc, pos), (0, -1, -1) when nothing
  *   matches, or (LLMA_E_INVAL, -1, -1) when the kernel finds that doc_offsets does not start at 0,
  *   decreases somewhere or does not end at ref_len (the host cannot read device memory to check).
- * The one buffer the scan needs beyond inputs and outputs (the document index of every reference
- * position) is a static device array of LLMA_TRIGGER_STATIC_MAX_REF ints (4 MiB) that every GPU
- * the library runs on holds until the process ends; ref_len beyond it returns LLMA_E_RANGE (use
+ * The one buffer the scan needs beyond inputs and outputs (the best candidate of every 4096 reference
+ * positions) is a static device array of 2 KiB that every GPU the library runs on holds until the
+ * process ends; ref_len beyond LLMA_TRIGGER_STATIC_MAX_REF returns LLMA_E_RANGE (use
  * llma_find_trigger).  All calls on one GPU share that array: calls that overlap in time on
  * the same GPU (different streams or threads) race and must be serialised by the caller; calls
  * one after the other on a stream are fine (every entry a call reads it has written first).

@@ -36,13 +36,15 @@ struct StepState {            // device pointers describing the rows of the step
 struct GenState {             // device-resident state of llma_generate, one per sequence of the batch
     int *y; int *n_out; int *n_steps; int *trace;  // y[max_new], trace[max_new][4]
     int *cur;                            // [2] (doc, pos) of the trigger of the step in flight
-    const int *ref; const int *doc_offsets; const int *ref_doc; int ref_len, n_docs;
+    const int *ref; const int *doc_offsets; int ref_len, n_docs;
     int n, k, max_new;
     const int *prompt;                   // device copy of the prompt (prefill)
 };
 
 // rows of a verify step: row (b, j) = pending[slot_b] (j = 0) or draft[b][j-1]; pos = T[slot_b] + j
-void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, hipStream_t st);
+// generation steps (gen_dev set): the drafts are those of the best of part[b][0 .. spans), and keff / draft are filled
+void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, const GenState *gen_dev,
+                            const unsigned long long *part, int spans, hipStream_t st);
 // rows of a prefill chunk for one slot: tokens prompt[T[slot] - *base_dev + j], pos = T[slot] + j
 void launch_setup_prefill_rows(const StepState &s, const int *prompt_dev, const int *base_dev, int m, int slot,
                                const float *cs, int half, hipStream_t st);
@@ -57,10 +59,13 @@ void launch_rope_kv_f32(const float *qkv, const StepState &s, const float *cs_ta
 // final arg max over the per-row partials, then prefix accept + KV truncate + bookkeeping
 void launch_argmax_accept(const float *pval, const int *pidx, int n_part, const StepState &s, int n_seqs, int m,
                           int max_k, int vocab, const GenState *gen /*device array [n_seqs] or null*/, hipStream_t st);
-// trigger scan for each sequence being generated (gen_dev[b]); fills keff[b] / draft[b][:]
-void launch_trigger(const GenState *gen_dev, const StepState &s, int n_seqs, int max_k, hipStream_t st);
-// stateless trigger on device arrays (llma_find_trigger): result[0..2] = matched, doc, pos; with
-// check_offsets the kernel itself validates doc_offsets and reports (-1, -1, -1) for a bad list
-void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *doc_offsets, const int *ref_doc,
-                          int ref_len, int n_docs, int n, int *result, bool check_offsets, hipStream_t st);
-void launch_fill_ref_doc(const int *doc_offsets, int n_docs, int *ref_doc, int ref_len, hipStream_t st);
+// trigger: a reference is scanned in spans of TRIGGER_SPAN positions, one workgroup each
+#define TRIGGER_SPAN 4096
+static inline int trigger_spans(int ref_len) { return ref_len < 1 ? 1 : (ref_len - 1) / TRIGGER_SPAN + 1; }
+// for each sequence being generated: part[b][span] = the span's best key (0 = none).  spans: at least trigger_spans of
+// the longest reference
+void launch_trigger_scan(const GenState *gen_dev, int n_seqs, int spans, unsigned long long *part, hipStream_t st);
+// stateless trigger on device arrays (llma_find_trigger): result[0..2] = matched, doc, pos; part: scratch
+// [trigger_spans(ref_len)]; with check_offsets the kernel itself validates doc_offsets and reports (-1, -1, -1) for a bad list
+void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *doc_offsets, int ref_len, int n_docs, int n,
+                          unsigned long long *part, int *result, bool check_offsets, hipStream_t st);

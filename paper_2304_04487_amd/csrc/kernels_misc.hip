@@ -6,26 +6,201 @@
 #include "kernels.h"
 
 // ---------------------------------------------------------------------------------------------
+// trigger: scan of the reference for the n-token tail of y
+// ---------------------------------------------------------------------------------------------
+// Flat position p is a candidate when it lies at least n tokens into its document and the n
+// tokens before it equal the tail of y; its score is how far that agreement extends backwards
+// (bounded by the document start and by the start of y).  The best candidate maximises
+// (score, then smallest flat position) -- flat order is (document, position) order.
+//
+// What bounds it: one workgroup reads at the rate of its own loads in flight (600 011 tokens: 180 us = 13 GB/s),
+// so a reference is cut into spans of TRIGGER_SPAN positions, one workgroup each, 16 loads per thread in flight;
+// the spans' best keys are merged by whoever needs them (a maximum: the order does not matter).  Nearly every
+// position stops at the one-token test; a survivor is extended by its whole wave, 64 tokens per step, and only
+// survivors look their document up (binary search; it used to be a table filled by a kernel of its own).
+// A call over 600 011 tokens on the device: 245 -> 8.1 us; one span (the usual reference of a few documents) is one
+// launch (1472 host tokens: 44.3 -> 41.1 us, the rest is the copies).
+//
+// The document list may come from device memory the host cannot check: a start below 0 is taken as 0, so that no
+// list makes the backward walk leave the reference.
+__device__ __forceinline__ int doc_of(const int *doc_offsets, int n_docs, int p) {
+    int lo = 0, hi = n_docs;              // largest j with doc_offsets[j] <= p
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (doc_offsets[mid] <= p) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+__device__ __forceinline__ unsigned long long block_max(unsigned long long best) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        unsigned long long o = __shfl_xor(best, off);
+        best = o > best ? o : best;
+    }
+    __shared__ unsigned long long wbest[4];                     // (256 threads)
+    if ((threadIdx.x & 63) == 0) wbest[threadIdx.x >> 6] = best;
+    __syncthreads();
+    best = wbest[0];
+    for (int w = 1; w < 4; ++w) best = wbest[w] > best ? wbest[w] : best;
+    return best;
+}
+
+// best key (score << 32 | ~position) of the positions [p_lo, p_hi), p_hi - p_lo <= TRIGGER_SPAN; 256 threads
+__device__ __forceinline__ unsigned long long scan_span(const int *y, int i, const int *ref, const int *doc_offsets, int n_docs,
+                                                        int p_lo, int p_hi, int n) {
+    constexpr int U = TRIGGER_SPAN / 256;
+    unsigned long long best = 0ull;
+    if (i >= n && p_lo < p_hi) {                                // uniform
+        const int lane = threadIdx.x & 63;
+        const int last = y[i - 1];
+        int prev[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = p_lo + u * 256 + (int)threadIdx.x;
+            prev[u] = ref[p < 1 ? 0 : (p < p_hi ? p - 1 : p_hi - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = p_lo + u * 256 + (int)threadIdx.x;
+            unsigned long long hits = __ballot(p >= 1 && p < p_hi && prev[u] == last);
+            while (hits != 0ull) {                              // survivors, one after the other, each by the whole wave
+                const int src = __ffsll(hits) - 1;
+                hits &= hits - 1;
+                const int q = p - lane + src;
+                int start = doc_offsets[doc_of(doc_offsets, n_docs, q)];
+                start = start > 0 ? start : 0;
+                const int limit = q - start < i ? q - start : i;
+                int score = 0;
+                for (; score < limit; score += 64) {
+                    const int t = score + lane;
+                    const bool differs = t >= limit || ref[q - 1 - t] != y[i - 1 - t];
+                    const unsigned long long stop = __ballot(differs);
+                    if (stop != 0ull) { score += __ffsll(stop) - 1; break; }
+                }
+                if (score >= n) {
+                    const unsigned long long key = ((unsigned long long)score << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)q);
+                    best = key > best ? key : best;
+                }
+            }
+        }
+    }
+    return block_max(best);
+}
+__device__ __forceinline__ int key_position(unsigned long long key) { return (int)(0xFFFFFFFFu - (unsigned)(key & 0xFFFFFFFFull)); }
+
+// llma_generate: grid (spans of the longest reference, sequences); part[sequence][span] = the span's best key
+__global__ __launch_bounds__(256) void trigger_scan_kernel(const GenState *gp, unsigned long long *part) {
+    const GenState G = gp[blockIdx.y];
+    const int i = *G.n_out;
+    const long first = (long)blockIdx.x * TRIGGER_SPAN;         // (the grid may be larger than this sequence's reference)
+    const int p_lo = first < G.ref_len ? (int)first : G.ref_len;
+    int p_hi = G.ref_len - p_lo > TRIGGER_SPAN ? p_lo + TRIGGER_SPAN : G.ref_len;
+    if (G.k <= 0 || i >= G.max_new) p_hi = p_lo;
+    const unsigned long long best = scan_span(G.y, i, G.ref, G.doc_offsets, G.n_docs, p_lo, p_hi, G.n);
+    if (threadIdx.x == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = best;
+}
+void launch_trigger_scan(const GenState *gen_dev, int n_seqs, int spans, unsigned long long *part, hipStream_t st) {
+    hipLaunchKernelGGL(trigger_scan_kernel, dim3(spans, n_seqs), dim3(256), 0, st, gen_dev, part);
+}
+
+// check_offsets (callers whose document list lives in device memory, where the host cannot look):
+// the list must start at 0, never decrease and end at ref_len; otherwise result = (-1, -1, -1).  Every
+// workgroup checks a share of the list; a fault is the largest of all keys.
+#define TRIGGER_BAD_LIST (~0ull)
+__device__ __forceinline__ void trigger_write_result(unsigned long long best, const int *doc_offsets, int n_docs, int *result) {
+    if (best == TRIGGER_BAD_LIST) { result[0] = -1; result[1] = -1; result[2] = -1; return; }
+    if (best == 0ull) { result[0] = 0; result[1] = -1; result[2] = -1; return; }
+    const int p = key_position(best), doc = doc_of(doc_offsets, n_docs, p);
+    result[0] = 1; result[1] = doc; result[2] = p - doc_offsets[doc];
+}
+__global__ __launch_bounds__(256) void trigger_plain_kernel(const int *y, int y_len, const int *ref, const int *doc_offsets, int ref_len,
+                                                            int n_docs, int n, unsigned long long *part, int *result, int check_offsets) {
+    if (ref_len <= 0 || n_docs <= 0) {
+        if (threadIdx.x == 0) { result[0] = 0; result[1] = -1; result[2] = -1; }
+        return;
+    }
+    int bad = 0;
+    if (check_offsets) {
+        for (int j = blockIdx.x * 256 + threadIdx.x; j < n_docs; j += gridDim.x * 256) bad |= doc_offsets[j + 1] < doc_offsets[j];
+        if (blockIdx.x == 0 && threadIdx.x == 0) bad |= (doc_offsets[0] != 0) | (doc_offsets[n_docs] != ref_len);
+    }
+    const int p_lo = (int)blockIdx.x * TRIGGER_SPAN;
+    const int p_hi = ref_len - p_lo > TRIGGER_SPAN ? p_lo + TRIGGER_SPAN : ref_len;
+    unsigned long long best = scan_span(y, y_len, ref, doc_offsets, n_docs, p_lo, p_hi, n);
+    if (check_offsets && __syncthreads_or(bad)) best = TRIGGER_BAD_LIST;
+    if (threadIdx.x != 0) return;
+    if (gridDim.x == 1) trigger_write_result(best, doc_offsets, n_docs, result);
+    else part[blockIdx.x] = best;
+}
+__global__ __launch_bounds__(256) void trigger_plain_merge_kernel(const unsigned long long *part, int spans, const int *doc_offsets, int n_docs, int *result) {
+    unsigned long long best = 0ull;
+    for (int t = threadIdx.x; t < spans; t += 256) {
+        const unsigned long long o = part[t];
+        best = o > best ? o : best;
+    }
+    best = block_max(best);
+    if (threadIdx.x == 0) trigger_write_result(best, doc_offsets, n_docs, result);
+}
+void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *doc_offsets, int ref_len, int n_docs, int n,
+                          unsigned long long *part, int *result, bool check_offsets, hipStream_t st) {
+    const int spans = (ref_len <= 0 || n_docs <= 0) ? 1 : trigger_spans(ref_len);
+    hipLaunchKernelGGL(trigger_plain_kernel, dim3(spans), dim3(256), 0, st, y, y_len, ref, doc_offsets, ref_len, n_docs, n, part, result,
+                       check_offsets ? 1 : 0);
+    if (spans > 1) hipLaunchKernelGGL(trigger_plain_merge_kernel, dim3(1), dim3(256), 0, st, part, spans, doc_offsets, n_docs, result);
+}
+
+// ---------------------------------------------------------------------------------------------
 // row set-up
 // ---------------------------------------------------------------------------------------------
-// one workgroup per row; also copies the row's rotary (cos, sin) pairs out of the position table
-__global__ void setup_step_rows_kernel(StepState s, int m, int max_k, const float *cs, int half) {
+// one workgroup per row; also copies the row's rotary (cos, sin) pairs out of the position table.
+// Generation steps (gp set): the spans' trigger keys are merged here, by every row's workgroup for itself (a
+// handful of loads, instead of a launch between the scan and this one); the first row's publishes keff, the
+// drafts and the trigger's place.
+__global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m, int max_k, const float *cs, int half,
+                                                              const GenState *gp, const unsigned long long *part, int spans) {
     const int idx = blockIdx.x;
     const int b = idx / m, j = idx % m;
     const int slot = s.batch_slots[b];
     const int pos = s.T[slot] + j;
+    for (int i = threadIdx.x; i < 2 * half; i += 256) s.row_cs[(size_t)idx * 2 * half + i] = cs[(size_t)pos * 2 * half + i];
+    int keff, tok = s.pending[slot];
+    if (gp != nullptr) {
+        const GenState G = gp[b];
+        unsigned long long best = 0ull;
+        for (int t = threadIdx.x; t < spans; t += 256) {
+            const unsigned long long o = part[(size_t)b * spans + t];
+            best = o > best ? o : best;
+        }
+        best = block_max(best);
+        keff = 0;
+        if (best != 0ull) {
+            const int p = key_position(best), doc = doc_of(G.doc_offsets, G.n_docs, p);
+            const int left_in_doc = G.doc_offsets[doc + 1] - p;
+            const int budget = G.max_new - *G.n_out - 1;
+            keff = G.k < left_in_doc ? G.k : left_in_doc;
+            keff = keff < budget ? keff : budget;
+            keff = keff < 0 ? 0 : keff;
+            if (j > 0 && j <= keff) tok = G.ref[p + j - 1];
+            if (j == 0) {
+                if (threadIdx.x == 0) { G.cur[0] = doc; G.cur[1] = p - G.doc_offsets[doc]; }
+                for (int t = threadIdx.x; t < keff; t += 256) s.draft[b * max_k + t] = G.ref[p + t];
+            }
+        }
+        if (j == 0 && threadIdx.x == 0) s.keff[b] = keff;
+    } else {
+        keff = s.keff[b];
+        if (j > 0 && j <= keff) tok = s.draft[b * max_k + j - 1];
+    }
     if (threadIdx.x == 0) {
-        int tok;
-        if (j == 0) tok = s.pending[slot];
-        else tok = (j - 1 < s.keff[b]) ? s.draft[b * max_k + j - 1] : 0;   // rows past keff are padding
-        s.row_tok[idx] = tok;
+        s.row_tok[idx] = j <= keff ? tok : 0;                     // rows past keff are padding
         s.row_pos[idx] = pos;
         s.row_slot[idx] = slot;
     }
-    for (int i = threadIdx.x; i < 2 * half; i += blockDim.x) s.row_cs[(size_t)idx * 2 * half + i] = cs[(size_t)pos * 2 * half + i];
 }
-void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, hipStream_t st) {
-    hipLaunchKernelGGL(setup_step_rows_kernel, dim3(n_seqs * m), dim3(64), 0, st, s, m, max_k, cs, half);
+void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, const GenState *gen_dev,
+                            const unsigned long long *part, int spans, hipStream_t st) {
+    hipLaunchKernelGGL(setup_step_rows_kernel, dim3(n_seqs * m), dim3(256), 0, st, s, m, max_k, cs, half, gen_dev, part, spans);
 }
 
 __global__ void setup_prefill_rows_kernel(StepState s, const int *prompt, const int *base, int slot, const float *cs, int half) {
@@ -176,130 +351,4 @@ __global__ __launch_bounds__(256) void argmax_accept_kernel(const float *__restr
 void launch_argmax_accept(const float *pval, const int *pidx, int n_part, const StepState &s, int n_seqs, int m,
                           int max_k, int vocab, const GenState *gen, hipStream_t st) {
     hipLaunchKernelGGL(argmax_accept_kernel, dim3(n_seqs), dim3(256), 0, st, pval, pidx, n_part, s, m, max_k, vocab, gen);
-}
-
-// ---------------------------------------------------------------------------------------------
-// trigger: wavefront-parallel scan of the reference for the n-token tail of y
-// ---------------------------------------------------------------------------------------------
-// Flat position p is a candidate when it lies at least n tokens into its document and the n
-// tokens before it equal the tail of y; its score is how far that agreement extends backwards
-// (bounded by the document start and by the start of y).  The best candidate maximises
-// (score, then smallest flat position) -- flat order is (document, position) order.
-__device__ __forceinline__ unsigned long long scan_reference(const int *y, int i, const int *ref, const int *doc_offsets,
-                                                             const int *ref_doc, int ref_len, int n) {
-    unsigned long long best = 0ull;
-    if (i >= n) {
-        // first pass, eight positions per thread in flight: does the token before p equal the last
-        // token of y?  (necessary for a match; nearly all positions stop here)
-        const int last = y[i - 1];
-        for (int p0 = threadIdx.x; p0 < ref_len; p0 += blockDim.x * 8) {
-            int prev[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = p0 + u * blockDim.x;
-                prev[u] = (p >= 1 && p < ref_len) ? ref[p - 1] : -1;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = p0 + u * blockDim.x;
-                if (prev[u] != last || p >= ref_len) continue;      // (token ids are >= 0)
-                const int pos = p - doc_offsets[ref_doc[p]];
-                if (pos < n) continue;
-                bool ok = true;
-                for (int t = 1; t < n; ++t)
-                    if (ref[p - 1 - t] != y[i - 1 - t]) { ok = false; break; }
-                if (!ok) continue;
-                int score = n;
-                while (score < pos && score < i && ref[p - 1 - score] == y[i - 1 - score]) ++score;
-                unsigned long long key = ((unsigned long long)score << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)p);
-                best = key > best ? key : best;
-            }
-        }
-    }
-    // wave, then workgroup maximum
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        unsigned long long o = __shfl_xor(best, off);
-        best = o > best ? o : best;
-    }
-    __shared__ unsigned long long wbest[16];
-    if ((threadIdx.x & 63) == 0) wbest[threadIdx.x >> 6] = best;
-    __syncthreads();
-    const int waves = blockDim.x >> 6;
-    best = wbest[0];
-    for (int w = 1; w < waves; ++w) best = wbest[w] > best ? wbest[w] : best;
-    return best;
-}
-
-__global__ __launch_bounds__(256) void trigger_kernel(const GenState *gp, StepState s, int max_k) {
-    const int b = blockIdx.x;                                    // one workgroup per sequence of the batch
-    const GenState G = gp[b];
-    const int i = *G.n_out;
-    unsigned long long best = 0ull;
-    if (G.ref_len > 0 && G.k > 0 && i < G.max_new)
-        best = scan_reference(G.y, i, G.ref, G.doc_offsets, G.ref_doc, G.ref_len, G.n);
-    int keff = 0, p = 0;
-    if (best != 0ull) {
-        p = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));
-        const int doc = G.ref_doc[p];
-        const int left_in_doc = G.doc_offsets[doc + 1] - p;
-        const int budget = G.max_new - i - 1;
-        keff = G.k < left_in_doc ? G.k : left_in_doc;
-        keff = keff < budget ? keff : budget;
-        keff = keff < 0 ? 0 : keff;
-        if (threadIdx.x == 0) { G.cur[0] = doc; G.cur[1] = p - G.doc_offsets[doc]; }
-    }
-    if (threadIdx.x == 0) s.keff[b] = keff;
-    for (int j = threadIdx.x; j < keff; j += blockDim.x) s.draft[b * max_k + j] = G.ref[p + j];
-}
-void launch_trigger(const GenState *gen_dev, const StepState &s, int n_seqs, int max_k, hipStream_t st) {
-    hipLaunchKernelGGL(trigger_kernel, dim3(n_seqs), dim3(256), 0, st, gen_dev, s, max_k);
-}
-
-// check_offsets (callers whose document list lives in device memory, where the host cannot look):
-// the list must start at 0, never decrease and end at ref_len; otherwise result = (-1, -1, -1) and
-// nothing is scanned (the scan's backward walk relies on positions inside their documents).
-__global__ __launch_bounds__(256) void trigger_plain_kernel(const int *y, int y_len, const int *ref, const int *doc_offsets,
-                                                            const int *ref_doc, int ref_len, int n_docs, int n, int *result,
-                                                            int check_offsets) {
-    if (ref_len <= 0 || n_docs <= 0) {
-        if (threadIdx.x == 0) { result[0] = 0; result[1] = -1; result[2] = -1; }
-        return;
-    }
-    if (check_offsets) {
-        int bad = 0;
-        for (int j = threadIdx.x; j < n_docs; j += blockDim.x) bad |= doc_offsets[j + 1] < doc_offsets[j];
-        if (threadIdx.x == 0) bad |= (doc_offsets[0] != 0) | (doc_offsets[n_docs] != ref_len);
-        if (__syncthreads_or(bad)) {
-            if (threadIdx.x == 0) { result[0] = -1; result[1] = -1; result[2] = -1; }
-            return;
-        }
-    }
-    unsigned long long best = scan_reference(y, y_len, ref, doc_offsets, ref_doc, ref_len, n);
-    if (threadIdx.x != 0) return;
-    if (best == 0ull) { result[0] = 0; result[1] = -1; result[2] = -1; return; }
-    int p = (int)(0xFFFFFFFFu - (unsigned)(best & 0xFFFFFFFFull));
-    int doc = ref_doc[p];
-    result[0] = 1; result[1] = doc; result[2] = p - doc_offsets[doc];
-}
-void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *doc_offsets, const int *ref_doc,
-                          int ref_len, int n_docs, int n, int *result, bool check_offsets, hipStream_t st) {
-    hipLaunchKernelGGL(trigger_plain_kernel, dim3(1), dim3(256), 0, st, y, y_len, ref, doc_offsets, ref_doc, ref_len, n_docs, n,
-                       result, check_offsets ? 1 : 0);
-}
-
-// ref_doc[p] = the document that contains flat position p (doc_offsets non-decreasing)
-__global__ void fill_ref_doc_kernel(const int *doc_offsets, int n_docs, int *ref_doc, int ref_len) {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= ref_len) return;
-    int lo = 0, hi = n_docs;              // largest j with doc_offsets[j] <= p
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (doc_offsets[mid] <= p) lo = mid; else hi = mid;
-    }
-    ref_doc[p] = lo;
-}
-void launch_fill_ref_doc(const int *doc_offsets, int n_docs, int *ref_doc, int ref_len, hipStream_t st) {
-    if (ref_len <= 0) return;
-    hipLaunchKernelGGL(fill_ref_doc_kernel, dim3((ref_len + 255) / 256), dim3(256), 0, st, doc_offsets, n_docs, ref_doc, ref_len);
 }

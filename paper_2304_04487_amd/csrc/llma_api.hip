@@ -28,8 +28,8 @@ struct EventPair { hipEvent_t a, b; };
 
 enum StepKind { STEP_PREFILL = 0, STEP_VERIFY = 1, STEP_GEN = 2 };
 
-// what a captured step graph was recorded for: (kind, sequences, rows per sequence, attention chunks, slot)
-typedef std::array<int, 5> GraphKey;
+// what a captured step graph was recorded for: (kind, sequences, rows per sequence, attention chunks, slot, trigger spans)
+typedef std::array<int, 6> GraphKey;
 struct GraphSlot { int seen = 0; hipGraphExec_t exec = nullptr; };
 
 struct llma_ctx {
@@ -75,10 +75,12 @@ struct llma_ctx {
 
     StepState s{};
     GenState *gen_dev = nullptr;
-    int *gen_prompt = nullptr, *gen_ref = nullptr, *gen_doc_offsets = nullptr, *gen_ref_doc = nullptr;
+    int *gen_prompt = nullptr, *gen_ref = nullptr, *gen_doc_offsets = nullptr;
+    int *gen_part = nullptr;                      // the trigger's keys, [sequence of the batch][gen_spans] 64-bit words
+    int gen_spans = 1;                            // spans the trigger scans per sequence in the current generation
     int *gen_y = nullptr, *gen_trace = nullptr;   // [sequence of the batch][max_new + 64] tokens, x 4 trace words
     int *gen_counters = nullptr;                  // n_out[max_batch], n_steps[max_batch], cur[max_batch][2], prefill base
-    int cap_prompt = 0, cap_ref = 0, cap_refdoc = 0, cap_docs = 0, cap_y = 0, cap_trace = 0;
+    int cap_prompt = 0, cap_ref = 0, cap_part = 0, cap_docs = 0, cap_y = 0, cap_trace = 0;
 
     std::vector<int> T_host, pending_host;
     // Caches imported as bf16 values have all-zero lo planes: positions below lo_from[slot] (device
@@ -618,11 +620,13 @@ static int step_body(llma_ctx *c, int kind, int n_seqs, int m, int n_chunks, int
         return LLMA_OK;
     }
     c->rows_live = (kind == STEP_GEN && n_seqs == 1) ? c->s.keff : nullptr;
-    if (kind == STEP_GEN) launch_trigger(c->gen_dev, c->s, n_seqs, mk, st);
-    launch_setup_step_rows(c->s, n_seqs, m, mk, c->cs_table, c->cfg.head_dim / 2, st);
+    const GenState *gen = kind == STEP_GEN ? c->gen_dev : nullptr;
+    unsigned long long *part = (unsigned long long *)c->gen_part;
+    if (gen) launch_trigger_scan(gen, n_seqs, c->gen_spans, part, st);
+    launch_setup_step_rows(c->s, n_seqs, m, mk, c->cs_table, c->cfg.head_dim / 2, gen, part, c->gen_spans, st);
     int rc = forward(c, n_seqs, m, n_chunks, true, slot);
     if (rc) return rc;
-    launch_argmax_accept(c->pval, c->pidx, c->n_part, c->s, n_seqs, m, mk, c->cfg.vocab, kind == STEP_GEN ? c->gen_dev : nullptr, st);
+    launch_argmax_accept(c->pval, c->pidx, c->n_part, c->s, n_seqs, m, mk, c->cfg.vocab, gen, st);
     return LLMA_OK;
 }
 
@@ -643,7 +647,7 @@ static int run_step(llma_ctx *c, int kind, int n_seqs, int m, int t_max, int slo
     if (c->bf16 && n_chunks > c->nc_max) n_chunks = c->nc_max;
     c->run_st = c->st;
     if (!c->opt_graph || c->opt_timing || c->graphs.size() > 256) return step_body(c, kind, n_seqs, m, n_chunks, slot);
-    const GraphKey key = {kind, n_seqs, m, n_chunks, slot};     // every field that shapes a launch or is baked into one
+    const GraphKey key = {kind, n_seqs, m, n_chunks, slot, kind == STEP_GEN ? c->gen_spans : 0};     // every field that shapes a launch or is baked into one
     GraphSlot &gs = c->graphs[key];
     if (gs.exec == nullptr) {
         if (gs.seen++ == 0) return step_body(c, kind, n_seqs, m, n_chunks, slot);   // first time eagerly
@@ -814,21 +818,21 @@ extern "C" int llma_find_trigger(const int32_t *y, int32_t y_len, const int32_t 
     const int ref_len = n_docs > 0 ? doc_offsets[n_docs] : 0;
     if (ref_len > 0 && !ref) return fail(nullptr, LLMA_E_INVAL, "llma_find_trigger: null reference");
     if (ref_len == 0 || y_len < n) return 0;
-    // device scratch for this call: [y | ref | doc_offsets | result(4)] copied in at once, then ref_doc
+    // device scratch for this call: [y | ref | doc_offsets | result(4)] copied in at once, then the spans' keys (64 bits each)
     const size_t n_in = (size_t)y_len + (size_t)ref_len + (size_t)(n_docs + 1) + 4;
     std::vector<int> stage(n_in);
     memcpy(stage.data(), y, (size_t)y_len * 4);
     memcpy(stage.data() + y_len, ref, (size_t)ref_len * 4);
     memcpy(stage.data() + y_len + ref_len, doc_offsets, (size_t)(n_docs + 1) * 4);
     int *buf = nullptr;
-    hipError_t e = hipMalloc((void **)&buf, (n_in + (size_t)ref_len) * 4);
+    hipError_t e = hipMalloc((void **)&buf, (n_in + 1) / 2 * 8 + (size_t)trigger_spans(ref_len) * 8);
     if (e != hipSuccess) return fail(nullptr, LLMA_E_NOMEM, "llma_find_trigger: hipMalloc: %s", hipGetErrorString(e));
-    int *dy = buf, *dref = dy + y_len, *doff = dref + ref_len, *dres = doff + n_docs + 1, *ddoc = dres + 4;
+    int *dy = buf, *dref = dy + y_len, *doff = dref + ref_len, *dres = doff + n_docs + 1;
+    unsigned long long *part = (unsigned long long *)buf + (n_in + 1) / 2;
     int res[3] = {0, -1, -1};
     e = hipMemcpy(buf, stage.data(), n_in * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) {
-        launch_fill_ref_doc(doff, n_docs, ddoc, ref_len, nullptr);
-        launch_trigger_plain(dy, y_len, dref, doff, ddoc, ref_len, n_docs, n, dres, false, nullptr);
+        launch_trigger_plain(dy, y_len, dref, doff, ref_len, n_docs, n, part, dres, false, nullptr);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpy(res, dres, 12, hipMemcpyDeviceToHost);
@@ -953,7 +957,12 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
     const int ystride = max_new + 64;                       // per-sequence output / trace rows on the device
     if ((rc = ensure_cap(c, &c->gen_prompt, &c->cap_prompt, max_prompt))) return rc;
     if ((rc = ensure_cap(c, &c->gen_ref, &c->cap_ref, total_ref))) return rc;
-    if ((rc = ensure_cap(c, &c->gen_ref_doc, &c->cap_refdoc, total_ref))) return rc;
+    // spans the trigger scans per sequence: enough for the longest reference, a power of two (few distinct launch shapes)
+    int max_ref = 0, spans = 1;
+    for (int b = 0; b < n_seqs; ++b) max_ref = ref_start[b + 1] - ref_start[b] > max_ref ? ref_start[b + 1] - ref_start[b] : max_ref;
+    while (spans < trigger_spans(max_ref)) spans *= 2;
+    c->gen_spans = spans;
+    if ((rc = ensure_cap(c, &c->gen_part, &c->cap_part, 2 * n_seqs * spans))) return rc;
     if ((rc = ensure_cap(c, &c->gen_doc_offsets, &c->cap_docs, docs_start[n_seqs] + n_seqs))) return rc;
     if ((rc = ensure_cap(c, &c->gen_y, &c->cap_y, n_seqs * ystride))) return rc;
     if ((rc = ensure_cap(c, &c->gen_trace, &c->cap_trace, 4 * n_seqs * ystride))) return rc;
@@ -972,11 +981,10 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
     int *const cnt_out = c->gen_counters, *const cnt_steps = c->gen_counters + g.max_batch, *const cnt_cur = c->gen_counters + 2 * g.max_batch;
     for (int b = 0; b < n_seqs; ++b) {
         const int nd = n_docs ? n_docs[b] : 0, rlen = ref_start[b + 1] - ref_start[b];
-        if (rlen) launch_fill_ref_doc(c->gen_doc_offsets + dof_at[b], nd, c->gen_ref_doc + ref_start[b], rlen, st);
         GenState &s = G[b];
         s.y = c->gen_y + (size_t)b * ystride; s.trace = c->gen_trace + (size_t)4 * b * ystride;
         s.n_out = cnt_out + b; s.n_steps = cnt_steps + b; s.cur = cnt_cur + 2 * b;
-        s.ref = c->gen_ref + ref_start[b]; s.doc_offsets = c->gen_doc_offsets + dof_at[b]; s.ref_doc = c->gen_ref_doc + ref_start[b];
+        s.ref = c->gen_ref + ref_start[b]; s.doc_offsets = c->gen_doc_offsets + dof_at[b];
         s.ref_len = rlen; s.n_docs = nd; s.n = n; s.k = k; s.max_new = max_new; s.prompt = c->gen_prompt;
     }
     HIP_TRY(c, hipMemcpyAsync(c->gen_dev, G.data(), sizeof(GenState) * n_seqs, hipMemcpyHostToDevice, st));
