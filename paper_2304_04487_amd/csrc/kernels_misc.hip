@@ -290,32 +290,43 @@ void launch_rope_kv_f32(const float *qkv, const StepState &s, const float *cs_ta
 // o_i == draft_i; the step emits o_0..o_a, the cache keeps the rows of the pending token and
 // of the a accepted drafts (T += a + 1; rows beyond are overwritten by the next step), and
 // o_a becomes the pending token.
-__global__ __launch_bounds__(256) void argmax_accept_kernel(const float *__restrict__ pval, const int *__restrict__ pidx,
-                                                            int n_part, StepState s, int m, int max_k, int vocab, const GenState *gen) {
+// Bound by latency: a row is 2000 partials (16 KB) at vocabulary 32000, and the decision is a chain of small reads.
+// Sixteen waves take a row each (33 rows: three rounds), 16 partials per lane in flight, requested before the draft
+// count is known; the drafts are compared by 33 lanes at once instead of one thread walking them (that walk was a
+// read per draft, one after the other).  17 rows 23.5 -> 8.3 us, 33 rows 40.8 -> 11.9 us, one row 5.6 -> 4.6 us.
+#define ACCEPT_THREADS 1024
+__global__ __launch_bounds__(ACCEPT_THREADS) void argmax_accept_kernel(const float *__restrict__ pval, const int *__restrict__ pidx,
+                                                                       int n_part, StepState s, int m, int max_k, int vocab, const GenState *gen) {
+    constexpr int U = 16, WAVES = ACCEPT_THREADS / 64;
     __shared__ int o[40];
     const int b = blockIdx.x;
-    if (gen != nullptr) gen += b;                                // llma_generate: one GenState per sequence of the batch
-    if (gen != nullptr && *gen->n_out >= gen->max_new) return;   // a finished sequence / a step enqueued past the end: leave all state alone
-    const int keff = s.keff[b];
-    // one row per wave at a time: wave w reduces rows w, w + 4, ... over the per-tile partials
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int j = wave; j <= keff; j += 4) {
+    if (gen != nullptr) gen += b;                                // llma_generate: one GenState per sequence of the batch
+    const int keff = s.keff[b];
+    const int slot = s.batch_slots[b];
+    int n_out = 0;
+    if (gen != nullptr) n_out = *gen->n_out;
+    // one row per wave at a time: wave w reduces rows w, w + 16, ... over the per-tile partials (rows past keff are
+    // rows of the step too: their partials exist, what they say is dropped)
+    for (int j = wave; j < m; j += WAVES) {
         const size_t r = (size_t)b * m + j;
         float bv = LLMA_NEG_INF;
         int bi = 0x7fffffff;
-        for (int t0 = lane; t0 < n_part; t0 += 64 * 8) {      // 8 partials per lane in flight
-            float v[8];
-            int id[8];
+        for (int t0 = lane; t0 < n_part; t0 += 64 * U) {
+            float v[U];
+            int id[U];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int t = t0 + 64 * u;
-                v[u] = t < n_part ? pval[r * n_part + t] : LLMA_NEG_INF;
-                id[u] = t < n_part ? pidx[r * n_part + t] : 0x7fffffff;
+            for (int u = 0; u < U; ++u) {
+                const int t = t0 + 64 * u < n_part ? t0 + 64 * u : lane;        // (a partial read twice changes nothing)
+                v[u] = pval[r * n_part + t];
+                id[u] = pidx[r * n_part + t];
             }
+            if (j > keff) break;                                 // uniform; padding (the count arrived with the first partials)
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+            for (int u = 0; u < U; ++u)
                 if (v[u] > bv || (v[u] == bv && id[u] < bi)) { bv = v[u]; bi = id[u]; }
         }
+        if (j > keff) break;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
             float ov = __shfl_xor(bv, off);
@@ -325,30 +336,34 @@ __global__ __launch_bounds__(256) void argmax_accept_kernel(const float *__restr
         // a row without any comparable logit (all NaN: reachable through imported caches or weights that
         // hold non-finite values) must still yield a token id the next step's embedding gather can use
         if ((unsigned)bi >= (unsigned)vocab) bi = 0;
-        if (lane == 0) { o[j] = bi; s.otok[r] = bi; }
+        if (lane == 0) o[j] = bi;
     }
+    // the first wave decides: lane j compares draft j
+    const int draft = wave == 0 && lane < keff ? s.draft[b * max_k + lane] : -1;
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    int a = 0;
-    while (a < keff && o[a] == s.draft[b * max_k + a]) ++a;
-    const int slot = s.batch_slots[b];
+    if (wave != 0) return;
+    if (gen != nullptr && n_out >= gen->max_new) return;         // a finished sequence / a step enqueued past the end: leave all state alone
+    const unsigned long long same = __ballot(lane < keff && o[lane < keff ? lane : 0] == draft);
+    const int a = __ffsll(~same) - 1;                            // (lane keff <= 32 never agrees)
+    if (lane <= keff) s.otok[(size_t)b * m + lane] = o[lane];
+    if (lane <= a) s.emit[b * (max_k + 1) + lane] = o[lane];
+    if (gen != nullptr && lane <= a) gen->y[n_out + lane] = o[lane];
+    if (lane != 0) return;
     s.nacc[b] = a;
     s.next[b] = o[a];
-    for (int j = 0; j <= a; ++j) s.emit[b * (max_k + 1) + j] = o[j];
     s.T[slot] += a + 1;
     s.pending[slot] = o[a];
     if (gen != nullptr) {
-        int i = *gen->n_out, st = *gen->n_steps;
-        for (int j = 0; j <= a; ++j) gen->y[i + j] = o[j];
+        const int st = *gen->n_steps;
         gen->trace[st * 4 + 0] = 1 + keff;
         gen->trace[st * 4 + 1] = a + 1;
         gen->trace[st * 4 + 2] = keff > 0 ? gen->cur[0] : -1;
         gen->trace[st * 4 + 3] = keff > 0 ? gen->cur[1] : -1;
-        *gen->n_out = i + a + 1;
+        *gen->n_out = n_out + a + 1;
         *gen->n_steps = st + 1;
     }
 }
 void launch_argmax_accept(const float *pval, const int *pidx, int n_part, const StepState &s, int n_seqs, int m,
                           int max_k, int vocab, const GenState *gen, hipStream_t st) {
-    hipLaunchKernelGGL(argmax_accept_kernel, dim3(n_seqs), dim3(256), 0, st, pval, pidx, n_part, s, m, max_k, vocab, gen);
+    hipLaunchKernelGGL(argmax_accept_kernel, dim3(n_seqs), dim3(ACCEPT_THREADS), 0, st, pval, pidx, n_part, s, m, max_k, vocab, gen);
 }
