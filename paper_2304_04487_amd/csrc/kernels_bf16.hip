@@ -302,28 +302,54 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
     }
 }
 
+// 16 bytes per lane through a buffer descriptor: base and size are wave-uniform, an offset past the size reads zeros
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+#define BUFFER_NOWHERE 0x40000000u     // past the end of every buffer here (all below 1 GiB), also with an offset inside one added
+__device__ __forceinline__ rsrc_t buffer_of(const void *p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)bytes, 0x00027000);
+}
+template <bool NON_TEMPORAL>
+__device__ __forceinline__ u32x4 buffer_load16(rsrc_t r, unsigned off) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, NON_TEMPORAL ? 2 : 0);
+}
+
+// the arguments as seen from row r0 (a multiple of 16) on
+__device__ __forceinline__ void offset_rows(GemmArgs &a, const GemmPlan &p, int r0) {
+    const int t0 = r0 / 16;
+    a.rows = a.rows - r0;
+    if (a.out) a.out += (size_t)r0 * p.N;
+    if (a.nx_hi) { a.nx_hi = (bf16_t *)a.nx_hi + (size_t)t0 * a.nx_KSp * 512; a.nx_lo = (bf16_t *)a.nx_lo + (size_t)t0 * a.nx_KSp * 512; }
+    if (a.ssq_out) a.ssq_out += (size_t)r0 * (p.N / 16);
+    if (a.act_hi) { a.act_hi = (bf16_t *)a.act_hi + (size_t)t0 * a.act_KSp * 512; a.act_lo = (bf16_t *)a.act_lo + (size_t)t0 * a.act_KSp * 512; }
+    if (a.pval) { a.pval += (size_t)r0 * a.n_part; a.pidx += (size_t)r0 * a.n_part; }
+    if (a.row_pos) { a.row_pos += r0; a.row_slot += r0; a.row_cs += (size_t)r0 * a.dh; }
+    if (a.q_hi) { a.q_hi = (bf16_t *)a.q_hi + (size_t)t0 * (a.H * a.dh / 32) * 512; a.q_lo = (bf16_t *)a.q_lo + (size_t)t0 * (a.H * a.dh / 32) * 512; }
+}
+
 // ---------------------------------------------------------------------------------------------
 // tile-K kernel (decoding steps): one workgroup per FT consecutive feature tiles, its waves split
 // the K axis; each wave streams its weight blocks from HBM with non-temporal 1 KiB loads, the
 // next batch in flight while the current one feeds the MFMAs; B operands come straight from the
 // tiled activation planes (1 KiB contiguous per k-step and plane, shared through L2 by all
-// workgroups); the waves' partial sums meet in LDS and are added in wave order; the first FT
-// waves run the fused epilogue.  FT and the number of K slices depend on the matrix shape only, so
-// the order of every sum is the same for any number of rows; with several feature tiles AND several
-// row tiles (more than four tile pairs in all) a wave takes two K slices one after the other (half the
-// waves, twice the registers).
+// workgroups); the waves' partial sums meet in LDS and are added in slice order; the waves share the
+// (feature tile, row tile) pairs of the fused epilogue.  The number of K slices depends on the matrix shape only, so
+// the order of every sum is the same for any number of rows and any FT.  With 16 slices and more than one row tile a
+// wave takes two slices one after the other (half the waves, twice the registers).
+// Bound by the weight stream at one row; with more rows by the activations, which every workgroup reads: see
+// tilek_ft_default.  Per layer of 7B, back to back: 75 us at one row (405 MB), 80 at 9 (84 before three gate/up pairs
+// shared a workgroup), 98 at 17 (108), 122 at 33 (147).  13B at 33 rows 229 -> 201 us: eight waves instead of four
+// for O and down (28 -> 23, 64 -> 53 us).
+// A ring of single k-steps with every load unconditional (zeros past the slice) was slower: the blocks of a
+// tile are best requested several in a row (O 10.4 us in ones, 9.1 in fours, 8.7 with the requests past the end left out).
 // ---------------------------------------------------------------------------------------------
 #ifndef TK_TRACE
 #define TK_TRACE(slot)      // (timeline probe of the one-off microbenchmarks; nothing in the library build)
 #endif
-template <int NT, int FT>
-struct TileKShape {
-    static constexpr int SL = (FT > 1 && NT > 1 && FT * NT > 4) ? 2 : 1;   // K slices per wave
-    static constexpr int MAX_THREADS = (NT == 1) ? 1024 : 512;     // one row tile: up to 16 waves of <= 128 registers
-};
+// threads the kernel is built for, i.e. registers per wave: 128 at one row tile (16 waves, or two workgroups of 8, per
+// compute unit); 256 with more row tiles, and for three or four gate/up pairs (that matrix always has 8 K slices)
+constexpr int tilek_max_threads(int nt, int tiles_per_task, int ft) { return nt == 1 && (tiles_per_task == 1 || ft < 3) ? 1024 : 512; }
 template <int NT, int EPI, bool SPLIT, int FT>
-__global__ __launch_bounds__((TileKShape<NT, FT>::MAX_THREADS)) void gemm_tilek_bf16(GemmArgs a) {
-    constexpr int SL = TileKShape<NT, FT>::SL;
+__global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, FT))) void gemm_tilek_bf16(GemmArgs a) {
     constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1;
     constexpr int AT = FT * TILES;                 // weight tiles per k-step
     // k-steps per load batch (two batches in flight): one weight tile and one row tile per wave (O, down at
@@ -331,7 +357,8 @@ __global__ __launch_bounds__((TileKShape<NT, FT>::MAX_THREADS)) void gemm_tilek_
     constexpr int UB = (AT * NT >= 4) ? 1 : (AT * NT == 1 ? 4 : 2);
     constexpr int PL = SPLIT ? 2 : 1;
     extern __shared__ f32x4 red[];                 // [S][AT][NT][64], then rstd[16*NT] floats
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, S = (blockDim.x >> 6) * SL;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6, S = a.plan.tk_waves;
+    const int SL = EPI == EPI_SWIGLU ? 1 : S / W;  // K slices per wave (gate/up: 8 slices, 8 waves)
     TK_TRACE(0);
     // llma_generate launches k + 1 rows in every step; how many of them carry a token (1 + the
     // drafts the trigger found) is only known on the device.  The dead rows cost nothing here:
@@ -360,17 +387,22 @@ __global__ __launch_bounds__((TileKShape<NT, FT>::MAX_THREADS)) void gemm_tilek_
     auto k_turn = [&](int len) { return len > 1 ? (turn_grp * 5) % len : 0; };
     float *rstd_s = (float *)(red + (size_t)S * AT * NT * 64);
 
-    const u32x4 *wp[AT];
+    // Every operand is fetched through a buffer descriptor of its own (one per weight tile, one per activation plane):
+    // wave-uniform base and size, one 32-bit offset per lane and k-step for all tiles (a 64-bit pointer per tile took
+    // twice the registers: three gate/up pairs at three row tiles spilled, 51 -> 40 us at 33 rows).  Rows without a
+    // token get an offset past the end: zeros, and no traffic.
+    rsrc_t wb[AT];
 #pragma unroll
     for (int f = 0; f < FT; ++f)
 #pragma unroll
         for (int i = 0; i < TILES; ++i) {
             int task = task0 + f;
             task = task < p.tasks ? task : p.tasks - 1;          // ragged last workgroup: recompute the last tile
-            wp[f * TILES + i] = (const u32x4 *)a.W + ((size_t)(task + i * p.tasks) * KSp) * 64 + lane;
+            wb[f * TILES + i] = buffer_of((const char *)a.W + ((size_t)(task + i * p.tasks) * KSp) * 1024, (unsigned)KSp * 1024u);
         }
     // One row tile (the usual decoding step): the wave's first weight blocks are requested before
     // the live-row count is read, which is a round trip to memory of its own.
+    const unsigned w_lane = (unsigned)lane * 16u;
     u32x4 avA[AT][UB];
     if (NT == 1) {
         const int k_lo = (KSp * wave * SL) >> s_sh, k_hi = (KSp * (wave * SL + 1)) >> s_sh;
@@ -380,16 +412,18 @@ __global__ __launch_bounds__((TileKShape<NT, FT>::MAX_THREADS)) void gemm_tilek_
                 int k = (k_lo + u < k_hi ? k_lo + u : k_hi - 1) + k_turn(k_hi - k_lo);
                 k = k >= k_hi ? k - (k_hi - k_lo) : k;
 #pragma unroll
-                for (int i = 0; i < AT; ++i) avA[i][u] = __builtin_nontemporal_load(wp[i] + (size_t)k * 64);
+                for (int i = 0; i < AT; ++i) avA[i][u] = buffer_load16<true>(wb[i], (unsigned)k * 1024u + w_lane);
             }
         }
         clamp_rows();
     }
-    const u32x4 *xh = (const u32x4 *)a.Xhi, *xl = (const u32x4 *)a.Xlo;
+    const unsigned x_bytes = (unsigned)(NT * KSp) * 1024u;
+    const rsrc_t xh = buffer_of(a.Xhi, x_bytes), xl = buffer_of(a.Xlo, x_bytes);
     const int nt_live = (a.rows + 15) >> 4;        // row tiles with at least one live row (uniform)
-    int xpc[NT];                                   // lanes of rows past the end re-read the tile's first row:
-#pragma unroll                                     // no extra cache line, no divergence; their results are dropped
-    for (int t = 0; t < NT; ++t) xpc[t] = (t * 16 + (lane & 15) < a.rows) ? xtile_piece(lane) : (lane >> 4);
+    unsigned x_lane[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+        x_lane[t] = t * 16 + (lane & 15) < a.rows ? (unsigned)(t * KSp) * 1024u + (unsigned)xtile_piece(lane) * 16u : BUFFER_NOWHERE;
 
     auto issue = [&](int ks, u32x4 (&av)[AT][UB], u32x4 (&bv)[PL][NT][UB], bool weights = true) {
 #pragma unroll
@@ -397,14 +431,15 @@ __global__ __launch_bounds__((TileKShape<NT, FT>::MAX_THREADS)) void gemm_tilek_
             int k = ks + u;
             k = (k < ks1 ? k : ks1 - 1) + turn;
             k = k >= ks1 ? k - (ks1 - ks0) : k;
+            const unsigned off = (unsigned)k * 1024u;
             if (weights)
 #pragma unroll
-            for (int i = 0; i < AT; ++i) av[i][u] = __builtin_nontemporal_load(wp[i] + (size_t)k * 64);
+            for (int i = 0; i < AT; ++i) av[i][u] = buffer_load16<true>(wb[i], off + w_lane);
 #pragma unroll
             for (int t = 0; t < NT; ++t)
                 if (t == 0 || t < nt_live) {           // a row tile without a live row is skipped altogether
-                    bv[0][t][u] = xh[((size_t)t * KSp + k) * 64 + xpc[t]];
-                    if (SPLIT) bv[PL - 1][t][u] = xl[((size_t)t * KSp + k) * 64 + xpc[t]];
+                    bv[0][t][u] = buffer_load16<false>(xh, off + x_lane[t]);
+                    if (SPLIT) bv[PL - 1][t][u] = buffer_load16<false>(xl, off + x_lane[t]);
                 }
         }
     };
@@ -431,10 +466,14 @@ __global__ __launch_bounds__((TileKShape<NT, FT>::MAX_THREADS)) void gemm_tilek_
     ks0 = ks; turn = k_turn(ks1 - ks0);
     if (ks < ks1) issue(ks, avA, bvA, NT > 1);      // (one row tile: the weights are already on their way)
     // epilogue inputs and rstd while the first batch is in flight
-    EpiIn<NT> in;
-    const int my_task = task0 + wave;                           // waves 0..FT-1 finish one tile each
-    const bool finisher = wave < FT && my_task < p.tasks;
-    if (finisher) epi_prefetch<NT, EPI>(a, p, my_task, lane, in);
+    // (after the sums, wave w finishes the (feature tile, row tile) pairs w, w + W, ...)
+    constexpr int UNITS = FT * NT;
+    EpiIn<1> in;
+    if (wave < UNITS && task0 + wave / NT < p.tasks) {
+        GemmArgs at = a;
+        offset_rows(at, p, (wave % NT) * 16);
+        epi_prefetch<1, EPI>(at, p, task0 + wave / NT, lane, in);
+    }
     if (EPI != EPI_RESID && threadIdx.x < 256) {
         const int row = threadIdx.x >> 4, i = threadIdx.x & 15;
         const int chunk = (a.ssq_tiles + 15) / 16;
@@ -460,7 +499,6 @@ __global__ __launch_bounds__((TileKShape<NT, FT>::MAX_THREADS)) void gemm_tilek_
             if (i == 0) rstd_s[r] = 1.0f / sqrtf(ss / (float)(a.ssq_tiles * 16) + a.eps);
         }
     }
-#pragma unroll
     for (int sl = 0; sl < SL; ++sl) {
         if (sl > 0) {
             slice = wave * SL + sl;
@@ -491,46 +529,70 @@ __global__ __launch_bounds__((TileKShape<NT, FT>::MAX_THREADS)) void gemm_tilek_
     }
     TK_TRACE(2);
     __syncthreads();
-    if (!finisher) return;
-    f32x4 sum[TILES][NT];
+    for (int u = wave; u < UNITS; u += W) {
+        const int f = u / NT, t = u % NT, task = task0 + f;
+        if (task >= p.tasks || t >= nt_live) continue;
+        GemmArgs at = a;
+        offset_rows(at, p, t * 16);
+        if (u != wave) epi_prefetch<1, EPI>(at, p, task, lane, in);
+        f32x4 sum[TILES][1];
 #pragma unroll
-    for (int i = 0; i < TILES; ++i)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            f32x4 v = red[((0 * AT + wave * TILES + i) * NT + t) * 64 + lane];
-            for (int w = 1; w < S; ++w) v += red[((w * AT + wave * TILES + i) * NT + t) * 64 + lane];
-            sum[i][t] = v;
+        for (int i = 0; i < TILES; ++i) {
+            f32x4 v = red[((0 * AT + f * TILES + i) * NT + t) * 64 + lane];
+            for (int w = 1; w < S; ++w) v += red[((w * AT + f * TILES + i) * NT + t) * 64 + lane];
+            sum[i][0] = v;
         }
-    gemm_epilogue<NT, EPI, TILES>(a, p, my_task, lane, sum, rstd_s, in);
+        gemm_epilogue<1, EPI, TILES>(at, p, task, lane, sum, rstd_s + 16 * t, in);
+    }
     TK_TRACE(3);
 }
 
 // Which (feature tiles per workgroup) values the tile-K kernel can run for a matrix at nt row tiles: the
-// waves' partial sums (K slices x tiles x row tiles KiB) must fit LDS, every finishing wave needs a tile,
-// and a single-tile workgroup with several row tiles runs one slice per wave (at most 8 waves).
+// K slices' partial sums (slices x tiles x row tiles KiB) must fit LDS.
 bool tilek_ft_valid(const GemmPlan &p, int nt, int ft) {
     if (ft < 1 || ft > 4 || nt < 1 || nt > 3) return false;
-    const int tiles = p.tiles_per_task * ft;
-    const int sl = (ft > 1 && nt > 1 && ft * nt > 4) ? 2 : 1, waves = p.tk_waves / sl;     // (TileKShape::SL)
-    if (waves < ft || waves * 64 > (nt == 1 ? 1024 : 512)) return false;
-    if (p.tiles_per_task == 2 && ft > 2) return false;
-    return (size_t)p.tk_waves * tiles * nt * 1024 + 256 <= 160 * 1024 - 1024;
+    return (size_t)p.tk_waves * p.tiles_per_task * ft * nt * 1024 + 256 <= 160 * 1024 - 1024;
 }
-int tilek_ft_default(const GemmPlan &p, int nt) {
-    const int want = (p.tiles_per_task == 2) ? 1 : (p.tk_waves == 16 ? 3 : 1);
-    for (int ft = want; ft <= 4; ++ft)
-        if (tilek_ft_valid(p, nt, ft)) return ft;
-    for (int ft = want - 1; ft >= 1; --ft)
-        if (tilek_ft_valid(p, nt, ft)) return ft;
-    return 1;
+static int cu_count() {
+    static std::atomic<int> n_cu{0};                  // (the same for every device of this kind; concurrent first calls find the same)
+    int n = n_cu.load(std::memory_order_relaxed);
+    if (n == 0) {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n = prop.multiProcessorCount;
+        if (n <= 0) n = 256;
+        n_cu.store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+// A workgroup streams from its compute unit alone, so a launch takes as long as the unit with the most tiles: rounds of
+// workgroups x tiles per workgroup.  The value with the least of that wins, of equal ones the largest: every workgroup
+// reads all rows' activations, which is half of the traffic at 16 rows and one tile (pair) each.  7B gate/up, 688 pairs:
+// three per workgroup (230 workgroups, one round) instead of one takes 30.6 instead of 34.9 us at nine rows, 33.4
+// instead of 43.9 at 17, 39.3 instead of 63.6 at 33; two (344 workgroups) 37.  Steps of up to four rows have next to
+// no activation traffic: there the smallest of equal values wins for the matrices with 8 slices (gate/up at one row
+// 29.6 against 30.1 us: two workgroups per compute unit overlap each other's start and end).
+long tilek_cost(const GemmPlan &p, int ft) {
+    const long n_cu = cu_count();
+    return ((p.tasks + ft - 1) / ft + n_cu - 1) / n_cu * ft;
+}
+int tilek_ft_default(const GemmPlan &p, int nt, bool few_rows) {
+    int best = 1;
+    long best_cost = 0;
+    for (int ft = 1; ft <= 4; ++ft) {
+        if (!tilek_ft_valid(p, nt, ft)) continue;
+        const long cost = tilek_cost(p, ft);
+        if (best_cost == 0 || cost < best_cost || (cost == best_cost && !(few_rows && p.tk_waves == 8))) { best = ft; best_cost = cost; }
+    }
+    return best;
 }
 
 template <int NT, int EPI, int FT>
 static void launch_tilek(const GemmArgs &a, hipStream_t st) {
     constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1;
     const GemmPlan &p = a.plan;
-    const int S = p.tk_waves;                                        // K slices
-    const int W = S / TileKShape<NT, FT>::SL;
+    const int S = p.tk_waves, max_waves = tilek_max_threads(NT, TILES, FT) / 64;
+    const int W = S < max_waves ? S : max_waves;                     // waves; S, the K slices, is 8 or 16
     const size_t lds = (size_t)S * FT * TILES * NT * 1024 + 256;
     dim3 grid((p.tasks + FT - 1) / FT), block(W * 64);
     if (a.split) {
@@ -546,11 +608,14 @@ static void launch_tilek(const GemmArgs &a, hipStream_t st) {
 
 template <int NT, int EPI>
 static void launch_gemm_nt_epi(const GemmArgs &a, hipStream_t st) {
-    switch (tilek_ft_valid(a.plan, NT, a.plan.tk_ft[NT - 1]) ? a.plan.tk_ft[NT - 1] : tilek_ft_default(a.plan, NT)) {
+    const int ft = a.plan.tk_ft[tilek_bucket(a.rows)];
+    switch (tilek_ft_valid(a.plan, NT, ft) ? ft : tilek_ft_default(a.plan, NT, a.rows <= 4)) {
         case 1: launch_tilek<NT, EPI, 1>(a, st); break;
         case 2: launch_tilek<NT, EPI, 2>(a, st); break;
         case 3: launch_tilek<NT, EPI, 3>(a, st); break;
-        default: launch_tilek<NT, EPI, 4>(a, st); break;
+        default:
+            if constexpr (!(EPI == EPI_SWIGLU && NT == 3)) launch_tilek<NT, EPI, 4>(a, st);     // (its partial sums exceed LDS)
+            break;
     }
 }
 
@@ -573,18 +638,6 @@ static void launch_gemm_nt(const GemmArgs &a, hipStream_t st) {
 // global memory / L2, where the workgroups of the other row blocks find them again.  MFMA-bound
 // by design: FT*TILES*RT*2 MFMAs per k-step and wave against RT*2 LDS operand reads.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ void offset_rows(GemmArgs &a, const GemmPlan &p, int r0) {
-    const int t0 = r0 / 16;
-    a.rows = a.rows - r0;
-    if (a.out) a.out += (size_t)r0 * p.N;
-    if (a.nx_hi) { a.nx_hi = (bf16_t *)a.nx_hi + (size_t)t0 * a.nx_KSp * 512; a.nx_lo = (bf16_t *)a.nx_lo + (size_t)t0 * a.nx_KSp * 512; }
-    if (a.ssq_out) a.ssq_out += (size_t)r0 * (p.N / 16);
-    if (a.act_hi) { a.act_hi = (bf16_t *)a.act_hi + (size_t)t0 * a.act_KSp * 512; a.act_lo = (bf16_t *)a.act_lo + (size_t)t0 * a.act_KSp * 512; }
-    if (a.pval) { a.pval += (size_t)r0 * a.n_part; a.pidx += (size_t)r0 * a.n_part; }
-    if (a.row_pos) { a.row_pos += r0; a.row_slot += r0; a.row_cs += (size_t)r0 * a.dh; }
-    if (a.q_hi) { a.q_hi = (bf16_t *)a.q_hi + (size_t)t0 * (a.H * a.dh / 32) * 512; a.q_lo = (bf16_t *)a.q_lo + (size_t)t0 * (a.H * a.dh / 32) * 512; }
-}
-
 // rstd[row] = rsqrt(sum of the row's per-tile sums of squares / d + eps), same summation order as
 // the decoding kernels' in-kernel version (16 threads per row, contiguous chunks, butterfly); r = the
 // calling thread's row (whole waves call this: the butterfly runs over 16-lane groups)
@@ -878,14 +931,7 @@ static void launch_panel_cfg(const GemmArgs &a, hipStream_t st) {
 // them idle: 28 vs 33 us, 47 vs 58 us).
 template <int EPI, int FT, int WV>
 static void launch_panel_wv(const GemmArgs &a, hipStream_t st) {
-    static int n_cu = 0;
-    if (n_cu == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n_cu = prop.multiProcessorCount;
-        if (n_cu <= 0) n_cu = 256;
-    }
-    const int slots = n_cu * (8 / WV);                   // workgroups resident at once
+    const int slots = cu_count() * (8 / WV);                   // workgroups resident at once
     const int fb = ((a.plan.tasks + WV * FT - 1) / (WV * FT) + 7) / 8 * 8;
     const int row_tiles = (a.rows + 15) / 16;
     const int ns = a.ksplit > 1 ? a.ksplit : 1;
@@ -930,20 +976,18 @@ bool launch_gemm_bf16(const GemmArgs &a, hipStream_t st) {
     return true;
 }
 
-// how a [N][K] weight matrix is cut into work for the tile-K kernel: three feature tiles per
-// workgroup and 16 K slices for matrices of 640+ tiles (QKV, LM head), else one tile (pair) and 8
-// slices -- the combinations measured fastest on the 7B and 13B shapes
+// how a [N][K] weight matrix is cut into work
 GemmPlan make_gemm_plan(int N, int K, int tiles_per_task) {
     GemmPlan p;
     p.N = N; p.K = K;
     p.KSp = K / 32;
     p.tasks = N / 16;
-    // K slices: 16 for matrices of 640+ tiles (QKV, LM head), else 8; feature tiles per workgroup: three
-    // resp. one by default (the values measured fastest on the 7B shapes), re-tuned per context by timing
-    // (llma_create), which cannot change any result
+    // tile-K kernel, K slices: 16 for matrices of 640+ tiles (QKV, LM head), else 8; feature tiles per workgroup by
+    // tilek_ft_default, re-tuned per context by timing (llma_create), which cannot change any result
     p.tiles_per_task = tiles_per_task;
     p.tk_waves = (tiles_per_task != 2 && p.tasks >= 640) ? 16 : 8;
-    for (int nt = 1; nt <= 3; ++nt) p.tk_ft[nt - 1] = tilek_ft_default(p, nt);
+    for (int nt = 1; nt <= 3; ++nt) p.tk_ft[nt - 1] = tilek_ft_default(p, nt, false);
+    p.tk_ft[3] = tilek_ft_default(p, 1, true);
     // split-K form of the panel kernel: enough ranges that feature blocks x ranges is about 200
     // workgroups per row block (2..8, a function of the matrix only, so a row's sums do not depend on
     // how many rows share the step)

@@ -355,10 +355,10 @@ static GemmArgs step_gemm_args(llma_ctx *c, int which, int layer, int rows) {
 
 // How many feature tiles a workgroup of the decoding GEMM takes is pure work division (a tile's sums are
 // the same for any value), and which value streams a matrix fastest depends on how its tile count falls
-// on the device's compute units (7B: one tile per workgroup for the 256-tile O / down matrices; 13B, 320
-// tiles: two, 35.6 -> 27.0 us for down; QKV 960 tiles: four, 34.0 -> 26.1 us).  So it is measured: every
-// admissible value, for 1 / 17 / 33 rows (one, two, three row tiles), on the context's own matrices and
-// zeroed scratch, a few dozen launches each; a value has to beat the default by 5 % to replace it.
+// on the device's compute units (tilek_ft_default's rule) and on how well the device hides the last round.  So it is
+// measured: every value that can win, at one row (for steps of up to 4) and at the middle of one, two and three row
+// tiles (9, 25, 41 rows), on the context's own matrices and zeroed scratch, a few dozen launches each; a value has
+// to beat the default by 5 % to replace it (2 % at one row, where they differ least).
 static int autotune_tilek(llma_ctx *c) {
     if (!c->bf16 || getenv("LLMA_NO_AUTOTUNE") != nullptr) return LLMA_OK;
     const llma_model_cfg &g = c->cfg;
@@ -367,7 +367,7 @@ static int autotune_tilek(llma_ctx *c) {
         const int ft = atoi(forced);
         for (GemmPlan *p : plans)
             for (int nt = 1; nt <= 3; ++nt)
-                if (tilek_ft_valid(*p, nt, ft)) p->tk_ft[nt - 1] = ft;
+                if (tilek_ft_valid(*p, nt, ft)) { p->tk_ft[nt - 1] = ft; if (nt == 1) p->tk_ft[3] = ft; }
         return LLMA_OK;
     }
     const int step_rows = g.max_batch * (g.max_k + 1);
@@ -376,14 +376,18 @@ static int autotune_tilek(llma_ctx *c) {
     HIP_TRY(c, hipEventCreate(&e1));
     const int reps = g.n_layers < 8 ? 16 : (2 * g.n_layers < 48 ? 2 * g.n_layers : 48);
     for (int which = 0; which < 5; ++which)
-        for (int nt = 1; nt <= 3; ++nt) {
-            const int rows = nt == 1 ? 1 : 16 * (nt - 1) + 1;
-            if (rows > step_rows || rows > 48) continue;                  // this context never launches that many row tiles
+        for (int at = 0; at < 4; ++at) {                                  // (index into GemmPlan::tk_ft)
+            const int nt = at == 3 ? 1 : at + 1;
+            if (16 * (nt - 1) + 1 > step_rows) continue;                  // this context never launches that many row tiles
+            int rows = at == 3 ? 1 : 16 * nt - 7;
+            rows = rows < step_rows ? rows : step_rows;
             GemmPlan &p = *plans[which];
-            const int dflt = p.tk_ft[nt - 1];
+            if (tilek_bucket(rows) != at) continue;                       // a context of up to 4 rows per step
+            const float win = at == 3 ? 0.98f : 0.95f;
+            const int dflt = p.tk_ft[at];
             // mean launch time of this matrix at `rows` rows with FT = ft
             auto time_ft = [&](int ft, float *us) -> int {
-                p.tk_ft[nt - 1] = ft;
+                p.tk_ft[at] = ft;
                 float ms = 0.f;
                 for (int pass = 0; pass < 2; ++pass) {                    // pass 0 warms up
                     const int n = pass ? reps : 3;
@@ -399,26 +403,31 @@ static int autotune_tilek(llma_ctx *c) {
                 *us = ms * 1e3f / reps;
                 return LLMA_OK;
             };
+            // values that leave the busiest compute unit a quarter more to stream are not worth a try
+            auto worth = [&](int ft) { return tilek_ft_valid(p, nt, ft) && 4 * tilek_cost(p, ft) <= 5 * tilek_cost(p, dflt); };
+            int n_worth = 0;
+            for (int ft = 1; ft <= 4; ++ft) n_worth += worth(ft);
+            if (n_worth < 2) continue;
             float best_us = 0.f, dflt_us = 0.f;
             int best = dflt;
             for (int ft = 1; ft <= 4; ++ft) {
-                if (!tilek_ft_valid(p, nt, ft)) continue;
+                if (!worth(ft)) continue;
                 float us = 0.f;
                 if (int rc = time_ft(ft, &us)) return rc;
                 if (ft == dflt) dflt_us = us;
                 if (best_us == 0.f || us < best_us) { best_us = us; best = ft; }
             }
-            // A candidate replaces the default only if it wins by 5 % twice: in the sweep and again
+            // A candidate replaces the default only if it wins by 5 % (one row: 2 %) twice: in the sweep and again
             // head to head (default first, candidate second), so that one disturbed measurement
             // -- clocks still ramping, another process on the card -- cannot pick a slower shape.
-            bool adopt = best != dflt && dflt_us > 0.f && best_us < 0.95f * dflt_us;
+            bool adopt = best != dflt && dflt_us > 0.f && best_us < win * dflt_us;
             if (adopt) {
                 float d2 = 0.f, b2 = 0.f;
                 if (int rc = time_ft(dflt, &d2)) return rc;
                 if (int rc = time_ft(best, &b2)) return rc;
-                adopt = b2 < 0.95f * d2;
+                adopt = b2 < win * d2;
             }
-            p.tk_ft[nt - 1] = adopt ? best : dflt;
+            p.tk_ft[at] = adopt ? best : dflt;
         }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -472,9 +481,9 @@ extern "C" int llma_describe(const llma_ctx *c, char *buf, int32_t cap) {
     if (!c->bf16) { snprintf(buf, (size_t)cap, "fp32 path (plain vector-ALU kernels, nothing tuned)"); return LLMA_OK; }
     const GemmPlan *pl[5] = {&c->plan_qkv, &c->plan_o, &c->plan_gu, &c->plan_down, &c->plan_lm};
     const char *nm[5] = {"qkv", "o", "gate_up", "down", "lm_head"};
-    int n = snprintf(buf, (size_t)cap, "decoding GEMM, feature tiles per workgroup at 1/2/3 row tiles (K slices):");
+    int n = snprintf(buf, (size_t)cap, "decoding GEMM, feature tiles per workgroup at 1/2/3 row tiles, up to 4 rows (K slices):");
     for (int i = 0; i < 5 && n > 0 && n < cap; ++i)
-        n += snprintf(buf + n, (size_t)(cap - n), " %s %d/%d/%d (%d)", nm[i], pl[i]->tk_ft[0], pl[i]->tk_ft[1], pl[i]->tk_ft[2], pl[i]->tk_waves);
+        n += snprintf(buf + n, (size_t)(cap - n), " %s %d/%d/%d, %d (%d)", nm[i], pl[i]->tk_ft[0], pl[i]->tk_ft[1], pl[i]->tk_ft[2], pl[i]->tk_ft[3], pl[i]->tk_waves);
     return LLMA_OK;
 }
 
