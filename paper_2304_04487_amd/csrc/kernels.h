@@ -15,6 +15,8 @@ void launch_embed_prep_bf16(const void *embed, const int *row_tok, const float *
                             float *ssq_out, int R, int d, int KSp, hipStream_t st);
 bool launch_gemm_bf16(const GemmArgs &a, hipStream_t st);   // false (nothing launched) unless 1 <= rows <= 48
 void launch_gemm_panel_bf16(const GemmArgs &a, hipStream_t st);
+int panel_prompt_split(const GemmPlan &p, int rows);                   // K ranges that suit a prompt pass of so many rows (1: no split)
+size_t panel_part_bytes(const GemmPlan &p, int rows, int ns);          // scratch for the partial sums of ns ranges
 void launch_rstd_rows(const float *ssq, int ssq_tiles, float eps, float *rstd, int rows, hipStream_t st);
 void launch_attn_bf16(const AttnArgs &a, hipStream_t st);
 

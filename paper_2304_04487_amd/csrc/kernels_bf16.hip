@@ -630,13 +630,19 @@ static void launch_gemm_nt(const GemmArgs &a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Panel GEMM for prompt processing (hundreds of rows): a workgroup computes a block of
-// WV*FT feature tiles x RT row tiles over the whole K axis -- no K split, no partial sums.  The
-// block's activation rows are staged through LDS in chunks of KC k-steps (double-buffered,
-// 16-byte pieces gathered from the planes' row-major piece order into lane order) and shared by the
-// waves; every wave streams the weight blocks of its own FT feature tiles (TILES each) from
-// global memory / L2, where the workgroups of the other row blocks find them again.  MFMA-bound
-// by design: FT*TILES*RT*2 MFMAs per k-step and wave against RT*2 LDS operand reads.
+// Panel GEMM (prompt passes and steps of more than 48 rows): a workgroup computes a block of 16 (or 8) weight tiles x
+// RT row tiles over a range of the K axis.  Its 8 waves take two (one) weight tiles each and all RT row tiles.  The
+// block's activations pass through LDS in chunks of KC k-steps, three chunks deep, loaded straight into LDS (buffer
+// loads; no registers, no LDS stores); every wave streams its own weight blocks from memory / L2, where the workgroups
+// of the other row blocks find them again, into a ring of WD register sets.  One barrier per chunk.
+// Bound by MFMA issue on long prompts (1535 rows, four layers: 4.97 TFLOP of bf16 products in 4.1 ms = 1.2 PFLOP/s; a
+// large library product runs at 1.37 here), by the weight stream and the start and end of each launch at few rows.
+// What made the difference (7B, four layers' prompt pass of 1535 rows / a layer's GEMMs at 144 rows: 5.44 ms / 194 us
+// before): the order of requests is the source's (the compiler moved every one next to its use), the activations
+// take no registers on the way to LDS, no mask on the weights and no early exit inside a turn of the ring (either
+// made every turn end with a wait for all loads in flight), and the buffer form of the loads into LDS (the global
+// form counts as a flat access: behind one the compiler waits for everything).  4.85 ms / 177 us.  Waves that take four
+// weight tiles and half of the rows (half the LDS reads, each weight block loaded by two waves): 5.18 ms / 208 us.
 // ---------------------------------------------------------------------------------------------
 // rstd[row] = rsqrt(sum of the row's per-tile sums of squares / d + eps), same summation order as
 // the decoding kernels' in-kernel version (16 threads per row, contiguous chunks, butterfly); r = the
@@ -662,31 +668,45 @@ __device__ __forceinline__ void rstd_of_row(const float *__restrict__ ssq, int s
     if (i == 0 && r < rows) rstd[r] = 1.0f / sqrtf(ss / (float)(ssq_tiles * 16) + eps);
 }
 
-// calls f(integral_constant<int, 0>), f(..1), ... in order until one returns false
-template <class F, int... I>
-__device__ __forceinline__ void chunks_in_order(std::integer_sequence<int, I...>, F &&f) {
-    bool go = true;
-    ((go = go && f(std::integral_constant<int, I>{})), ...);
-}
-
 #define PANEL_KC 2          // k-steps per LDS chunk
+#define PANEL_TURN 8        // k-steps of weights in registers; the K axis is cut into ranges of whole turns of this ring
+#define PANEL_RT_MAX 10     // row tiles per workgroup: 4 .. 10
+#define PANEL_STAGES 3      // chunks of activations in LDS: one in use, the others on their way
 #ifndef PN_TRACE
 #define PN_TRACE(slot, chunk)   // (timeline probe of the one-off microbenchmarks; nothing in the library build)
 #endif
-#ifndef PANEL_WD
-#define PANEL_WD 8          // k-steps of weights in registers (one in use, the others in flight)
-#endif
-// (four or more weight tiles per wave: accumulators for up to 9 row tiles each need the whole register
-//  file of a SIMD lane, 512 registers, i.e. one wave per SIMD; otherwise two)
-template <int RT, int EPI, int FT, int WV>
-__global__ __launch_bounds__(WV * 64, (FT * (EPI == EPI_SWIGLU ? 2 : 1) >= 4 ? 1 : 2)) void gemm_panel_bf16(GemmArgs a0) {
-    constexpr int NTHR = WV * 64;
-    constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1;
-    constexpr int AT = FT * TILES;
-    constexpr int KC = PANEL_KC;                   // k-steps per LDS chunk
-    constexpr int CH = RT * KC * 64;               // 16-byte pieces per plane and chunk
-    constexpr int PER = (2 * CH + NTHR - 1) / NTHR; // pieces per thread and chunk (both planes)
-    extern __shared__ u32x4 xs[];                  // [2 buffers][2 planes][RT][KC][64], then rstd[16*RT]
+// 16 bytes per lane from a buffer straight into LDS (lane l's land at lds + 16 l); counted like any load.  (The buffer
+// form: behind a global_load_lds the compiler waits for every load in flight before it uses any other load's value.)
+__device__ __forceinline__ void load_to_lds(rsrc_t r, unsigned lane_off, unsigned off, u32x4 *lds) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds, 16, (int)lane_off, (int)off, 0, 0);
+}
+// waits until at most N of the wave's loads are outstanding and its LDS reads are done, then for the workgroup;
+// no memory access moves across it in either direction
+template <int N>
+__device__ __forceinline__ void wait_loads_and_barrier() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory"); }
+
+// the counted wait above relies on the order in which a wave's loads were issued
+__device__ __forceinline__ void requests_stay_in_order() { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); }
+
+template <int RT, int EPI, int PT>
+struct PanelShape {
+    static constexpr int AT = PT / 8;                                    // weight tiles per wave
+    static constexpr int TG = (RT + 3) / 4, TB = (RT + TG - 1) / TG;     // row tiles whose operands are read from LDS together
+    static constexpr int WD = PANEL_TURN;                                // k-steps of weights in registers
+    static constexpr int XB = (2 * RT * PANEL_KC + 7) / 8;               // activation blocks a wave fetches per chunk
+    // loads a wave has certainly requested after a chunk's activations when it comes to wait for them: the next
+    // chunk's, and the weights of two chunks (before the first chunk: of the ring's first turn)
+    static constexpr int LATER = XB + (WD - PANEL_KC < 2 * PANEL_KC ? WD - PANEL_KC : 2 * PANEL_KC) * AT;
+    static_assert(LATER <= 63, "the wait counter has six bits");
+};
+template <int RT, int EPI, int PT>
+__global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
+    using Shape = PanelShape<RT, EPI, PT>;
+    constexpr int AT = Shape::AT, WD = Shape::WD, XB = Shape::XB;
+    constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1, FT = AT / TILES;
+    constexpr int KC = PANEL_KC;
+    constexpr int CH = 2 * RT * KC * 64;           // 16-byte pieces per stage (both planes)
+    extern __shared__ u32x4 xs[];                  // [stages][2 planes][RT][KC][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const GemmPlan &p = a0.plan;
     const int KSp = p.KSp;
@@ -694,7 +714,7 @@ __global__ __launch_bounds__(WV * 64, (FT * (EPI == EPI_SWIGLU ? 2 : 1) >= 4 ? 1
         // split-K form: one workgroup more than the tiles need turns the rows' sums of squares into
         // rstd for the finishing kernel, beside the others instead of in a launch of its own
         if (blockIdx.y == 0)
-            for (int r = threadIdx.x >> 4; r < ((a0.rows + 15) & ~15); r += NTHR / 16)
+            for (int r = threadIdx.x >> 4; r < ((a0.rows + 15) & ~15); r += 512 / 16)
                 rstd_of_row(a0.ssq_in, a0.ssq_tiles, a0.eps, a0.rstd_out, a0.rows, r, threadIdx.x & 15);
         return;
     }
@@ -706,59 +726,47 @@ __global__ __launch_bounds__(WV * 64, (FT * (EPI == EPI_SWIGLU ? 2 : 1) >= 4 ? 1
     const int fb = grp * 8 + (within & 7), rb = within >> 3;
     const int r0 = rb * (16 * RT);
     const int rt0 = r0 / 16;
-    float *rstd_s = (float *)(xs + 2 * 2 * CH);
     GemmArgs a = a0;
     offset_rows(a, p, r0);
-    const int task0 = (fb * WV + wave) * FT;        // may lie past the last tile (padding feature blocks): clamped loads, no epilogue
+    const int task0 = (fb * 8 + wave) * FT;         // may lie past the last tile (padding feature blocks): clamped loads, no epilogue
 
-    const char *wb[AT];                            // first weight block of each tile (wave-uniform)
+    rsrc_t wb[AT];                                 // a descriptor per weight tile (wave-uniform)
 #pragma unroll
     for (int f = 0; f < FT; ++f)
 #pragma unroll
         for (int i = 0; i < TILES; ++i) {
             int task = task0 + f;
             task = task < p.tasks ? task : p.tasks - 1;
-            wb[f * TILES + i] = (const char *)a.W + ((size_t)(task + i * p.tasks) * KSp) * 1024;
+            wb[f * TILES + i] = buffer_of((const char *)a.W + ((size_t)(task + i * p.tasks) * KSp) * 1024, (unsigned)KSp * 1024u);
         }
-    const char *xh = (const char *)a.Xhi, *xl = (const char *)a.Xlo;
     const int n_rt_total = (a0.rows + 15) / 16;    // row tiles that exist in the planes
+    const unsigned x_bytes = (unsigned)n_rt_total * (unsigned)KSp * 1024u;
+    const rsrc_t xh = buffer_of(a.Xhi, x_bytes), xl = buffer_of(a.Xlo, x_bytes);
 
     // Operand fetches.  Every address below is a wave-uniform base (scalar registers, scalar
     // arithmetic) plus one per-lane byte offset that never changes (the lane's 16 bytes of a 1 KiB
-    // block), so the chunk loop spends no vector instructions on addressing; every load is
-    // unconditional (indices are clamped instead): a load under a branch makes the compiler's count
-    // of loads in flight inexact, and it then waits for all of them.
-    // Activation chunk kc -> registers: wave w fetches the 1 KiB blocks q = j WV + w of the chunk's
-    // [2 planes][RT][KC] blocks; blocks of row tiles past the end read tile 0.
+    // block); every load is unconditional (indices are clamped instead): a load under a branch makes the
+    // compiler's count of loads in flight inexact, and it then waits for all of them.
+    // Activation chunk kc -> LDS stage: wave w fetches the 1 KiB blocks q = j 8 + w of the chunk's
+    // [2 planes][RT][KC] blocks (the last ones twice if they do not divide); blocks of row tiles past the end read tile 0.
     const unsigned x_lane = (unsigned)xtile_piece(lane) * 16u;     // LDS holds the block in lane order
     const unsigned w_lane = (unsigned)lane * 16u;
-    auto fetch_x = [&](int kc, u32x4 (&v)[PER]) {
+    auto fetch_x = [&](int kc, int stage) {
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            int q = j * WV + wave;
+        for (int j = 0; j < XB; ++j) {
+            int q = j * 8 + wave;
             q = q < 2 * RT * KC ? q : 2 * RT * KC - 1;
             const int pl = q / (RT * KC), t = (q % (RT * KC)) / KC, kk = q % KC;
             int k = kc * KC + kk;
             k = k < KSp ? k : KSp - 1;
             const int tt = (rt0 + t < n_rt_total) ? rt0 + t : 0;
-            const char *blk = (const char *)(pl ? xl : xh) + ((size_t)tt * KSp + k) * 1024;
-            v[j] = *(const u32x4 *)(blk + x_lane);
+            load_to_lds(pl ? xl : xh, x_lane, (unsigned)(tt * KSp + k) * 1024u, xs + stage * CH + q * 64);
         }
     };
-    auto stash_x = [&](int buf, u32x4 (&v)[PER]) {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int q = j * WV + wave;
-            if (q < 2 * RT * KC) xs[(buf * 2 * RT * KC + q) * 64 + lane] = v[j];
-        }
-    };
-    // weights of k-step k0, one 1 KiB block per tile; a k-step past the end of K (ragged last chunk)
-    // gets zeros and adds nothing
+    // weights of k-step k0, one 1 KiB block per tile; a k-step past the end of K lies outside the descriptor: zeros
     auto fetch_w = [&](int k0, u32x4 (&av)[AT]) {
-        const int k = k0 < KSp ? k0 : KSp - 1;
-        const unsigned keep = k0 < KSp ? 0xffffffffu : 0u;          // (a mask, not a select: the load stays unconditional)
 #pragma unroll
-        for (int i = 0; i < AT; ++i) av[i] = *(const u32x4 *)(wb[i] + (size_t)k * 1024 + w_lane) & keep;
+        for (int i = 0; i < AT; ++i) av[i] = buffer_load16<false>(wb[i], (unsigned)k0 * 1024u + w_lane);
     };
 
     f32x4 acc[AT][RT];
@@ -767,71 +775,80 @@ __global__ __launch_bounds__(WV * 64, (FT * (EPI == EPI_SWIGLU ? 2 : 1) >= 4 ? 1
 #pragma unroll
         for (int t = 0; t < RT; ++t) acc[i][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    // split-K form (batched decoding steps, too few rows to fill the chip otherwise): blockIdx.y picks
-    // one of a0.ksplit contiguous ranges of k-chunks; the raw sums go to a0.part and a second kernel
+    // split-K form (too few rows to fill the chip otherwise): blockIdx.y picks
+    // one of a0.ksplit contiguous ranges of whole turns; the raw sums go to a0.part and a second kernel
     // adds the ranges in order and runs the epilogue
     const int n_split = a0.ksplit > 1 ? a0.ksplit : 1;
-    const int NC_all = (KSp + KC - 1) / KC;
-    const int kc_lo = (int)((long)NC_all * blockIdx.y / n_split), NC = (int)((long)NC_all * (blockIdx.y + 1) / n_split);
-    // The weights come straight from HBM, whose latency under load (2 us and more) is several chunks
-    // of MFMA work, so they are requested WD - 1 k-steps ahead into a ring of WD register sets; the loop
-    // below is unrolled over one turn of the ring (WD / KC chunks), which gives every set and both
-    // activation staging arrays one fixed role per call site (one body taking either role made the
-    // compiler copy registers between the roles every chunk, behind a wait for all loads in flight).
-    // A wave's loads complete in the order it issued them, so an activation block (an L2 hit) waits
-    // behind every weight block requested before it: the activations are requested two chunks before
-    // they are parked in LDS.
-    constexpr int WD = PANEL_WD;
-    static_assert(WD % (2 * KC) == 0, "one turn of the weight ring is a whole number of LDS buffer pairs");
-    u32x4 xvA[PER], xvB[PER], wr[WD][AT];
+    const int turns = (KSp + PANEL_TURN - 1) / PANEL_TURN;
+    const int kc_lo = (int)((long)turns * blockIdx.y / n_split) * (PANEL_TURN / KC), kc_hi = (int)((long)turns * (blockIdx.y + 1) / n_split) * (PANEL_TURN / KC);
+    u32x4 wreg[WD][AT];
     PN_TRACE(0, 63);
-    fetch_x(kc_lo, xvA);
+    fetch_x(kc_lo, 0);
+    fetch_x(kc_lo + 1, 1);
+    requests_stay_in_order();
 #pragma unroll
-    for (int j = 0; j < WD - 1; ++j) fetch_w(kc_lo * KC + j, wr[j]);
-    fetch_x(kc_lo + 1, xvB);
-    if (EPI != EPI_RESID && n_split == 1)
-        for (int r = threadIdx.x; r < 16 * RT; r += NTHR) rstd_s[r] = (r < a.rows) ? a.rstd_in[r0 + r] : 0.f;
-    stash_x(0, xvA);
-    __syncthreads();
+    for (int j = 0; j < WD - KC; ++j) fetch_w(kc_lo * KC + j, wreg[j]);
     PN_TRACE(1, 63);
-    // One chunk: request operands (the weights WD - 1 k-steps ahead, the activations of the chunk after
-    // the next: they still have to pass through LDS), run this chunk's MFMAs out of LDS buffer c & 1
-    // and the ring, park the next chunk's activations (requested a chunk ago) in the other LDS buffer,
-    // which was last read before the previous barrier.  (Requests past the end of the range or of K
-    // are clamped, unused.)
-    auto chunk = [&](int kc0, auto slot) -> bool {
-        constexpr int c = decltype(slot)::value;        // chunk within the turn of the ring
-        constexpr int buf = c & 1;
-        const int kc = kc0 + c;
-        if (kc >= NC) return false;
+    int stage = 0;
+    // One chunk: wait for its activations (requested two chunks ago; behind them the wave has requested the next
+    // chunk's and the weights of two chunks), meet the other waves -- which also says that the previous chunk's
+    // stage has been read by all --, request the chunk after the next into that stage and the weights WD - KC k-steps
+    // ahead into the ring sets of the previous chunk, and run the MFMAs, a group of row tiles at a time while the
+    // next group's operands come from LDS.  (Requests past the end of the range or of K are unused.)  The order is
+    // the source's: left alone, the compiler moves every request next to its use.
+    auto chunk = [&](int kc, auto slot) {
+        constexpr int c = decltype(slot)::value;        // chunk within the turn of the weight ring
+        constexpr int TG = Shape::TG, TB = Shape::TB, NG = KC * TG;
         PN_TRACE(0, kc - kc_lo);
-        u32x4 (&x_park)[PER] = buf ? xvA : xvB;
-        u32x4 (&x_req)[PER] = buf ? xvB : xvA;          // held this chunk's activations, in LDS since the last barrier
-        fetch_x(kc + 2, x_req);
-#pragma unroll
-        for (int u = 0; u < KC; ++u) {
-            const int j = c * KC + u;                   // ring set of this k-step (a constant after unrolling)
-            fetch_w(kc * KC + u + WD - 1, wr[(j + WD - 1) % WD]);   // into the set the previous k-step used
-#pragma unroll
-            for (int t = 0; t < RT; ++t) {
-                const u32x4 bh = xs[buf * 2 * CH + (t * KC + u) * 64 + lane];
-                const u32x4 bl = xs[buf * 2 * CH + CH + (t * KC + u) * 64 + lane];
-#pragma unroll
-                for (int i = 0; i < AT; ++i) {
-                    acc[i][t] = mfma16x16x32(wr[j][i], bh, acc[i][t]);
-                    acc[i][t] = mfma16x16x32(wr[j][i], bl, acc[i][t]);
-                }
-            }
-        }
+        wait_loads_and_barrier<Shape::LATER>();
         PN_TRACE(1, kc - kc_lo);
-        stash_x(buf ^ 1, x_park);
+        const u32x4 *xb = xs + stage * CH + lane;
+        u32x4 b[2][TB][2];
+        auto read_group = [&](int g) {
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+                if ((g % TG) * TB + t < RT) {
+                    const int at = (((g % TG) * TB + t) * KC + g / TG) * 64;
+                    b[g & 1][t][0] = xb[at];
+                    b[g & 1][t][1] = xb[CH / 2 + at];
+                }
+        };
+        read_group(0);
+        const int prev = stage == 0 ? PANEL_STAGES - 1 : stage - 1;
+        fetch_x(kc + 2, prev);
+        requests_stay_in_order();
+#pragma unroll
+        for (int u = 0; u < KC; ++u) fetch_w(kc * KC + u + WD - KC, wreg[(c * KC + u + WD - KC) % WD]);
+        requests_stay_in_order();
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            if (g + 1 < NG) read_group(g + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            const int j = c * KC + g / TG;              // ring set of this k-step (a constant after unrolling)
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+                if ((g % TG) * TB + t < RT)
+#pragma unroll
+                    for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                        for (int i = 0; i < AT; ++i) {
+                            f32x4 &ac = acc[i][(g % TG) * TB + t < RT ? (g % TG) * TB + t : 0];
+                            ac = mfma16x16x32(wreg[j][i], b[g & 1][t][pl], ac);
+                        }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        stage = stage == PANEL_STAGES - 1 ? 0 : stage + 1;
         PN_TRACE(2, kc - kc_lo);
-        __syncthreads();
-        PN_TRACE(3, kc - kc_lo);
-        return true;
     };
-    for (int kc = kc_lo; kc < NC; kc += WD / KC)
-        chunks_in_order(std::make_integer_sequence<int, WD / KC>{}, [&](auto slot) { return chunk(kc, slot); });
+    // (no way out of a turn: an early exit made the compiler copy the ring's registers at the end of every turn, behind
+    // a wait for all loads in flight)
+    for (int kc = kc_lo; kc < kc_hi; kc += WD / KC) {
+        chunk(kc, std::integral_constant<int, 0>{});
+        chunk(kc + 1, std::integral_constant<int, 1>{});
+        chunk(kc + 2, std::integral_constant<int, 2>{});
+        chunk(kc + 3, std::integral_constant<int, 3>{});
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing may still be on its way into LDS when the workgroup ends
 
     if (n_split > 1) {
         // partial sums as register images: [range][tile (SwiGLU: gate tiles, then up tiles)][row tile][lane]
@@ -859,7 +876,7 @@ __global__ __launch_bounds__(WV * 64, (FT * (EPI == EPI_SWIGLU ? 2 : 1) >= 4 ? 1
             for (int i = 0; i < TILES; ++i)
 #pragma unroll
                 for (int t = 0; t < RT; ++t) sum[i][t] = acc[f * TILES + i][t];
-            gemm_epilogue<RT, EPI, TILES>(a, p, task, lane, sum, rstd_s, in);
+            gemm_epilogue<RT, EPI, TILES>(a, p, task, lane, sum, a0.rstd_in + r0, in);
         }
     }
 }
@@ -893,9 +910,13 @@ __global__ __launch_bounds__(256) void gemm_splitk_finish_bf16(GemmArgs a0) {
 #pragma unroll
     for (int i = 0; i < TILES; ++i) {
         const size_t tile = (size_t)(task + i * p.tasks) * n_rt + t, stride = (size_t)p.tasks * TILES * n_rt;
-        f32x4 v = part[tile * 64 + lane];
-        for (int s = 1; s < a0.ksplit; ++s) v += part[(s * stride + tile) * 64 + lane];
-        sum[i][0] = v;
+        f32x4 v[8];                                             // (at most 8 ranges; all requested before the first is added)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = part[((s < a0.ksplit ? s : 0) * stride + tile) * 64 + lane];
+#pragma unroll
+        for (int s = 1; s < 8; ++s)
+            if (s < a0.ksplit) v[0] += v[s];
+        sum[i][0] = v[0];
     }
     gemm_epilogue<1, EPI, TILES>(a, p, task, lane, sum, rstd_sh[wave], in);
 }
@@ -905,63 +926,82 @@ static void launch_splitk_finish(const GemmArgs &a, hipStream_t st) {
     hipLaunchKernelGGL((gemm_splitk_finish_bf16<EPI>), dim3((units + 3) / 4), dim3(256), 0, st, a);
 }
 
-template <int RT, int EPI, int FT, int WV>
+// feature blocks of PT weight tiles, padded to whole groups of 8 (see the kernel's workgroup order)
+static int panel_feature_blocks(const GemmPlan &p, int pt) {
+    const int per = pt / p.tiles_per_task;
+    return ((p.tasks + per - 1) / per + 7) / 8 * 8;
+}
+// How a launch over `rows` rows is cut: row tiles and weight tiles per workgroup, K ranges.  The times are a model of
+// measured launches (7B shapes): a round of workgroups, one per compute unit, costs 5 us to start and end plus
+// 0.073 (RT + 3) us per k-step (0.88 at 9 row tiles, 0.51 at 4), three quarters of that with 8 weight tiles; a
+// split costs the finishing kernel, 5 us, and its partial sums once written and once read at 4 TB/s.
+// O and down of a 54-row step: 8 tiles per workgroup, 256 workgroups instead of 128: 17.7 -> 16.3 and 35.0 -> 28.0 us.
+// 189 prompt rows: splits of 2 .. 8, 2.01 -> 1.01 ms for four layers; from 1535 rows on nothing is split.
+struct PanelCut { int rt, pt; double us; };
+static PanelCut panel_cut(const GemmPlan &p, int rows, int ns) {
+    const int row_tiles = (rows + 15) / 16, turns = (p.KSp + PANEL_TURN - 1) / PANEL_TURN;
+    PanelCut best{0, 0, 0.0};
+    for (int pt = 16; pt >= 8 * p.tiles_per_task; pt -= 8)
+        for (int rt = 4; rt <= PANEL_RT_MAX; ++rt) {
+            if (pt == 8 && rt > 5) break;
+            const long groups = (long)panel_feature_blocks(p, pt) * ((row_tiles + rt - 1) / rt) * ns;
+            const double us = (double)((groups + cu_count() - 1) / cu_count()) * (5.0 + (double)((turns + ns - 1) / ns) * PANEL_TURN * (pt == 16 ? 0.073 * (rt + 3) : 0.055 * (rt + 3)));
+            if (best.rt == 0 || us <= best.us) best = PanelCut{rt, pt, us};        // (ties: fewer, taller row blocks stream the weights less often)
+        }
+    return best;
+}
+size_t panel_part_bytes(const GemmPlan &p, int rows, int ns) { return ns > 1 ? (size_t)ns * p.tasks * p.tiles_per_task * ((rows + 15) / 16) * 1024 : 0; }
+int panel_prompt_split(const GemmPlan &p, int rows) {
+    int best = 1;
+    double best_us = 0.0;
+    for (int ns = 1; ns <= 8 && ns <= (p.KSp + PANEL_TURN - 1) / PANEL_TURN; ++ns) {
+        const double us = panel_cut(p, rows, ns).us + (ns > 1 ? 5.0 + 2e-6 * (double)panel_part_bytes(p, rows, ns) / 4.0 : 0.0);
+        if (best_us == 0.0 || us < best_us) { best = ns; best_us = us; }
+    }
+    return best;
+}
+
+template <int RT, int EPI, int PT>
 static void launch_panel_cfg(const GemmArgs &a, hipStream_t st) {
     const GemmPlan &p = a.plan;
-    const size_t lds = (size_t)2 * 2 * RT * PANEL_KC * 1024 + 16 * RT * sizeof(float);
-    const int FB = ((p.tasks + WV * FT - 1) / (WV * FT) + 7) / 8 * 8;    // feature blocks, padded to whole groups of 8
+    const size_t lds = (size_t)PANEL_STAGES * 2 * RT * PANEL_KC * 1024;
+    const int FB = panel_feature_blocks(p, PT);
     GemmArgs a2 = a;
     a2.panel_rb = (a.rows + 16 * RT - 1) / (16 * RT);
     if (a.ksplit <= 1) a2.rstd_out = nullptr;
-    dim3 grid(FB * a2.panel_rb + (a2.rstd_out ? 1 : 0), a.ksplit > 1 ? a.ksplit : 1), block(WV * 64);
+    dim3 grid(FB * a2.panel_rb + (a2.rstd_out ? 1 : 0), a.ksplit > 1 ? a.ksplit : 1), block(512);
     static std::atomic<uint64_t> done{0};
-    allow_full_lds((const void *)gemm_panel_bf16<RT, EPI, FT, WV>, done);
-    hipLaunchKernelGGL((gemm_panel_bf16<RT, EPI, FT, WV>), grid, block, lds, st, a2);
+    allow_full_lds((const void *)gemm_panel_bf16<RT, EPI, PT>, done);
+    hipLaunchKernelGGL((gemm_panel_bf16<RT, EPI, PT>), grid, block, lds, st, a2);
 }
 
-// prompt-processing GEMM over any number of rows (needs a.rstd_in for the norm-scaled epilogues).
-// A workgroup owns WV = 8 waves x FT feature tiles (FT = 2; SwiGLU: one gate/up pair) and RT = 5..9 row
-// tiles, one workgroup per compute unit (two workgroups of 4 waves, whose chunk barriers fall at
-// different times, were 8 % slower on the 1535-row prompt pass once the weights were requested a ring
-// ahead: 46.7 vs 43.0 ms).  A launch runs in rounds of that many workgroups; a round costs about RT + 3
-// (the weight stream and chunk barriers of a workgroup do not shrink with its height), and the height
-// with the least rounds x (RT + 3) wins: 1535 prompt rows: 6 for QKV, O and down, 9 for gate/up; 144
-// rows of a batched step: 9 for QKV and gate/up (one row block, the weights pass once: 64 -> 51 us,
-// 104 -> 82 us), 5 for O and down (two row blocks fill the 256 compute units, one would leave half of
-// them idle: 28 vs 33 us, 47 vs 58 us).
-template <int EPI, int FT, int WV>
-static void launch_panel_wv(const GemmArgs &a, hipStream_t st) {
-    const int slots = cu_count() * (8 / WV);                   // workgroups resident at once
-    const int fb = ((a.plan.tasks + WV * FT - 1) / (WV * FT) + 7) / 8 * 8;
-    const int row_tiles = (a.rows + 15) / 16;
-    const int ns = a.ksplit > 1 ? a.ksplit : 1;
-    auto cost = [&](int rt) { return (long)((fb * ((row_tiles + rt - 1) / rt) * ns + slots - 1) / slots) * (rt + 3); };
-    constexpr int RT_MAX = (WV == 8) ? 9 : 8;            // (9 row tiles of accumulators need the 8-wave form's register budget)
-    int best = 5;
-    for (int rt = 6; rt <= RT_MAX; ++rt)
-        if (cost(rt) <= cost(best)) best = rt;            // (ties: fewer, taller row blocks stream the weights less often)
-    switch (best) {
-        case 5: launch_panel_cfg<5, EPI, FT, WV>(a, st); break;
-        case 6: launch_panel_cfg<6, EPI, FT, WV>(a, st); break;
-        case 7: launch_panel_cfg<7, EPI, FT, WV>(a, st); break;
-        case 8: launch_panel_cfg<8, EPI, FT, WV>(a, st); break;
-        default:
-            if constexpr (WV == 8) launch_panel_cfg<9, EPI, FT, WV>(a, st);
-            else launch_panel_cfg<8, EPI, FT, WV>(a, st);
-            break;
-    }
-    if (a.ksplit > 1) launch_splitk_finish<EPI>(a, st);
-}
-template <int EPI, int FT>
+template <int EPI>
 static void launch_panel_epi(const GemmArgs &a, hipStream_t st) {
-    launch_panel_wv<EPI, FT, 8>(a, st);
+    const PanelCut cut = panel_cut(a.plan, a.rows, a.ksplit > 1 ? a.ksplit : 1);
+    if constexpr (EPI != EPI_SWIGLU) {
+        if (cut.pt == 8) {
+            if (cut.rt == 4) launch_panel_cfg<4, EPI, 8>(a, st);
+            else launch_panel_cfg<5, EPI, 8>(a, st);
+        }
+    }
+    if (cut.pt == 16)
+        switch (cut.rt) {
+            case 4: launch_panel_cfg<4, EPI, 16>(a, st); break;
+            case 5: launch_panel_cfg<5, EPI, 16>(a, st); break;
+            case 6: launch_panel_cfg<6, EPI, 16>(a, st); break;
+            case 7: launch_panel_cfg<7, EPI, 16>(a, st); break;
+            case 8: launch_panel_cfg<8, EPI, 16>(a, st); break;
+            case 9: launch_panel_cfg<9, EPI, 16>(a, st); break;
+            default: launch_panel_cfg<10, EPI, 16>(a, st); break;
+        }
+    if (a.ksplit > 1) launch_splitk_finish<EPI>(a, st);
 }
 void launch_gemm_panel_bf16(const GemmArgs &a, hipStream_t st) {
     switch (a.epi) {
-        case EPI_RESID: launch_panel_epi<EPI_RESID, 2>(a, st); break;
-        case EPI_SWIGLU: launch_panel_epi<EPI_SWIGLU, 1>(a, st); break;
-        case EPI_QKV: launch_panel_epi<EPI_QKV, 2>(a, st); break;
-        default: launch_panel_epi<EPI_LMHEAD, 2>(a, st); break;
+        case EPI_RESID: launch_panel_epi<EPI_RESID>(a, st); break;
+        case EPI_SWIGLU: launch_panel_epi<EPI_SWIGLU>(a, st); break;
+        case EPI_QKV: launch_panel_epi<EPI_QKV>(a, st); break;
+        default: launch_panel_epi<EPI_LMHEAD>(a, st); break;
     }
 }
 
@@ -994,8 +1034,8 @@ GemmPlan make_gemm_plan(int N, int K, int tiles_per_task) {
     const int fb = (p.tasks + (tiles_per_task == 2 ? 8 : 16) - 1) / (tiles_per_task == 2 ? 8 : 16);
     int ns = (192 + fb / 2) / fb;
     ns = ns < 2 ? 2 : (ns > 8 ? 8 : ns);
-    const int chunks = (p.KSp + PANEL_KC - 1) / PANEL_KC;
-    p.n_split = ns < chunks ? ns : (chunks > 0 ? chunks : 1);
+    const int turns = (p.KSp + PANEL_TURN - 1) / PANEL_TURN;
+    p.n_split = ns < turns ? ns : (turns > 0 ? turns : 1);
     return p;
 }
 

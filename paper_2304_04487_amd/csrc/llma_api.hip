@@ -8,6 +8,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <array>
 #include <map>
 #include <string>
@@ -257,16 +258,19 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
         // attention partials: [sequences][heads][chunks][rows], up to 48 rows per sequence (longer
         // prompt passes run the walking kernel, which has no partials)
         const size_t np = (size_t)g.max_batch * H * c->nc_max * 48;
-        // partial sums of the split-K GEMM of batched steps (more than 48 rows in a step)
+        // partial sums of the split-K GEMM: batched steps of more than 48 rows, and prompt passes too short to fill
+        // the chip without a split
         const int step_rows = g.max_batch * (g.max_k + 1);
-        if (step_rows > 48) {
-            size_t tiles = 0;
-            for (const GemmPlan *pl : {&c->plan_qkv, &c->plan_o, &c->plan_gu, &c->plan_down, &c->plan_lm}) {
-                const size_t t = (size_t)pl->n_split * pl->tasks * (pl == &c->plan_gu ? 2 : 1);
-                tiles = t > tiles ? t : tiles;
-            }
-            ALLOC(c, c->part, tiles * ((step_rows + 15) / 16) * 1024);
+        size_t part = 0;
+        for (const GemmPlan *pl : {&c->plan_qkv, &c->plan_o, &c->plan_gu, &c->plan_down, &c->plan_lm}) {
+            if (step_rows > 48) part = std::max(part, panel_part_bytes(*pl, step_rows, pl->n_split));
+            if (pl != &c->plan_lm)
+                for (int rows = 49; rows < c->Pmax + 16; rows += 16) {
+                    const int r = rows < c->Pmax ? rows : c->Pmax;
+                    part = std::max(part, panel_part_bytes(*pl, (r + 15) / 16 * 16, panel_prompt_split(*pl, r)));
+                }
         }
+        if (part > 0) ALLOC(c, c->part, part);
         ALLOC(c, c->po, np * dh * 4);
         ALLOC(c, c->pm, np * 4);
         ALLOC(c, c->pl, np * 4);
@@ -538,20 +542,22 @@ static int forward_bf16(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_he
     GemmArgs base{};
     base.rows = R; base.split = c->opt_split; base.eps = g.rms_eps;
     base.rows_live = c->rows_live;                         // llma_generate, one sequence: the trigger's draft count (device)
-    // prompt passes (no LM head) and batched steps of more than 48 rows use the panel GEMM (weights
-    // streamed once for all rows); the steps in its split-K form, because a few hundred rows alone make
-    // too few workgroups to fill the chip.  Steps of up to 48 rows use the tile-K GEMM.
-    const bool panel = !lm_head || R > 48;
+    // Steps and prompt passes of up to 48 rows use the tile-K GEMM, longer ones the panel GEMM (weights streamed once
+    // for all rows): the steps in its split-K form, because a few hundred rows alone make too few workgroups to
+    // fill the chip, and so do prompt passes as far as that pays for the partial sums (7B, 189 rows: 2.01 -> 1.01 ms for
+    // four layers; 15 rows: 1.83 -> 0.44 ms through the tile-K GEMM).
+    const bool panel = R > 48;
     bool refused = false;
     auto tilek_gemm = [&](GemmArgs &ga) { refused = !launch_gemm_bf16(ga, st) || refused; };
+    auto split_of = [&](const GemmArgs &ga) { return lm_head ? ga.plan.n_split : panel_prompt_split(ga.plan, R); };
     auto panel_gemm = [&](GemmArgs &ga) {
-        if (lm_head && ga.plan.n_split > 1) { ga.ksplit = ga.plan.n_split; ga.part = c->part; }
+        if (split_of(ga) > 1) { ga.ksplit = split_of(ga); ga.part = c->part; }
         launch_gemm_panel_bf16(ga, st);
     };
     // panel GEMM whose epilogue scales by the rows' rstd: the split-K form computes it in an extra
     // workgroup of its first kernel (its finishing kernel is the reader), otherwise a launch of its own
     auto panel_norm_gemm = [&](GemmArgs &ga) {
-        if (lm_head && ga.plan.n_split > 1) ga.rstd_out = c->rstd;
+        if (split_of(ga) > 1) ga.rstd_out = c->rstd;
         else launch_rstd_rows(c->ssq, d / 16, g.rms_eps, c->rstd, R, st);
         panel_gemm(ga);
     };
