@@ -27,6 +27,11 @@ void launch_gemm_f32(const GemmArgs &a, hipStream_t st);
 void launch_attn_f32(const AttnArgs &a, hipStream_t st);
 
 // ---- shared small kernels (kernels_misc.hip)
+struct HostIo {               // pinned host memory the kernels of a step read and write directly (device addresses)
+    int *slot, *keff, *T, *pending, *lo_from;   // in, [n_seqs]: what the host knows about each sequence of a verification step
+    int *draft;                          // in, [n_seqs][max_k]
+    int *nacc, *next, *emit;             // out: [n_seqs], [n_seqs], [n_seqs][max_k+1]
+};
 struct StepState {            // device pointers describing the rows of the step in flight
     int *row_tok, *row_pos, *row_slot;   // [R]
     float *row_cs;                       // [R][head_dim/2][2] (cos, sin) of each row's position
@@ -34,18 +39,20 @@ struct StepState {            // device pointers describing the rows of the step
     int *batch_slots;                    // [n_seqs]
     int *keff;                           // [n_seqs] drafts actually used per sequence
     int *draft;                          // [n_seqs][max_k]
-    int *nacc, *next, *emit;             // results: [n_seqs], [n_seqs], [n_seqs][max_k+1]
-    int *otok;                           // [R] arg max per row
+    int *lo_from;                        // [max_batch], may be null (see AttnArgs)
+    HostIo io;
 };
 struct GenState {             // device-resident state of llma_generate, one per sequence of the batch
     int *y; int *n_out; int *n_steps; int *trace;  // y[max_new], trace[max_new][4]
     int *cur;                            // [2] (doc, pos) of the trigger of the step in flight
+    int *host_count; int host_stride;    // pinned: [2][host_stride], n_out after the even / odd steps
     const int *ref; const int *doc_offsets; int ref_len, n_docs;
     int n, k, max_new;
     const int *prompt;                   // device copy of the prompt (prefill)
 };
 
-// rows of a verify step: row (b, j) = pending[slot_b] (j = 0) or draft[b][j-1]; pos = T[slot_b] + j
+// rows of a step: row (b, j) = pending[slot_b] (j = 0) or draft[b][j-1]; pos = T[slot_b] + j.  A verification step
+// takes all of that from s.io and brings the device's copies up to date;
 // generation steps (gen_dev set): the drafts are those of the best of part[b][0 .. spans), and keff / draft are filled
 void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, const GenState *gen_dev,
                             const unsigned long long *part, int spans, hipStream_t st);

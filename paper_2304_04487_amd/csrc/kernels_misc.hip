@@ -153,19 +153,42 @@ void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *do
 // ---------------------------------------------------------------------------------------------
 // row set-up
 // ---------------------------------------------------------------------------------------------
+// Host memory is read and written by these kernels directly, a handful of words per sequence: every copy between host and
+// device was a launch of its own (3.6 us on the device, more on the host), six to nine of them per verification step.
+// A four-layer 7B step of one row: 474 -> AA us per call, 16 sequences: BB -> CC us.
+__device__ __forceinline__ int host_read(const int *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+__device__ __forceinline__ void host_write(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+
 // one workgroup per row; also copies the row's rotary (cos, sin) pairs out of the position table.
 // Generation steps (gp set): the spans' trigger keys are merged here, by every row's workgroup for itself (a
 // handful of loads, instead of a launch between the scan and this one); the first row's publishes keff, the
-// drafts and the trigger's place.
+// drafts and the trigger's place.  Verification steps: everything about the sequence comes from s.io, and the first
+// row's workgroup brings the device's copies up to date.
 __global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m, int max_k, const float *cs, int half,
                                                               const GenState *gp, const unsigned long long *part, int spans) {
     const int idx = blockIdx.x;
     const int b = idx / m, j = idx % m;
-    const int slot = s.batch_slots[b];
-    const int pos = s.T[slot] + j;
-    for (int i = threadIdx.x; i < 2 * half; i += 256) s.row_cs[(size_t)idx * 2 * half + i] = cs[(size_t)pos * 2 * half + i];
-    int keff, tok = s.pending[slot];
-    if (gp != nullptr) {
+    int slot, T, keff, tok;
+    if (gp == nullptr) {
+        const int pending = host_read(s.io.pending + b), draft = host_read(s.io.draft + b * max_k + (j > 0 ? j - 1 : 0));
+        slot = host_read(s.io.slot + b);
+        T = host_read(s.io.T + b);
+        keff = host_read(s.io.keff + b);
+        tok = j == 0 ? pending : draft;
+        if (j == 0) {
+            if (threadIdx.x == 0) {
+                s.batch_slots[b] = slot;
+                s.keff[b] = keff;
+                s.T[slot] = T;
+                s.pending[slot] = pending;
+                if (s.lo_from != nullptr) s.lo_from[slot] = host_read(s.io.lo_from + b);
+            }
+            for (int t = threadIdx.x; t < keff; t += 256) s.draft[b * max_k + t] = host_read(s.io.draft + b * max_k + t);
+        }
+    } else {
+        slot = s.batch_slots[b];
+        T = s.T[slot];
+        tok = s.pending[slot];
         const GenState G = gp[b];
         unsigned long long best = 0ull;
         for (int t = threadIdx.x; t < spans; t += 256) {
@@ -188,10 +211,9 @@ __global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m
             }
         }
         if (j == 0 && threadIdx.x == 0) s.keff[b] = keff;
-    } else {
-        keff = s.keff[b];
-        if (j > 0 && j <= keff) tok = s.draft[b * max_k + j - 1];
     }
+    const int pos = T + j;
+    for (int i = threadIdx.x; i < 2 * half; i += 256) s.row_cs[(size_t)idx * 2 * half + i] = cs[(size_t)pos * 2 * half + i];
     if (threadIdx.x == 0) {
         s.row_tok[idx] = j <= keff ? tok : 0;                     // rows past keff are padding
         s.row_pos[idx] = pos;
@@ -345,12 +367,15 @@ __global__ __launch_bounds__(ACCEPT_THREADS) void argmax_accept_kernel(const flo
     if (gen != nullptr && n_out >= gen->max_new) return;         // a finished sequence / a step enqueued past the end: leave all state alone
     const unsigned long long same = __ballot(lane < keff && o[lane < keff ? lane : 0] == draft);
     const int a = __ffsll(~same) - 1;                            // (lane keff <= 32 never agrees)
-    if (lane <= keff) s.otok[(size_t)b * m + lane] = o[lane];
-    if (lane <= a) s.emit[b * (max_k + 1) + lane] = o[lane];
-    if (gen != nullptr && lane <= a) gen->y[n_out + lane] = o[lane];
+    if (lane <= a) {
+        if (gen != nullptr) gen->y[n_out + lane] = o[lane];
+        else host_write(s.io.emit + b * (max_k + 1) + lane, o[lane]);
+    }
     if (lane != 0) return;
-    s.nacc[b] = a;
-    s.next[b] = o[a];
+    if (gen == nullptr) {
+        host_write(s.io.nacc + b, a);
+        host_write(s.io.next + b, o[a]);
+    }
     s.T[slot] += a + 1;
     s.pending[slot] = o[a];
     if (gen != nullptr) {
@@ -359,8 +384,13 @@ __global__ __launch_bounds__(ACCEPT_THREADS) void argmax_accept_kernel(const flo
         gen->trace[st * 4 + 1] = a + 1;
         gen->trace[st * 4 + 2] = keff > 0 ? gen->cur[0] : -1;
         gen->trace[st * 4 + 3] = keff > 0 ? gen->cur[1] : -1;
-        *gen->n_out = n_out + a + 1;
+        const int now = n_out + a + 1;
+        *gen->n_out = now;
         *gen->n_steps = st + 1;
+        // the host reads the count of step st after that step's event, while the next step may be running: two places
+        // in turn; the last step of a sequence fills both
+        host_write(gen->host_count + (size_t)(st & 1) * gen->host_stride, now);
+        if (now >= gen->max_new) host_write(gen->host_count + (size_t)((st & 1) ^ 1) * gen->host_stride, now);
     }
 }
 void launch_argmax_accept(const float *pval, const int *pidx, int n_part, const StepState &s, int n_seqs, int m,

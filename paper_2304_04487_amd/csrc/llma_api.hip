@@ -39,7 +39,9 @@ struct llma_ctx {
     hipStream_t run_st = nullptr;      // where the launchers enqueue: st, or cap_st while capturing
     hipStream_t cap_st = nullptr;      // private stream used only to capture step graphs
     std::map<GraphKey, GraphSlot> graphs;
-    int *pin_counts = nullptr;         // pinned host ints the decoding loop's output counts are copied into
+    int *pin = nullptr;                // pinned host memory of steps: HostIo's arrays, then the decoding loop's output counts [2][max_batch]
+    HostIo host{};                     // host addresses of the arrays (s.io: the device's)
+    int *pin_counts = nullptr, *pin_counts_dev = nullptr;
     hipEvent_t cnt_ev[2] = {nullptr, nullptr};
     bool bf16 = false;
     std::vector<void *> allocs;
@@ -83,7 +85,10 @@ struct llma_ctx {
     int *gen_counters = nullptr;                  // n_out[max_batch], n_steps[max_batch], cur[max_batch][2], prefill base
     int cap_prompt = 0, cap_ref = 0, cap_part = 0, cap_docs = 0, cap_y = 0, cap_trace = 0;
 
+    // what the host knows about every slot; the device's copies (s.T, s.pending, lo_from) are brought up to date by the
+    // next verification step, which carries them, or by sync_state before anything else reads them
     std::vector<int> T_host, pending_host;
+    std::vector<char> stale;
     // Caches imported as bf16 values have all-zero lo planes: positions below lo_from[slot] (device
     // ints, host mirror) need no lo reads.  It is set when all layers of a slot have been imported
     // with one length and nothing was computed on the slot in between (imp_len records the lengths
@@ -296,10 +301,6 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
     ALLOC(c, s.batch_slots, g.max_batch * 4);
     ALLOC(c, s.keff, g.max_batch * 4);
     ALLOC(c, s.draft, (size_t)g.max_batch * (g.max_k + 1) * 4);
-    ALLOC(c, s.nacc, g.max_batch * 4);
-    ALLOC(c, s.next, g.max_batch * 4);
-    ALLOC(c, s.emit, (size_t)g.max_batch * m_max * 4);
-    ALLOC(c, s.otok, Rp * 4);
     HIP_TRY(c, hipMemsetAsync(s.T, 0, g.max_batch * 4, c->st));
     HIP_TRY(c, hipMemsetAsync(s.pending, 0xFF, g.max_batch * 4, c->st));
     HIP_TRY(c, hipMemsetAsync(s.keff, 0, g.max_batch * 4, c->st));
@@ -309,12 +310,28 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
     ALLOC(c, c->gen_counters, (size_t)(4 * g.max_batch + 4) * 4);
     c->T_host.assign(g.max_batch, 0);
     c->pending_host.assign(g.max_batch, -1);
+    c->stale.assign(g.max_batch, 0);
     c->lo_from_host.assign(g.max_batch, 0);
     c->imp_len.assign((size_t)g.max_batch * g.n_layers, -1);
     ALLOC(c, c->lo_from, g.max_batch * 4);
     HIP_TRY(c, hipMemsetAsync(c->lo_from, 0, g.max_batch * 4, c->st));
+    s.lo_from = c->lo_from;
     HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_st, hipStreamNonBlocking));
-    HIP_TRY(c, hipHostMalloc((void **)&c->pin_counts, (size_t)2 * g.max_batch * sizeof(int), hipHostMallocDefault));
+    {
+        const size_t B = g.max_batch, sizes[9] = {B, B, B, B, B, B * (g.max_k + 1), B, B, B * m_max};
+        size_t words = 2 * B;
+        for (size_t n : sizes) words += n;
+        HIP_TRY(c, hipHostMalloc((void **)&c->pin, words * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent));
+        memset(c->pin, 0, words * sizeof(int));
+        int *dev = nullptr;
+        HIP_TRY(c, hipHostGetDevicePointer((void **)&dev, c->pin, 0));
+        int **h[9] = {&c->host.slot, &c->host.keff, &c->host.T, &c->host.pending, &c->host.lo_from, &c->host.draft, &c->host.nacc, &c->host.next, &c->host.emit};
+        int **d[9] = {&s.io.slot, &s.io.keff, &s.io.T, &s.io.pending, &s.io.lo_from, &s.io.draft, &s.io.nacc, &s.io.next, &s.io.emit};
+        size_t at = 0;
+        for (int i = 0; i < 9; at += sizes[i], ++i) { *h[i] = c->pin + at; *d[i] = dev + at; }
+        c->pin_counts = c->pin + at;
+        c->pin_counts_dev = dev + at;
+    }
     HIP_TRY(c, hipEventCreateWithFlags(&c->cnt_ev[0], hipEventDisableTiming));
     HIP_TRY(c, hipEventCreateWithFlags(&c->cnt_ev[1], hipEventDisableTiming));
     HIP_TRY(c, hipStreamSynchronize(c->st));
@@ -469,7 +486,7 @@ extern "C" int llma_destroy(llma_ctx *c) {
     (void)hipStreamSynchronize(c->st);
     for (auto &g : c->graphs) if (g.second.exec) (void)hipGraphExecDestroy(g.second.exec);
     if (c->cap_st) (void)hipStreamDestroy(c->cap_st);
-    if (c->pin_counts) (void)hipHostFree(c->pin_counts);
+    if (c->pin) (void)hipHostFree(c->pin);
     for (int i = 0; i < 2; ++i) if (c->cnt_ev[i]) (void)hipEventDestroy(c->cnt_ev[i]);
     for (auto &e : c->events) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }
     for (void *p : c->allocs) (void)hipFree(p);
@@ -695,8 +712,10 @@ static int push_state(llma_ctx *c, int seq) {       // host mirror -> device
     HIP_TRY(c, hipMemcpyAsync(c->s.pending + seq, &c->pending_host[seq], 4, hipMemcpyHostToDevice, c->st));
     HIP_TRY(c, hipMemcpyAsync(c->lo_from + seq, &c->lo_from_host[seq], 4, hipMemcpyHostToDevice, c->st));
     HIP_TRY(c, hipStreamSynchronize(c->st));
+    c->stale[seq] = 0;
     return LLMA_OK;
 }
+static int sync_state(llma_ctx *c, int seq) { return c->stale[seq] ? push_state(c, seq) : LLMA_OK; }
 // something is about to be computed on the slot: the record of imported lengths no longer describes a pure import
 static void forget_imports(llma_ctx *c, int seq) {
     for (int l = 0; l < c->cfg.n_layers; ++l) c->imp_len[(size_t)seq * c->cfg.n_layers + l] = -1;
@@ -709,12 +728,14 @@ extern "C" int llma_reset(llma_ctx *c, int32_t seq) {
     c->pending_host[seq] = -1;
     c->lo_from_host[seq] = 0;
     forget_imports(c, seq);
-    return push_state(c, seq);
+    c->stale[seq] = 1;
+    return LLMA_OK;
 }
 
 extern "C" int llma_get_state(llma_ctx *c, int32_t seq, int32_t *T, int32_t *pending) {
     int rc = check_slot(c, seq, "llma_get_state");
     if (rc) return rc;
+    if ((rc = sync_state(c, seq))) return rc;
     int t = 0, p = -1;
     HIP_TRY(c, hipMemcpyAsync(&t, c->s.T + seq, 4, hipMemcpyDeviceToHost, c->st));
     HIP_TRY(c, hipMemcpyAsync(&p, c->s.pending + seq, 4, hipMemcpyDeviceToHost, c->st));
@@ -731,7 +752,8 @@ extern "C" int llma_truncate(llma_ctx *c, int32_t seq, int32_t new_len) {
         return fail(c, LLMA_E_RANGE, "llma_truncate: new length %d outside [0, T = %d]", new_len, c->T_host[seq]);
     c->T_host[seq] = new_len;
     if (c->lo_from_host[seq] > new_len) c->lo_from_host[seq] = new_len;    // rows written from here on have lo planes
-    return push_state(c, seq);
+    c->stale[seq] = 1;
+    return LLMA_OK;
 }
 
 extern "C" int llma_set_pending(llma_ctx *c, int32_t seq, int32_t token) {
@@ -739,7 +761,8 @@ extern "C" int llma_set_pending(llma_ctx *c, int32_t seq, int32_t token) {
     if (rc) return rc;
     if (token < 0 || token >= c->cfg.vocab) return fail(c, LLMA_E_RANGE, "llma_set_pending: token %d outside [0,%d)", token, c->cfg.vocab);
     c->pending_host[seq] = token;
-    return push_state(c, seq);
+    c->stale[seq] = 1;
+    return LLMA_OK;
 }
 
 extern "C" int llma_kv_import(llma_ctx *c, int32_t seq, int32_t layer, const void *k, const void *v, int32_t len) {
@@ -810,6 +833,7 @@ extern "C" int llma_prefill(llma_ctx *c, int32_t seq, const int32_t *prompt, int
     if ((rc = ensure_cap(c, &c->gen_prompt, &c->cap_prompt, len))) return rc;
     HIP_TRY(c, hipMemcpyAsync(c->gen_prompt, prompt, (size_t)len * 4, hipMemcpyHostToDevice, c->st));
     forget_imports(c, seq);
+    if ((rc = sync_state(c, seq))) return rc;
     if ((rc = prefill_rows(c, seq, len - 1))) return rc;
     c->pending_host[seq] = prompt[len - 1];
     HIP_TRY(c, hipMemcpyAsync(c->s.pending + seq, &c->pending_host[seq], 4, hipMemcpyHostToDevice, c->st));
@@ -885,22 +909,23 @@ extern "C" int llma_verify_step_batch(llma_ctx *c, int32_t n_seqs, const int32_t
     if (c->logits_dump && n_seqs * (k + 1) > c->dump_rows)
         return fail(c, LLMA_E_RANGE, "llma_verify_step: logits dump holds %d rows, step has %d", c->dump_rows, n_seqs * (k + 1));
     const int m = k + 1, mk = g.max_k;
-    hipStream_t st = c->st;
-    std::vector<int> keff(n_seqs, k), dr((size_t)n_seqs * (mk > 0 ? mk : 1), 0);
-    for (int b = 0; b < n_seqs; ++b)
-        for (int j = 0; j < k; ++j) dr[(size_t)b * mk + j] = drafts[(size_t)b * k + j];
-    HIP_TRY(c, hipMemcpyAsync(c->s.batch_slots, seqs, (size_t)n_seqs * 4, hipMemcpyHostToDevice, st));
-    HIP_TRY(c, hipMemcpyAsync(c->s.keff, keff.data(), (size_t)n_seqs * 4, hipMemcpyHostToDevice, st));
-    if (k > 0) HIP_TRY(c, hipMemcpyAsync(c->s.draft, dr.data(), (size_t)n_seqs * mk * 4, hipMemcpyHostToDevice, st));
+    const HostIo &io = c->host;                // (nothing reads or writes it between two steps: every step is waited for)
+    for (int b = 0; b < n_seqs; ++b) {
+        io.slot[b] = seqs[b];
+        io.keff[b] = k;
+        io.T[b] = c->T_host[seqs[b]];
+        io.pending[b] = c->pending_host[seqs[b]];
+        io.lo_from[b] = c->lo_from_host[seqs[b]];
+        for (int j = 0; j < k; ++j) io.draft[(size_t)b * mk + j] = drafts[(size_t)b * k + j];
+        io.nacc[b] = -1;                       // (checked below)
+    }
     for (int b = 0; b < n_seqs; ++b) forget_imports(c, seqs[b]);
     int rc = run_step(c, STEP_VERIFY, n_seqs, m, t_max, n_seqs == 1 ? seqs[0] : 0);
     if (rc) return rc;
-    std::vector<int> nacc(n_seqs), nxt(n_seqs), em((size_t)n_seqs * (mk + 1));
-    HIP_TRY(c, hipMemcpyAsync(nacc.data(), c->s.nacc, (size_t)n_seqs * 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipMemcpyAsync(nxt.data(), c->s.next, (size_t)n_seqs * 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipMemcpyAsync(em.data(), c->s.emit, (size_t)n_seqs * (mk + 1) * 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipStreamSynchronize(st));
+    HIP_TRY(c, hipStreamSynchronize(c->st));
     HIP_TRY(c, hipGetLastError());
+    const int *const nacc = io.nacc, *const nxt = io.next, *const em = io.emit;
+    for (int b = 0; b < n_seqs; ++b) c->stale[seqs[b]] = 0;
     for (int b = 0; b < n_seqs; ++b) {
         bool ok = nacc[b] >= 0 && nacc[b] <= k && nxt[b] >= 0 && nxt[b] < g.vocab;
         for (int j = 0; ok && j <= nacc[b]; ++j) ok = em[(size_t)b * (mk + 1) + j] >= 0 && em[(size_t)b * (mk + 1) + j] < g.vocab;
@@ -992,6 +1017,7 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
     }
     HIP_TRY(c, hipMemcpyAsync(c->gen_doc_offsets, dof_host.data(), dof_host.size() * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(c, hipMemsetAsync(c->gen_counters, 0, (size_t)(4 * g.max_batch + 4) * 4, st));
+    memset(c->pin_counts, 0, (size_t)2 * g.max_batch * sizeof(int));
     std::vector<GenState> G(n_seqs);
     int *const cnt_out = c->gen_counters, *const cnt_steps = c->gen_counters + g.max_batch, *const cnt_cur = c->gen_counters + 2 * g.max_batch;
     for (int b = 0; b < n_seqs; ++b) {
@@ -999,6 +1025,7 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
         GenState &s = G[b];
         s.y = c->gen_y + (size_t)b * ystride; s.trace = c->gen_trace + (size_t)4 * b * ystride;
         s.n_out = cnt_out + b; s.n_steps = cnt_steps + b; s.cur = cnt_cur + 2 * b;
+        s.host_count = c->pin_counts_dev + b; s.host_stride = g.max_batch;
         s.ref = c->gen_ref + ref_start[b]; s.doc_offsets = c->gen_doc_offsets + dof_at[b];
         s.ref_len = rlen; s.n_docs = nd; s.n = n; s.k = k; s.max_new = max_new; s.prompt = c->gen_prompt;
     }
@@ -1036,7 +1063,6 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
         for (int b = 0; b < n_seqs; ++b) t_max = T0[b] + produced[b] > t_max ? T0[b] + produced[b] : t_max;
         int r = run_step(c, STEP_GEN, n_seqs, m, t_max + 2 * m, n_seqs == 1 ? seqs[0] : 0);
         if (r) return r;
-        HIP_TRY(c, hipMemcpyAsync(c->pin_counts + (size_t)(enq & 1) * g.max_batch, cnt_out, (size_t)n_seqs * 4, hipMemcpyDeviceToHost, st));
         HIP_TRY(c, hipEventRecord(c->cnt_ev[enq & 1], st));
         ++enq;
         return LLMA_OK;
@@ -1047,7 +1073,7 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
         HIP_TRY(c, hipEventSynchronize(c->cnt_ev[steps & 1]));
         bool done = true;
         for (int b = 0; b < n_seqs; ++b) {
-            const int now = c->pin_counts[(size_t)(steps & 1) * g.max_batch + b];
+            const int now = __atomic_load_n(&c->pin_counts[(size_t)(steps & 1) * g.max_batch + b], __ATOMIC_ACQUIRE);
             if (now > max_new || now < produced[b] || (now == produced[b] && produced[b] < max_new))
                 return fail(c, LLMA_E_HIP, "llma_generate: device output count of sequence %d went %d -> %d", b, produced[b], now);
             produced[b] = now;
