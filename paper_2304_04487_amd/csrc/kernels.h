@@ -39,7 +39,7 @@ struct StepState {            // device pointers describing the rows of the step
     int *batch_slots;                    // [n_seqs]
     int *keff;                           // [n_seqs] drafts actually used per sequence
     int *draft;                          // [n_seqs][max_k]
-    int *lo_from;                        // [max_batch], may be null (see AttnArgs)
+    int *lo_from;                        // [max_batch] (see AttnArgs)
     HostIo io;
 };
 struct GenState {             // device-resident state of llma_generate, one per sequence of the batch
@@ -51,8 +51,9 @@ struct GenState {             // device-resident state of llma_generate, one per
     const int *prompt;                   // device copy of the prompt (prefill)
 };
 
-// rows of a step: row (b, j) = pending[slot_b] (j = 0) or draft[b][j-1]; pos = T[slot_b] + j.  A verification step
-// takes all of that from s.io and brings the device's copies up to date;
+// verification step: slots, lengths, pending tokens and drafts from s.io (the host's) into the device's copies
+void launch_take_step(const StepState &s, int n_seqs, int max_k, hipStream_t st);
+// rows of a step: row (b, j) = pending[slot_b] (j = 0) or draft[b][j-1]; pos = T[slot_b] + j;
 // generation steps (gen_dev set): the drafts are those of the best of part[b][0 .. spans), and keff / draft are filled
 void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, const GenState *gen_dev,
                             const unsigned long long *part, int spans, hipStream_t st);

@@ -155,40 +155,41 @@ void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *do
 // ---------------------------------------------------------------------------------------------
 // Host memory is read and written by these kernels directly, a handful of words per sequence: every copy between host and
 // device was a launch of its own (3.6 us on the device, more on the host), six to nine of them per verification step.
-// A four-layer 7B step of one row: 474 -> AA us per call, 16 sequences: BB -> CC us.
-__device__ __forceinline__ int host_read(const int *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+// A four-layer 7B step of one row: 474 -> 426 us per call.  One workgroup reads, each word once: uncached words asked for by
+// every thread that needs them cost 135 us at 144 rows.
 __device__ __forceinline__ void host_write(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+
+// verification steps: brings the device's copies of what the host knows up to date
+__global__ __launch_bounds__(256) void take_step_kernel(StepState s, int n_seqs, int max_k) {
+    for (int i = threadIdx.x; i < n_seqs * max_k; i += 256) s.draft[i] = s.io.draft[i];
+    for (int b = threadIdx.x; b < n_seqs; b += 256) {
+        const int slot = s.io.slot[b], keff = s.io.keff[b], T = s.io.T[b], pending = s.io.pending[b], lo_from = s.io.lo_from[b];
+        s.batch_slots[b] = slot;
+        s.keff[b] = keff;
+        s.T[slot] = T;
+        s.pending[slot] = pending;
+        s.lo_from[slot] = lo_from;
+    }
+}
+void launch_take_step(const StepState &s, int n_seqs, int max_k, hipStream_t st) {
+    hipLaunchKernelGGL(take_step_kernel, dim3(1), dim3(256), 0, st, s, n_seqs, max_k);
+}
 
 // one workgroup per row; also copies the row's rotary (cos, sin) pairs out of the position table.
 // Generation steps (gp set): the spans' trigger keys are merged here, by every row's workgroup for itself (a
 // handful of loads, instead of a launch between the scan and this one); the first row's publishes keff, the
-// drafts and the trigger's place.  Verification steps: everything about the sequence comes from s.io, and the first
-// row's workgroup brings the device's copies up to date.
+// drafts and the trigger's place.
 __global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m, int max_k, const float *cs, int half,
                                                               const GenState *gp, const unsigned long long *part, int spans) {
     const int idx = blockIdx.x;
     const int b = idx / m, j = idx % m;
-    int slot, T, keff, tok;
+    const int slot = s.batch_slots[b];
+    const int T = s.T[slot];
+    int keff, tok = s.pending[slot];
     if (gp == nullptr) {
-        const int pending = host_read(s.io.pending + b), draft = host_read(s.io.draft + b * max_k + (j > 0 ? j - 1 : 0));
-        slot = host_read(s.io.slot + b);
-        T = host_read(s.io.T + b);
-        keff = host_read(s.io.keff + b);
-        tok = j == 0 ? pending : draft;
-        if (j == 0) {
-            if (threadIdx.x == 0) {
-                s.batch_slots[b] = slot;
-                s.keff[b] = keff;
-                s.T[slot] = T;
-                s.pending[slot] = pending;
-                if (s.lo_from != nullptr) s.lo_from[slot] = host_read(s.io.lo_from + b);
-            }
-            for (int t = threadIdx.x; t < keff; t += 256) s.draft[b * max_k + t] = host_read(s.io.draft + b * max_k + t);
-        }
+        keff = s.keff[b];
+        if (j > 0) tok = s.draft[b * max_k + j - 1];
     } else {
-        slot = s.batch_slots[b];
-        T = s.T[slot];
-        tok = s.pending[slot];
         const GenState G = gp[b];
         unsigned long long best = 0ull;
         for (int t = threadIdx.x; t < spans; t += 256) {

@@ -655,6 +655,7 @@ static int step_body(llma_ctx *c, int kind, int n_seqs, int m, int n_chunks, int
     const GenState *gen = kind == STEP_GEN ? c->gen_dev : nullptr;
     unsigned long long *part = (unsigned long long *)c->gen_part;
     if (gen) launch_trigger_scan(gen, n_seqs, c->gen_spans, part, st);
+    else launch_take_step(c->s, n_seqs, mk, st);
     launch_setup_step_rows(c->s, n_seqs, m, mk, c->cs_table, c->cfg.head_dim / 2, gen, part, c->gen_spans, st);
     int rc = forward(c, n_seqs, m, n_chunks, true, slot);
     if (rc) return rc;
