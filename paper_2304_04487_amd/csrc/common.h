@@ -101,7 +101,7 @@ __host__ __device__ __forceinline__ size_t vcache_off(int pos, int c, int dh) {
 }
 
 // ---- launcher argument structs --------------------------------------------------------------
-enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_QKV = 4 };
+enum { EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_QKV = 4 };
 
 // how one weight matrix is cut into work: a function of its shape only (never of the row count)
 struct GemmPlan {
@@ -134,8 +134,8 @@ struct GemmArgs {          // bf16 path (fields marked f32 are used by the fp32 
     int panel_rb;          // panel GEMM only: row blocks (set by the launcher)
     int ksplit;            // panel GEMM only: > 1 = the K axis is cut into this many ranges of k-chunks, partial sums via `part`
     float *part;           //   [ksplit][tiles][row tiles][64 lanes x 4] fp32 partial sums (register images)
-    // EPI_STORE (f32) / EPI_RESID / EPI_LMHEAD
-    float *out;            // STORE: [rows][N]; RESID: h[rows][N] += ; LMHEAD: optional logits dump (may be null)
+    // EPI_RESID / EPI_LMHEAD
+    float *out;            // RESID: h[rows][N] += ; LMHEAD: optional logits dump (may be null)
     // EPI_RESID: prepares the next RMSNorm'd GEMM input
     const float *gain;     // [N] gains of the next norm
     void *nx_hi, *nx_lo;   // tiled planes over N columns with nx_KSp k-steps per row tile: (h * gain) hi / lo

@@ -63,11 +63,6 @@ void launch_setup_prefill_rows(const StepState &s, const int *prompt_dev, const 
 void launch_advance_T(const StepState &s, int slot, int by, hipStream_t st);
 // fp32 path: h[r][:] = embed[row_tok[r]][:]
 void launch_embed_f32(const float *embed, const int *row_tok, float *h, int R, int d, hipStream_t st);
-// fp32 path: x = RMSNorm(h; g)
-void launch_rmsnorm_f32(const float *h, const float *g, float eps, float *out, int R, int d, hipStream_t st);
-// fp32 path: rotate q, k of every row at its position, write q, append k and v to the cache
-void launch_rope_kv_f32(const float *qkv, const StepState &s, const float *cs_table, float *q_out, float *kc, float *vc,
-                        int R, int H, int dh, int max_seq, hipStream_t st);
 // final arg max over the per-row partials, then prefix accept + KV truncate + bookkeeping
 void launch_argmax_accept(const float *pval, const int *pidx, int n_part, const StepState &s, int n_seqs, int m,
                           int max_k, int vocab, const GenState *gen /*device array [n_seqs] or null*/, hipStream_t st);

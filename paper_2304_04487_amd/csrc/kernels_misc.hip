@@ -1,5 +1,4 @@
-// Small kernels around the GEMMs and attention: row set-up, the fp32 path's embedding gather /
-// RMSNorm / RoPE + KV append, the vocabulary arg max with the prefix-accept / KV-truncate decision
+// Small kernels around the GEMMs and attention: row set-up, the fp32 path's embedding gather, the vocabulary arg max with the prefix-accept / KV-truncate decision
 // (paper: Algorithm 1, the compare loop after the verification forward), and the n-gram
 // trigger scan over the reference (paper: Method, the match that starts a copy).
 #include "common.h"
@@ -248,7 +247,7 @@ void launch_advance_T(const StepState &s, int slot, int by, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// fp32 path: embedding gather, RMSNorm, RoPE + KV append as separate small kernels
+// fp32 path: embedding gather
 // ---------------------------------------------------------------------------------------------
 __global__ void embed_f32_kernel(const float *embed, const int *row_tok, float *h, int d) {
     int r = blockIdx.x;
@@ -257,53 +256,6 @@ __global__ void embed_f32_kernel(const float *embed, const int *row_tok, float *
 }
 void launch_embed_f32(const float *embed, const int *row_tok, float *h, int R, int d, hipStream_t st) {
     hipLaunchKernelGGL(embed_f32_kernel, dim3(R), dim3(256), 0, st, embed, row_tok, h, d);
-}
-
-// one workgroup per row; fixed summation order (thread-strided, butterfly, wave order)
-__global__ __launch_bounds__(256) void rmsnorm_f32_kernel(const float *__restrict__ h, const float *__restrict__ g, float eps,
-                                                          float *__restrict__ out, int d) {
-    __shared__ float part[4];
-    const int r = blockIdx.x;
-    const float *x = h + (size_t)r * d;
-    float ss = 0.f;
-    for (int c = threadIdx.x; c < d; c += 256) ss += x[c] * x[c];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    float tot = ((part[0] + part[1]) + part[2]) + part[3];
-    float rstd = 1.0f / sqrtf(tot / (float)d + eps);
-    for (int c = threadIdx.x; c < d; c += 256) out[(size_t)r * d + c] = x[c] * rstd * g[c];
-}
-void launch_rmsnorm_f32(const float *h, const float *g, float eps, float *out, int R, int d, hipStream_t st) {
-    hipLaunchKernelGGL(rmsnorm_f32_kernel, dim3(R), dim3(256), 0, st, h, g, eps, out, d);
-}
-
-// grid (rows, heads), head_dim/2 threads: thread i rotates the pair (i, i + head_dim/2) of q and k
-// by angle pos * theta^(-2i/head_dim) (table built on the host)
-__global__ void rope_kv_f32_kernel(const float *__restrict__ qkv, StepState s, const float *__restrict__ cs,
-                                   float *q_out, float *kc, float *vc, int H, int dh, int max_seq) {
-    const int r = blockIdx.x, hh = blockIdx.y, i = threadIdx.x;
-    const int half = dh >> 1, d = H * dh;
-    const int pos = s.row_pos[r], slot = s.row_slot[r];
-    const float c = cs[((size_t)pos * half + i) * 2], sn = cs[((size_t)pos * half + i) * 2 + 1];
-    const float *row = qkv + (size_t)r * 3 * d;
-    const float q1 = row[hh * dh + i], q2 = row[hh * dh + i + half];
-    const float k1 = row[d + hh * dh + i], k2 = row[d + hh * dh + i + half];
-    const float v1 = row[2 * d + hh * dh + i], v2 = row[2 * d + hh * dh + i + half];
-    const size_t head_base = ((size_t)slot * H + hh) * (size_t)max_seq * dh;
-    float *q = q_out + (size_t)r * d + hh * dh;
-    q[i] = q1 * c - q2 * sn;
-    q[i + half] = q2 * c + q1 * sn;
-    float *kp = kc + head_base + (size_t)pos * dh, *vp = vc + head_base + (size_t)pos * dh;
-    kp[i] = k1 * c - k2 * sn;
-    kp[i + half] = k2 * c + k1 * sn;
-    vp[i] = v1;
-    vp[i + half] = v2;
-}
-void launch_rope_kv_f32(const float *qkv, const StepState &s, const float *cs_table, float *q_out, float *kc, float *vc,
-                        int R, int H, int dh, int max_seq, hipStream_t st) {
-    hipLaunchKernelGGL(rope_kv_f32_kernel, dim3(R, H), dim3(dh / 2), 0, st, qkv, s, cs_table, q_out, kc, vc, H, dh, max_seq);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -62,7 +62,7 @@ struct llma_ctx {
 
     // scratch for up to Rmax rows.  bf16: x/q/att/act are tiled hi/lo planes; fp32: row-major in *_hi
     int Rmax = 0;
-    float *h = nullptr, *qkv = nullptr;
+    float *h = nullptr;
     void *xhi = nullptr, *xlo = nullptr, *q = nullptr, *q_lo = nullptr, *att_hi = nullptr, *att_lo = nullptr, *act_hi = nullptr, *act_lo = nullptr;
     float *po = nullptr, *pm = nullptr, *pl = nullptr;
     const int *rows_live = nullptr;    // set per step: device count of live rows - 1 (generation, one sequence) or null
@@ -280,8 +280,7 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
         ALLOC(c, c->pm, np * 4);
         ALLOC(c, c->pl, np * 4);
     } else {
-        if ((rc = zalloc((void **)&c->qkv, Rp * 3 * d * 4)) || (rc = zalloc(&c->xhi, Rp * d * 4)) || (rc = zalloc(&c->q, Rp * d * 4)) ||
-            (rc = zalloc(&c->att_hi, Rp * d * 4)) || (rc = zalloc(&c->act_hi, Rp * F * 4)))
+        if ((rc = zalloc(&c->q, Rp * d * 4)) || (rc = zalloc(&c->att_hi, Rp * d * 4)) || (rc = zalloc(&c->act_hi, Rp * F * 4)))
             return rc;
     }
     for (auto &z : zero) HIP_TRY(c, hipMemsetAsync(z.first, 0, z.second, c->st));
@@ -518,28 +517,26 @@ static int forward_f32(llma_ctx *c, int n_seqs, int m, bool lm_head) {
     hipStream_t st = c->run_st;
     launch_embed_f32((const float *)c->embed, c->s.row_tok, c->h, R, d, st);
     GemmArgs ga{};
-    ga.rows = R;
+    ga.rows = R; ga.eps = g.rms_eps; ga.H = H; ga.dh = dh; ga.max_seq = c->seq_cap;
+    ga.row_pos = c->s.row_pos; ga.row_slot = c->s.row_slot; ga.row_cs = c->s.row_cs;
     AttnArgs aa{};
     aa.Qhi = c->q; aa.T = c->s.T; aa.batch_slots = c->s.batch_slots; aa.slot_const = -1; aa.n_seqs = n_seqs; aa.m = m; aa.H = H; aa.dh = dh;
     aa.max_seq = c->seq_cap; aa.scale = 1.0f / sqrtf((float)dh); aa.out_hi = c->att_hi;
-    for (int l = 0; l < L; ++l) {
-        launch_rmsnorm_f32(c->h, c->n1[l], g.rms_eps, (float *)c->xhi, R, d, st);
-        ga.W = c->wqkv[l]; ga.Xhi = c->xhi; ga.N = 3 * d; ga.K = d; ga.epi = EPI_STORE; ga.out = c->qkv;
+    for (int l = 0; l < L; ++l) {                          // (RMSNorm, RoPE and the cache append run inside the GEMMs)
+        ga.W = c->wqkv[l]; ga.Xhi = c->h; ga.N = 3 * d; ga.K = d; ga.epi = EPI_QKV; ga.gain = c->n1[l];
+        ga.q_hi = c->q; ga.k_hi = c->kc[l]; ga.v_hi = c->vc[l];
         launch_gemm_f32(ga, st);
-        launch_rope_kv_f32(c->qkv, c->s, c->cs_table, (float *)c->q, (float *)c->kc[l], (float *)c->vc[l], R, H, dh, c->seq_cap, st);
         aa.Khi = c->kc[l]; aa.Vhi = c->vc[l];
         launch_attn_f32(aa, st);
         ga.W = c->wo[l]; ga.Xhi = c->att_hi; ga.N = d; ga.K = d; ga.epi = EPI_RESID; ga.out = c->h;
         launch_gemm_f32(ga, st);
-        launch_rmsnorm_f32(c->h, c->n2[l], g.rms_eps, (float *)c->xhi, R, d, st);
-        ga.W = c->wgu[l]; ga.Xhi = c->xhi; ga.N = F; ga.K = d; ga.epi = EPI_SWIGLU; ga.out = nullptr; ga.act_hi = c->act_hi;
+        ga.W = c->wgu[l]; ga.Xhi = c->h; ga.N = F; ga.K = d; ga.epi = EPI_SWIGLU; ga.gain = c->n2[l]; ga.act_hi = c->act_hi;
         launch_gemm_f32(ga, st);
-        ga.W = c->wd[l]; ga.Xhi = c->act_hi; ga.N = d; ga.K = F; ga.epi = EPI_RESID; ga.out = c->h; ga.act_hi = nullptr;
+        ga.W = c->wd[l]; ga.Xhi = c->act_hi; ga.N = d; ga.K = F; ga.epi = EPI_RESID; ga.out = c->h;
         launch_gemm_f32(ga, st);
     }
     if (lm_head) {
-        launch_rmsnorm_f32(c->h, c->final_norm, g.rms_eps, (float *)c->xhi, R, d, st);
-        ga.W = c->lm_head; ga.Xhi = c->xhi; ga.N = V; ga.K = d; ga.epi = EPI_LMHEAD;
+        ga.W = c->lm_head; ga.Xhi = c->h; ga.N = V; ga.K = d; ga.epi = EPI_LMHEAD; ga.gain = c->final_norm;
         ga.out = c->logits_dump; ga.pval = c->pval; ga.pidx = c->pidx; ga.n_part = c->n_part;
         launch_gemm_f32(ga, st);
     }

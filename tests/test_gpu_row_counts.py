@@ -57,3 +57,28 @@ def test_step_rows(setup, seqs, k):
         got = ctx.logits(seqs * (k + 1))
         assert np.all(np.abs(got - want) <= ATOL + RTOL * np.abs(want)), float(np.abs(got - want).max())
     ctx.close()
+
+
+@pytest.mark.parametrize("d,heads,dh,ffn,vocab", [(128, 4, 32, 258, 300), (192, 3, 64, 511, 97), (256, 2, 128, 1028, 512), (640, 5, 128, 516, 64)])
+def test_fp32_shapes(d, heads, dh, ffn, vocab):
+    """FFN widths that are no multiple of 4, several head widths, more and fewer elements than a pass of 512; 1, 8, 9 and 10 rows"""
+    import paper_2304_04487_amd as llma
+    cfg = synth.ModelCfg("f32", 2, d, heads, dh, ffn, vocab, "fp32")
+    w = synth.make_weights(cfg, 41, gain_jitter=0.2)
+    om = OracleModel(cfg, w)
+    ctx = llma.Context(cfg, w, max_seq=200, max_batch=2, max_k=9)
+    ctx.enable_logits_dump(20)
+    prompt = synth.uniform_tokens(3, d, 120, vocab)
+    for k in (0, 7, 8, 9):
+        drafts = synth.uniform_tokens(4, k, k, vocab)
+        want = om.forward(np.concatenate([prompt, drafts]), om.new_cache(200), 0)[-(k + 1):]
+        for b in range(2):
+            ctx.reset(b)
+            ctx.prefill(prompt, seq=b)
+        ctx.verify_step(drafts)
+        assert np.abs(ctx.logits(k + 1) - want).max() <= 1e-4
+        ctx.reset(0)
+        ctx.prefill(prompt)
+        ctx.verify_step_batch([1, 0], np.stack([drafts, drafts]))
+        assert np.abs(ctx.logits(2 * (k + 1)) - np.concatenate([want, want])).max() <= 1e-4
+    ctx.close()
