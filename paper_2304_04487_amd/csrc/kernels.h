@@ -11,8 +11,6 @@ static inline int tilek_bucket(int rows) { return rows <= 4 ? 3 : (rows + 15) / 
 void launch_pack_weight(const void *src, void *dst, int N, int K, int KSp, int rope_dh, int d, hipStream_t st);
 void launch_kv_import_bf16(const void *k, const void *v, void *kh, void *kl, void *vh, void *vl, int H, int len, int dh,
                            int max_seq, hipStream_t st);
-void launch_embed_prep_bf16(const void *embed, const int *row_tok, const float *gain, float *h, void *nx_hi, void *nx_lo,
-                            float *ssq_out, int R, int d, int KSp, hipStream_t st);
 bool launch_gemm_bf16(const GemmArgs &a, hipStream_t st);   // false (nothing launched) unless 1 <= rows <= 48
 void launch_gemm_panel_bf16(const GemmArgs &a, hipStream_t st);
 int panel_prompt_split(const GemmPlan &p, int rows);                   // K ranges that suit a prompt pass of so many rows (1: no split)
@@ -53,16 +51,19 @@ struct GenState {             // device-resident state of llma_generate, one per
 
 // verification step: slots, lengths, pending tokens and drafts from s.io (the host's) into the device's copies
 void launch_take_step(const StepState &s, int n_seqs, int max_k, hipStream_t st);
-// rows of a step: row (b, j) = pending[slot_b] (j = 0) or draft[b][j-1]; pos = T[slot_b] + j;
-// generation steps (gen_dev set): the drafts are those of the best of part[b][0 .. spans), and keff / draft are filled
-void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, const GenState *gen_dev,
-                            const unsigned long long *part, int spans, hipStream_t st);
+struct EmbedArgs {            // what the row set-up does with a row's token: h[r] = embed[token], and for bf16 models the first GEMM's input
+    const void *embed; float *h; int d;
+    const float *gain; void *nx_hi, *nx_lo; float *ssq_out; int KSp;   // bf16 only (gain null: fp32): x = h * gain as tiled planes, sums of squares
+};
+// rows of a step: row (b, j) = pending[slot_b] (j = 0) or draft[b][j-1]; pos = T[slot_b] + j; embedded into e.h.
+// Generation steps (gen_dev set): the drafts are those of the best of part[b][0 .. spans), or with one span of the
+// reference's scan, which then runs here; keff / draft are filled
+void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, const EmbedArgs &e,
+                            const GenState *gen_dev, const unsigned long long *part, int spans, hipStream_t st);
 // rows of a prefill chunk for one slot: tokens prompt[T[slot] - *base_dev + j], pos = T[slot] + j
 void launch_setup_prefill_rows(const StepState &s, const int *prompt_dev, const int *base_dev, int m, int slot,
-                               const float *cs, int half, hipStream_t st);
+                               const float *cs, int half, const EmbedArgs &e, hipStream_t st);
 void launch_advance_T(const StepState &s, int slot, int by, hipStream_t st);
-// fp32 path: h[r][:] = embed[row_tok[r]][:]
-void launch_embed_f32(const float *embed, const int *row_tok, float *h, int R, int d, hipStream_t st);
 // final arg max over the per-row partials, then prefix accept + KV truncate + bookkeeping
 void launch_argmax_accept(const float *pval, const int *pidx, int n_part, const StepState &s, int n_seqs, int m,
                           int max_k, int vocab, const GenState *gen /*device array [n_seqs] or null*/, hipStream_t st);

@@ -103,51 +103,6 @@ void launch_kv_import_bf16(const void *k, const void *v, void *kh, void *kl, voi
 }
 
 // =============================================================================================
-// embedding gather + preparation of the first RMSNorm'd GEMM input
-// =============================================================================================
-// h[r] = E[tok_r]; x = h * gain as hi/lo tiled planes; per (row, 16-feature tile) sum of squares.
-// One thread per 16-feature tile.
-__global__ __launch_bounds__(256) void embed_prep_bf16_kernel(const bf16_t *__restrict__ embed, const int *__restrict__ row_tok,
-                                                              const float *__restrict__ gain, float *__restrict__ h,
-                                                              bf16_t *__restrict__ nx_hi, bf16_t *__restrict__ nx_lo,
-                                                              float *__restrict__ ssq_out, int d, int KSp) {
-    const int r = blockIdx.x;
-    const size_t base = (size_t)row_tok[r] * d;
-    const int n_tiles = d / 16;
-    for (int ft = threadIdx.x; ft < n_tiles; ft += 256) {
-        const u32x4 *src = (const u32x4 *)(embed + base + ft * 16);
-        u32x4 raw[2] = {src[0], src[1]};
-        float ss = 0.f;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            float v[8], x[8];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                v[2 * j] = __uint_as_float(raw[half][j] << 16);
-                v[2 * j + 1] = __uint_as_float(raw[half][j] & 0xFFFF0000u);
-            }
-            const int c0 = ft * 16 + half * 8;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) { ss += v[j] * v[j]; x[j] = v[j] * gain[c0 + j]; }
-            *(f32x4 *)(h + (size_t)r * d + c0) = (f32x4){v[0], v[1], v[2], v[3]};
-            *(f32x4 *)(h + (size_t)r * d + c0 + 4) = (f32x4){v[4], v[5], v[6], v[7]};
-            u32x2 h0, l0, h1, l1;
-            split4(x, h0, l0);
-            split4(x + 4, h1, l1);
-            const size_t o = xtile_off(r, c0, KSp);
-            *(u32x4 *)(nx_hi + o) = (u32x4){h0[0], h0[1], h1[0], h1[1]};
-            *(u32x4 *)(nx_lo + o) = (u32x4){l0[0], l0[1], l1[0], l1[1]};
-        }
-        ssq_out[(size_t)r * n_tiles + ft] = ss;
-    }
-}
-void launch_embed_prep_bf16(const void *embed, const int *row_tok, const float *gain, float *h, void *nx_hi, void *nx_lo,
-                            float *ssq_out, int R, int d, int KSp, hipStream_t st) {
-    hipLaunchKernelGGL(embed_prep_bf16_kernel, dim3(R), dim3(256), 0, st, (const bf16_t *)embed, row_tok, gain, h,
-                       (bf16_t *)nx_hi, (bf16_t *)nx_lo, ssq_out, d, KSp);
-}
-
-// =============================================================================================
 // skinny GEMM  Y[rows][N] = X[rows][K] . W[N][K]^T,  rows <= 16*NT
 // =============================================================================================
 // Two kernels share the fused epilogues below: the tile-K kernel for decoding steps (few rows,

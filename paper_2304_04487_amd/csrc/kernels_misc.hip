@@ -1,4 +1,4 @@
-// Small kernels around the GEMMs and attention: row set-up, the fp32 path's embedding gather, the vocabulary arg max with the prefix-accept / KV-truncate decision
+// Small kernels around the GEMMs and attention: row set-up with the embedding gather, the vocabulary arg max with the prefix-accept / KV-truncate decision
 // (paper: Algorithm 1, the compare loop after the verification forward), and the n-gram
 // trigger scan over the reference (paper: Method, the match that starts a copy).
 #include "common.h"
@@ -174,11 +174,49 @@ void launch_take_step(const StepState &s, int n_seqs, int max_k, hipStream_t st)
     hipLaunchKernelGGL(take_step_kernel, dim3(1), dim3(256), 0, st, s, n_seqs, max_k);
 }
 
-// one workgroup per row; also copies the row's rotary (cos, sin) pairs out of the position table.
-// Generation steps (gp set): the spans' trigger keys are merged here, by every row's workgroup for itself (a
-// handful of loads, instead of a launch between the scan and this one); the first row's publishes keff, the
-// drafts and the trigger's place.
-__global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m, int max_k, const float *cs, int half,
+// h[r] = E[tok]; bf16: x = h * gain as hi/lo tiled planes, per (row, 16-feature tile) sum of squares, one thread per tile
+template <bool BF16>
+__device__ __forceinline__ void embed_row(const EmbedArgs &e, int r, int tok) {
+    if (!BF16) {
+        const float *src = (const float *)e.embed + (size_t)tok * e.d;
+        for (int c = threadIdx.x; c < e.d; c += 256) e.h[(size_t)r * e.d + c] = src[c];
+        return;
+    }
+    const int n_tiles = e.d / 16;
+    for (int ft = threadIdx.x; ft < n_tiles; ft += 256) {
+        const u32x4 *src = (const u32x4 *)((const bf16_t *)e.embed + (size_t)tok * e.d + ft * 16);
+        u32x4 raw[2] = {src[0], src[1]};
+        float ss = 0.f;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            float v[8], x[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[2 * j] = __uint_as_float(raw[half][j] << 16);
+                v[2 * j + 1] = __uint_as_float(raw[half][j] & 0xFFFF0000u);
+            }
+            const int c0 = ft * 16 + half * 8;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { ss += v[j] * v[j]; x[j] = v[j] * e.gain[c0 + j]; }
+            *(f32x4 *)(e.h + (size_t)r * e.d + c0) = (f32x4){v[0], v[1], v[2], v[3]};
+            *(f32x4 *)(e.h + (size_t)r * e.d + c0 + 4) = (f32x4){v[4], v[5], v[6], v[7]};
+            u32x2 h0, l0, h1, l1;
+            split4(x, h0, l0);
+            split4(x + 4, h1, l1);
+            const size_t o = xtile_off(r, c0, e.KSp);
+            *(u32x4 *)((bf16_t *)e.nx_hi + o) = (u32x4){h0[0], h0[1], h1[0], h1[1]};
+            *(u32x4 *)((bf16_t *)e.nx_lo + o) = (u32x4){l0[0], l0[1], l1[0], l1[1]};
+        }
+        e.ssq_out[(size_t)r * n_tiles + ft] = ss;
+    }
+}
+
+// One workgroup per row: token, position, slot, the row's rotary (cos, sin) pairs out of the position table, and the
+// row's embedding.  Generation steps (gp set): every row's workgroup finds the step's trigger for itself -- the maximum
+// over the spans' keys, or the scan itself when the reference is one span -- and the first row's publishes keff, the
+// drafts and the trigger's place.  Three launches (scan, set-up, embedding: 3.3 + 3.4 + 2.7 us at d = 512, nine rows) became one of 5.9 us.
+template <bool BF16>
+__global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m, int max_k, const float *cs, int half, EmbedArgs e,
                                                               const GenState *gp, const unsigned long long *part, int spans) {
     const int idx = blockIdx.x;
     const int b = idx / m, j = idx % m;
@@ -190,17 +228,22 @@ __global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m
         if (j > 0) tok = s.draft[b * max_k + j - 1];
     } else {
         const GenState G = gp[b];
+        const int n_out = *G.n_out;
         unsigned long long best = 0ull;
-        for (int t = threadIdx.x; t < spans; t += 256) {
-            const unsigned long long o = part[(size_t)b * spans + t];
-            best = o > best ? o : best;
+        if (spans == 1) {
+            best = scan_span(G.y, n_out, G.ref, G.doc_offsets, G.n_docs, 0, G.k > 0 && n_out < G.max_new ? G.ref_len : 0, G.n);
+        } else {
+            for (int t = threadIdx.x; t < spans; t += 256) {
+                const unsigned long long o = part[(size_t)b * spans + t];
+                best = o > best ? o : best;
+            }
+            best = block_max(best);
         }
-        best = block_max(best);
         keff = 0;
         if (best != 0ull) {
             const int p = key_position(best), doc = doc_of(G.doc_offsets, G.n_docs, p);
             const int left_in_doc = G.doc_offsets[doc + 1] - p;
-            const int budget = G.max_new - *G.n_out - 1;
+            const int budget = G.max_new - n_out - 1;
             keff = G.k < left_in_doc ? G.k : left_in_doc;
             keff = keff < budget ? keff : budget;
             keff = keff < 0 ? 0 : keff;
@@ -212,50 +255,45 @@ __global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m
         }
         if (j == 0 && threadIdx.x == 0) s.keff[b] = keff;
     }
+    tok = j <= keff ? tok : 0;                                    // rows past keff are padding
     const int pos = T + j;
+    embed_row<BF16>(e, idx, tok);
     for (int i = threadIdx.x; i < 2 * half; i += 256) s.row_cs[(size_t)idx * 2 * half + i] = cs[(size_t)pos * 2 * half + i];
     if (threadIdx.x == 0) {
-        s.row_tok[idx] = j <= keff ? tok : 0;                     // rows past keff are padding
+        s.row_tok[idx] = tok;
         s.row_pos[idx] = pos;
         s.row_slot[idx] = slot;
     }
 }
-void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, const GenState *gen_dev,
-                            const unsigned long long *part, int spans, hipStream_t st) {
-    hipLaunchKernelGGL(setup_step_rows_kernel, dim3(n_seqs * m), dim3(256), 0, st, s, m, max_k, cs, half, gen_dev, part, spans);
+void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, const EmbedArgs &e,
+                            const GenState *gen_dev, const unsigned long long *part, int spans, hipStream_t st) {
+    if (e.gain) hipLaunchKernelGGL((setup_step_rows_kernel<true>), dim3(n_seqs * m), dim3(256), 0, st, s, m, max_k, cs, half, e, gen_dev, part, spans);
+    else hipLaunchKernelGGL((setup_step_rows_kernel<false>), dim3(n_seqs * m), dim3(256), 0, st, s, m, max_k, cs, half, e, gen_dev, part, spans);
 }
 
-__global__ void setup_prefill_rows_kernel(StepState s, const int *prompt, const int *base, int slot, const float *cs, int half) {
+template <bool BF16>
+__global__ __launch_bounds__(256) void setup_prefill_rows_kernel(StepState s, const int *prompt, const int *base, int slot, const float *cs, int half, EmbedArgs e) {
     const int j = blockIdx.x;
     const int pos = s.T[slot] + j;
+    const int tok = prompt[pos - *base];
+    embed_row<BF16>(e, j, tok);
     if (threadIdx.x == 0) {
-        s.row_tok[j] = prompt[pos - *base];
+        s.row_tok[j] = tok;
         s.row_pos[j] = pos;
         s.row_slot[j] = slot;
         if (j == 0) s.batch_slots[0] = slot;
     }
-    for (int i = threadIdx.x; i < 2 * half; i += blockDim.x) s.row_cs[(size_t)j * 2 * half + i] = cs[(size_t)pos * 2 * half + i];
+    for (int i = threadIdx.x; i < 2 * half; i += 256) s.row_cs[(size_t)j * 2 * half + i] = cs[(size_t)pos * 2 * half + i];
 }
 void launch_setup_prefill_rows(const StepState &s, const int *prompt_dev, const int *base_dev, int m, int slot,
-                               const float *cs, int half, hipStream_t st) {
-    hipLaunchKernelGGL(setup_prefill_rows_kernel, dim3(m), dim3(64), 0, st, s, prompt_dev, base_dev, slot, cs, half);
+                               const float *cs, int half, const EmbedArgs &e, hipStream_t st) {
+    if (e.gain) hipLaunchKernelGGL((setup_prefill_rows_kernel<true>), dim3(m), dim3(256), 0, st, s, prompt_dev, base_dev, slot, cs, half, e);
+    else hipLaunchKernelGGL((setup_prefill_rows_kernel<false>), dim3(m), dim3(256), 0, st, s, prompt_dev, base_dev, slot, cs, half, e);
 }
 
 __global__ void advance_T_kernel(StepState s, int slot, int by) { s.T[slot] += by; }
 void launch_advance_T(const StepState &s, int slot, int by, hipStream_t st) {
     hipLaunchKernelGGL(advance_T_kernel, dim3(1), dim3(1), 0, st, s, slot, by);
-}
-
-// ---------------------------------------------------------------------------------------------
-// fp32 path: embedding gather
-// ---------------------------------------------------------------------------------------------
-__global__ void embed_f32_kernel(const float *embed, const int *row_tok, float *h, int d) {
-    int r = blockIdx.x;
-    size_t base = (size_t)row_tok[r] * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) h[(size_t)r * d + c] = embed[base + c];
-}
-void launch_embed_f32(const float *embed, const int *row_tok, float *h, int R, int d, hipStream_t st) {
-    hipLaunchKernelGGL(embed_f32_kernel, dim3(R), dim3(256), 0, st, embed, row_tok, h, d);
 }
 
 // ---------------------------------------------------------------------------------------------

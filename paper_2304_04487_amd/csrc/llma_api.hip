@@ -515,7 +515,6 @@ static int forward_f32(llma_ctx *c, int n_seqs, int m, bool lm_head) {
     const int d = g.d_model, F = g.d_ffn, V = g.vocab, H = g.n_heads, dh = g.head_dim, L = g.n_layers;
     const int R = n_seqs * m;
     hipStream_t st = c->run_st;
-    launch_embed_f32((const float *)c->embed, c->s.row_tok, c->h, R, d, st);
     GemmArgs ga{};
     ga.rows = R; ga.eps = g.rms_eps; ga.H = H; ga.dh = dh; ga.max_seq = c->seq_cap;
     ga.row_pos = c->s.row_pos; ga.row_slot = c->s.row_slot; ga.row_cs = c->s.row_cs;
@@ -552,7 +551,6 @@ static int forward_bf16(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_he
     const int R = n_seqs * m;
     hipStream_t st = c->run_st;
     const int ksp_d = c->plan_qkv.KSp;          // k-steps per row tile of every activation plane that feeds a K = d GEMM
-    launch_embed_prep_bf16(c->embed, c->s.row_tok, c->n1[0], c->h, c->xhi, c->xlo, c->ssq, R, d, ksp_d, st);
     GemmArgs base{};
     base.rows = R; base.split = c->opt_split; base.eps = g.rms_eps;
     base.rows_live = c->rows_live;                         // llma_generate, one sequence: the trigger's draft count (device)
@@ -640,9 +638,12 @@ static int forward(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_head, i
 static int step_body(llma_ctx *c, int kind, int n_seqs, int m, int n_chunks, int slot) {
     hipStream_t st = c->run_st;
     const int mk = c->cfg.max_k;
+    EmbedArgs e{};
+    e.embed = c->embed; e.h = c->h; e.d = c->cfg.d_model;
+    if (c->bf16) { e.gain = c->n1[0]; e.nx_hi = c->xhi; e.nx_lo = c->xlo; e.ssq_out = c->ssq; e.KSp = c->plan_qkv.KSp; }
     c->rows_live = nullptr;
     if (kind == STEP_PREFILL) {
-        launch_setup_prefill_rows(c->s, c->gen_prompt, c->gen_counters + 4 * c->cfg.max_batch, m, slot, c->cs_table, c->cfg.head_dim / 2, st);
+        launch_setup_prefill_rows(c->s, c->gen_prompt, c->gen_counters + 4 * c->cfg.max_batch, m, slot, c->cs_table, c->cfg.head_dim / 2, e, st);
         int rc = forward(c, 1, m, n_chunks, false, slot);
         if (rc) return rc;
         launch_advance_T(c->s, slot, m, st);
@@ -651,9 +652,9 @@ static int step_body(llma_ctx *c, int kind, int n_seqs, int m, int n_chunks, int
     c->rows_live = (kind == STEP_GEN && n_seqs == 1) ? c->s.keff : nullptr;
     const GenState *gen = kind == STEP_GEN ? c->gen_dev : nullptr;
     unsigned long long *part = (unsigned long long *)c->gen_part;
-    if (gen) launch_trigger_scan(gen, n_seqs, c->gen_spans, part, st);
-    else launch_take_step(c->s, n_seqs, mk, st);
-    launch_setup_step_rows(c->s, n_seqs, m, mk, c->cs_table, c->cfg.head_dim / 2, gen, part, c->gen_spans, st);
+    if (!gen) launch_take_step(c->s, n_seqs, mk, st);
+    else if (c->gen_spans > 1) launch_trigger_scan(gen, n_seqs, c->gen_spans, part, st);
+    launch_setup_step_rows(c->s, n_seqs, m, mk, c->cs_table, c->cfg.head_dim / 2, e, gen, part, c->gen_spans, st);
     int rc = forward(c, n_seqs, m, n_chunks, true, slot);
     if (rc) return rc;
     launch_argmax_accept(c->pval, c->pidx, c->n_part, c->s, n_seqs, m, mk, c->cfg.vocab, gen, st);
