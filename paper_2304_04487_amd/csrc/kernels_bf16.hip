@@ -303,7 +303,10 @@ __device__ __forceinline__ void offset_rows(GemmArgs &a, const GemmPlan &p, int 
 // threads the kernel is built for, i.e. registers per wave: 128 at one row tile (16 waves, or two workgroups of 8, per
 // compute unit); 256 with more row tiles, and for three or four gate/up pairs (that matrix always has 8 K slices)
 constexpr int tilek_max_threads(int nt, int tiles_per_task, int ft) { return nt == 1 && (tiles_per_task == 1 || ft < 3) ? 1024 : 512; }
-template <int NT, int EPI, bool SPLIT, int FT>
+// SL, K slices per wave, is a constant of the kernel: as a runtime count it cost the matrices of one slice per wave
+// registers (O and down of 13B in launches of 17 rows, mostly one of them live: 123 registers and 28.5 us on average,
+// 94 and 21.2 as a constant)
+template <int NT, int EPI, bool SPLIT, int FT, int SL = 1>
 __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, FT))) void gemm_tilek_bf16(GemmArgs a) {
     constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1;
     constexpr int AT = FT * TILES;                 // weight tiles per k-step
@@ -312,8 +315,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
     constexpr int UB = (AT * NT >= 4) ? 1 : (AT * NT == 1 ? 4 : 2);
     constexpr int PL = SPLIT ? 2 : 1;
     extern __shared__ f32x4 red[];                 // [S][AT][NT][64], then rstd[16*NT] floats
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6, S = a.plan.tk_waves;
-    const int SL = EPI == EPI_SWIGLU ? 1 : S / W;  // K slices per wave (gate/up: 8 slices, 8 waves)
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6, S = W * SL;
     TK_TRACE(0);
     // llma_generate launches k + 1 rows in every step; how many of them carry a token (1 + the
     // drafts the trigger found) is only known on the device.  The dead rows cost nothing here:
@@ -454,6 +456,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
             if (i == 0) rstd_s[r] = 1.0f / sqrtf(ss / (float)(a.ssq_tiles * 16) + a.eps);
         }
     }
+#pragma unroll
     for (int sl = 0; sl < SL; ++sl) {
         if (sl > 0) {
             slice = wave * SL + sl;
@@ -542,23 +545,32 @@ int tilek_ft_default(const GemmPlan &p, int nt, bool few_rows) {
     return best;
 }
 
-template <int NT, int EPI, int FT>
-static void launch_tilek(const GemmArgs &a, hipStream_t st) {
+template <int NT, int EPI, int FT, int SL>
+static void launch_tilek_slices(const GemmArgs &a, hipStream_t st) {
     constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1;
     const GemmPlan &p = a.plan;
-    const int S = p.tk_waves, max_waves = tilek_max_threads(NT, TILES, FT) / 64;
-    const int W = S < max_waves ? S : max_waves;                     // waves; S, the K slices, is 8 or 16
+    const int S = p.tk_waves, W = S / SL;                            // K slices (8 or 16) and waves
     const size_t lds = (size_t)S * FT * TILES * NT * 1024 + 256;
     dim3 grid((p.tasks + FT - 1) / FT), block(W * 64);
     if (a.split) {
         static std::atomic<uint64_t> done{0};
-        allow_full_lds((const void *)gemm_tilek_bf16<NT, EPI, true, FT>, done);
-        hipLaunchKernelGGL((gemm_tilek_bf16<NT, EPI, true, FT>), grid, block, lds, st, a);
+        allow_full_lds((const void *)gemm_tilek_bf16<NT, EPI, true, FT, SL>, done);
+        hipLaunchKernelGGL((gemm_tilek_bf16<NT, EPI, true, FT, SL>), grid, block, lds, st, a);
     } else {
         static std::atomic<uint64_t> done{0};
-        allow_full_lds((const void *)gemm_tilek_bf16<NT, EPI, false, FT>, done);
-        hipLaunchKernelGGL((gemm_tilek_bf16<NT, EPI, false, FT>), grid, block, lds, st, a);
+        allow_full_lds((const void *)gemm_tilek_bf16<NT, EPI, false, FT, SL>, done);
+        hipLaunchKernelGGL((gemm_tilek_bf16<NT, EPI, false, FT, SL>), grid, block, lds, st, a);
     }
+}
+
+template <int NT, int EPI, int FT>
+static void launch_tilek(const GemmArgs &a, hipStream_t st) {
+    // 16 slices and more than one row tile: eight waves of two slices (gate/up always has eight slices)
+    constexpr int MAX_WAVES = tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, FT) / 64;
+    if constexpr (NT > 1 && EPI != EPI_SWIGLU) {
+        if (a.plan.tk_waves > MAX_WAVES) return launch_tilek_slices<NT, EPI, FT, 2>(a, st);
+    }
+    launch_tilek_slices<NT, EPI, FT, 1>(a, st);
 }
 
 template <int NT, int EPI>
