@@ -14,11 +14,14 @@
 //
 // What bounds it: one workgroup reads at the rate of its own loads in flight (600 011 tokens: 180 us = 13 GB/s),
 // so a reference is cut into spans of TRIGGER_SPAN positions, one workgroup each, 16 loads per thread in flight;
-// the spans' best keys are merged by whoever needs them (a maximum: the order does not matter).  Nearly every
-// position stops at the one-token test; a survivor is extended by its whole wave, 64 tokens per step, and only
-// survivors look their document up (binary search; it used to be a table filled by a kernel of its own).
-// A call over 600 011 tokens on the device: 245 -> 8.1 us; one span (the usual reference of a few documents) is one
-// launch (1472 host tokens: 44.3 -> 41.1 us, the rest is the copies).
+// the spans' best keys are merged by whoever needs them (a maximum: the order does not matter).  Most positions stop at
+// the one-token test.  What survives it is one position in 32000 for uniform ids, but 5 % of a text whose last token is a
+// comma or a newline, so the survivors are gathered and handled a thread each: the document by binary search, seven more
+// tokens, all requested at once.  The few that go on are followed one at a time by their wave, 64 tokens per step, best
+// prospect first -- in a repetitive text the first drops all others -- and side by side, 16 tokens per step, while there are many.
+// (Every survivor followed by its wave, one after the other, took 31 us at 5 % of 4096 positions, 223 at 50 %: now 7 and 12.)
+// A call over 600 011 tokens on the device: 245 us in one workgroup, now 8.1; one span (the usual reference of a few
+// documents) is one launch (1472 host tokens: 44.3 -> 41.1 us, the rest is the copies).
 //
 // The document list may come from device memory the host cannot check: a start below 0 is taken as 0, so that no
 // list makes the backward walk leave the reference.
@@ -45,48 +48,113 @@ __device__ __forceinline__ unsigned long long block_max(unsigned long long best)
     return best;
 }
 
+__device__ __forceinline__ unsigned long long trigger_key(int score, int p) {
+    return ((unsigned long long)score << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)p);
+}
+__device__ __forceinline__ int key_position(unsigned long long key) { return (int)(0xFFFFFFFFu - (unsigned)(key & 0xFFFFFFFFull)); }
+
 // best key (score << 32 | ~position) of the positions [p_lo, p_hi), p_hi - p_lo <= TRIGGER_SPAN; 256 threads
 __device__ __forceinline__ unsigned long long scan_span(const int *y, int i, const int *ref, const int *doc_offsets, int n_docs,
                                                         int p_lo, int p_hi, int n) {
-    constexpr int U = TRIGGER_SPAN / 256;
+    constexpr int U = TRIGGER_SPAN / 256, PROBE = 8, STRIDE = 16;
+    __shared__ unsigned short hit[TRIGGER_SPAN];                // the survivors of the one-token test, p - p_lo, in no order
+    __shared__ int n_hit;
     unsigned long long best = 0ull;
     if (i >= n && p_lo < p_hi) {                                // uniform
         const int lane = threadIdx.x & 63;
-        const int last = y[i - 1];
-        int prev[U];
+        const auto token_before = [&](int q, int t) { return ref[q - 1 - t > 0 ? q - 1 - t : 0]; };    // (compared only where it exists)
+        const auto tail = [&](int t) { return y[i - 1 - t > 0 ? i - 1 - t : 0]; };
+        if (threadIdx.x == 0) n_hit = 0;
+        int prev[U], want[PROBE];
+#pragma unroll
+        for (int t = 0; t < PROBE; ++t) want[t] = tail(t);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int p = p_lo + u * 256 + (int)threadIdx.x;
             prev[u] = ref[p < 1 ? 0 : (p < p_hi ? p - 1 : p_hi - 1)];
         }
+        __syncthreads();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int p = p_lo + u * 256 + (int)threadIdx.x;
-            unsigned long long hits = __ballot(p >= 1 && p < p_hi && prev[u] == last);
-            while (hits != 0ull) {                              // survivors, one after the other, each by the whole wave
-                const int src = __ffsll(hits) - 1;
-                hits &= hits - 1;
-                const int q = p - lane + src;
-                int start = doc_offsets[doc_of(doc_offsets, n_docs, q)];
-                start = start > 0 ? start : 0;
-                const int limit = q - start < i ? q - start : i;
-                int score = 0;
-                for (; score < limit; score += 64) {
-                    const int t = score + lane;
-                    const bool differs = t >= limit || ref[q - 1 - t] != y[i - 1 - t];
-                    const unsigned long long stop = __ballot(differs);
-                    if (stop != 0ull) { score += __ffsll(stop) - 1; break; }
+            const bool same = p >= 1 && p < p_hi && prev[u] == want[0];
+            const unsigned long long hits = __ballot(same);
+            if (hits == 0ull) continue;
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&n_hit, __popcll(hits));
+            base = __shfl(base, 0);
+            if (same) hit[base + __popcll(hits & ((1ull << lane) - 1ull))] = (unsigned short)(p - p_lo);
+        }
+        __syncthreads();
+        const int total = n_hit;
+        for (int h0 = 0; h0 < total; h0 += 256) {               // a survivor per thread
+            const bool mine = h0 + (int)threadIdx.x < total;
+            const int q = p_lo + hit[mine ? h0 + (int)threadIdx.x : 0];
+            int got[PROBE];
+#pragma unroll
+            for (int t = 1; t < PROBE; ++t) got[t] = token_before(q, t);
+            int start = doc_offsets[doc_of(doc_offsets, n_docs, q)];
+            start = start > 0 ? start : 0;
+            const int limit = !mine ? 0 : (q - start < i ? q - start : i);
+            int score = limit > 0 ? 1 : 0;                      // (limit < 0: a document list that decreases)
+#pragma unroll
+            for (int t = 1; t < PROBE; ++t)
+                if (score == t && t < limit && got[t] == want[t]) score = t + 1;
+            bool more = score == PROBE && limit > PROBE;        // the comparison goes on
+            if (!more && score >= n) {
+                const unsigned long long key = trigger_key(score, q);
+                best = key > best ? key : best;
+            }
+            while (__ballot(more) != 0ull) {
+                // what cannot beat the wave's best is dropped; of the others the one with the most to gain is
+                // followed to its end by the whole wave, 64 tokens at a time
+                unsigned long long top = best, bound = more ? trigger_key(limit, q) : 0ull;
+                unsigned long long lead = bound;
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) {
+                    const unsigned long long a = __shfl_xor(top, off), b = __shfl_xor(lead, off);
+                    top = a > top ? a : top;
+                    lead = b > lead ? b : lead;
                 }
-                if (score >= n) {
-                    const unsigned long long key = ((unsigned long long)score << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)q);
+                if (lead <= top) break;
+                const int src = __ffsll(__ballot(bound == lead)) - 1;
+                const int ql = key_position(lead), ll = (int)(lead >> 32);
+                int sl = __shfl(score, src);
+                for (; sl < ll; sl += 64) {
+                    const int t = sl + lane;
+                    const unsigned long long stop = __ballot(t >= ll || token_before(ql, t) != tail(t));
+                    if (stop != 0ull) { sl += __ffsll(stop) - 1; break; }
+                }
+                if (sl >= n) {
+                    const unsigned long long key = trigger_key(sl, ql);
                     best = key > best ? key : best;
+                    top = key > top ? key : top;
+                }
+                more = more && lane != src && bound > top;
+                if (__popcll(__ballot(more)) <= 4) continue;
+                // many left: each goes on by itself for a while
+                int x[STRIDE], z[STRIDE];
+#pragma unroll
+                for (int e = 0; e < STRIDE; ++e) { x[e] = token_before(q, score + e); z[e] = tail(score + e); }
+                const int from = score;
+                bool go = more;
+#pragma unroll
+                for (int e = 0; e < STRIDE; ++e) {
+                    go = go && from + e < limit && x[e] == z[e];
+                    score += go;
+                }
+                if (more && !go) {
+                    if (score >= n) {
+                        const unsigned long long key = trigger_key(score, q);
+                        best = key > best ? key : best;
+                    }
+                    more = false;
                 }
             }
         }
     }
     return block_max(best);
 }
-__device__ __forceinline__ int key_position(unsigned long long key) { return (int)(0xFFFFFFFFu - (unsigned)(key & 0xFFFFFFFFull)); }
 
 // llma_generate: grid (spans of the longest reference, sequences); part[sequence][span] = the span's best key
 __global__ __launch_bounds__(256) void trigger_scan_kernel(const GenState *gp, unsigned long long *part) {

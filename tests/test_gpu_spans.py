@@ -86,3 +86,85 @@ def test_generate_with_references_of_several_spans(llma):
     got = ctx.generate_batch([prompt] * 3, refs, wl.n, wl.k, wl.max_new)
     assert [g[0].tolist() for g in got] == [t for t, _ in want] and [g[1] for g in got] == [t for _, t in want]
     ctx.close()
+
+
+def skewed(rng, length, share, last):
+    ref = rng.randint(1000, 2000, length)
+    ref[rng.rand(length) < share] = last
+    return ref
+
+
+@pytest.mark.parametrize("length", [48, 1472, 4096, 9000])
+@pytest.mark.parametrize("share", [0.02, 0.3, 0.97])
+def test_frequent_last_token(llma, length, share):
+    """the last token of y makes up a good part of the reference: few, hundreds or nearly all positions survive the
+    one-token test, matches of 1 .. 300 tokens among them"""
+    rng = np.random.RandomState(length + int(100 * share))
+    for y_len in (1, 7, 8, 9, 300):
+        y = np.append(rng.randint(1000, 2000, y_len - 1), 13)
+        ref = skewed(rng, length, share, 13)
+        for tail in (2, 8, 9, 24, 25, 299):                     # (the copies of a tail: two, the later one a token longer)
+            for at, t in ((length // 3, tail), (length - 1, tail + 1)):
+                t = min(t, at, y_len)
+                ref[at - t:at] = y[y_len - t:]
+        for offs in ([0, length], [0, 0, length // 3 - 1, length // 3 + 5, length]):
+            for n in (1, 2, 9):
+                want = match_ngrams(y.tolist(), docs_from_flat(ref, offs), n)
+                assert both(llma, y, ref, offs, n) == (want, want), (y_len, offs, n)
+
+
+@pytest.mark.parametrize("period,noise", [(1, 0.0), (1, 0.01), (2, 0.0), (16, 0.0), (16, 0.01), (50, 0.002)])
+def test_repetitive_references(llma, period, noise):
+    """periodic texts with a few changed tokens: many long agreements of different lengths, ties go to the smallest position"""
+    rng = np.random.RandomState(period)
+    text = np.arange(9000) % period
+    hit = rng.rand(9000) < noise
+    text[hit] = rng.randint(0, max(period, 2), int(hit.sum()))
+    for length, y_len in ((4096, 600), (9000, 90)):
+        ref = text[:length]
+        for y in (text[:y_len], np.arange(y_len) % period):
+            for offs in ([0, length], [0, 777, 4090, length]):
+                want = match_ngrams(y.tolist(), docs_from_flat(ref, offs), 2)
+                assert both(llma, y, ref, offs, 2) == (want, want), (length, y_len, offs)
+
+
+def test_frequent_tokens_cost_no_serial_chain(llma):
+    """2048 of 4096 positions survive the one-token test: less than six times the call without any (followed one after
+    the other they cost 50 times, side by side twice as much)"""
+    import torch
+    rng = np.random.RandomState(1)
+    y = np.append(rng.randint(1000, 2000, 255), 13)
+    res = torch.zeros(3, dtype=torch.int32, device="cuda")
+    us = {}
+    for share in (0.0, 0.5):
+        a = [torch.tensor(np.asarray(x, np.int32), device="cuda") for x in (y, skewed(rng, 4096, share, 13), [0, 1500, 4096])]
+        best = 1e9
+        for _ in range(6):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(50):
+                llma.llma_find_trigger_static(*a, 2, res)
+            t1.record()
+            torch.cuda.synchronize()
+            best = min(best, t0.elapsed_time(t1) * 20)
+        us[share] = best
+    assert us[0.5] < 6 * us[0.0], us
+
+
+def test_generate_with_frequent_tokens(llma):
+    """references made of the generation's own tokens: every step's last token occurs about a hundred times in them"""
+    wl = synth.WORKLOADS["tiny"]
+    w = synth.make_weights(wl.model, wl.seed)
+    om = OracleModel(wl.model, w)
+    prompt = synth.make_prompt(wl)
+    y = greedy_decode(CachedLLM(om, prompt, 160), wl.max_new)
+    rng = np.random.RandomState(9)
+    refs = [(rng.choice(y, size).astype(np.int32), np.array([0, size // 3, size], np.int32)) for size in (3000, 4096, 9000)]
+    want = [llma_decode(CachedLLM(om, prompt, 160), docs_from_flat(*r), 1, 8, wl.max_new) for r in refs]
+    ctx = llma.Context(wl.model, w, max_seq=160, max_batch=3, max_k=8)
+    for b, r in enumerate(refs):
+        toks, trace = ctx.generate(prompt, *r, 1, 8, wl.max_new, seq=b)
+        assert toks.tolist() == want[b][0] and trace == want[b][1]
+    got = ctx.generate_batch([prompt] * 3, refs, 1, 8, wl.max_new)
+    assert [g[0].tolist() for g in got] == [t for t, _ in want] and [g[1] for g in got] == [t for _, t in want]
+    ctx.close()
