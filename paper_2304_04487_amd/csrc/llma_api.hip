@@ -883,6 +883,13 @@ extern "C" int llma_find_trigger(const int32_t *y, int32_t y_len, const int32_t 
 // ------------------------------------------------------------------------------------------------
 // verify step
 // ------------------------------------------------------------------------------------------------
+// Error return of a call that has enqueued part of a step: the step's kernels read and write pinned host memory, which the
+// next call rewrites at once, so none of them may still be on its way.
+static int drained(llma_ctx *c, int rc) {
+    (void)hipStreamSynchronize(c->st);
+    return rc;
+}
+
 extern "C" int llma_verify_step_batch(llma_ctx *c, int32_t n_seqs, const int32_t *seqs, const int32_t *drafts, int32_t k,
                                       int32_t *n_accepted, int32_t *next_token, int32_t *emitted) {
     if (!c) return fail(nullptr, LLMA_E_INVAL, "llma_verify_step: null context");
@@ -908,7 +915,7 @@ extern "C" int llma_verify_step_batch(llma_ctx *c, int32_t n_seqs, const int32_t
     if (c->logits_dump && n_seqs * (k + 1) > c->dump_rows)
         return fail(c, LLMA_E_RANGE, "llma_verify_step: logits dump holds %d rows, step has %d", c->dump_rows, n_seqs * (k + 1));
     const int m = k + 1, mk = g.max_k;
-    const HostIo &io = c->host;                // (nothing reads or writes it between two steps: every step is waited for)
+    const HostIo &io = c->host;                // (nothing on the device reads or writes it now: every step is waited for, failed ones too)
     for (int b = 0; b < n_seqs; ++b) {
         io.slot[b] = seqs[b];
         io.keff[b] = k;
@@ -920,7 +927,7 @@ extern "C" int llma_verify_step_batch(llma_ctx *c, int32_t n_seqs, const int32_t
     }
     for (int b = 0; b < n_seqs; ++b) forget_imports(c, seqs[b]);
     int rc = run_step(c, STEP_VERIFY, n_seqs, m, t_max, n_seqs == 1 ? seqs[0] : 0);
-    if (rc) return rc;
+    if (rc) return drained(c, rc);
     HIP_TRY(c, hipStreamSynchronize(c->st));
     HIP_TRY(c, hipGetLastError());
     const int *const nacc = io.nacc, *const nxt = io.next, *const em = io.emit;
@@ -1016,7 +1023,6 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
     }
     HIP_TRY(c, hipMemcpyAsync(c->gen_doc_offsets, dof_host.data(), dof_host.size() * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(c, hipMemsetAsync(c->gen_counters, 0, (size_t)(4 * g.max_batch + 4) * 4, st));
-    memset(c->pin_counts, 0, (size_t)2 * g.max_batch * sizeof(int));
     std::vector<GenState> G(n_seqs);
     int *const cnt_out = c->gen_counters, *const cnt_steps = c->gen_counters + g.max_batch, *const cnt_cur = c->gen_counters + 2 * g.max_batch;
     for (int b = 0; b < n_seqs; ++b) {
@@ -1030,6 +1036,7 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
     }
     HIP_TRY(c, hipMemcpyAsync(c->gen_dev, G.data(), sizeof(GenState) * n_seqs, hipMemcpyHostToDevice, st));
     HIP_TRY(c, hipStreamSynchronize(st));     // the host staging buffers may go out of scope / change
+    memset(c->pin_counts, 0, (size_t)2 * g.max_batch * sizeof(int));    // (written by the accept kernels directly: not before the wait)
 
     // ---- x: reset each slot, feed prompt[0..len-2], prompt[len-1] becomes the pending token
     std::vector<int> T0(n_seqs);
@@ -1066,21 +1073,25 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
         ++enq;
         return LLMA_OK;
     };
-    if ((rc = enqueue())) return rc;
-    while (true) {
-        if ((rc = enqueue())) return rc;                        // one step ahead
-        HIP_TRY(c, hipEventSynchronize(c->cnt_ev[steps & 1]));
-        bool done = true;
-        for (int b = 0; b < n_seqs; ++b) {
-            const int now = __atomic_load_n(&c->pin_counts[(size_t)(steps & 1) * g.max_batch + b], __ATOMIC_ACQUIRE);
-            if (now > max_new || now < produced[b] || (now == produced[b] && produced[b] < max_new))
-                return fail(c, LLMA_E_HIP, "llma_generate: device output count of sequence %d went %d -> %d", b, produced[b], now);
-            produced[b] = now;
-            done = done && now >= max_new;
+    auto decode = [&]() -> int {
+        int r = enqueue();
+        while (r == LLMA_OK) {
+            if ((r = enqueue())) break;                         // one step ahead
+            HIP_TRY(c, hipEventSynchronize(c->cnt_ev[steps & 1]));
+            bool done = true;
+            for (int b = 0; b < n_seqs; ++b) {
+                const int now = __atomic_load_n(&c->pin_counts[(size_t)(steps & 1) * g.max_batch + b], __ATOMIC_ACQUIRE);
+                if (now > max_new || now < produced[b] || (now == produced[b] && produced[b] < max_new))
+                    return fail(c, LLMA_E_HIP, "llma_generate: device output count of sequence %d went %d -> %d", b, produced[b], now);
+                produced[b] = now;
+                done = done && now >= max_new;
+            }
+            ++steps;
+            if (done) break;
         }
-        ++steps;
-        if (done) break;
-    }
+        return r;
+    };
+    if ((rc = decode())) return drained(c, rc);
     HIP_TRY(c, hipStreamSynchronize(st));                       // drains the step that ran ahead
     std::vector<int> nst(n_seqs);
     HIP_TRY(c, hipMemcpyAsync(nst.data(), cnt_steps, (size_t)n_seqs * 4, hipMemcpyDeviceToHost, st));

@@ -1,0 +1,124 @@
+"""The library's host side on the CPU: llma_api.hip compiled for the host alone and linked against tests/host_stub.cpp,
+where a stream is a queue that runs when it is waited for and every launcher notes its arguments.  What a GPU cannot
+show reliably: what is still in flight when a call returns, and what the host had told the device by then."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2304_04487_amd as llma
+from paper_2304_04487_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+def run(cmd):
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("host")
+    objs = []
+    for src in (os.path.join(build.CSRC, "llma_api.hip"), os.path.join(HERE, "host_stub.cpp")):
+        objs.append(str(tmp / (os.path.basename(src) + ".o")))
+        run([build._hipcc(), "-std=c++17", "-O1", "-fPIC", "-x", "hip", "--offload-arch=gfx950", "--cuda-host-only", "-Wno-unused-result",
+             "-I", build.CSRC, "-c", src, "-o", objs[-1]])
+    out = tmp / "libhost.so"
+    run(["g++", "-shared", "-Wl,-Bsymbolic", "-Wl,--no-undefined", "-o", str(out), *objs])     # (its own HIP calls, whatever else is loaded)
+    lib = ctypes.CDLL(str(out))
+    lib.llma_last_error.restype = ctypes.c_char_p
+    return lib
+
+
+def i32(*values):
+    return (ctypes.c_int32 * len(values))(*values)
+
+
+class Ctx:
+    """a context of zero weights on the stubbed runtime"""
+
+    def __init__(self, lib, dtype, n_layers=3, max_batch=2, max_k=4):
+        self.lib, self.L = lib, n_layers
+        bf16 = dtype == "bf16"
+        d, F, V = 128, 256, 64
+        cfg = llma.ModelCfgC(n_layers, d, 2, 64, F, V, 128, max_batch, max_k, llma.LLMA_DTYPE_BF16 if bf16 else llma.LLMA_DTYPE_F32, 1, 1e-6, 1e4)
+        self.keep = np.zeros(2 * F * d + 3 * d * d + 2 * V * d, np.float32)
+        p = self.keep.ctypes.data
+        per = (ctypes.c_void_p * n_layers)(*[p] * n_layers)
+        w = llma.WeightsC(p, p, p, per, per, per, per, per, per)
+        self.h = ctypes.c_void_p()
+        assert lib.llma_create(ctypes.byref(cfg), ctypes.byref(w), None, ctypes.byref(self.h)) == 0, lib.llma_last_error(None)
+        self.notes()
+
+    def notes(self):
+        """(prompt passes' start lengths, rows of the decoding GEMMs, their split flags) since the last look"""
+        out = []
+        for f in (self.lib.stub_prompt_T, self.lib.stub_gemm_rows, self.lib.stub_gemm_split):
+            a = (ctypes.c_int32 * 4096)()
+            out.append(list(a[:f(a, 4096)]))
+        return out
+
+    def prefill(self, n, seq=0):
+        assert self.lib.llma_prefill(self.h, seq, i32(*[1] * n), n) == 0
+
+    def verify(self, drafts, seq=0):
+        return self.lib.llma_verify_step(self.h, seq, i32(*drafts), len(drafts), None, None, None)
+
+    def generate(self, max_new, prompt=8, k=2):
+        self.out, n_out = np.full(max_new, -1, np.int32), ctypes.c_int32()
+        offs = i32(0, 0)
+        return self.lib.llma_generate(self.h, 0, i32(*[1] * prompt), prompt, None, offs, 0, 1, k, max_new,
+                                      self.out.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), ctypes.byref(n_out), None, None)
+
+    def state(self, seq=0):
+        t, p = ctypes.c_int32(), ctypes.c_int32()
+        assert self.lib.llma_get_state(self.h, seq, ctypes.byref(t), ctypes.byref(p)) == 0
+        return t.value, p.value
+
+
+@pytest.fixture
+def ctx(lib, request, monkeypatch):
+    monkeypatch.setenv("LLMA_NO_AUTOTUNE", "1")
+    c = Ctx(lib, request.param)
+    yield c
+    lib.stub_fail_last_error(-1)
+    lib.stub_fail_event_record(-1)
+    lib.llma_destroy(c.h)
+
+
+both_types = pytest.mark.parametrize("ctx", ["fp32", "bf16"], indirect=True)
+
+
+@both_types
+def test_calls_run_on_the_stub(ctx):
+    ctx.prefill(20)
+    assert ctx.state() == (19, 1)
+    assert ctx.verify([2, 3]) == 0 and ctx.state() == (20, 7)
+    assert ctx.generate(9) == 0 and ctx.out.tolist() == [7] * 9
+    assert ctx.state() == (7 + 9, 7)
+
+
+@both_types
+def test_failed_step_leaves_nothing_in_flight(ctx):
+    """launches of a step that failed half way read the host's words in pinned memory, which the next call rewrites: a
+    step of other slots and fewer rows would then write K / V at positions the failed step's row count runs past"""
+    ctx.prefill(20)
+    ctx.lib.stub_fail_last_error(0)
+    assert ctx.verify([2, 3, 4]) == llma.LLMA_E_HIP
+    assert ctx.lib.stub_pending() == 0
+    ctx.prefill(30, seq=1)
+    assert ctx.verify([], seq=1) == 0 and ctx.state(1) == (30, 7) and ctx.state(0) == (19, 1)
+
+
+@both_types
+@pytest.mark.parametrize("record", [0, 1, 4])
+def test_failed_generation_leaves_nothing_in_flight(ctx, record):
+    """the step that runs ahead writes output counts the next generation clears and waits on"""
+    ctx.lib.stub_fail_event_record(record)
+    assert ctx.generate(9) == llma.LLMA_E_HIP
+    assert ctx.lib.stub_pending() == 0
+    assert ctx.generate(5) == 0 and ctx.out.tolist() == [7] * 5
