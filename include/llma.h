@@ -222,7 +222,8 @@ int llma_set_logits_dump(llma_ctx *ctx, float *dev_buf, int32_t capacity_rows);
                                    two bf16 numbers (hi + lo) -- doubles the (free, memory-bound)
                                    MFMA work, removes the activation rounding error. default 1 */
 #define LLMA_OPT_KERNEL_TIMING 2 /* bracket every launch of the FFN gate/up GEMM (the kernel
-                                   that streams the most bytes) with HIP events. default 0 */
+                                   that streams the most bytes) in decoding steps of up to
+                                   48 rows with HIP events; prompt passes are not. default 0 */
 #define LLMA_OPT_USE_GRAPH   3  /* replay captured HIP graphs for the per-step kernel sequence. default 1 */
 int llma_set_option(llma_ctx *ctx, int32_t option, int32_t value);
 /* Sums the event pairs recorded since the last call: *launches = number of gate/up GEMM

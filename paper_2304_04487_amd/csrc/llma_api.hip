@@ -599,7 +599,7 @@ static int forward_bf16(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_he
         ga.act_hi = c->act_hi; ga.act_lo = c->act_lo; ga.act_KSp = c->plan_down.KSp;
         if (panel) {
             panel_norm_gemm(ga);
-        } else if (c->opt_timing) {
+        } else if (c->opt_timing && lm_head) {                 // (decoding steps only)
             EventPair ep;
             HIP_TRY(c, hipEventCreate(&ep.a));
             HIP_TRY(c, hipEventCreate(&ep.b));

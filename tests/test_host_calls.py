@@ -122,3 +122,19 @@ def test_failed_generation_leaves_nothing_in_flight(ctx, record):
     assert ctx.generate(9) == llma.LLMA_E_HIP
     assert ctx.lib.stub_pending() == 0
     assert ctx.generate(5) == 0 and ctx.out.tolist() == [7] * 5
+
+
+@pytest.mark.parametrize("ctx", ["bf16"], indirect=True)
+def test_kernel_timing_counts_steps_only(ctx):
+    """prompt passes are not bracketed, whatever GEMM they use"""
+    def launches():
+        n, ms = ctypes.c_int64(), ctypes.c_double()
+        assert ctx.lib.llma_get_kernel_timing(ctx.h, ctypes.byref(n), ctypes.byref(ms)) == 0
+        return n.value
+    assert ctx.lib.llma_set_option(ctx.h, llma.LLMA_OPT_KERNEL_TIMING, 1) == 0
+    for n in (2, 20, 49, 50):
+        ctx.prefill(n, seq=1)
+        assert ctx.lib.llma_reset(ctx.h, 1) == 0
+    assert launches() == 0
+    ctx.prefill(20)
+    assert ctx.verify([2, 3]) == 0 and launches() == ctx.L
