@@ -220,7 +220,9 @@ int llma_set_logits_dump(llma_ctx *ctx, float *dev_buf, int32_t capacity_rows);
 
 #define LLMA_OPT_ACT_SPLIT   1  /* bf16 only: feed activations to the MFMA GEMMs as the sum of
                                    two bf16 numbers (hi + lo) -- doubles the (free, memory-bound)
-                                   MFMA work, removes the activation rounding error. default 1 */
+                                   MFMA work, removes the activation rounding error. default 1.
+                                   0 concerns decoding steps of up to 48 rows; prompt passes and
+                                   larger steps always take both */
 #define LLMA_OPT_KERNEL_TIMING 2 /* bracket every launch of the FFN gate/up GEMM (the kernel
                                    that streams the most bytes) in decoding steps of up to
                                    48 rows with HIP events; prompt passes are not. default 0 */

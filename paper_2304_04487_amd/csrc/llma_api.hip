@@ -552,7 +552,8 @@ static int forward_bf16(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_he
     hipStream_t st = c->run_st;
     const int ksp_d = c->plan_qkv.KSp;          // k-steps per row tile of every activation plane that feeds a K = d GEMM
     GemmArgs base{};
-    base.rows = R; base.split = c->opt_split; base.eps = g.rms_eps;
+    base.rows = R; base.eps = g.rms_eps;
+    base.split = c->opt_split || !lm_head;                 // (the option is about steps; the panel GEMM always feeds both planes)
     base.rows_live = c->rows_live;                         // llma_generate, one sequence: the trigger's draft count (device)
     // Steps and prompt passes of up to 48 rows use the tile-K GEMM, longer ones the panel GEMM (weights streamed once
     // for all rows): the steps in its split-K form, because a few hundred rows alone make too few workgroups to

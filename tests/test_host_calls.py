@@ -138,3 +138,18 @@ def test_kernel_timing_counts_steps_only(ctx):
     assert launches() == 0
     ctx.prefill(20)
     assert ctx.verify([2, 3]) == 0 and launches() == ctx.L
+
+
+@pytest.mark.parametrize("ctx", ["bf16"], indirect=True)
+def test_prompt_passes_keep_both_activation_planes(ctx):
+    """LLMA_OPT_ACT_SPLIT = 0 rounds the activations of decoding steps of up to 48 rows; every prompt pass and every
+    larger step feeds hi + lo"""
+    ctx.prefill(20)
+    ctx.notes()
+    assert ctx.lib.llma_set_option(ctx.h, llma.LLMA_OPT_ACT_SPLIT, 0) == 0
+    ctx.prefill(20, seq=1)
+    _, rows, split = ctx.notes()
+    assert rows == [19] * (4 * ctx.L) and split == [1] * (4 * ctx.L)
+    assert ctx.verify([2]) == 0
+    _, rows, split = ctx.notes()
+    assert rows == [2] * (4 * ctx.L + 1) and split == [0] * (4 * ctx.L + 1)
