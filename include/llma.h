@@ -57,7 +57,7 @@ typedef struct {
                               pos * rope_theta^(-2i/head_dim)                               */
 } llma_model_cfg;
 /* bf16 requires d_model % 32 == 0, d_ffn % 32 == 0, vocab % 16 == 0, head_dim in {64,128},
- * n_heads * head_dim == d_model.  fp32 requires head_dim in {32,64,128}. */
+ * n_heads * head_dim == d_model, d_model and d_ffn <= 2^23.  fp32 requires head_dim in {32,64,128}. */
 
 /* Weights: DEVICE pointers to row-major [out_features, in_features] matrices of the
  * configured dtype (bf16 = 16-bit patterns); gains are fp32 on the DEVICE.  The arrays of

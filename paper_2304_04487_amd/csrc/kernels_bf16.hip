@@ -259,7 +259,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
 
 // 16 bytes per lane through a buffer descriptor: base and size are wave-uniform, an offset past the size reads zeros
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
-#define BUFFER_NOWHERE 0x40000000u     // past the end of every buffer here (all below 1 GiB), also with an offset inside one added
+#define BUFFER_NOWHERE 0x40000000u     // past the end of every buffer it is used with (48 rows of at most 2^23 columns: below 1 GiB), also with an offset inside one added
 __device__ __forceinline__ rsrc_t buffer_of(const void *p, unsigned bytes) {
     return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)bytes, 0x00027000);
 }
@@ -706,16 +706,19 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
             task = task < p.tasks ? task : p.tasks - 1;
             wb[f * TILES + i] = buffer_of((const char *)a.W + ((size_t)(task + i * p.tasks) * KSp) * 1024, (unsigned)KSp * 1024u);
         }
-    const int n_rt_total = (a0.rows + 15) / 16;    // row tiles that exist in the planes
-    const unsigned x_bytes = (unsigned)n_rt_total * (unsigned)KSp * 1024u;
-    const rsrc_t xh = buffer_of(a.Xhi, x_bytes), xl = buffer_of(a.Xlo, x_bytes);
+    // the row block's part of the activation planes (a plane may be larger than the 4 GiB of a 32-bit offset)
+    const int n_rt_total = (a0.rows + 15) / 16;                              // row tiles that exist
+    const int n_rt = n_rt_total - rt0 < RT ? n_rt_total - rt0 : RT;          // and those of this block
+    const unsigned x_bytes = (unsigned)n_rt * (unsigned)KSp * 1024u;
+    const size_t x_start = (size_t)rt0 * KSp * 1024;
+    const rsrc_t xh = buffer_of((const char *)a.Xhi + x_start, x_bytes), xl = buffer_of((const char *)a.Xlo + x_start, x_bytes);
 
     // Operand fetches.  Every address below is a wave-uniform base (scalar registers, scalar
     // arithmetic) plus one per-lane byte offset that never changes (the lane's 16 bytes of a 1 KiB
     // block); every load is unconditional (indices are clamped instead): a load under a branch makes the
     // compiler's count of loads in flight inexact, and it then waits for all of them.
     // Activation chunk kc -> LDS stage: wave w fetches the 1 KiB blocks q = j 8 + w of the chunk's
-    // [2 planes][RT][KC] blocks (the last ones twice if they do not divide); blocks of row tiles past the end read tile 0.
+    // [2 planes][RT][KC] blocks (the last ones twice if they do not divide); row tiles past the end read the block's first.
     const unsigned x_lane = (unsigned)xtile_piece(lane) * 16u;     // LDS holds the block in lane order
     const unsigned w_lane = (unsigned)lane * 16u;
     auto fetch_x = [&](int kc, int stage) {
@@ -726,7 +729,7 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
             const int pl = q / (RT * KC), t = (q % (RT * KC)) / KC, kk = q % KC;
             int k = kc * KC + kk;
             k = k < KSp ? k : KSp - 1;
-            const int tt = (rt0 + t < n_rt_total) ? rt0 + t : 0;
+            const int tt = t < n_rt ? t : 0;
             load_to_lds(pl ? xl : xh, x_lane, (unsigned)(tt * KSp + k) * 1024u, xs + stage * CH + q * 64);
         }
     };

@@ -63,3 +63,7 @@ def test_argument_errors_without_device_work():
     cfg = llma.ModelCfgC(2, 128, 4, 32, 512, 512, 128, 1, 4, llma.LLMA_DTYPE_F32, 0, 1e-6, 10000.0)
     assert lib.llma_create(ctypes.byref(cfg), ctypes.byref(w), None, ctypes.byref(h)) == llma.LLMA_E_INVAL  # null weights
     assert not h.value
+    # ... and widths beyond the kernels' 32-bit offsets
+    cfg = llma.ModelCfgC(2, 128, 2, 64, (1 << 23) + 32, 512, 128, 1, 4, llma.LLMA_DTYPE_BF16, 0, 1e-6, 10000.0)
+    assert lib.llma_create(ctypes.byref(cfg), ctypes.byref(w), None, ctypes.byref(h)) == llma.LLMA_E_INVAL
+    assert b"2^23" in lib.llma_last_error(None)

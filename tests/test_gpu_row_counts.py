@@ -82,3 +82,28 @@ def test_fp32_shapes(d, heads, dh, ffn, vocab):
         ctx.verify_step_batch([1, 0], np.stack([drafts, drafts]))
         assert np.abs(ctx.logits(2 * (k + 1)) - np.concatenate([want, want])).max() <= 1e-4
     ctx.close()
+
+
+def test_activation_planes_beyond_4_gib():
+    """2112 rows of an FFN 2^20 wide: each plane of the down projection's input holds 4.4 GB.  The matrices repeat 4096
+    hidden features 256 times, with the down projection scaled by 2^-8, so the model equals a small one for the oracle."""
+    import paper_2304_04487_amd as llma
+    small = synth.ModelCfg("narrow", 1, 128, 2, 64, 4096, 512, "bf16")
+    w = synth.make_weights(small, 51, gain_jitter=0.2)
+    om = OracleModel(small, w)
+    lay = w["layers"][0]
+    wd = synth.f32_to_bf16(synth.bf16_to_f32(lay["wd"]) / 256.0)
+    wide = synth.ModelCfg("wide", 1, 128, 2, 64, 4096 * 256, 512, "bf16")
+    layer = dict(lay, wgu=np.concatenate([np.tile(lay["wgu"][:4096], (256, 1)), np.tile(lay["wgu"][4096:], (256, 1))]), wd=np.tile(wd, (1, 256)))
+    seqs, k = 64, 32
+    ctx = llma.Context(wide, dict(w, layers=[layer]), max_seq=64, max_batch=seqs, max_k=k)
+    ctx.enable_logits_dump(seqs * (k + 1))
+    prompts = [synth.uniform_tokens(5, b, 3, 512) for b in range(seqs)]
+    drafts = np.stack([synth.uniform_tokens(6, b, k, 512) for b in range(seqs)])
+    want = np.concatenate([om.forward(np.concatenate([p, d]), om.new_cache(64), 0)[-(k + 1):] for p, d in zip(prompts, drafts)])
+    for b, p in enumerate(prompts):
+        ctx.prefill(p, seq=b)
+    ctx.verify_step_batch(list(range(seqs)), drafts)
+    got = ctx.logits(seqs * (k + 1))
+    assert np.all(np.abs(got - want) <= ATOL + RTOL * np.abs(want)), float(np.abs(got - want).max())
+    ctx.close()
