@@ -347,19 +347,29 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
     // Every operand is fetched through a buffer descriptor of its own (one per weight tile, one per activation plane):
     // wave-uniform base and size, one 32-bit offset per lane and k-step for all tiles (a 64-bit pointer per tile took
     // twice the registers: three gate/up pairs at three row tiles spilled, 51 -> 40 us at 33 rows).  Rows without a
-    // token get an offset past the end: zeros, and no traffic.
+    // token get an offset past the end: zeros, and no traffic.  Three weight tiles and one row tile are the exception, their
+    // weights go by pointer: QKV of 7B at one row 18.15 us through descriptors, 17.9 by pointer; with one, two or four
+    // tiles pointers are no better or worse (13B at one row: O 11.8 and 12.0 us, QKV 25.9 and 26.0).
+    constexpr bool W_BY_POINTER = NT == 1 && AT == 3;
+    const unsigned w_lane = (unsigned)lane * 16u;
     rsrc_t wb[AT];
+    const u32x4 *wp[AT];
 #pragma unroll
     for (int f = 0; f < FT; ++f)
 #pragma unroll
         for (int i = 0; i < TILES; ++i) {
             int task = task0 + f;
             task = task < p.tasks ? task : p.tasks - 1;          // ragged last workgroup: recompute the last tile
-            wb[f * TILES + i] = buffer_of((const char *)a.W + ((size_t)(task + i * p.tasks) * KSp) * 1024, (unsigned)KSp * 1024u);
+            const char *tile = (const char *)a.W + ((size_t)(task + i * p.tasks) * KSp) * 1024;
+            if (W_BY_POINTER) wp[f * TILES + i] = (const u32x4 *)(tile + w_lane);
+            else wb[f * TILES + i] = buffer_of(tile, (unsigned)KSp * 1024u);
         }
+    auto load_w = [&](int i, int k) -> u32x4 {
+        if constexpr (W_BY_POINTER) return __builtin_nontemporal_load(wp[i] + (size_t)k * 64);
+        else return buffer_load16<true>(wb[i], (unsigned)k * 1024u + w_lane);
+    };
     // One row tile (the usual decoding step): the wave's first weight blocks are requested before
     // the live-row count is read, which is a round trip to memory of its own.
-    const unsigned w_lane = (unsigned)lane * 16u;
     u32x4 avA[AT][UB];
     if (NT == 1) {
         const int k_lo = (KSp * wave * SL) >> s_sh, k_hi = (KSp * (wave * SL + 1)) >> s_sh;
@@ -369,7 +379,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
                 int k = (k_lo + u < k_hi ? k_lo + u : k_hi - 1) + k_turn(k_hi - k_lo);
                 k = k >= k_hi ? k - (k_hi - k_lo) : k;
 #pragma unroll
-                for (int i = 0; i < AT; ++i) avA[i][u] = buffer_load16<true>(wb[i], (unsigned)k * 1024u + w_lane);
+                for (int i = 0; i < AT; ++i) avA[i][u] = load_w(i, k);
             }
         }
         clamp_rows();
@@ -391,7 +401,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
             const unsigned off = (unsigned)k * 1024u;
             if (weights)
 #pragma unroll
-            for (int i = 0; i < AT; ++i) av[i][u] = buffer_load16<true>(wb[i], off + w_lane);
+            for (int i = 0; i < AT; ++i) av[i][u] = load_w(i, k);
 #pragma unroll
             for (int t = 0; t < NT; ++t)
                 if (t == 0 || t < nt_live) {           // a row tile without a live row is skipped altogether
@@ -550,7 +560,11 @@ static void launch_tilek_slices(const GemmArgs &a, hipStream_t st) {
     constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1;
     const GemmPlan &p = a.plan;
     const int S = p.tk_waves, W = S / SL;                            // K slices (8 or 16) and waves
-    const size_t lds = (size_t)S * FT * TILES * NT * 1024 + 256;
+    size_t lds = (size_t)S * FT * TILES * NT * 1024 + 256;
+    // One gate/up pair per workgroup: at most two workgroups per compute unit, by asking for more than a third of its LDS.
+    // The kernel's 77 registers would let three in; with two, the workgroups of the last round go to whichever units are
+    // done first: 7B at one row (688 workgroups) 30.1 -> 29.35 us, a k = 0 step of 32 layers 2.96 -> 2.93 ms; 13B 44.6 -> 44.4
+    if (NT == 1 && EPI == EPI_SWIGLU && FT == 1 && lds < 56 * 1024) lds = 56 * 1024;
     dim3 grid((p.tasks + FT - 1) / FT), block(W * 64);
     if (a.split) {
         static std::atomic<uint64_t> done{0};
