@@ -1,17 +1,19 @@
 """Prompt passes and batched steps over the row counts at which the GEMMs change their form (48 / 49 rows: tile-K to
 panel; a K split or none; row tiles and weight tiles per workgroup), on a shape whose k-steps fill no whole turn of
 the panel kernel's weight ring (36 and 89 k-steps) and whose last feature blocks are ragged.  Logits against the oracle
-in float64 within the project's bf16 tolerance, tokens exact."""
+in float64 within four times the error measured on this shape; accepted counts and tokens of every step exactly those the
+step's own logits say, and the oracle's wherever its two best logits are further apart than that error allows to swap."""
 import numpy as np
 import pytest
 
 import synth
-from oracle import OracleModel
+from oracle import OracleModel, CachedLLM, argmax_tokens, greedy_decode, top2_gap
 
 pytestmark = pytest.mark.gpu
 
 CFG = synth.ModelCfg("rows", 2, 1152, 9, 128, 2848, 1040, "bf16")
-ATOL, RTOL = 1e-2, 2e-2                     # measured here: below 1e-3 absolute
+# largest error over all cases below: 2.3e-4 (logits of rms 0.68; a lost k-step of 36 or a lost split range is above 1e-2)
+ATOL = 1e-3
 
 
 @pytest.fixture(scope="module")
@@ -21,20 +23,47 @@ def setup():
     return llma, w, OracleModel(CFG, w)
 
 
+def drafts_for(om, prompt, k, n_good, seed):
+    """k drafts after the prompt of which the oracle's own continuation gives the first n_good, the next one is wrong;
+    and the oracle's logits of the step's rows"""
+    cache = om.new_cache(len(prompt) + k + 1)
+    om.forward(prompt[:-1], cache, 0)
+    tok, out = int(prompt[-1]), synth.uniform_tokens(10, seed, k, CFG.vocab)
+    for j in range(min(n_good + 1, k)):
+        tok = int(argmax_tokens(om.forward([tok], cache, len(prompt) - 1 + j))[0])
+        out[j] = tok if j < n_good else (tok + 1) % CFG.vocab
+        tok = int(out[j])
+    return out, om.forward(np.concatenate([prompt, out]), om.new_cache(len(prompt) + k + 1), 0)[-(k + 1):]
+
+
+def check_step(got, want, draft, result, what, atol=ATOL):
+    """one sequence's rows: logits against the oracle, (accepted, next, emitted) against the logits' arg max"""
+    err = float(np.abs(got - want).max())
+    assert err <= atol, (what, err)
+    o = np.argmax(got, axis=-1)                                 # (first of equals: the lowest id)
+    clear = np.array([top2_gap(row) > 2 * atol for row in want])
+    assert np.array_equal(o[clear], argmax_tokens(want)[clear]), what
+    a = 0
+    while a < len(draft) and o[a] == draft[a]:
+        a += 1
+    n_acc, nxt, emitted = result
+    assert (int(n_acc), int(nxt), [int(t) for t in emitted]) == (a, int(o[a]), o[:a + 1].tolist()), what
+    return a
+
+
 @pytest.mark.parametrize("length", [2, 17, 18, 33, 49, 50, 65, 66, 81, 97, 145, 161, 162, 200, 321, 640])
 def test_prompt_lengths(setup, length):
     llma, w, om = setup
     ctx = llma.Context(CFG, w, max_seq=700, max_batch=1, max_k=4)
     ctx.enable_logits_dump(5)
     prompt = synth.uniform_tokens(7, length, length, CFG.vocab)
-    drafts = synth.uniform_tokens(8, length, 4, CFG.vocab).tolist()
-    want = om.forward(np.concatenate([prompt, drafts]), om.new_cache(700), 0)[-5:]
+    draft, want = drafts_for(om, prompt, 4, length % 5, length)
     for _ in range(3):                      # eager, captured, replayed
         ctx.reset()
         ctx.prefill(prompt)
-        ctx.verify_step(drafts)
-        got = ctx.logits(5)
-        assert np.all(np.abs(got - want) <= ATOL + RTOL * np.abs(want)), float(np.abs(got - want).max())
+        result = ctx.verify_step(draft)
+        check_step(ctx.logits(5), want, draft, result, length)
+        assert ctx.get_state() == (len(prompt) + result[0], result[1])
     ctx.close()
 
 
@@ -45,23 +74,80 @@ def test_step_rows(setup, seqs, k):
     ctx = llma.Context(CFG, w, max_seq=160, max_batch=seqs, max_k=k)
     ctx.enable_logits_dump(seqs * (k + 1))
     prompts = [synth.uniform_tokens(9, 10 * seqs + b, 20 + 3 * b, CFG.vocab) for b in range(seqs)]
-    drafts = np.stack([synth.uniform_tokens(10, 10 * seqs + b, k, CFG.vocab) for b in range(seqs)])
-    want = np.concatenate([om.forward(np.concatenate([p, d]), om.new_cache(160), 0)[-(k + 1):] for p, d in zip(prompts, drafts)])
+    steps = [drafts_for(om, p, k, (5 * b + 1) % (k + 1), 10 * seqs + b) for b, p in enumerate(prompts)]
     for b, p in enumerate(prompts):
         ctx.prefill(p, seq=b)
+    accepted = []
     for _ in range(3):
         for b, p in enumerate(prompts):
             ctx.truncate(len(p) - 1, seq=b)
             ctx.set_pending(p[-1], seq=b)
-        ctx.verify_step_batch(list(range(seqs)), drafts)
-        got = ctx.logits(seqs * (k + 1))
-        assert np.all(np.abs(got - want) <= ATOL + RTOL * np.abs(want)), float(np.abs(got - want).max())
+        n_acc, nxt, em = ctx.verify_step_batch(list(range(seqs)), np.stack([d for d, _ in steps]))
+        got = ctx.logits(seqs * (k + 1)).reshape(seqs, k + 1, -1)
+        accepted = [check_step(got[b], want, d, (n_acc[b], nxt[b], em[b]), (seqs, k, b)) for b, (d, want) in enumerate(steps)]
+        assert [ctx.get_state(b) for b in range(seqs)] == [(len(p) + accepted[b], int(nxt[b])) for b, p in enumerate(prompts)]
+    assert max(accepted) > 0
+    ctx.close()
+
+
+def test_prefix_of_passes_of_different_lengths(setup):
+    """K/V of a shared prefix, seen through the logits of a step on top of it: passes of up to 48 rows give the same bits
+    whatever their length (the decoding GEMM's K slices are a function of the shape), longer passes cut K by their row
+    count and differ by rounding only (measured 3.4e-5; the oracle is 1.5e-4 away from either)"""
+    llma, w, om = setup
+    toks = synth.uniform_tokens(12, 1, 700, CFG.vocab)
+    drafts = synth.uniform_tokens(12, 2, 4, CFG.vocab)
+    ctx = llma.Context(CFG, w, max_seq=700, max_batch=1, max_k=4)
+    ctx.enable_logits_dump(5)
+    first = None
+    for rows in (40, 41, 47, 48, 49, 65, 98, 145, 199, 320, 639):
+        ctx.reset()
+        ctx.prefill(toks[:rows + 1])
+        ctx.truncate(40)
+        ctx.set_pending(int(toks[40]))
+        ctx.verify_step(drafts)
+        got = ctx.logits(5).copy()
+        first = got if first is None else first
+        assert np.abs(got - first).max() <= (0.0 if rows <= 48 else 1.4e-4), rows
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_prompt_on_top_of_a_truncated_slot(setup, dtype):
+    """truncate and set_pending reach the device with the next step or the next prompt, whichever comes first"""
+    llma, w, om = setup
+    cfg = CFG
+    if dtype == "fp32":
+        cfg = synth.ModelCfg("f32", 2, 128, 4, 32, 258, 300, "fp32")
+        w = synth.make_weights(cfg, 41, gain_jitter=0.2)
+        om = OracleModel(cfg, w)
+    tol = ATOL if dtype == "bf16" else 1e-4
+    a, b, c = (synth.uniform_tokens(13, i, n, cfg.vocab) for i, n in ((0, 130), (1, 70), (2, 20)))
+    ctx = llma.Context(cfg, w, max_seq=400, max_batch=2, max_k=2)
+    ctx.enable_logits_dump(3)
+    for seq in (1, 0):
+        ctx.prefill(a, seq=seq)
+        for cut, more in ((100, b), (37, c), (0, b)):
+            ctx.truncate(cut, seq=seq)
+            ctx.prefill(more, seq=seq)
+            kept = np.concatenate([a[:cut], more])              # (each cut lies inside what is left of a)
+            assert ctx.get_state(seq) == (len(kept) - 1, int(kept[-1]))
+            ctx.verify_step([1, 2], seq=seq)
+            want = om.forward(np.concatenate([kept, [1, 2]]), om.new_cache(400), 0)[-3:]
+            assert np.abs(ctx.logits(3) - want).max() <= tol, (seq, cut)
+            ctx.truncate(len(kept) - 1, seq=seq)
+            ctx.set_pending(int(a[0]), seq=seq)
+            ctx.prefill(c, seq=seq)                             # a prompt replaces the pending token, it is not fed
+            ctx.verify_step([], seq=seq)
+            want = om.forward(np.concatenate([kept[:-1], c]), om.new_cache(400), 0)[-1:]
+            assert np.abs(ctx.logits(1) - want).max() <= tol, (seq, cut)
     ctx.close()
 
 
 @pytest.mark.parametrize("d,heads,dh,ffn,vocab", [(128, 4, 32, 258, 300), (192, 3, 64, 511, 97), (256, 2, 128, 1028, 512), (640, 5, 128, 516, 64)])
 def test_fp32_shapes(d, heads, dh, ffn, vocab):
-    """FFN widths that are no multiple of 4, several head widths, more and fewer elements than a pass of 512; 1, 8, 9 and 10 rows"""
+    """FFN widths that are no multiple of 4, several head widths, more and fewer elements than a pass of 512; 1, 8, 9 and 10 rows
+    (largest error measured: 3.7e-7)"""
     import paper_2304_04487_amd as llma
     cfg = synth.ModelCfg("f32", 2, d, heads, dh, ffn, vocab, "fp32")
     w = synth.make_weights(cfg, 41, gain_jitter=0.2)
@@ -69,18 +155,22 @@ def test_fp32_shapes(d, heads, dh, ffn, vocab):
     ctx = llma.Context(cfg, w, max_seq=200, max_batch=2, max_k=9)
     ctx.enable_logits_dump(20)
     prompt = synth.uniform_tokens(3, d, 120, vocab)
+    greedy = greedy_decode(CachedLLM(om, prompt, 200), 9)
     for k in (0, 7, 8, 9):
         drafts = synth.uniform_tokens(4, k, k, vocab)
+        drafts[:k // 2] = greedy[:k // 2]
         want = om.forward(np.concatenate([prompt, drafts]), om.new_cache(200), 0)[-(k + 1):]
         for b in range(2):
             ctx.reset(b)
             ctx.prefill(prompt, seq=b)
-        ctx.verify_step(drafts)
-        assert np.abs(ctx.logits(k + 1) - want).max() <= 1e-4
+        result = ctx.verify_step(drafts)
+        assert check_step(ctx.logits(k + 1), want, drafts, result, (d, k), 2e-6) >= k // 2
         ctx.reset(0)
         ctx.prefill(prompt)
-        ctx.verify_step_batch([1, 0], np.stack([drafts, drafts]))
-        assert np.abs(ctx.logits(2 * (k + 1)) - np.concatenate([want, want])).max() <= 1e-4
+        n_acc, nxt, em = ctx.verify_step_batch([1, 0], np.stack([drafts, drafts]))
+        got = ctx.logits(2 * (k + 1)).reshape(2, k + 1, -1)
+        for b in range(2):
+            check_step(got[b], want, drafts, (n_acc[b], nxt[b], em[b]), (d, k, b), 2e-6)
     ctx.close()
 
 
@@ -105,5 +195,5 @@ def test_activation_planes_beyond_4_gib():
         ctx.prefill(p, seq=b)
     ctx.verify_step_batch(list(range(seqs)), drafts)
     got = ctx.logits(seqs * (k + 1))
-    assert np.all(np.abs(got - want) <= ATOL + RTOL * np.abs(want)), float(np.abs(got - want).max())
+    assert np.all(np.abs(got - want) <= 1e-2 + 2e-2 * np.abs(want)), float(np.abs(got - want).max())     # (without the MLP: 0.9)
     ctx.close()

@@ -153,3 +153,17 @@ def test_prompt_passes_keep_both_activation_planes(ctx):
     assert ctx.verify([2]) == 0
     _, rows, split = ctx.notes()
     assert rows == [2] * (4 * ctx.L + 1) and split == [0] * (4 * ctx.L + 1)
+
+
+@both_types
+def test_state_calls_reach_the_next_prompt(ctx):
+    """reset, truncate and set_pending change the host's copy only; a prompt brings the device's up to date before it starts"""
+    ctx.prefill(20)
+    ctx.notes()
+    assert ctx.lib.llma_truncate(ctx.h, 0, 11) == 0 and ctx.lib.llma_set_pending(ctx.h, 0, 5) == 0
+    ctx.prefill(10)
+    assert ctx.notes()[0] == [11] and ctx.state() == (20, 1)
+    assert ctx.verify([1]) == 0 and ctx.state() == (21, 7)
+    assert ctx.lib.llma_reset(ctx.h, 0) == 0
+    ctx.prefill(4)
+    assert ctx.notes()[0] == [0] and ctx.state() == (3, 1)
