@@ -94,7 +94,11 @@ int llma_reset(llma_ctx *ctx, int32_t seq);
 /* Prompt processing (paper: the x of LLM(x, y)).  prompt: HOST int32[len], len >= 1.
  * Feeds prompt[0..len-2] through the model on top of the slot's current cache (T += len-1)
  * and makes prompt[len-1] the pending token, so the next step's first output is the first
- * generated token y_0.  Errors: RANGE if T + len - 1 + 1 > max_seq or a token id is out of range. */
+ * generated token y_0.  The prompt runs in passes of up to 2048 rows.  The sums of a pass of up to
+ * 48 rows are taken in the order of a decoding step, those of a longer one in an order that
+ * depends on its row count and on the device's number of compute units: K and V of the same
+ * tokens can differ in their last bits between prompts of different lengths or cut differently.
+ * Errors: RANGE if T + len - 1 + 1 > max_seq or a token id is out of range. */
 int llma_prefill(llma_ctx *ctx, int32_t seq, const int32_t *prompt, int32_t len);
 /* Reads the slot's state into HOST ints (either pointer may be NULL). pending = -1 if none. */
 int llma_get_state(llma_ctx *ctx, int32_t seq, int32_t *T, int32_t *pending);

@@ -9,9 +9,13 @@
 // coalesced 16-byte-per-lane loads, and use the MFMA unit because it consumes those
 // registers directly.  Activations enter the MFMAs as hi + lo bf16 pairs (the extra MFMAs are
 // free while memory-bound), which keeps 16 significand bits of every activation.
-// Reduction orders are fixed by the matrix shapes and by absolute key positions, never by the
-// number of rows in the step, so row j of a k-row step is bit-identical to the same token
-// processed in a one-row step.
+// In decoding steps, and in everything else of up to 48 rows, reduction orders are fixed by the matrix
+// shapes and by absolute key positions, never by the number of rows: row j of a k-row step is
+// bit-identical to the same token processed in a one-row step, in another step or in a short prompt
+// pass.  Steps of more rows share another order, fixed by the shape too (GemmPlan::n_split).  Prompt
+// passes of more than 48 rows cut the K axis by how many rows they have and how many compute units
+// there are (panel_prompt_split), so the K/V of a prefix differ at rounding level between passes of
+// different lengths (logits on top by 3e-5 where the oracle is 1.5e-4 away).
 #include <stdlib.h>
 
 #include <atomic>
@@ -319,7 +323,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
     TK_TRACE(0);
     // llma_generate launches k + 1 rows in every step; how many of them carry a token (1 + the
     // drafts the trigger found) is only known on the device.  The dead rows cost nothing here:
-    // their lanes re-read the first row's operands and the epilogue skips them.
+    // their lanes read past the end of a descriptor (zeros, no traffic) and the epilogue skips them.
     auto clamp_rows = [&]() {
         if (a.rows_live != nullptr) {
             const int live = *a.rows_live + 1;
