@@ -16,10 +16,10 @@
 // so a reference is cut into spans of TRIGGER_SPAN positions, one workgroup each, 16 loads per thread in flight;
 // the spans' best keys are merged by whoever needs them (a maximum: the order does not matter).  Most positions stop at
 // the one-token test.  What survives it is one position in 32000 for uniform ids, but 5 % of a text whose last token is a
-// comma or a newline, so the survivors are gathered and handled a thread each: the document by binary search, seven more
+// comma or a newline, so each wave gathers its survivors and handles them a lane each: the document by binary search, seven more
 // tokens, all requested at once.  The few that go on are followed one at a time by their wave, 64 tokens per step, best
 // prospect first -- in a repetitive text the first drops all others -- and side by side, 16 tokens per step, while there are many.
-// (Every survivor followed by its wave, one after the other, took 31 us at 5 % of 4096 positions, 223 at 50 %: now 7 and 12.)
+// (Every survivor followed by its wave, one after the other, took 31 us at 5 % of 4096 positions, 223 at 50 %: now 5 and 10.)
 // A call over 600 011 tokens on the device: 245 us in one workgroup, now 8.1; one span (the usual reference of a few
 // documents) is one launch (1472 host tokens: 44.3 -> 41.1 us, the rest is the copies).
 //
@@ -57,14 +57,14 @@ __device__ __forceinline__ int key_position(unsigned long long key) { return (in
 __device__ __forceinline__ unsigned long long scan_span(const int *y, int i, const int *ref, const int *doc_offsets, int n_docs,
                                                         int p_lo, int p_hi, int n) {
     constexpr int U = TRIGGER_SPAN / 256, PROBE = 8, STRIDE = 16;
-    __shared__ unsigned short hit[TRIGGER_SPAN];                // the survivors of the one-token test, p - p_lo, in no order
-    __shared__ int n_hit;
+    __shared__ unsigned short hits_of[4][TRIGGER_SPAN / 4];     // each wave's survivors of the one-token test: p - p_lo, ascending
     unsigned long long best = 0ull;
     if (i >= n && p_lo < p_hi) {                                // uniform
         const int lane = threadIdx.x & 63;
         const auto token_before = [&](int q, int t) { return ref[q - 1 - t > 0 ? q - 1 - t : 0]; };    // (compared only where it exists)
         const auto tail = [&](int t) { return y[i - 1 - t > 0 ? i - 1 - t : 0]; };
-        if (threadIdx.x == 0) n_hit = 0;
+        unsigned short *const hit = hits_of[threadIdx.x >> 6];
+        int total = 0;
         int prev[U], want[PROBE];
 #pragma unroll
         for (int t = 0; t < PROBE; ++t) want[t] = tail(t);
@@ -73,23 +73,18 @@ __device__ __forceinline__ unsigned long long scan_span(const int *y, int i, con
             const int p = p_lo + u * 256 + (int)threadIdx.x;
             prev[u] = ref[p < 1 ? 0 : (p < p_hi ? p - 1 : p_hi - 1)];
         }
-        __syncthreads();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int p = p_lo + u * 256 + (int)threadIdx.x;
             const bool same = p >= 1 && p < p_hi && prev[u] == want[0];
             const unsigned long long hits = __ballot(same);
-            if (hits == 0ull) continue;
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&n_hit, __popcll(hits));
-            base = __shfl(base, 0);
-            if (same) hit[base + __popcll(hits & ((1ull << lane) - 1ull))] = (unsigned short)(p - p_lo);
+            if (same) hit[total + __popcll(hits & ((1ull << lane) - 1ull))] = (unsigned short)(p - p_lo);
+            total += __popcll(hits);
         }
-        __syncthreads();
-        const int total = n_hit;
-        for (int h0 = 0; h0 < total; h0 += 256) {               // a survivor per thread
-            const bool mine = h0 + (int)threadIdx.x < total;
-            const int q = p_lo + hit[mine ? h0 + (int)threadIdx.x : 0];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (what one lane wrote, another reads: within the wave, no barrier)
+        for (int h0 = 0; h0 < total; h0 += 64) {                // a survivor per lane
+            const bool mine = h0 + lane < total;
+            const int q = p_lo + hit[mine ? h0 + lane : 0];
             int got[PROBE];
 #pragma unroll
             for (int t = 1; t < PROBE; ++t) got[t] = token_before(q, t);
@@ -105,19 +100,24 @@ __device__ __forceinline__ unsigned long long scan_span(const int *y, int i, con
                 const unsigned long long key = trigger_key(score, q);
                 best = key > best ? key : best;
             }
-            while (__ballot(more) != 0ull) {
+            for (unsigned long long left; (left = __ballot(more)) != 0ull;) {
                 // what cannot beat the wave's best is dropped; of the others the one with the most to gain is
                 // followed to its end by the whole wave, 64 tokens at a time
-                unsigned long long top = best, bound = more ? trigger_key(limit, q) : 0ull;
+                unsigned long long top = best;
+                const unsigned long long bound = more ? trigger_key(limit, q) : 0ull;
                 unsigned long long lead = bound;
+                if ((left & (left - 1ull)) != 0ull) {           // (one alone is simply followed)
 #pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) {
-                    const unsigned long long a = __shfl_xor(top, off), b = __shfl_xor(lead, off);
-                    top = a > top ? a : top;
-                    lead = b > lead ? b : lead;
+                    for (int off = 32; off >= 1; off >>= 1) {
+                        const unsigned long long a = __shfl_xor(top, off), b = __shfl_xor(lead, off);
+                        top = a > top ? a : top;
+                        lead = b > lead ? b : lead;
+                    }
+                    if (lead <= top) break;
+                    left = __ballot(bound == lead);
                 }
-                if (lead <= top) break;
-                const int src = __ffsll(__ballot(bound == lead)) - 1;
+                const int src = __ffsll(left) - 1;
+                lead = __shfl(bound, src);
                 const int ql = key_position(lead), ll = (int)(lead >> 32);
                 int sl = __shfl(score, src);
                 for (; sl < ll; sl += 64) {
