@@ -29,7 +29,7 @@ void launch_kv_import_f32(const void *k, const void *v, void *kc, void *vc, int 
 // RMSNorm runs inside: the wave sees every element of its rows anyway, so it adds their squares and scales the sums
 // (W (x g)) rstd at the end; RoPE and the cache append run in the epilogue.  Latency-bound at the shapes it
 // is used for (d 128, five rows): all loads of a pass over 512 elements are in flight together, where one element per
-// lane and trip left a round trip to memory per 64 elements.  Per step of the tiny model: 22 launches -> 15, O and down
+// lane and trip left a round trip to memory per 64 elements.  Per step of the tiny model: 22 launches -> 13 (with the row set-up that scans and embeds), O and down
 // 13.7 -> 3.9 us on average, SwiGLU 8.9 -> 5.1, QKV 6.7 (+ 3.0 + 3.6 for RoPE and RMSNorm) -> 5.1.
 template <int EPI, bool VEC>
 __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs a) {
