@@ -73,13 +73,22 @@ __device__ __forceinline__ f32x4 mfma16x16x32(u32x4 a, u32x4 b, f32x4 c) {
 // ---- tiled activation layout (bf16) ---------------------------------------------------------
 // Activations X[rows][K] that feed a GEMM are stored as the matching B-operand images, one
 // plane for the hi part and one for the lo part of each value: block (t, ks) of 1 KiB holds rows
-// 16 t .. 16 t+15, columns 32 ks .. +31; lane l owns X[16 t + l%16][32 ks + 8 (l/16) .. +7] and
-// finds it in the block's 16-byte piece xtile_piece(l) = 4 (l%16) + l/16: the pieces of a row are
-// adjacent (64 bytes), so a step with r live rows in a tile touches only the first 64 r bytes of
-// each block (lanes of rows past the end do not load at all).
-__host__ __device__ __forceinline__ int xtile_piece(int lane) { return ((lane & 15) << 2) | (lane >> 4); }
-__host__ __device__ __forceinline__ size_t xtile_off(int row, int col, int KSp) {
-    return ((size_t)((row >> 4) * KSp + (col >> 5)) * 64 + (size_t)((row & 15) * 4 + ((col & 31) >> 3))) * 8 + (col & 7);
+// 16 t .. 16 t+15, columns 32 ks .. +31; lane l owns X[16 t + l%16][32 ks + 8 (l/16) .. +7], one of
+// the block's 64 pieces of 16 bytes.  Where it lies depends on how many rows the step has (every kernel
+// of a step is told the same):
+//   up to XTILE_ROWWISE rows: piece 4 (l%16) + l/16.  The pieces of a row are adjacent (64 bytes), so a step
+//   with r rows touches only the first 64 r bytes of each block (lanes of rows past the end do not load at all);
+//   more rows: groups of four rows, piece 16 (l%16 / 4) + 4 (l/16) + l%4.  Four neighbouring lanes read 64 adjacent
+//   bytes, where the order above sends them to two cache lines and halves the rate of the CU's cache.
+// 7B layer, back to back, by row / by four rows: 9 rows 79.2 / 79.9 us, 48 rows 137.5 / 131.1, 144 rows 175.9 / 170.7,
+// 288 rows 279.4 / 272.3 (groups of two rows: no gain at 48; of eight: 83.9 at 9 rows, no better above).  At 17 rows the second
+// tile's one row makes it a loss (six steps of 13B 2.594 / 2.625 ms).
+#define XTILE_ROWWISE 32
+__host__ __device__ __forceinline__ int xtile_piece(int lane, bool quads) {
+    return quads ? (lane & 12) << 2 | (lane >> 4) << 2 | (lane & 3) : (lane & 15) << 2 | (lane >> 4);
+}
+__host__ __device__ __forceinline__ size_t xtile_off(int row, int col, int KSp, bool quads) {
+    return ((size_t)((row >> 4) * KSp + (col >> 5)) * 64 + (size_t)xtile_piece((row & 15) | (col & 24) << 1, quads)) * 8 + (col & 7);
 }
 
 // ---- KV cache layout (bf16), per (slot, head): max_seq x head_dim elements per plane ---------
@@ -168,6 +177,7 @@ struct AttnArgs {
     const int *lo_from;     // may be null: [max_batch] device ints, positions below lo_from[slot] have all-zero lo planes (imported bf16 caches)
     int n_rblocks;          // row blocks per sequence (set by the launcher)
     float scale;
+    bool quads;             // order of the pieces in Q and out tiles (xtile_piece): more than XTILE_ROWWISE rows in all
     float *po, *pm, *pl;    // partials
     void *out_hi, *out_lo;  // bf16: tiled planes over d_model (out_KSp k-steps per row tile); f32: out_hi = [R][d_model]
     int out_KSp;

@@ -53,7 +53,7 @@ struct GenState {             // device-resident state of llma_generate, one per
 void launch_take_step(const StepState &s, int n_seqs, int max_k, hipStream_t st);
 struct EmbedArgs {            // what the row set-up does with a row's token: h[r] = embed[token], and for bf16 models the first GEMM's input
     const void *embed; float *h; int d;
-    const float *gain; void *nx_hi, *nx_lo; float *ssq_out; int KSp;   // bf16 only (gain null: fp32): x = h * gain as tiled planes, sums of squares
+    const float *gain; void *nx_hi, *nx_lo; float *ssq_out; int KSp; bool quads;   // bf16 only (gain null: fp32): x = h * gain as tiled planes, sums of squares
 };
 // rows of a step: row (b, j) = pending[slot_b] (j = 0) or draft[b][j-1]; pos = T[slot_b] + j; embedded into e.h.
 // Generation steps (gen_dev set): the drafts are those of the best of part[b][0 .. spans), or with one span of the

@@ -147,7 +147,8 @@ __device__ __forceinline__ void epi_prefetch(const GemmArgs &a, const GemmPlan &
     }
 }
 
-template <int NT, int EPI, int TILES>
+// QUADS: the order of the pieces in activation tiles (xtile_piece)
+template <int NT, int EPI, int TILES, bool QUADS>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan &p, int task, int lane,
                                               f32x4 (&acc)[TILES][NT], const float *rstd_s, const EpiIn<NT> &in) {
     const int n = lane & 15, g4 = lane >> 4;
@@ -166,7 +167,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
                 *(f32x4 *)(a.out + (size_t)row * p.N + f0) = hv;
                 u32x2 hi, lo;
                 split4(x, hi, lo);
-                const size_t o = xtile_off(row, f0, a.nx_KSp);
+                const size_t o = xtile_off(row, f0, a.nx_KSp, QUADS);
                 *(u32x2 *)((bf16_t *)a.nx_hi + o) = hi;
                 *(u32x2 *)((bf16_t *)a.nx_lo + o) = lo;
             }
@@ -184,7 +185,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
                 }
                 u32x2 hi, lo;
                 split4(v, hi, lo);
-                const size_t o = xtile_off(row, f0, a.act_KSp);
+                const size_t o = xtile_off(row, f0, a.act_KSp, QUADS);
                 *(u32x2 *)((bf16_t *)a.act_hi + o) = hi;
                 *(u32x2 *)((bf16_t *)a.act_lo + o) = lo;
             }
@@ -233,7 +234,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
                     u32x2 hi, lo;
                     split4(o4, hi, lo);
                     if (sec == 0) {
-                        const size_t o = xtile_off(row, head * a.dh + c0, d / 32);
+                        const size_t o = xtile_off(row, head * a.dh + c0, d / 32, QUADS);
                         *(u32x2 *)((bf16_t *)a.q_hi + o) = hi;
                         *(u32x2 *)((bf16_t *)a.q_lo + o) = lo;
                     } else {
@@ -318,6 +319,8 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
     // up to 16 rows: 256 workgroups, one per compute unit) need four for enough bytes in flight
     constexpr int UB = (AT * NT >= 4) ? 1 : (AT * NT == 1 ? 4 : 2);
     constexpr int PL = SPLIT ? 2 : 1;
+    constexpr bool QUADS = NT * 16 > XTILE_ROWWISE;  // (a launch of NT row tiles has more than 16 (NT - 1) rows)
+    static_assert(XTILE_ROWWISE % 16 == 0 && XTILE_ROWWISE <= 48, "every launch of NT row tiles must use one order; the panel kernel has more than 48 rows");
     extern __shared__ f32x4 red[];                 // [S][AT][NT][64], then rstd[16*NT] floats
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6, S = W * SL;
     TK_TRACE(0);
@@ -394,7 +397,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
     unsigned x_lane[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
-        x_lane[t] = t * 16 + (lane & 15) < a.rows ? (unsigned)(t * KSp) * 1024u + (unsigned)xtile_piece(lane) * 16u : BUFFER_NOWHERE;
+        x_lane[t] = t * 16 + (lane & 15) < a.rows ? (unsigned)(t * KSp) * 1024u + (unsigned)xtile_piece(lane, QUADS) * 16u : BUFFER_NOWHERE;
 
     auto issue = [&](int ks, u32x4 (&av)[AT][UB], u32x4 (&bv)[PL][NT][UB], bool weights = true) {
 #pragma unroll
@@ -514,7 +517,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
             for (int w = 1; w < S; ++w) v += red[((w * AT + f * TILES + i) * NT + t) * 64 + lane];
             sum[i][0] = v;
         }
-        gemm_epilogue<1, EPI, TILES>(at, p, task, lane, sum, rstd_s + 16 * t, in);
+        gemm_epilogue<1, EPI, TILES, QUADS>(at, p, task, lane, sum, rstd_s + 16 * t, in);
     }
     TK_TRACE(3);
 }
@@ -737,7 +740,7 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
     // compiler's count of loads in flight inexact, and it then waits for all of them.
     // Activation chunk kc -> LDS stage: wave w fetches the 1 KiB blocks q = j 8 + w of the chunk's
     // [2 planes][RT][KC] blocks (the last ones twice if they do not divide); row tiles past the end read the block's first.
-    const unsigned x_lane = (unsigned)xtile_piece(lane) * 16u;     // LDS holds the block in lane order
+    const unsigned x_lane = (unsigned)xtile_piece(lane, true) * 16u;     // LDS holds the block in lane order
     const unsigned w_lane = (unsigned)lane * 16u;
     auto fetch_x = [&](int kc, int stage) {
 #pragma unroll
@@ -864,7 +867,7 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
             for (int i = 0; i < TILES; ++i)
 #pragma unroll
                 for (int t = 0; t < RT; ++t) sum[i][t] = acc[f * TILES + i][t];
-            gemm_epilogue<RT, EPI, TILES>(a, p, task, lane, sum, a0.rstd_in + r0, in);
+            gemm_epilogue<RT, EPI, TILES, true>(a, p, task, lane, sum, a0.rstd_in + r0, in);
         }
     }
 }
@@ -906,7 +909,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_finish_bf16(GemmArgs a0) {
             if (s < a0.ksplit) v[0] += v[s];
         sum[i][0] = v[0];
     }
-    gemm_epilogue<1, EPI, TILES>(a, p, task, lane, sum, rstd_sh[wave], in);
+    gemm_epilogue<1, EPI, TILES, true>(a, p, task, lane, sum, rstd_sh[wave], in);
 }
 template <int EPI>
 static void launch_splitk_finish(const GemmArgs &a, hipStream_t st) {
@@ -1100,7 +1103,7 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
         const int r = b * m + (j < m ? j : 0);
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s) {
-            const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32);
+            const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32, a.quads);
             qh0[s] = (*(const u32x4 *)((const bf16_t *)a.Qhi + off));
             ql0[s] = (*(const u32x4 *)((const bf16_t *)a.Qlo + off));
         }
@@ -1157,7 +1160,7 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
 #pragma unroll
             for (int s = 0; s < KSTEPS; ++s) {
                 if (NTQ == 1) { qh[s] = qh0[s]; ql[s] = ql0[s]; continue; }
-                const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32);
+                const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32, a.quads);
                 qh[s] = *(const u32x4 *)((const bf16_t *)a.Qhi + off);
                 ql[s] = *(const u32x4 *)((const bf16_t *)a.Qlo + off);
             }
@@ -1347,7 +1350,7 @@ __global__ __launch_bounds__(256, 2) void attn_walk_bf16_kernel(AttnArgs a) {
                 u32x4 qh[KSTEPS], ql[KSTEPS];
 #pragma unroll
                 for (int s = 0; s < KSTEPS; ++s) {
-                    const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32);
+                    const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32, true);
                     qh[s] = *(const u32x4 *)((const bf16_t *)a.Qhi + off);
                     ql[s] = *(const u32x4 *)((const bf16_t *)a.Qlo + off);
                 }
@@ -1507,13 +1510,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (!QLDS) {
 #pragma unroll
             for (int s = 0; s < KSTEPS; ++s) {
-                const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32);
+                const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32, true);
                 qh[q][s] = *(const u32x4 *)((const bf16_t *)a.Qhi + off);
                 ql[q][s] = *(const u32x4 *)((const bf16_t *)a.Qlo + off);
             }
         } else {
             for (int s = wave; s < KSTEPS; s += 4) {                 // (the four waves share the staging)
-                const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32);
+                const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32, true);
                 qs[((q * 2 + 0) * KSTEPS + s) * 64 + lane] = *(const u32x4 *)((const bf16_t *)a.Qhi + off);
                 qs[((q * 2 + 1) * KSTEPS + s) * 64 + lane] = *(const u32x4 *)((const bf16_t *)a.Qlo + off);
             }
@@ -1709,7 +1712,7 @@ __global__ void attn_combine_bf16_kernel(AttnArgs a, int rq) {
     float v[4] = {acc[0] / L, acc[1] / L, acc[2] / L, acc[3] / L};
     u32x2 hi, lo;
     split4(v, hi, lo);
-    const size_t o = xtile_off(r, h * DH + d4 * 4, a.out_KSp);
+    const size_t o = xtile_off(r, h * DH + d4 * 4, a.out_KSp, a.quads);
     *(u32x2 *)((bf16_t *)a.out_hi + o) = hi;
     *(u32x2 *)((bf16_t *)a.out_lo + o) = lo;
 }
@@ -1754,7 +1757,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int j = j0 + q * 16 + n;
         rpos[q] = j < m ? T + j : -1;
         for (int s = wave; s < KSTEPS; s += 4) {
-            const size_t off = xtile_off(j < m ? j : 0, h * DH + s * 32 + g * 8, d_model / 32);
+            const size_t off = xtile_off(j < m ? j : 0, h * DH + s * 32 + g * 8, d_model / 32, true);
             qs[((q * 2 + 0) * KSTEPS + s) * 64 + lane] = *(const u32x4 *)((const bf16_t *)a.Qhi + off);
             qs[((q * 2 + 1) * KSTEPS + s) * 64 + lane] = *(const u32x4 *)((const bf16_t *)a.Qlo + off);
         }
@@ -1899,7 +1902,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         float v[4] = {acc[0] / L, acc[1] / L, acc[2] / L, acc[3] / L};
         u32x2 hi, lo;
         split4(v, hi, lo);
-        const size_t off = xtile_off(j0 + j, h * DH + d4 * 4, a.out_KSp);
+        const size_t off = xtile_off(j0 + j, h * DH + d4 * 4, a.out_KSp, true);
         *(u32x2 *)((bf16_t *)a.out_hi + off) = hi;
         *(u32x2 *)((bf16_t *)a.out_lo + off) = lo;
     }

@@ -271,7 +271,7 @@ __device__ __forceinline__ void embed_row(const EmbedArgs &e, int r, int tok) {
             u32x2 h0, l0, h1, l1;
             split4(x, h0, l0);
             split4(x + 4, h1, l1);
-            const size_t o = xtile_off(r, c0, e.KSp);
+            const size_t o = xtile_off(r, c0, e.KSp, e.quads);
             *(u32x4 *)((bf16_t *)e.nx_hi + o) = (u32x4){h0[0], h0[1], h1[0], h1[1]};
             *(u32x4 *)((bf16_t *)e.nx_lo + o) = (u32x4){l0[0], l0[1], l1[0], l1[1]};
         }

@@ -583,7 +583,7 @@ static int forward_bf16(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_he
     aa.rows_live = c->rows_live;
     aa.lo_from = c->kv_split ? c->lo_from : nullptr;
     aa.max_seq = c->seq_cap; aa.n_chunks = n_chunks; aa.scale = 1.0f / sqrtf((float)dh);
-    aa.po = c->po; aa.pm = c->pm; aa.pl = c->pl; aa.out_hi = c->att_hi; aa.out_lo = c->att_lo; aa.out_KSp = ksp_d;
+    aa.po = c->po; aa.pm = c->pm; aa.pl = c->pl; aa.out_hi = c->att_hi; aa.out_lo = c->att_lo; aa.out_KSp = ksp_d; aa.quads = R > XTILE_ROWWISE;
     for (int l = 0; l < L; ++l) {
         GemmArgs ga = base;
         ga.W = c->wqkv[l]; ga.plan = c->plan_qkv; ga.Xhi = c->xhi; ga.Xlo = c->xlo; ga.epi = EPI_QKV; ga.ssq_in = c->ssq;
@@ -643,7 +643,7 @@ static int step_body(llma_ctx *c, int kind, int n_seqs, int m, int n_chunks, int
     const int mk = c->cfg.max_k;
     EmbedArgs e{};
     e.embed = c->embed; e.h = c->h; e.d = c->cfg.d_model;
-    if (c->bf16) { e.gain = c->n1[0]; e.nx_hi = c->xhi; e.nx_lo = c->xlo; e.ssq_out = c->ssq; e.KSp = c->plan_qkv.KSp; }
+    if (c->bf16) { e.gain = c->n1[0]; e.nx_hi = c->xhi; e.nx_lo = c->xlo; e.ssq_out = c->ssq; e.KSp = c->plan_qkv.KSp; e.quads = n_seqs * m > XTILE_ROWWISE; }
     c->rows_live = nullptr;
     if (kind == STEP_PREFILL) {
         launch_setup_prefill_rows(c->s, c->gen_prompt, c->gen_counters + 4 * c->cfg.max_batch, m, slot, c->cs_table, c->cfg.head_dim / 2, e, st);
