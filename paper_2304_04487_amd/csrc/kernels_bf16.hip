@@ -629,8 +629,12 @@ static void launch_gemm_nt(const GemmArgs &a, hipStream_t st) {
 // before): the order of requests is the source's (the compiler moved every one next to its use), the activations
 // take no registers on the way to LDS, no mask on the weights and no early exit inside a turn of the ring (either
 // made every turn end with a wait for all loads in flight), and the buffer form of the loads into LDS (the global
-// form counts as a flat access: behind one the compiler waits for everything).  4.85 ms / 177 us.  Waves that take four
-// weight tiles and half of the rows (half the LDS reads, each weight block loaded by two waves): 5.18 ms / 208 us.
+// form counts as a flat access: behind one the compiler waits for everything).  4.85 ms / 177 us.  Then the requests
+// spread over the chunk's MFMAs (all made at its start they kept the wave from its first MFMA for a third of the chunk)
+// and the barrier moved before its last group: 4.63 -> 4.51 ms / 170.5 -> 167.0 us, 288 rows 272 -> 258, 528 rows 441 -> 410.  A chunk
+// of 9 row tiles went from 3420 to 3070 cycles, 2304 of them MFMA, but the clock from 1.62 to 1.51 GHz: long prompts
+// are bound by the card's power.  Waves that take four weight tiles and half of the rows (half the LDS reads, each weight
+// block loaded by two waves): 5.18 ms / 208 us; four waves of four tiles and all rows, 512 registers: 4.6 % slower than eight.
 // ---------------------------------------------------------------------------------------------
 // rstd[row] = rsqrt(sum of the row's per-tile sums of squares / d + eps), same summation order as
 // the decoding kernels' in-kernel version (16 threads per row, contiguous chunks, butterfly); r = the
@@ -679,6 +683,7 @@ __device__ __forceinline__ void requests_stay_in_order() { asm volatile("" ::: "
 template <int RT, int EPI, int PT>
 struct PanelShape {
     static constexpr int AT = PT / 8;                                    // weight tiles per wave
+    static_assert(PANEL_KC % 2 == 0, "an even number of groups per chunk: the first group's registers are the same in every chunk");
     static constexpr int TG = (RT + 3) / 4, TB = (RT + TG - 1) / TG;     // row tiles whose operands are read from LDS together
     static constexpr int WD = PANEL_TURN;                                // k-steps of weights in registers
     static constexpr int XB = (2 * RT * PANEL_KC + 7) / 8;               // activation blocks a wave fetches per chunk
@@ -738,27 +743,21 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
     // arithmetic) plus one per-lane byte offset that never changes (the lane's 16 bytes of a 1 KiB
     // block); every load is unconditional (indices are clamped instead): a load under a branch makes the
     // compiler's count of loads in flight inexact, and it then waits for all of them.
-    // Activation chunk kc -> LDS stage: wave w fetches the 1 KiB blocks q = j 8 + w of the chunk's
+    // Activation chunk kc -> LDS stage: wave w fetches the 1 KiB blocks q = j 8 + w, j < XB, of the chunk's
     // [2 planes][RT][KC] blocks (the last ones twice if they do not divide); row tiles past the end read the block's first.
     const unsigned x_lane = (unsigned)xtile_piece(lane, true) * 16u;     // LDS holds the block in lane order
     const unsigned w_lane = (unsigned)lane * 16u;
-    auto fetch_x = [&](int kc, int stage) {
-#pragma unroll
-        for (int j = 0; j < XB; ++j) {
-            int q = j * 8 + wave;
-            q = q < 2 * RT * KC ? q : 2 * RT * KC - 1;
-            const int pl = q / (RT * KC), t = (q % (RT * KC)) / KC, kk = q % KC;
-            int k = kc * KC + kk;
-            k = k < KSp ? k : KSp - 1;
-            const int tt = t < n_rt ? t : 0;
-            load_to_lds(pl ? xl : xh, x_lane, (unsigned)(tt * KSp + k) * 1024u, xs + stage * CH + q * 64);
-        }
+    auto fetch_x = [&](int kc, int stage, int j) {
+        int q = j * 8 + wave;
+        q = q < 2 * RT * KC ? q : 2 * RT * KC - 1;
+        const int pl = q / (RT * KC), t = (q % (RT * KC)) / KC, kk = q % KC;
+        int k = kc * KC + kk;
+        k = k < KSp ? k : KSp - 1;
+        const int tt = t < n_rt ? t : 0;
+        load_to_lds(pl ? xl : xh, x_lane, (unsigned)(tt * KSp + k) * 1024u, xs + stage * CH + q * 64);
     };
-    // weights of k-step k0, one 1 KiB block per tile; a k-step past the end of K lies outside the descriptor: zeros
-    auto fetch_w = [&](int k0, u32x4 (&av)[AT]) {
-#pragma unroll
-        for (int i = 0; i < AT; ++i) av[i] = buffer_load16<false>(wb[i], (unsigned)k0 * 1024u + w_lane);
-    };
+    // weights of tile i, k-step k0: a 1 KiB block; a k-step past the end of K lies outside the descriptor: zeros
+    auto fetch_w = [&](int k0, int i) -> u32x4 { return buffer_load16<false>(wb[i], (unsigned)k0 * 1024u + w_lane); };
 
     f32x4 acc[AT][RT];
 #pragma unroll
@@ -774,47 +773,62 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
     const int kc_lo = (int)((long)turns * blockIdx.y / n_split) * (PANEL_TURN / KC), kc_hi = (int)((long)turns * (blockIdx.y + 1) / n_split) * (PANEL_TURN / KC);
     u32x4 wreg[WD][AT];
     PN_TRACE(0, 63);
-    fetch_x(kc_lo, 0);
-    fetch_x(kc_lo + 1, 1);
+#pragma unroll
+    for (int l = 0; l < 2 * XB; ++l) fetch_x(kc_lo + l / XB, l / XB, l % XB);
     requests_stay_in_order();
 #pragma unroll
-    for (int j = 0; j < WD - KC; ++j) fetch_w(kc_lo * KC + j, wreg[j]);
+    for (int j = 0; j < WD - KC; ++j)
+#pragma unroll
+        for (int i = 0; i < AT; ++i) wreg[j][i] = fetch_w(kc_lo * KC + j, i);
     PN_TRACE(1, 63);
+    // The MFMAs of a chunk run in groups of TB row tiles of one k-step; a group's operands come from LDS while the
+    // group before it multiplies.
+    constexpr int TG = Shape::TG, TB = Shape::TB, NG = KC * TG;
+    u32x4 b[2][TB][2];
+    auto read_group = [&](const u32x4 *xb, int g, u32x4 (&to)[TB][2]) {
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+            if ((g % TG) * TB + t < RT) {
+                const int at = (((g % TG) * TB + t) * KC + g / TG) * 64;
+                to[t][0] = xb[at];
+                to[t][1] = xb[CH / 2 + at];
+            }
+    };
+    wait_loads_and_barrier<Shape::LATER>();
+    read_group(xs + lane, 0, b[0]);
     int stage = 0;
-    // One chunk: wait for its activations (requested two chunks ago; behind them the wave has requested the next
-    // chunk's and the weights of two chunks), meet the other waves -- which also says that the previous chunk's
-    // stage has been read by all --, request the chunk after the next into that stage and the weights WD - KC k-steps
-    // ahead into the ring sets of the previous chunk, and run the MFMAs, a group of row tiles at a time while the
-    // next group's operands come from LDS.  (Requests past the end of the range or of K are unused.)  The order is
-    // the source's: left alone, the compiler moves every request next to its use.
+    // One chunk.  Its first group's operands are in registers already.  During its groups the wave requests, one or two
+    // at a time, the activations of the chunk after the next (into the stage of the previous chunk, which all waves
+    // have read) and the weights WD - KC k-steps ahead (into the ring sets of the previous chunk).  Before the last group it waits for the
+    // next chunk's activations -- requested during the previous chunk; behind them it has requested the weights of two chunks and one
+    // chunk's activations --, meets the other waves, and reads the next chunk's first group.  (Requests past the end
+    // of the range or of K are unused.)  The order is the source's: left alone, the compiler moves every request next to its use.
     auto chunk = [&](int kc, auto slot) {
         constexpr int c = decltype(slot)::value;        // chunk within the turn of the weight ring
-        constexpr int TG = Shape::TG, TB = Shape::TB, NG = KC * TG;
-        PN_TRACE(0, kc - kc_lo);
-        wait_loads_and_barrier<Shape::LATER>();
-        PN_TRACE(1, kc - kc_lo);
+        constexpr int REQ = XB + KC * AT;               // requests, all made before the last group
         const u32x4 *xb = xs + stage * CH + lane;
-        u32x4 b[2][TB][2];
-        auto read_group = [&](int g) {
-#pragma unroll
-            for (int t = 0; t < TB; ++t)
-                if ((g % TG) * TB + t < RT) {
-                    const int at = (((g % TG) * TB + t) * KC + g / TG) * 64;
-                    b[g & 1][t][0] = xb[at];
-                    b[g & 1][t][1] = xb[CH / 2 + at];
-                }
+        const int prev = stage == 0 ? PANEL_STAGES - 1 : stage - 1, next = stage == PANEL_STAGES - 1 ? 0 : stage + 1;
+        auto request = [&](int l) {
+            const int u = (l - XB) / AT, i = (l - XB) % AT;
+            if (l < XB) fetch_x(kc + 2, prev, l);
+            else wreg[(c * KC + u + WD - KC) % WD][i] = fetch_w(kc * KC + u + WD - KC, i);
         };
-        read_group(0);
-        const int prev = stage == 0 ? PANEL_STAGES - 1 : stage - 1;
-        fetch_x(kc + 2, prev);
-        requests_stay_in_order();
-#pragma unroll
-        for (int u = 0; u < KC; ++u) fetch_w(kc * KC + u + WD - KC, wreg[(c * KC + u + WD - KC) % WD]);
+        PN_TRACE(0, kc - kc_lo);
         requests_stay_in_order();
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-            if (g + 1 < NG) read_group(g + 1);
+            if (g + 1 < NG) {
+                read_group(xb, g + 1, b[(g + 1) & 1]);
+            } else {
+                PN_TRACE(1, kc - kc_lo);
+                wait_loads_and_barrier<Shape::LATER>();
+                PN_TRACE(2, kc - kc_lo);
+                read_group(xs + next * CH + lane, 0, b[0]);
+            }
             __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int l = 0; l < REQ; ++l)
+                if (l * (NG - 1) / REQ == g) { request(l); requests_stay_in_order(); }
             const int j = c * KC + g / TG;              // ring set of this k-step (a constant after unrolling)
 #pragma unroll
             for (int t = 0; t < TB; ++t)
@@ -828,8 +842,7 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
                         }
             __builtin_amdgcn_sched_barrier(0);
         }
-        stage = stage == PANEL_STAGES - 1 ? 0 : stage + 1;
-        PN_TRACE(2, kc - kc_lo);
+        stage = next;
     };
     // (no way out of a turn: an early exit made the compiler copy the ring's registers at the end of every turn, behind
     // a wait for all loads in flight)

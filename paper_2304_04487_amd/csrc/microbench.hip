@@ -25,8 +25,8 @@ __device__ unsigned long long tk_trace[TR_WG * 16 * 4];
 #define TK_TRACE_1 if ((threadIdx.x & 63) == 0 && !tk_seen) { tk_seen = 1; TK_STAMP(1); }
 #define TK_TRACE_2 if ((threadIdx.x & 63) == 0) TK_STAMP(2)
 #define TK_TRACE_3 if ((threadIdx.x & 63) == 0) TK_STAMP(3)
-// panel GEMM (batched steps): per wave and chunk of the K loop: 0 chunk start, 1 MFMAs issued, 2 next chunk's
-// activations parked in LDS, 3 past the chunk barrier; chunk 63: 0 kernel entry, 1 first chunk staged, 2 partial sums written
+// panel GEMM (batched steps): per wave and chunk of the K loop: 0 chunk start, 1 all requests and all MFMAs but the
+// last group's issued, 2 past the barrier; chunk 63: 0 kernel entry, 1 first loads requested, 2 partial sums written
 #define PN_WG 1024
 __device__ unsigned long long pn_trace[(size_t)PN_WG * 8 * 64 * 4];
 #ifdef MICROBENCH_TIMELINE
@@ -177,15 +177,14 @@ static void timeline_panel(const Shape &sh, const Bufs &b, int rows, float *part
     int G = 0;
     for (int g = 0; g < PN_WG; ++g) if (at(g, 0, 63, 0)) { G = g + 1; t0 = std::min(t0, at(g, 0, 63, 0)); }
     printf("%s, %d rows, %d K ranges: %d workgroups traced, event pair around panel + finishing kernel %.2f us\n", sh.name, rows, a.ksplit, G, ms * 1e3);
-    std::vector<double> entry, staged, done, mf, park, bar, nch;
+    std::vector<double> entry, asked, done, mf, bar, nch;
     for (int g = 0; g < G; ++g)
         for (int w = 0; w < 8; ++w) {
-            entry.push_back((at(g, w, 63, 0) - t0) * 0.01); staged.push_back((at(g, w, 63, 1) - at(g, w, 63, 0)) * 0.01);
+            entry.push_back((at(g, w, 63, 0) - t0) * 0.01); asked.push_back((at(g, w, 63, 1) - at(g, w, 63, 0)) * 0.01);
             done.push_back((at(g, w, 63, 2) - t0) * 0.01);
             int n = 0;
-            for (int ch = 0; ch < 63 && at(g, w, ch, 3); ++ch, ++n) {
-                mf.push_back((at(g, w, ch, 1) - at(g, w, ch, 0)) * 0.01); park.push_back((at(g, w, ch, 2) - at(g, w, ch, 1)) * 0.01);
-                bar.push_back((at(g, w, ch, 3) - at(g, w, ch, 2)) * 0.01);
+            for (int ch = 0; ch < 63 && at(g, w, ch, 2); ++ch, ++n) {
+                mf.push_back((at(g, w, ch, 1) - at(g, w, ch, 0)) * 0.01); bar.push_back((at(g, w, ch, 2) - at(g, w, ch, 1)) * 0.01);
             }
             nch.push_back(n);
         }
@@ -193,14 +192,14 @@ static void timeline_panel(const Shape &sh, const Bufs &b, int rows, float *part
         std::sort(v.begin(), v.end()); const size_t n = v.size(); double sum = 0; for (double x : v) sum += x;
         printf("   %-34s mean %6.2f  min %6.2f  p10 %6.2f  p50 %6.2f  p90 %6.2f  max %6.2f us\n", nm, sum / n, v[0], v[n / 10], v[n / 2], v[n * 9 / 10], v[n - 1]);
     };
-    show("wave entry (after first entry)", entry); show("entry -> first chunk staged", staged); show("chunks per wave", nch);
-    show("chunk: start -> MFMAs issued", mf); show("chunk: park next activations", park); show("chunk: barrier", bar);
+    show("wave entry (after first entry)", entry); show("entry -> first loads requested", asked); show("chunks per wave", nch);
+    show("chunk: start -> before the wait", mf); show("chunk: wait and barrier", bar);
     show("partial sums written (after first entry)", done);
     // one wave in detail
-    printf("   workgroup 0, wave 0, per chunk (start since entry | MFMAs | park | barrier):");
-    for (int ch = 0; ch < 63 && at(0, 0, ch, 3); ++ch)
-        printf("%s %5.2f|%4.2f|%4.2f|%4.2f", ch % 4 == 0 ? "\n     " : "  ", (at(0, 0, ch, 0) - at(0, 0, 63, 0)) * 0.01, (at(0, 0, ch, 1) - at(0, 0, ch, 0)) * 0.01,
-               (at(0, 0, ch, 2) - at(0, 0, ch, 1)) * 0.01, (at(0, 0, ch, 3) - at(0, 0, ch, 2)) * 0.01);
+    printf("   workgroup 0, wave 0, per chunk (start since entry | before the wait | wait and barrier):");
+    for (int ch = 0; ch < 63 && at(0, 0, ch, 2); ++ch)
+        printf("%s %5.2f|%4.2f|%4.2f", ch % 4 == 0 ? "\n     " : "  ", (at(0, 0, ch, 0) - at(0, 0, 63, 0)) * 0.01, (at(0, 0, ch, 1) - at(0, 0, ch, 0)) * 0.01,
+               (at(0, 0, ch, 2) - at(0, 0, ch, 1)) * 0.01);
     printf("\n");
 }
 static void cmd_panel() {
