@@ -110,7 +110,7 @@ __host__ __device__ __forceinline__ size_t vcache_off(int pos, int c, int dh) {
 }
 
 // ---- launcher argument structs --------------------------------------------------------------
-enum { EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_QKV = 4 };
+enum { EPI_RAW = 0 /* panel GEMM, split-K form: partial sums, a second kernel runs the epilogue */, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_QKV = 4 };
 
 // how one weight matrix is cut into work: a function of its shape only (never of the row count)
 struct GemmPlan {
@@ -138,7 +138,7 @@ struct GemmArgs {          // bf16 path (fields marked f32 are used by the fp32 
     int ssq_tiles;         //   rstd[row] = rsqrt(sum / (16 ssq_tiles) + eps)
     float eps;
     const float *rstd_in;  // panel GEMM only: [rows] precomputed rstd (instead of ssq_in)
-    float *rstd_out;       // panel GEMM, split-K form: if set, one extra workgroup computes every row's rstd from ssq_in into it (for the finishing kernel)
+    float *rstd_out;       // panel GEMM, split-K form: if set, every row's rstd is computed from ssq_in into it beside the products (for the finishing kernel)
     const int *rows_live;  // tile-K GEMM only, may be null: device int, rows 0 .. *rows_live carry tokens (the rest of `rows` is padding)
     int panel_rb;          // panel GEMM only: row blocks (set by the launcher)
     int ksplit;            // panel GEMM only: > 1 = the K axis is cut into this many ranges of k-chunks, partial sums via `part`

@@ -618,8 +618,9 @@ static void launch_gemm_nt(const GemmArgs &a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Panel GEMM (prompt passes and steps of more than 48 rows): a workgroup computes a block of 16 (or 8) weight tiles x
-// RT row tiles over a range of the K axis.  Its 8 waves take two (one) weight tiles each and all RT row tiles.  The
+// Panel GEMM (prompt passes and steps of more than 48 rows): a workgroup computes a block of weight tiles x
+// RT row tiles over a range of the K axis.  Its 8 waves take two (or one) weight tiles each and all RT row tiles; where the K
+// axis is split, 5 to 7 waves of two tiles are another way to give every compute unit one workgroup (panel_cut).  The
 // block's activations pass through LDS in chunks of KC k-steps, three chunks deep, loaded straight into LDS (buffer
 // loads; no registers, no LDS stores); every wave streams its own weight blocks from memory / L2, where the workgroups
 // of the other row blocks find them again, into a ring of WD register sets.  One barrier per chunk.
@@ -680,22 +681,22 @@ __device__ __forceinline__ void wait_loads_and_barrier() { asm volatile("s_waitc
 // the counted wait above relies on the order in which a wave's loads were issued
 __device__ __forceinline__ void requests_stay_in_order() { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); }
 
-template <int RT, int EPI, int PT>
+// RT row tiles, NW waves of AT weight tiles each
+template <int RT, int AT, int NW>
 struct PanelShape {
-    static constexpr int AT = PT / 8;                                    // weight tiles per wave
     static_assert(PANEL_KC % 2 == 0, "an even number of groups per chunk: the first group's registers are the same in every chunk");
     static constexpr int TG = (RT + 3) / 4, TB = (RT + TG - 1) / TG;     // row tiles whose operands are read from LDS together
     static constexpr int WD = PANEL_TURN;                                // k-steps of weights in registers
-    static constexpr int XB = (2 * RT * PANEL_KC + 7) / 8;               // activation blocks a wave fetches per chunk
+    static constexpr int XB = (2 * RT * PANEL_KC + NW - 1) / NW;         // activation blocks a wave fetches per chunk
     // loads a wave has certainly requested after a chunk's activations when it comes to wait for them: the next
     // chunk's, and the weights of two chunks (before the first chunk: of the ring's first turn)
     static constexpr int LATER = XB + (WD - PANEL_KC < 2 * PANEL_KC ? WD - PANEL_KC : 2 * PANEL_KC) * AT;
     static_assert(LATER <= 63, "the wait counter has six bits");
 };
-template <int RT, int EPI, int PT>
-__global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
-    using Shape = PanelShape<RT, EPI, PT>;
-    constexpr int AT = Shape::AT, WD = Shape::WD, XB = Shape::XB;
+template <int RT, int EPI, int AT, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
+    using Shape = PanelShape<RT, AT, NW>;
+    constexpr int WD = Shape::WD, XB = Shape::XB;
     constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1, FT = AT / TILES;
     constexpr int KC = PANEL_KC;
     constexpr int CH = 2 * RT * KC * 64;           // 16-byte pieces per stage (both planes)
@@ -703,25 +704,18 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const GemmPlan &p = a0.plan;
     const int KSp = p.KSp;
-    if (a0.rstd_out != nullptr && blockIdx.x == gridDim.x - 1) {
-        // split-K form: one workgroup more than the tiles need turns the rows' sums of squares into
-        // rstd for the finishing kernel, beside the others instead of in a launch of its own
-        if (blockIdx.y == 0)
-            for (int r = threadIdx.x >> 4; r < ((a0.rows + 15) & ~15); r += 512 / 16)
-                rstd_of_row(a0.ssq_in, a0.ssq_tiles, a0.eps, a0.rstd_out, a0.rows, r, threadIdx.x & 15);
-        return;
-    }
     // Workgroup order: the row blocks of one feature block get ids that differ by multiples of 8, i.e.
     // they are dispatched close together and onto the same XCD, so the feature block's weights are
     // fetched from HBM once and found in that XCD's L2 by the other row blocks.
     const int RB = a0.panel_rb;
     const int grp = blockIdx.x / (8 * RB), within = blockIdx.x % (8 * RB);
     const int fb = grp * 8 + (within & 7), rb = within >> 3;
+    if (fb * NW * FT >= p.tasks) return;           // (feature blocks are padded to whole groups of 8)
     const int r0 = rb * (16 * RT);
     const int rt0 = r0 / 16;
     GemmArgs a = a0;
     offset_rows(a, p, r0);
-    const int task0 = (fb * 8 + wave) * FT;         // may lie past the last tile (padding feature blocks): clamped loads, no epilogue
+    const int task0 = (fb * NW + wave) * FT;         // may lie past the last tile (padding feature blocks): clamped loads, no epilogue
 
     rsrc_t wb[AT];                                 // a descriptor per weight tile (wave-uniform)
 #pragma unroll
@@ -743,12 +737,12 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
     // arithmetic) plus one per-lane byte offset that never changes (the lane's 16 bytes of a 1 KiB
     // block); every load is unconditional (indices are clamped instead): a load under a branch makes the
     // compiler's count of loads in flight inexact, and it then waits for all of them.
-    // Activation chunk kc -> LDS stage: wave w fetches the 1 KiB blocks q = j 8 + w, j < XB, of the chunk's
+    // Activation chunk kc -> LDS stage: wave w fetches the 1 KiB blocks q = j NW + w, j < XB, of the chunk's
     // [2 planes][RT][KC] blocks (the last ones twice if they do not divide); row tiles past the end read the block's first.
     const unsigned x_lane = (unsigned)xtile_piece(lane, true) * 16u;     // LDS holds the block in lane order
     const unsigned w_lane = (unsigned)lane * 16u;
     auto fetch_x = [&](int kc, int stage, int j) {
-        int q = j * 8 + wave;
+        int q = j * NW + wave;
         q = q < 2 * RT * KC ? q : 2 * RT * KC - 1;
         const int pl = q / (RT * KC), t = (q % (RT * KC)) / KC, kk = q % KC;
         int k = kc * KC + kk;
@@ -781,6 +775,13 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
 #pragma unroll
         for (int i = 0; i < AT; ++i) wreg[j][i] = fetch_w(kc_lo * KC + j, i);
     PN_TRACE(1, 63);
+    if (EPI == EPI_RAW && a0.rstd_out != nullptr) {
+        // the rows' sums of squares become rstd for the finishing kernel here, four rows per wave of as many workgroups as that
+        // takes (one wave of each, as far as they go round), while the first operands are on their way
+        const int blocks = (p.tasks + NW * FT - 1) / (NW * FT) * RB;
+        const int id = ((int)blockIdx.y * blocks + fb * RB + rb) + blocks * (int)gridDim.y * wave;
+        if (id * 4 < a0.rows) rstd_of_row(a0.ssq_in, a0.ssq_tiles, a0.eps, a0.rstd_out, a0.rows, id * 4 + (lane >> 4), lane & 15);
+    }
     // The MFMAs of a chunk run in groups of TB row tiles of one k-step; a group's operands come from LDS while the
     // group before it multiplies.
     constexpr int TG = Shape::TG, TB = Shape::TB, NG = KC * TG;
@@ -854,21 +855,20 @@ __global__ __launch_bounds__(512, 2) void gemm_panel_bf16(GemmArgs a0) {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing may still be on its way into LDS when the workgroup ends
 
-    if (n_split > 1) {
-        // partial sums as register images: [range][tile (SwiGLU: gate tiles, then up tiles)][row tile][lane]
+    if constexpr (EPI == EPI_RAW) {
+        // partial sums as register images: [range][tile (gate/up: gate tiles, then up tiles)][row tile][lane]
         f32x4 *part = (f32x4 *)a0.part;
 #pragma unroll
-        for (int f = 0; f < FT; ++f)
+        for (int f = 0; f < AT; ++f)
 #pragma unroll
-            for (int i = 0; i < TILES; ++i)
-#pragma unroll
-                for (int t = 0; t < RT; ++t)
-                    if (task0 + f < p.tasks && rt0 + t < n_rt_total)
-                        part[(((size_t)blockIdx.y * (p.tasks * TILES) + task0 + f + i * p.tasks) * n_rt_total + rt0 + t) * 64 + lane] = acc[f * TILES + i][t];
+            for (int t = 0; t < RT; ++t)
+                if (task0 + f < p.tasks && rt0 + t < n_rt_total)
+                    part[(((size_t)blockIdx.y * p.tasks + task0 + f) * n_rt_total + rt0 + t) * 64 + lane] = acc[f][t];
         PN_TRACE(2, 63);
         return;
     }
     // ---- epilogues, one feature tile (pair) at a time
+    if constexpr (EPI != EPI_RAW)
 #pragma unroll
     for (int f = 0; f < FT; ++f) {
         const int task = task0 + f;
@@ -935,23 +935,40 @@ static int panel_feature_blocks(const GemmPlan &p, int pt) {
     const int per = pt / p.tiles_per_task;
     return ((p.tasks + per - 1) / per + 7) / 8 * 8;
 }
-// How a launch over `rows` rows is cut: row tiles and weight tiles per workgroup, K ranges.  The times are a model of
-// measured launches (7B shapes): a round of workgroups, one per compute unit, costs 5 us to start and end plus
-// 0.073 (RT + 3) us per k-step (0.88 at 9 row tiles, 0.51 at 4), three quarters of that with 8 weight tiles; a
-// split costs the finishing kernel, 5 us, and its partial sums once written and once read at 4 TB/s.
-// O and down of a 54-row step: 8 tiles per workgroup, 256 workgroups instead of 128: 17.7 -> 16.3 and 35.0 -> 28.0 us.
-// 189 prompt rows: splits of 2 .. 8, 2.01 -> 1.01 ms for four layers; from 1535 rows on nothing is split.
-struct PanelCut { int rt, pt; double us; };
+// the split-K form sums every weight tile for itself (gate and up tiles meet in the finishing kernel)
+static GemmPlan raw_plan(const GemmPlan &p) {
+    GemmPlan q = p;
+    q.tasks = p.tasks * p.tiles_per_task;
+    q.tiles_per_task = 1;
+    return q;
+}
+// How a launch over `rows` rows is cut: row tiles per workgroup, its waves and their weight tiles.  The times are a model of measured
+// launches (7B and 13B shapes): a round of workgroups, one per compute unit (the padding of
+// feature blocks counts: it keeps the work of a ragged group of 8 on some of the XCDs), costs 5 us to start and end, and a k-step what
+// its operands take to come in -- 44 KB/us per compute unit, weights and activations alike, whatever the shape -- or the
+// matrix cores under the card's power limit, 0.0056 us per pair of weight and row tile.  A split costs the finishing
+// kernel, 5 us, and its partial sums once written and once read at 4 TB/s.
+// So many workgroups as there are compute units is what counts: 12 weight tiles instead of 16 for gate/up of 7B (1376 tiles in two ranges)
+// 48.5 -> 43.8 us at 54 rows, 61.3 -> 57.6 at 144, for QKV (768 in four) 32.5 -> 30.3 and 41.8 -> 40.2; 10 for down of 13B (320 in eight)
+// 39.4 -> 34.2 at 54; 8 for O and down of 7B: 17.0 -> 15.9, 33.6 -> 27.4.  189 prompt rows: splits of 2 .. 8, 2.01 -> 0.98 ms for
+// four layers; from 1535 rows on nothing is split.
+struct PanelCut { int rt, nw, at; double us; };
 static PanelCut panel_cut(const GemmPlan &p, int rows, int ns) {
     const int row_tiles = (rows + 15) / 16, turns = (p.KSp + PANEL_TURN - 1) / PANEL_TURN;
-    PanelCut best{0, 0, 0.0};
-    for (int pt = 16; pt >= 8 * p.tiles_per_task; pt -= 8)
-        for (int rt = 4; rt <= PANEL_RT_MAX; ++rt) {
-            if (pt == 8 && rt > 5) break;
-            const long groups = (long)panel_feature_blocks(p, pt) * ((row_tiles + rt - 1) / rt) * ns;
-            const double us = (double)((groups + cu_count() - 1) / cu_count()) * (5.0 + (double)((turns + ns - 1) / ns) * PANEL_TURN * (pt == 16 ? 0.073 * (rt + 3) : 0.055 * (rt + 3)));
-            if (best.rt == 0 || us <= best.us) best = PanelCut{rt, pt, us};        // (ties: fewer, taller row blocks stream the weights less often)
+    const GemmPlan q = ns > 1 ? raw_plan(p) : p;
+    PanelCut best{0, 0, 0, 0.0};
+    auto consider = [&](int nw, int at) {
+        const int pt = nw * at;
+        for (int rt = 4; rt <= (at == 1 ? 5 : PANEL_RT_MAX); ++rt) {
+            const long groups = (long)panel_feature_blocks(q, pt) * ((row_tiles + rt - 1) / rt) * ns, rounds = (groups + cu_count() - 1) / cu_count();
+            const double in = (pt + 2 * rt) / 44.0, multiply = 0.0056 * pt * rt;
+            const double us = (double)rounds * (5.0 + (double)((turns + ns - 1) / ns) * PANEL_TURN * (in > multiply ? in : multiply));
+            if (best.rt == 0 || us <= best.us) best = PanelCut{rt, nw, at, us};        // (ties: fewer, taller row blocks stream the weights less often)
         }
+    };
+    consider(8, 2);
+    if (ns > 1) { consider(7, 2); consider(6, 2); consider(5, 2); }
+    if (q.tiles_per_task == 1) consider(8, 1);
     return best;
 }
 size_t panel_part_bytes(const GemmPlan &p, int rows, int ns) { return ns > 1 ? (size_t)ns * p.tasks * p.tiles_per_task * ((rows + 15) / 16) * 1024 : 0; }
@@ -960,45 +977,54 @@ int panel_prompt_split(const GemmPlan &p, int rows) {
     double best_us = 0.0;
     for (int ns = 1; ns <= 8 && ns <= (p.KSp + PANEL_TURN - 1) / PANEL_TURN; ++ns) {
         const double us = panel_cut(p, rows, ns).us + (ns > 1 ? 5.0 + 2e-6 * (double)panel_part_bytes(p, rows, ns) / 4.0 : 0.0);
-        if (best_us == 0.0 || us < best_us) { best = ns; best_us = us; }
+        if (best_us == 0.0 || us < 0.97 * best_us) { best = ns; best_us = us; }      // (a split has to promise 3 %: one more that promised 1 lost 6 in a prompt of 900 tokens at d 512)
     }
     return best;
 }
 
-template <int RT, int EPI, int PT>
+template <int RT, int EPI, int AT, int NW>
 static void launch_panel_cfg(const GemmArgs &a, hipStream_t st) {
-    const GemmPlan &p = a.plan;
     const size_t lds = (size_t)PANEL_STAGES * 2 * RT * PANEL_KC * 1024;
-    const int FB = panel_feature_blocks(p, PT);
     GemmArgs a2 = a;
+    if (EPI == EPI_RAW) a2.plan = raw_plan(a.plan);
+    else a2.rstd_out = nullptr;
+    const int FB = panel_feature_blocks(a2.plan, NW * AT);
     a2.panel_rb = (a.rows + 16 * RT - 1) / (16 * RT);
-    if (a.ksplit <= 1) a2.rstd_out = nullptr;
-    dim3 grid(FB * a2.panel_rb + (a2.rstd_out ? 1 : 0), a.ksplit > 1 ? a.ksplit : 1), block(512);
+    dim3 grid(FB * a2.panel_rb, a.ksplit > 1 ? a.ksplit : 1), block(NW * 64);
     static std::atomic<uint64_t> done{0};
-    allow_full_lds((const void *)gemm_panel_bf16<RT, EPI, PT>, done);
-    hipLaunchKernelGGL((gemm_panel_bf16<RT, EPI, PT>), grid, block, lds, st, a2);
+    allow_full_lds((const void *)gemm_panel_bf16<RT, EPI, AT, NW>, done);
+    hipLaunchKernelGGL((gemm_panel_bf16<RT, EPI, AT, NW>), grid, block, lds, st, a2);
 }
-
+template <int EPI, int AT, int NW>
+static void launch_panel_rt(int rt, const GemmArgs &a, hipStream_t st) {
+    switch (rt) {
+        case 4: launch_panel_cfg<4, EPI, AT, NW>(a, st); return;
+        case 5: launch_panel_cfg<5, EPI, AT, NW>(a, st); return;
+    }
+    if constexpr (AT > 1)
+        switch (rt) {
+            case 6: launch_panel_cfg<6, EPI, AT, NW>(a, st); return;
+            case 7: launch_panel_cfg<7, EPI, AT, NW>(a, st); return;
+            case 8: launch_panel_cfg<8, EPI, AT, NW>(a, st); return;
+            case 9: launch_panel_cfg<9, EPI, AT, NW>(a, st); return;
+            default: launch_panel_cfg<10, EPI, AT, NW>(a, st); return;
+        }
+}
 template <int EPI>
 static void launch_panel_epi(const GemmArgs &a, hipStream_t st) {
     const PanelCut cut = panel_cut(a.plan, a.rows, a.ksplit > 1 ? a.ksplit : 1);
-    if constexpr (EPI != EPI_SWIGLU) {
-        if (cut.pt == 8) {
-            if (cut.rt == 4) launch_panel_cfg<4, EPI, 8>(a, st);
-            else launch_panel_cfg<5, EPI, 8>(a, st);
-        }
+    if (a.ksplit > 1) {
+        if (cut.at == 1) launch_panel_rt<EPI_RAW, 1, 8>(cut.rt, a, st);
+        else if (cut.nw == 8) launch_panel_rt<EPI_RAW, 2, 8>(cut.rt, a, st);
+        else if (cut.nw == 7) launch_panel_rt<EPI_RAW, 2, 7>(cut.rt, a, st);
+        else if (cut.nw == 6) launch_panel_rt<EPI_RAW, 2, 6>(cut.rt, a, st);
+        else launch_panel_rt<EPI_RAW, 2, 5>(cut.rt, a, st);
+        launch_splitk_finish<EPI>(a, st);
+        return;
     }
-    if (cut.pt == 16)
-        switch (cut.rt) {
-            case 4: launch_panel_cfg<4, EPI, 16>(a, st); break;
-            case 5: launch_panel_cfg<5, EPI, 16>(a, st); break;
-            case 6: launch_panel_cfg<6, EPI, 16>(a, st); break;
-            case 7: launch_panel_cfg<7, EPI, 16>(a, st); break;
-            case 8: launch_panel_cfg<8, EPI, 16>(a, st); break;
-            case 9: launch_panel_cfg<9, EPI, 16>(a, st); break;
-            default: launch_panel_cfg<10, EPI, 16>(a, st); break;
-        }
-    if (a.ksplit > 1) launch_splitk_finish<EPI>(a, st);
+    if constexpr (EPI != EPI_SWIGLU)
+        if (cut.at == 1) { launch_panel_rt<EPI, 1, 8>(cut.rt, a, st); return; }
+    launch_panel_rt<EPI, 2, 8>(cut.rt, a, st);
 }
 void launch_gemm_panel_bf16(const GemmArgs &a, hipStream_t st) {
     switch (a.epi) {
