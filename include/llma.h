@@ -207,7 +207,8 @@ int llma_generate(llma_ctx *ctx, int32_t seq, const int32_t *prompt, int32_t pro
  * Needs n_seqs <= max_batch and prompt length + max_new + k <= max_seq for every sequence.
  * The tokens of a sequence are those the single-sequence call produces for it (bit for bit
  * while n_seqs * (k + 1) <= 48; larger steps run a different GEMM whose sums are taken in
- * another order, so a near-tie of two logits may then resolve differently).
+ * another order, so a near-tie of two logits may then resolve differently; bf16 prompts then
+ * share passes of up to 2048 rows, their sums as in llma_prefill).
  * Errors: INVAL, RANGE; on error before the first launch the context is unchanged. */
 int llma_generate_batch(llma_ctx *ctx, int32_t n_seqs, const int32_t *seqs,
                         const int32_t *prompts, const int32_t *prompt_offsets,

@@ -163,6 +163,24 @@ struct GemmArgs {          // bf16 path (fields marked f32 are used by the fp32 
     int H, dh, max_seq;
 };
 
+// one sequence's share of a prompt pass over several
+struct PromptSeg {
+    int row0, rows;        // its rows of the pass
+    int slot, tok0;        // cache slot; where in the prompt tokens the first of them stands
+    int blk0;              // its first row block in the attention's grid (blocks of PROMPT_BLOCK rows, sequence by sequence)
+};
+#define PROMPT_BLOCK 32
+// index of the last of n segments whose `first` field is at most v (segments in order, the first one's is 0); for a whole wave
+template <int PromptSeg::*first>
+__device__ __forceinline__ int segment_of(const PromptSeg *segs, int n, int v) {
+    int at = -1;
+    for (int i0 = 0; i0 < n; i0 += 64) {
+        const int i = i0 + (int)(threadIdx.x & 63);
+        at += __popcll(__ballot(i < n && segs[i < n ? i : 0].*first <= v));
+    }
+    return at;
+}
+
 struct AttnArgs {
     const void *Qhi, *Qlo;  // bf16: tiled planes over d_model; f32: Qhi = [R][d_model]
     const void *Khi, *Klo, *Vhi, *Vlo;   // this layer's cache (lo null without kv_split); f32: Khi, Vhi
@@ -176,6 +194,8 @@ struct AttnArgs {
     const int *rows_live;   // may be null: device int, rows 0 .. *rows_live of the (single) sequence carry tokens
     const int *lo_from;     // may be null: [max_batch] device ints, positions below lo_from[slot] have all-zero lo planes (imported bf16 caches)
     int n_rblocks;          // row blocks per sequence (set by the launcher)
+    const PromptSeg *segs;  // prompt pass over several sequences (else null): n_segs of them, n_chunks row blocks in all
+    int n_segs;
     float scale;
     bool quads;             // order of the pieces in Q and out tiles (xtile_piece): more than XTILE_ROWWISE rows in all
     float *po, *pm, *pl;    // partials

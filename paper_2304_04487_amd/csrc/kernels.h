@@ -54,13 +54,15 @@ void launch_take_step(const StepState &s, int n_seqs, int max_k, hipStream_t st)
 struct EmbedArgs {            // what the row set-up does with a row's token: h[r] = embed[token], and for bf16 models the first GEMM's input
     const void *embed; float *h; int d;
     const float *gain; void *nx_hi, *nx_lo; float *ssq_out; int KSp; bool quads;   // bf16 only (gain null: fp32): x = h * gain as tiled planes, sums of squares
+    const PromptSeg *segs; int n_segs;                                 // prompt pass over several sequences (else null)
 };
 // rows of a step: row (b, j) = pending[slot_b] (j = 0) or draft[b][j-1]; pos = T[slot_b] + j; embedded into e.h.
 // Generation steps (gen_dev set): the drafts are those of the best of part[b][0 .. spans), or with one span of the
 // reference's scan, which then runs here; keff / draft are filled
 void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, const float *cs, int half, const EmbedArgs &e,
                             const GenState *gen_dev, const unsigned long long *part, int spans, hipStream_t st);
-// rows of a prefill chunk for one slot: tokens prompt[T[slot] - *base_dev + j], pos = T[slot] + j
+// rows of a prefill chunk for one slot: tokens prompt[T[slot] - *base_dev + j], pos = T[slot] + j; with e.segs of several
+// sequences: each segment's tokens from prompt[tok0] on, at its own slot's T
 void launch_setup_prefill_rows(const StepState &s, const int *prompt_dev, const int *base_dev, int m, int slot,
                                const float *cs, int half, const EmbedArgs &e, hipStream_t st);
 void launch_advance_T(const StepState &s, int slot, int by, hipStream_t st);

@@ -1762,7 +1762,8 @@ __global__ void attn_combine_bf16_kernel(AttnArgs a, int rq) {
 // 32 w .. 32 w + 31 of every chunk and keeps its own running (max, sum, O) over them (online
 // softmax, no synchronisation inside the walk); at the end the four waves merge through LDS in wave order and the
 // normalised rows go straight to the hi/lo planes -- no partials, no combine kernel.  Row blocks
-// are numbered from the end of the prompt (longest walks start first).
+// are numbered from the end of the prompt (longest walks start first).  A pass over the prompts of several sequences
+// numbers their blocks one sequence after the other.
 // Bound by the wave's own chain of MFMAs and softmax arithmetic, so two waves per SIMD matter more than anything: the
 // query rows sit in LDS, and one set of K / V registers is refilled in place (K while the softmax runs, V while the
 // next scores are computed) where two sets took 474 registers and left one wave per SIMD.  A position's lo bytes are
@@ -1774,11 +1775,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr int KSTEPS = DH / 32, DT = DH / 16, NTQ = 2, RQ = NTQ * 16;
     __shared__ float sm[4][RQ], sl[4][RQ];
     __shared__ float so[4][RQ][DH + 4];
-    const int rb = gridDim.x - 1 - blockIdx.x, h = blockIdx.y;
+    static_assert(RQ == PROMPT_BLOCK, "the host counts the row blocks");
+    int rb = gridDim.x - 1 - blockIdx.x;
+    const int h = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, g = lane >> 4;
-    const int slot = a.slot_const;
-    const int m = a.m, j0 = rb * RQ;
+    int slot = a.slot_const, m = a.m, row0 = 0;         // the sequence, its rows, where they start in the pass
+    if (a.segs != nullptr) {
+        const PromptSeg seg = a.segs[__builtin_amdgcn_readfirstlane(segment_of<&PromptSeg::blk0>(a.segs, a.n_segs, rb))];
+        slot = seg.slot; m = seg.rows; row0 = seg.row0; rb -= seg.blk0;
+    }
+    const int j0 = rb * RQ;
     const int m_blk = (m - j0 < RQ) ? m - j0 : RQ;
     const int d_model = a.H * DH;
     const size_t head_base = ((size_t)slot * a.H + h) * (size_t)a.max_seq * DH;
@@ -1796,7 +1803,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int j = j0 + q * 16 + n;
         rpos[q] = j < m ? T + j : -1;
         for (int s = wave; s < KSTEPS; s += 4) {
-            const size_t off = xtile_off(j < m ? j : 0, h * DH + s * 32 + g * 8, d_model / 32, true);
+            const size_t off = xtile_off(row0 + (j < m ? j : 0), h * DH + s * 32 + g * 8, d_model / 32, true);
             qs[((q * 2 + 0) * KSTEPS + s) * 64 + lane] = *(const u32x4 *)((const bf16_t *)a.Qhi + off);
             qs[((q * 2 + 1) * KSTEPS + s) * 64 + lane] = *(const u32x4 *)((const bf16_t *)a.Qlo + off);
         }
@@ -1941,7 +1948,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         float v[4] = {acc[0] / L, acc[1] / L, acc[2] / L, acc[3] / L};
         u32x2 hi, lo;
         split4(v, hi, lo);
-        const size_t off = xtile_off(j0 + j, h * DH + d4 * 4, a.out_KSp, true);
+        const size_t off = xtile_off(row0 + j0 + j, h * DH + d4 * 4, a.out_KSp, true);
         *(u32x2 *)((bf16_t *)a.out_hi + off) = hi;
         *(u32x2 *)((bf16_t *)a.out_lo + off) = lo;
     }
@@ -1952,7 +1959,7 @@ static void launch_attn_dh(const AttnArgs &a0, hipStream_t st) {
     // up to 48 rows per workgroup; longer row lists (prompt processing) are cut into row blocks
     AttnArgs a = a0;
     if (a.n_seqs == 1 && a.m > 48 && a.slot_const >= 0) {           // prompt pass
-        hipLaunchKernelGGL((attn_prompt_bf16_kernel<DH, KVS>), dim3((a.m + 31) / 32, a.H), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((attn_prompt_bf16_kernel<DH, KVS>), dim3(a.segs ? a.n_chunks : (a.m + PROMPT_BLOCK - 1) / PROMPT_BLOCK, a.H), dim3(256), 0, st, a);
         return;
     }
     const int ntq = a.m > 32 ? 3 : (a.m + 15) / 16;

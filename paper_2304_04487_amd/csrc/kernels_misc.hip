@@ -377,8 +377,16 @@ void launch_setup_step_rows(const StepState &s, int n_seqs, int m, int max_k, co
 template <bool BF16>
 __global__ __launch_bounds__(256) void setup_prefill_rows_kernel(StepState s, const int *prompt, const int *base, int slot, const float *cs, int half, EmbedArgs e) {
     const int j = blockIdx.x;
-    const int pos = s.T[slot] + j;
-    const int tok = prompt[pos - *base];
+    int pos, tok;
+    if (e.segs != nullptr) {
+        const PromptSeg seg = e.segs[segment_of<&PromptSeg::row0>(e.segs, e.n_segs, j)];
+        slot = seg.slot;
+        pos = s.T[slot] + j - seg.row0;
+        tok = prompt[seg.tok0 + j - seg.row0];
+    } else {
+        pos = s.T[slot] + j;
+        tok = prompt[pos - *base];
+    }
     embed_row<BF16>(e, j, tok);
     if (threadIdx.x == 0) {
         s.row_tok[j] = tok;
