@@ -110,7 +110,7 @@ __host__ __device__ __forceinline__ size_t vcache_off(int pos, int c, int dh) {
 }
 
 // ---- launcher argument structs --------------------------------------------------------------
-enum { EPI_RAW = 0 /* panel GEMM, split-K form: partial sums, a second kernel runs the epilogue */, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_QKV = 4 };
+enum { EPI_RAW = 0 /* panel GEMM, split-K form: partial sums, a second kernel runs the epilogue */, EPI_SLICES = 5 /* the same over the tile-K kernel's K slices */, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_QKV = 4 };
 
 // how one weight matrix is cut into work: a function of its shape only (never of the row count)
 struct GemmPlan {

@@ -308,6 +308,8 @@ __device__ __forceinline__ void offset_rows(GemmArgs &a, const GemmPlan &p, int 
 // threads the kernel is built for, i.e. registers per wave: 128 at one row tile (16 waves, or two workgroups of 8, per
 // compute unit); 256 with more row tiles, and for three or four gate/up pairs (that matrix always has 8 K slices)
 constexpr int tilek_max_threads(int nt, int tiles_per_task, int ft) { return nt == 1 && (tiles_per_task == 1 || ft < 3) ? 1024 : 512; }
+constexpr int tilek_turn_group(int epi) { return epi == EPI_RESID || epi == EPI_SLICES ? 24 : 12; }
+__device__ __forceinline__ int tilek_turn(int group, int len) { return len > 1 ? (group * 5) % len : 0; }
 // SL, K slices per wave, is a constant of the kernel: as a runtime count it cost the matrices of one slice per wave
 // registers (O and down of 13B in launches of 17 rows, mostly one of them live: 123 registers and 28.5 us on average,
 // 94 and 21.2 as a constant)
@@ -345,10 +347,10 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
     // read the blocks of the same few k-steps of every tile -- addresses a fixed stride apart, which
     // fall on few memory channels.  So the walk over a slice starts `turn` k-steps in and wraps around
     // (QKV 18.9 -> 18.4 us, down 18.9 -> 17.9 us per launch at the 7B shapes).  The start is a
-    // function of the tile's group of 12 -- the same for 1, 2, 3 or 4 tiles per workgroup -- and of the
+    // function of the tile's group of 12 (O, down: 24, three workgroups of the form in slices) -- the same for 1, 2, 3 or 4 tiles per workgroup -- and of the
     // slice length, so a tile's sums are added in an order that no launch parameter changes.
-    const int turn_grp = task0 / 12;
-    auto k_turn = [&](int len) { return len > 1 ? (turn_grp * 5) % len : 0; };
+    const int turn_grp = task0 / tilek_turn_group(EPI);
+    auto k_turn = [&](int len) { return tilek_turn(turn_grp, len); };
     float *rstd_s = (float *)(red + (size_t)S * AT * NT * 64);
 
     // Every operand is fetched through a buffer descriptor of its own (one per weight tile, one per activation plane):
@@ -700,6 +702,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1, FT = AT / TILES;
     constexpr int KC = PANEL_KC;
     constexpr int CH = 2 * RT * KC * 64;           // 16-byte pieces per stage (both planes)
+    constexpr bool SLICED = EPI == EPI_SLICES, PARTIAL = SLICED || EPI == EPI_RAW;
     extern __shared__ u32x4 xs[];                  // [stages][2 planes][RT][KC][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const GemmPlan &p = a0.plan;
@@ -733,25 +736,35 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     const size_t x_start = (size_t)rt0 * KSp * 1024;
     const rsrc_t xh = buffer_of((const char *)a.Xhi + x_start, x_bytes), xl = buffer_of((const char *)a.Xlo + x_start, x_bytes);
 
+    // SLICED: the workgroup's range is one K slice of the tile-K kernel, walked from the same k-step on, so that the sums are
+    // the same; k-steps past its end read zeros
+    const int slice_lo = SLICED ? (int)((long)KSp * blockIdx.y / a0.ksplit) : 0, slice_len = SLICED ? (int)((long)KSp * (blockIdx.y + 1) / a0.ksplit) - slice_lo : 0;
+    const int slice_turn = SLICED ? tilek_turn(fb * (NW * AT) / tilek_turn_group(EPI), slice_len) : 0;
+    static_assert(!SLICED || tilek_turn_group(EPI) % (NW * AT) == 0, "one start for the workgroup's tiles");
+    auto slice_step = [&](int k) { const int t = k + slice_turn; return slice_lo + (k >= slice_len ? 0 : (t >= slice_len ? t - slice_len : t)); };
+
     // Operand fetches.  Every address below is a wave-uniform base (scalar registers, scalar
     // arithmetic) plus one per-lane byte offset that never changes (the lane's 16 bytes of a 1 KiB
     // block); every load is unconditional (indices are clamped instead): a load under a branch makes the
     // compiler's count of loads in flight inexact, and it then waits for all of them.
     // Activation chunk kc -> LDS stage: wave w fetches the 1 KiB blocks q = j NW + w, j < XB, of the chunk's
     // [2 planes][RT][KC] blocks (the last ones twice if they do not divide); row tiles past the end read the block's first.
-    const unsigned x_lane = (unsigned)xtile_piece(lane, true) * 16u;     // LDS holds the block in lane order
+    const unsigned x_lane = (unsigned)xtile_piece(lane, !SLICED || a0.rows > XTILE_ROWWISE) * 16u;     // LDS holds the block in lane order
     const unsigned w_lane = (unsigned)lane * 16u;
     auto fetch_x = [&](int kc, int stage, int j) {
         int q = j * NW + wave;
         q = q < 2 * RT * KC ? q : 2 * RT * KC - 1;
         const int pl = q / (RT * KC), t = (q % (RT * KC)) / KC, kk = q % KC;
         int k = kc * KC + kk;
-        k = k < KSp ? k : KSp - 1;
+        const unsigned nowhere = SLICED && k >= slice_len ? BUFFER_NOWHERE : 0u;
+        k = SLICED ? slice_step(k) : (k < KSp ? k : KSp - 1);
         const int tt = t < n_rt ? t : 0;
-        load_to_lds(pl ? xl : xh, x_lane, (unsigned)(tt * KSp + k) * 1024u, xs + stage * CH + q * 64);
+        load_to_lds(pl ? xl : xh, x_lane + nowhere, (unsigned)(tt * KSp + k) * 1024u, xs + stage * CH + q * 64);
     };
     // weights of tile i, k-step k0: a 1 KiB block; a k-step past the end of K lies outside the descriptor: zeros
-    auto fetch_w = [&](int k0, int i) -> u32x4 { return buffer_load16<false>(wb[i], (unsigned)k0 * 1024u + w_lane); };
+    auto fetch_w = [&](int k0, int i) -> u32x4 {
+        return buffer_load16<SLICED>(wb[i], (SLICED && k0 >= slice_len ? BUFFER_NOWHERE : (unsigned)(SLICED ? slice_step(k0) : k0) * 1024u) + w_lane);
+    };
 
     f32x4 acc[AT][RT];
 #pragma unroll
@@ -764,7 +777,8 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     // adds the ranges in order and runs the epilogue
     const int n_split = a0.ksplit > 1 ? a0.ksplit : 1;
     const int turns = (KSp + PANEL_TURN - 1) / PANEL_TURN;
-    const int kc_lo = (int)((long)turns * blockIdx.y / n_split) * (PANEL_TURN / KC), kc_hi = (int)((long)turns * (blockIdx.y + 1) / n_split) * (PANEL_TURN / KC);
+    const int kc_lo = SLICED ? 0 : (int)((long)turns * blockIdx.y / n_split) * (PANEL_TURN / KC);
+    const int kc_hi = SLICED ? (slice_len + PANEL_TURN - 1) / PANEL_TURN * (PANEL_TURN / KC) : (int)((long)turns * (blockIdx.y + 1) / n_split) * (PANEL_TURN / KC);
     u32x4 wreg[WD][AT];
     PN_TRACE(0, 63);
 #pragma unroll
@@ -855,7 +869,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing may still be on its way into LDS when the workgroup ends
 
-    if constexpr (EPI == EPI_RAW) {
+    if constexpr (PARTIAL) {
         // partial sums as register images: [range][tile (gate/up: gate tiles, then up tiles)][row tile][lane]
         f32x4 *part = (f32x4 *)a0.part;
 #pragma unroll
@@ -868,7 +882,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
         return;
     }
     // ---- epilogues, one feature tile (pair) at a time
-    if constexpr (EPI != EPI_RAW)
+    if constexpr (!PARTIAL)
 #pragma unroll
     for (int f = 0; f < FT; ++f) {
         const int task = task0 + f;
@@ -894,7 +908,7 @@ void launch_rstd_rows(const float *ssq, int ssq_tiles, float eps, float *rstd, i
 
 // second half of the split-K form: one wave per (feature tile (pair), row tile) adds the ranges'
 // partial sums in range order and runs the fused epilogue on the result
-template <int EPI>
+template <int EPI, bool QUADS>
 __global__ __launch_bounds__(256) void gemm_splitk_finish_bf16(GemmArgs a0) {
     constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1;
     __shared__ float rstd_sh[4][16];
@@ -922,12 +936,12 @@ __global__ __launch_bounds__(256) void gemm_splitk_finish_bf16(GemmArgs a0) {
             if (s < a0.ksplit) v[0] += v[s];
         sum[i][0] = v[0];
     }
-    gemm_epilogue<1, EPI, TILES, true>(a, p, task, lane, sum, rstd_sh[wave], in);
+    gemm_epilogue<1, EPI, TILES, QUADS>(a, p, task, lane, sum, rstd_sh[wave], in);
 }
-template <int EPI>
+template <int EPI, bool QUADS = true>
 static void launch_splitk_finish(const GemmArgs &a, hipStream_t st) {
     const int units = a.plan.tasks * ((a.rows + 15) / 16);
-    hipLaunchKernelGGL((gemm_splitk_finish_bf16<EPI>), dim3((units + 3) / 4), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((gemm_splitk_finish_bf16<EPI, QUADS>), dim3((units + 3) / 4), dim3(256), 0, st, a);
 }
 
 // feature blocks of PT weight tiles, padded to whole groups of 8 (see the kernel's workgroup order)
@@ -986,7 +1000,7 @@ template <int RT, int EPI, int AT, int NW>
 static void launch_panel_cfg(const GemmArgs &a, hipStream_t st) {
     const size_t lds = (size_t)PANEL_STAGES * 2 * RT * PANEL_KC * 1024;
     GemmArgs a2 = a;
-    if (EPI == EPI_RAW) a2.plan = raw_plan(a.plan);
+    if (EPI == EPI_RAW || EPI == EPI_SLICES) a2.plan = raw_plan(a.plan);
     else a2.rstd_out = nullptr;
     const int FB = panel_feature_blocks(a2.plan, NW * AT);
     a2.panel_rb = (a.rows + 16 * RT - 1) / (16 * RT);
@@ -1035,12 +1049,34 @@ void launch_gemm_panel_bf16(const GemmArgs &a, hipStream_t st) {
     }
 }
 
+// O and down projection of steps of 17 .. 48 rows, in slices: workgroups of 8 tiles take one of the tile-K kernel's K slices
+// each, their activations through LDS, and the finishing kernel adds the slices in the same order: the same sums, bit for bit.
+// The tile-K kernel has one or two tiles per workgroup there, and every workgroup reads all activations: what comes in
+// per compute unit -- 37 .. 59 KB/us, weights and activations alike -- is mostly activations (down of 7B at 33 rows: 372 MB beside
+// 90 of weights; in slices 45).  7B down 17 / 33 / 48 rows 25.9 / 35.2 / 40.8 -> 22.3 / 24.4 / 24.4 us, 13B 39.6 / 52.8 / 59.0 ->
+// 36.9 / 41.3 / 41.4.  It costs a second launch, 4 us: O of 7B 11.6 -> 13.7 at 17 rows, 14.7 -> 15.3 at 33, 16.6 -> 15.4 at 48, of 13B 22.3 ->
+// 23.3 at 33, down at d 512 (K 2048) 9.7 -> 9.1 at 48: from 700 KB of activations per workgroup on it pays.
+// Generation launches (rows_live) stay: mostly one of their rows is live, and then the launch counts.
+static void launch_gemm_slices(const GemmArgs &a, hipStream_t st) {
+    GemmArgs a2 = a;
+    a2.ksplit = a.plan.tk_waves;
+    a2.rstd_out = nullptr;
+    if (a.rows <= 32) launch_panel_cfg<2, EPI_SLICES, 1, 8>(a2, st);
+    else launch_panel_cfg<3, EPI_SLICES, 1, 8>(a2, st);
+    if (a.rows <= XTILE_ROWWISE) launch_splitk_finish<EPI_RESID, false>(a2, st);
+    else launch_splitk_finish<EPI_RESID, true>(a2, st);
+}
+static bool slices_pay(const GemmArgs &a) {
+    return a.epi == EPI_RESID && a.part != nullptr && a.rows_live == nullptr && a.split && a.plan.tk_waves == 8 && (long)a.rows * a.plan.K * 4 >= 700000;
+}
+
 // decoding-step GEMM: one launch for up to 48 rows (three row tiles).  More rows are refused (false,
 // nothing launched): every workgroup re-reads all rows' operands, so larger steps belong to the panel
 // kernel, and processing them here in blocks would stream the weights once per block.
 bool launch_gemm_bf16(const GemmArgs &a, hipStream_t st) {
     if (a.rows < 1 || a.rows > 48) return false;
     if (a.rows <= 16) launch_gemm_nt<1>(a, st);
+    else if (slices_pay(a)) launch_gemm_slices(a, st);
     else if (a.rows <= 32) launch_gemm_nt<2>(a, st);
     else launch_gemm_nt<3>(a, st);
     return true;

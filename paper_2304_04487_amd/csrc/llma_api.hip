@@ -281,6 +281,10 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
                     part = std::max(part, panel_part_bytes(*pl, (r + 15) / 16 * 16, panel_prompt_split(*pl, r)));
                 }
         }
+        // and O and down of steps and short passes of 17 .. 48 rows, in the decoding GEMM's K slices
+        const int few = std::min(48, std::max(step_rows, c->Pmax));
+        if (few > 16)
+            for (const GemmPlan *pl : {&c->plan_o, &c->plan_down}) part = std::max(part, panel_part_bytes(*pl, few, pl->tk_waves));
         if (part > 0) ALLOC(c, c->part, part);
         ALLOC(c, c->po, np * dh * 4);
         ALLOC(c, c->pm, np * 4);
@@ -581,6 +585,7 @@ static int forward_bf16(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_he
         panel_gemm(ga);
     };
     base.rstd_in = c->rstd;
+    base.part = c->part;
     base.ssq_tiles = d / 16; base.H = H; base.dh = dh; base.max_seq = c->seq_cap; base.nx_KSp = ksp_d;
     AttnArgs aa{};
     aa.Qhi = c->q; aa.Qlo = c->q_lo; aa.T = c->s.T; aa.batch_slots = c->s.batch_slots; aa.slot_const = n_seqs == 1 ? slot : -1; aa.n_seqs = n_seqs; aa.m = m; aa.H = H; aa.dh = dh;
@@ -1187,6 +1192,7 @@ extern "C" int llma_time_step_gemm(llma_ctx *c, int32_t which, int32_t rows, int
         HIP_TRY(c, hipEventRecord(e0, c->st));
         for (int r = 0; r < n; ++r) {
             GemmArgs ga = step_gemm_args(c, which, r % g.n_layers, rows);
+            ga.part = c->part;
             if (rows > 48) {                            // the step's own choice: panel kernel, split-K form
                 if (ga.plan.n_split > 1) { ga.ksplit = ga.plan.n_split; ga.part = c->part; if (ga.epi != EPI_RESID) ga.rstd_out = c->rstd; }
                 launch_gemm_panel_bf16(ga, c->st);
