@@ -124,6 +124,10 @@ struct GemmPlan {
     int n_split;     // panel kernel, batched steps: ranges the K axis is cut into (1 = no split)
 };
 
+// Groups of consecutive K slices that are summed before the groups are added (1: one slice after the other).  16 slices of equal,
+// even length: four groups, two for 1536 tiles or more; see launch_gemm_slices.
+__host__ __device__ __forceinline__ int tilek_groups(const GemmPlan &p) { return p.tk_waves == 16 && p.KSp % 32 == 0 ? (p.tasks < 1536 ? 4 : 2) : 1; }
+
 struct GemmArgs {          // bf16 path (fields marked f32 are used by the fp32 kernels only)
     const void *W;         // tiled bf16 weights, or row-major fp32 weights
     const void *Xhi;       // bf16: tiled activations, hi plane; f32: row-major [rows][K]

@@ -308,8 +308,8 @@ __device__ __forceinline__ void offset_rows(GemmArgs &a, const GemmPlan &p, int 
 // threads the kernel is built for, i.e. registers per wave: 128 at one row tile (16 waves, or two workgroups of 8, per
 // compute unit); 256 with more row tiles, and for three or four gate/up pairs (that matrix always has 8 K slices)
 constexpr int tilek_max_threads(int nt, int tiles_per_task, int ft) { return nt == 1 && (tiles_per_task == 1 || ft < 3) ? 1024 : 512; }
-constexpr int tilek_turn_group(int epi) { return epi == EPI_RESID || epi == EPI_SLICES ? 24 : 12; }
-__device__ __forceinline__ int tilek_turn(int group, int len) { return len > 1 ? (group * 5) % len : 0; }
+constexpr int tilek_turn_group(int epi) { return epi == EPI_RESID ? 24 : (epi == EPI_LMHEAD ? 48 : 12); }
+__device__ __forceinline__ int tilek_turn(int group, int len) { return len > 1 ? (group * 7) % len : 0; }
 // SL, K slices per wave, is a constant of the kernel: as a runtime count it cost the matrices of one slice per wave
 // registers (O and down of 13B in launches of 17 rows, mostly one of them live: 123 registers and 28.5 us on average,
 // 94 and 21.2 as a constant)
@@ -346,8 +346,9 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
     // If every workgroup walked its slices from their first k-step, the whole chip would at any moment
     // read the blocks of the same few k-steps of every tile -- addresses a fixed stride apart, which
     // fall on few memory channels.  So the walk over a slice starts `turn` k-steps in and wraps around
-    // (QKV 18.9 -> 18.4 us, down 18.9 -> 17.9 us per launch at the 7B shapes).  The start is a
-    // function of the tile's group of 12 (O, down: 24, three workgroups of the form in slices) -- the same for 1, 2, 3 or 4 tiles per workgroup -- and of the
+    // (QKV 18.9 -> 18.4 us, down 18.9 -> 17.9 us per launch at the 7B shapes), seven steps further from group to group (five: LM head
+    // of 7B 42.5 us at one row, seven or one: 39.8; QKV 18.85 and 18.4 at nine; three: 42.6 and 18.65).  The start is a
+    // function of the tile's group of 12 (24 for O and down, 48 for the LM head: whole workgroups of the form in slices) -- the same for 1, 2, 3 or 4 tiles per workgroup -- and of the
     // slice length, so a tile's sums are added in an order that no launch parameter changes.
     const int turn_grp = task0 / tilek_turn_group(EPI);
     auto k_turn = [&](int len) { return tilek_turn(turn_grp, len); };
@@ -515,8 +516,34 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
         f32x4 sum[TILES][1];
 #pragma unroll
         for (int i = 0; i < TILES; ++i) {
-            f32x4 v = red[((0 * AT + f * TILES + i) * NT + t) * 64 + lane];
-            for (int w = 1; w < S; ++w) v += red[((w * AT + f * TILES + i) * NT + t) * 64 + lane];
+            const f32x4 *const slices = red + ((f * TILES + i) * NT + t) * 64 + lane;
+            constexpr int STRIDE = AT * NT * 64;
+            f32x4 v = slices[0];
+            if ((EPI == EPI_QKV || EPI == EPI_LMHEAD) && S == 16) {
+                // in groups (tilek_groups): what one workgroup of the form in slices sums
+                f32x4 r[16];
+#pragma unroll
+                for (int w = 0; w < 16; ++w) r[w] = slices[w * STRIDE];
+                const int groups = tilek_groups(p);
+                if (groups == 4) {
+#pragma unroll
+                    for (int g = 0; g < 16; g += 4) r[g] = ((r[g] + r[g + 1]) + r[g + 2]) + r[g + 3];
+                    v = ((r[0] + r[4]) + r[8]) + r[12];
+                } else {
+#pragma unroll
+                    for (int w = 1; w < 8; ++w) r[0] += r[w];
+                    if (groups == 2) {
+#pragma unroll
+                        for (int w = 9; w < 16; ++w) r[8] += r[w];
+                        v = r[0] + r[8];
+                    } else {
+#pragma unroll
+                        for (int w = 8; w < 16; ++w) r[0] += r[w];
+                        v = r[0];
+                    }
+                }
+            } else
+                for (int w = 1; w < S; ++w) v += slices[w * STRIDE];
             sum[i][0] = v;
         }
         gemm_epilogue<1, EPI, TILES, QUADS>(at, p, task, lane, sum, rstd_s + 16 * t, in);
@@ -736,12 +763,29 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     const size_t x_start = (size_t)rt0 * KSp * 1024;
     const rsrc_t xh = buffer_of((const char *)a.Xhi + x_start, x_bytes), xl = buffer_of((const char *)a.Xlo + x_start, x_bytes);
 
-    // SLICED: the workgroup's range is one K slice of the tile-K kernel, walked from the same k-step on, so that the sums are
-    // the same; k-steps past its end read zeros
-    const int slice_lo = SLICED ? (int)((long)KSp * blockIdx.y / a0.ksplit) : 0, slice_len = SLICED ? (int)((long)KSp * (blockIdx.y + 1) / a0.ksplit) - slice_lo : 0;
-    const int slice_turn = SLICED ? tilek_turn(fb * (NW * AT) / tilek_turn_group(EPI), slice_len) : 0;
-    static_assert(!SLICED || tilek_turn_group(EPI) % (NW * AT) == 0, "one start for the workgroup's tiles");
-    auto slice_step = [&](int k) { const int t = k + slice_turn; return slice_lo + (k >= slice_len ? 0 : (t >= slice_len ? t - slice_len : t)); };
+    // SLICED: the workgroup's range is a group of a0.slices K slices of the tile-K kernel, each walked from the same k-step on and
+    // summed by itself, so that the sums are the same; k-steps past a range read zeros.  (Several slices: of equal, even length,
+    // so that a chunk lies in one of them.)
+    static_assert(!SLICED || KC == 2, "");
+    const int n_slices = SLICED ? p.tk_waves / (int)gridDim.y : 1, S = n_slices * (int)gridDim.y;
+    const int slice_lo = SLICED ? (int)((long)KSp * ((int)blockIdx.y * n_slices) / S) : 0;
+    const int slice_len = SLICED ? (int)((long)KSp * ((int)blockIdx.y * n_slices + 1) / S) - slice_lo : 0;
+    const int slice_turn = SLICED ? tilek_turn(fb * (NW * AT) / (AT == 1 ? tilek_turn_group(EPI_RESID) : (NW == 8 ? tilek_turn_group(EPI_LMHEAD) : tilek_turn_group(EPI_QKV))), slice_len) : 0;
+    // where a chunk lies: its slice's first k-step and its own place in the slice
+    struct Place { int lo, at; };
+    auto next_chunk = [&](Place &c) {
+        c.at += KC;
+        if (c.at >= slice_len && c.lo + slice_len < slice_lo + n_slices * slice_len) { c.at = 0; c.lo += slice_len; }
+    };
+    auto place_of = [&](int chunk) {
+        Place c = {slice_lo, 0};
+        for (int i = 0; i < chunk; ++i) next_chunk(c);
+        return c;
+    };
+    Place x_at = place_of(2), w_at = place_of((WD - KC) / KC);       // (the chunks requested while the first one is multiplied)
+    int in_slice = 0;                                               // k-steps of the present slice multiplied
+    auto slice_step = [&](const Place &c, int u) { const int t = c.at + u + slice_turn; return c.lo + (c.at + u >= slice_len ? 0 : (t >= slice_len ? t - slice_len : t)); };
+    auto past_slice = [&](const Place &c, int u) { return c.at + u >= slice_len; };
 
     // Operand fetches.  Every address below is a wave-uniform base (scalar registers, scalar
     // arithmetic) plus one per-lane byte offset that never changes (the lane's 16 bytes of a 1 KiB
@@ -751,19 +795,20 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     // [2 planes][RT][KC] blocks (the last ones twice if they do not divide); row tiles past the end read the block's first.
     const unsigned x_lane = (unsigned)xtile_piece(lane, !SLICED || a0.rows > XTILE_ROWWISE) * 16u;     // LDS holds the block in lane order
     const unsigned w_lane = (unsigned)lane * 16u;
-    auto fetch_x = [&](int kc, int stage, int j) {
+    auto fetch_x = [&](int kc, const Place &place, int stage, int j) {
         int q = j * NW + wave;
         q = q < 2 * RT * KC ? q : 2 * RT * KC - 1;
         const int pl = q / (RT * KC), t = (q % (RT * KC)) / KC, kk = q % KC;
         int k = kc * KC + kk;
-        const unsigned nowhere = SLICED && k >= slice_len ? BUFFER_NOWHERE : 0u;
-        k = SLICED ? slice_step(k) : (k < KSp ? k : KSp - 1);
+        const unsigned nowhere = SLICED && past_slice(place, kk) ? BUFFER_NOWHERE : 0u;
+        k = SLICED ? slice_step(place, kk) : (k < KSp ? k : KSp - 1);
         const int tt = t < n_rt ? t : 0;
         load_to_lds(pl ? xl : xh, x_lane + nowhere, (unsigned)(tt * KSp + k) * 1024u, xs + stage * CH + q * 64);
     };
-    // weights of tile i, k-step k0: a 1 KiB block; a k-step past the end of K lies outside the descriptor: zeros
-    auto fetch_w = [&](int k0, int i) -> u32x4 {
-        return buffer_load16<SLICED>(wb[i], (SLICED && k0 >= slice_len ? BUFFER_NOWHERE : (unsigned)(SLICED ? slice_step(k0) : k0) * 1024u) + w_lane);
+    // weights of tile i, k-step k0 (u-th of its chunk): a 1 KiB block; a k-step past the end of K lies outside the descriptor: zeros
+    auto fetch_w = [&](int k0, const Place &place, int u, int i) -> u32x4 {
+        const unsigned off = SLICED ? (past_slice(place, u) ? BUFFER_NOWHERE : (unsigned)slice_step(place, u) * 1024u) : (unsigned)k0 * 1024u;
+        return buffer_load16<SLICED>(wb[i], off + w_lane);
     };
 
     f32x4 acc[AT][RT];
@@ -771,6 +816,9 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     for (int i = 0; i < AT; ++i)
 #pragma unroll
         for (int t = 0; t < RT; ++t) acc[i][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    constexpr bool TOTAL = SLICED && AT > 1;            // several slices: their sums
+    f32x4 total[AT][RT];
+    bool first_slice = true;
 
     // split-K form (too few rows to fill the chip otherwise): blockIdx.y picks
     // one of a0.ksplit contiguous ranges of whole turns; the raw sums go to a0.part and a second kernel
@@ -778,18 +826,18 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     const int n_split = a0.ksplit > 1 ? a0.ksplit : 1;
     const int turns = (KSp + PANEL_TURN - 1) / PANEL_TURN;
     const int kc_lo = SLICED ? 0 : (int)((long)turns * blockIdx.y / n_split) * (PANEL_TURN / KC);
-    const int kc_hi = SLICED ? (slice_len + PANEL_TURN - 1) / PANEL_TURN * (PANEL_TURN / KC) : (int)((long)turns * (blockIdx.y + 1) / n_split) * (PANEL_TURN / KC);
+    const int kc_hi = SLICED ? (n_slices * slice_len + PANEL_TURN - 1) / PANEL_TURN * (PANEL_TURN / KC) : (int)((long)turns * (blockIdx.y + 1) / n_split) * (PANEL_TURN / KC);
     u32x4 wreg[WD][AT];
     PN_TRACE(0, 63);
 #pragma unroll
-    for (int l = 0; l < 2 * XB; ++l) fetch_x(kc_lo + l / XB, l / XB, l % XB);
+    for (int l = 0; l < 2 * XB; ++l) fetch_x(kc_lo + l / XB, place_of(l / XB), l / XB, l % XB);
     requests_stay_in_order();
 #pragma unroll
     for (int j = 0; j < WD - KC; ++j)
 #pragma unroll
-        for (int i = 0; i < AT; ++i) wreg[j][i] = fetch_w(kc_lo * KC + j, i);
+        for (int i = 0; i < AT; ++i) wreg[j][i] = fetch_w(kc_lo * KC + j, place_of(j / KC), j % KC, i);
     PN_TRACE(1, 63);
-    if (EPI == EPI_RAW && a0.rstd_out != nullptr) {
+    if (PARTIAL && a0.rstd_out != nullptr) {
         // the rows' sums of squares become rstd for the finishing kernel here, four rows per wave of as many workgroups as that
         // takes (one wave of each, as far as they go round), while the first operands are on their way
         const int blocks = (p.tasks + NW * FT - 1) / (NW * FT) * RB;
@@ -825,8 +873,8 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
         const int prev = stage == 0 ? PANEL_STAGES - 1 : stage - 1, next = stage == PANEL_STAGES - 1 ? 0 : stage + 1;
         auto request = [&](int l) {
             const int u = (l - XB) / AT, i = (l - XB) % AT;
-            if (l < XB) fetch_x(kc + 2, prev, l);
-            else wreg[(c * KC + u + WD - KC) % WD][i] = fetch_w(kc * KC + u + WD - KC, i);
+            if (l < XB) fetch_x(kc + 2, x_at, prev, l);
+            else wreg[(c * KC + u + WD - KC) % WD][i] = fetch_w(kc * KC + u + WD - KC, w_at, u, i);
         };
         PN_TRACE(0, kc - kc_lo);
         requests_stay_in_order();
@@ -858,6 +906,22 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
             __builtin_amdgcn_sched_barrier(0);
         }
         stage = next;
+        if constexpr (SLICED) {
+            next_chunk(x_at);
+            next_chunk(w_at);
+            in_slice += KC;
+            if (AT > 1 && in_slice == slice_len) {      // (uniform; one tile per wave: one slice per workgroup)
+                in_slice = 0;
+#pragma unroll
+                for (int i = 0; i < AT; ++i)
+#pragma unroll
+                    for (int t = 0; t < RT; ++t) {
+                        total[i][t] = first_slice ? acc[i][t] : total[i][t] + acc[i][t];
+                        acc[i][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                    }
+                first_slice = false;
+            }
+        }
     };
     // (no way out of a turn: an early exit made the compiler copy the ring's registers at the end of every turn, behind
     // a wait for all loads in flight)
@@ -877,7 +941,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
 #pragma unroll
             for (int t = 0; t < RT; ++t)
                 if (task0 + f < p.tasks && rt0 + t < n_rt_total)
-                    part[(((size_t)blockIdx.y * p.tasks + task0 + f) * n_rt_total + rt0 + t) * 64 + lane] = acc[f][t];
+                    part[(((size_t)blockIdx.y * p.tasks + task0 + f) * n_rt_total + rt0 + t) * 64 + lane] = TOTAL ? total[f][t] : acc[f][t];
         PN_TRACE(2, 63);
         return;
     }
@@ -1057,17 +1121,35 @@ void launch_gemm_panel_bf16(const GemmArgs &a, hipStream_t st) {
 // 36.9 / 41.3 / 41.4.  It costs a second launch, 4 us: O of 7B 11.6 -> 13.7 at 17 rows, 14.7 -> 15.3 at 33, 16.6 -> 15.4 at 48, of 13B 22.3 ->
 // 23.3 at 33, down at d 512 (K 2048) 9.7 -> 9.1 at 48: from 700 KB of activations per workgroup on it pays.
 // Generation launches (rows_live) stay: mostly one of their rows is live, and then the launch counts.
+//
+// QKV and the LM head have 16 slices: a workgroup takes a group of them (tilek_groups) and 12 or 16 tiles, two per wave.  They pay
+// where the tile-K kernel cannot take the matrix in one round of workgroups (more than four tiles each, or more partial sums
+// than LDS holds): LM head of 7B at 17 / 32 / 33 / 48 rows 55 / 61 / 85 / 97 -> 50 / 50 / 54 / 53 us, of 13B 59 / 69 / 105 / 117 -> 58 / 58 / 60 / 60;
+// QKV of 13B at 33 / 48 rows 53 / 59 -> 45; where one round does (QKV of 7B, three tiles) it is 29.7 against 28.4 at 33 rows.
+template <int EPI, int AT, int NW>
+static void launch_slices_rt(const GemmArgs &a, hipStream_t st) {
+    static_assert(tilek_turn_group(EPI) % (AT * NW) == 0, "one start of the walk for a workgroup's tiles");
+    if (a.rows <= 32) launch_panel_cfg<2, EPI_SLICES, AT, NW>(a, st);
+    else launch_panel_cfg<3, EPI_SLICES, AT, NW>(a, st);
+    if (a.rows <= XTILE_ROWWISE) launch_splitk_finish<EPI, false>(a, st);
+    else launch_splitk_finish<EPI, true>(a, st);
+}
 static void launch_gemm_slices(const GemmArgs &a, hipStream_t st) {
     GemmArgs a2 = a;
-    a2.ksplit = a.plan.tk_waves;
-    a2.rstd_out = nullptr;
-    if (a.rows <= 32) launch_panel_cfg<2, EPI_SLICES, 1, 8>(a2, st);
-    else launch_panel_cfg<3, EPI_SLICES, 1, 8>(a2, st);
-    if (a.rows <= XTILE_ROWWISE) launch_splitk_finish<EPI_RESID, false>(a2, st);
-    else launch_splitk_finish<EPI_RESID, true>(a2, st);
+    const bool grouped = a.epi != EPI_RESID;
+    a2.ksplit = grouped ? tilek_groups(a.plan) : a.plan.tk_waves;
+    if (!grouped) a2.rstd_out = nullptr;
+    if (a.epi == EPI_RESID) launch_slices_rt<EPI_RESID, 1, 8>(a2, st);
+    else if (a.epi == EPI_QKV) launch_slices_rt<EPI_QKV, 2, 6>(a2, st);
+    else launch_slices_rt<EPI_LMHEAD, 2, 8>(a2, st);
 }
 static bool slices_pay(const GemmArgs &a) {
-    return a.epi == EPI_RESID && a.part != nullptr && a.rows_live == nullptr && a.split && a.plan.tk_waves == 8 && (long)a.rows * a.plan.K * 4 >= 700000;
+    if (a.part == nullptr || a.rows_live != nullptr || !a.split) return false;
+    const GemmPlan &p = a.plan;
+    if (a.epi == EPI_RESID) return p.tk_waves == 8 && (long)a.rows * p.K * 4 >= 700000;
+    if (a.epi == EPI_SWIGLU || tilek_groups(p) == 1) return false;
+    const int one_round = (p.tasks + cu_count() - 1) / cu_count(), nt = (a.rows + 15) / 16;
+    return !tilek_ft_valid(p, nt, one_round);
 }
 
 // decoding-step GEMM: one launch for up to 48 rows (three row tiles).  More rows are refused (false,

@@ -283,8 +283,10 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
         }
         // and O and down of steps and short passes of 17 .. 48 rows, in the decoding GEMM's K slices
         const int few = std::min(48, std::max(step_rows, c->Pmax));
-        if (few > 16)
+        if (few > 16) {
             for (const GemmPlan *pl : {&c->plan_o, &c->plan_down}) part = std::max(part, panel_part_bytes(*pl, few, pl->tk_waves));
+            for (const GemmPlan *pl : {&c->plan_qkv, &c->plan_lm}) part = std::max(part, panel_part_bytes(*pl, few, tilek_groups(*pl)));
+        }
         if (part > 0) ALLOC(c, c->part, part);
         ALLOC(c, c->po, np * dh * 4);
         ALLOC(c, c->pm, np * 4);
@@ -599,8 +601,8 @@ static int forward_bf16(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_he
         ga.W = c->wqkv[l]; ga.plan = c->plan_qkv; ga.Xhi = c->xhi; ga.Xlo = c->xlo; ga.epi = EPI_QKV; ga.ssq_in = c->ssq;
         ga.row_pos = c->s.row_pos; ga.row_slot = c->s.row_slot; ga.row_cs = c->s.row_cs; ga.q_hi = c->q; ga.q_lo = c->q_lo;
         ga.k_hi = c->kc[l]; ga.k_lo = c->kc_lo[l]; ga.v_hi = c->vc[l]; ga.v_lo = c->vc_lo[l];
-        if (panel) panel_norm_gemm(ga);
-        else tilek_gemm(ga);
+        if (panel) { panel_norm_gemm(ga); }
+        else { ga.rstd_out = c->rstd; tilek_gemm(ga); }
         aa.Khi = c->kc[l]; aa.Klo = c->kc_lo[l]; aa.Vhi = c->vc[l]; aa.Vlo = c->vc_lo[l];
         launch_attn_bf16(aa, st);
         ga = base;
@@ -632,8 +634,8 @@ static int forward_bf16(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_he
         GemmArgs ga = base;
         ga.W = c->lm_head; ga.plan = c->plan_lm; ga.Xhi = c->xhi; ga.Xlo = c->xlo; ga.epi = EPI_LMHEAD; ga.ssq_in = c->ssq;
         ga.out = c->logits_dump; ga.pval = c->pval; ga.pidx = c->pidx; ga.n_part = c->n_part;
-        if (panel) panel_norm_gemm(ga);
-        else tilek_gemm(ga);
+        if (panel) { panel_norm_gemm(ga); }
+        else { ga.rstd_out = c->rstd; tilek_gemm(ga); }
     }
     if (refused) return fail(c, LLMA_E_INVAL, "forward: a step of %d rows reached the decoding-step GEMM (1..48 rows)", R);
     HIP_TRY(c, hipGetLastError());
@@ -1193,6 +1195,7 @@ extern "C" int llma_time_step_gemm(llma_ctx *c, int32_t which, int32_t rows, int
         for (int r = 0; r < n; ++r) {
             GemmArgs ga = step_gemm_args(c, which, r % g.n_layers, rows);
             ga.part = c->part;
+            if (rows <= 48 && ga.epi != EPI_RESID) ga.rstd_out = c->rstd;
             if (rows > 48) {                            // the step's own choice: panel kernel, split-K form
                 if (ga.plan.n_split > 1) { ga.ksplit = ga.plan.n_split; ga.part = c->part; if (ga.epi != EPI_RESID) ga.rstd_out = c->rstd; }
                 launch_gemm_panel_bf16(ga, c->st);

@@ -1,5 +1,5 @@
-"""Steps and short prompt passes of 17 .. 48 rows whose down projection (and, at the upper end, O projection) runs in K slices over
-several workgroups: the same bits as one-row steps give, for K slices of unequal length, ragged feature blocks, one to three row
+"""Steps and short prompt passes of 17 .. 48 rows whose down projection (and O projection, QKV, LM head) runs in K slices over
+several workgroups: the same bits as one-row steps give, for K slices of unequal length, groups of slices, ragged feature blocks, one to three row
 tiles and several sequences; and the oracle's logits (float64) within the bound of tests/test_gpu_row_counts.py."""
 import numpy as np
 import pytest
@@ -9,8 +9,11 @@ from oracle import OracleModel
 
 pytestmark = pytest.mark.gpu
 
-# k-steps: 325 (slices of 40 and 41) in the down projection, 36 (4 and 5) in O; 72 feature tiles.  `wide`: O takes slices from 38 rows on too
-CFGS = [synth.ModelCfg("deep-ffn", 1, 1152, 9, 128, 10400, 1040, "bf16"), synth.ModelCfg("wide", 1, 4672, 73, 64, 10304, 528, "bf16")]
+# k-steps: 325 (slices of 40 and 41) in the down projection, 36 (4 and 5) in O; 72 feature tiles.  `wide`: O takes slices from 38 rows on too.
+# LM head: 16 slices in two groups (1601 tiles, slices of two k-steps) and in four (1089 tiles, slices of four).  QKV: 960 tiles from 33 rows on
+CFGS = [synth.ModelCfg("deep-ffn", 1, 1152, 9, 128, 10400, 1040, "bf16"), synth.ModelCfg("wide", 1, 4672, 73, 64, 10304, 528, "bf16"),
+        synth.ModelCfg("head-2", 1, 1024, 8, 128, 512, 25616, "bf16"), synth.ModelCfg("head-4", 1, 2048, 16, 128, 512, 17424, "bf16"),
+        synth.ModelCfg("qkv", 1, 5120, 40, 128, 512, 528, "bf16")]
 ATOL = 1e-3
 
 
