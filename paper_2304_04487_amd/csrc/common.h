@@ -13,23 +13,24 @@ typedef uint16_t bf16_t;                       // raw bfloat16 bit pattern
 #define LLMA_NEG_INF (-__builtin_huge_valf())
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-// round-to-nearest-even; inputs are finite in this library
-__device__ __forceinline__ bf16_t f32_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (bf16_t)(u >> 16);
+// two floats as bf16, round-to-nearest-even, a in the lower half: one instruction on gfx950
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+    typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
 }
+__device__ __forceinline__ bf16_t f32_to_bf16(float f) { return (bf16_t)(bf16_pair(f, 0.f) & 0xffffu); }
 // x ~= hi + lo with hi = bf16(x), lo = bf16(x - hi): 16 significand bits kept
 __device__ __forceinline__ void split_bf16(float x, bf16_t &hi, bf16_t &lo) {
     hi = f32_to_bf16(x);
     lo = f32_to_bf16(x - bf16_to_f32(hi));
 }
 __device__ __forceinline__ void split4(const float v[4], u32x2 &hi, u32x2 &lo) {
-    bf16_t h[4], l[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) split_bf16(v[r], h[r], l[r]);
-    hi = (u32x2){(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-    lo = (u32x2){(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
+    for (int w = 0; w < 2; ++w) {
+        hi[w] = bf16_pair(v[2 * w], v[2 * w + 1]);
+        lo[w] = bf16_pair(v[2 * w] - __uint_as_float(hi[w] << 16), v[2 * w + 1] - __uint_as_float(hi[w] & 0xffff0000u));
+    }
 }
 // ---- the 8-bit lo plane of the K/V cache ----------------------------------------------------
 // A cached value x is kept as hi = bf16(x) plus lo = x - hi.  |lo| <= ulp(hi) / 2 = 2^-9 |x| at most, and four
@@ -44,16 +45,13 @@ __device__ __forceinline__ uint32_t lo8x2(float l0, float l1, uint32_t old, bool
 }
 __device__ __forceinline__ uint32_t lo8x4(const float l[4]) { return lo8x2(l[2], l[3], lo8x2(l[0], l[1], 0u, false), true); }
 __device__ __forceinline__ uint8_t lo8x1(float l) { return (uint8_t)(lo8x2(l, 0.f, 0u, false) & 0xffu); }
-// eight lo bytes (one lane's share of a block) -> the eight bf16 values the MFMA takes
+// eight lo bytes (one lane's share of a block) -> the eight bf16 values the MFMA takes (at most four significant bits: exact)
 __device__ __forceinline__ u32x4 lo8_operand(u32x2 p) {
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
     u32x4 r;
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
-        const f32x2_t a = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(p[w], 0.00390625f, false);
-        const f32x2_t b = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(p[w], 0.00390625f, true);
-        r[2 * w] = (__float_as_uint(a.x) >> 16) | (__float_as_uint(a.y) & 0xffff0000u);      // (at most four significant
-        r[2 * w + 1] = (__float_as_uint(b.x) >> 16) | (__float_as_uint(b.y) & 0xffff0000u);  //  bits: exact in bf16)
+        r[2 * w] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p[w], 0.00390625f, false));
+        r[2 * w + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(p[w], 0.00390625f, true));
     }
     return r;
 }
