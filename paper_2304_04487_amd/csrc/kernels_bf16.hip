@@ -690,6 +690,14 @@ __device__ __forceinline__ void rstd_of_row(const float *__restrict__ ssq, int s
     if (i == 0 && r < rows) rstd[r] = 1.0f / sqrtf(ss / (float)(ssq_tiles * 16) + eps);
 }
 
+// Split-K form of the panel GEMM: the rows whose rstd a wave computes are first .. first + 3 and every step-th group of four after
+// them.  A launch of few waves and many rows (a narrow matrix: one feature block) goes round several times.
+struct RstdShare { int first, step; };
+__host__ __device__ __forceinline__ RstdShare rstd_share(int tasks, int nw, int ft, int row_blocks, int fb, int rb, int range, int ranges, int wave) {
+    const int blocks = (tasks + nw * ft - 1) / (nw * ft) * row_blocks, workgroups = blocks * ranges;       // (those of padding feature blocks have left)
+    return RstdShare{4 * (range * blocks + fb * row_blocks + rb + workgroups * wave), 4 * workgroups * nw};
+}
+
 #define PANEL_KC 2          // k-steps per LDS chunk
 #define PANEL_TURN 8        // k-steps of weights in registers; the K axis is cut into ranges of whole turns of this ring
 #define PANEL_RT_MAX 10     // row tiles per workgroup: 4 .. 10
@@ -838,11 +846,10 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
         for (int i = 0; i < AT; ++i) wreg[j][i] = fetch_w(kc_lo * KC + j, place_of(j / KC), j % KC, i);
     PN_TRACE(1, 63);
     if (PARTIAL && a0.rstd_out != nullptr) {
-        // the rows' sums of squares become rstd for the finishing kernel here, four rows per wave of as many workgroups as that
-        // takes (one wave of each, as far as they go round), while the first operands are on their way
-        const int blocks = (p.tasks + NW * FT - 1) / (NW * FT) * RB;
-        const int id = ((int)blockIdx.y * blocks + fb * RB + rb) + blocks * (int)gridDim.y * wave;
-        if (id * 4 < a0.rows) rstd_of_row(a0.ssq_in, a0.ssq_tiles, a0.eps, a0.rstd_out, a0.rows, id * 4 + (lane >> 4), lane & 15);
+        // the rows' sums of squares become rstd for the finishing kernel here, four rows at a time by the launch's waves
+        // in turn, while the first operands are on their way
+        const RstdShare s = rstd_share(p.tasks, NW, FT, RB, fb, rb, blockIdx.y, gridDim.y, wave);
+        for (int r = s.first; r < a0.rows; r += s.step) rstd_of_row(a0.ssq_in, a0.ssq_tiles, a0.eps, a0.rstd_out, a0.rows, r + (lane >> 4), lane & 15);
     }
     // The MFMAs of a chunk run in groups of TB row tiles of one k-step; a group's operands come from LDS while the
     // group before it multiplies.

@@ -579,8 +579,8 @@ static int forward_bf16(llma_ctx *c, int n_seqs, int m, int n_chunks, bool lm_he
         if (split_of(ga) > 1) { ga.ksplit = split_of(ga); ga.part = c->part; }
         launch_gemm_panel_bf16(ga, st);
     };
-    // panel GEMM whose epilogue scales by the rows' rstd: the split-K form computes it in an extra
-    // workgroup of its first kernel (its finishing kernel is the reader), otherwise a launch of its own
+    // panel GEMM whose epilogue scales by the rows' rstd: in the split-K form the waves of its first kernel
+    // compute it (its finishing kernel is the reader), otherwise a launch of its own
     auto panel_norm_gemm = [&](GemmArgs &ga) {
         if (split_of(ga) > 1) ga.rstd_out = c->rstd;
         else launch_rstd_rows(c->ssq, d / 16, g.rms_eps, c->rstd, R, st);

@@ -1,0 +1,42 @@
+// The panel GEMM's host side on the CPU: kernels_bf16.hip compiled for the host alone, on a device whose number of
+// compute units the caller sets.
+#include <hip/hip_runtime.h>
+
+static int compute_units = 256;
+extern "C" void stub_compute_units(int n) { compute_units = n; }
+extern "C" hipError_t hipGetDevice(int *dev) { *dev = 0; return hipSuccess; }
+extern "C" hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) { p->multiProcessorCount = compute_units; return hipSuccess; }
+
+extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+extern "C" hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { return hipErrorNotSupported; }
+extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+extern "C" hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { return hipSuccess; }
+extern "C" void **__hipRegisterFatBinary(const void *) { return nullptr; }
+extern "C" void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
+extern "C" void __hipUnregisterFatBinary(void **) {}
+
+#include "kernels_bf16.hip"
+
+#include <vector>
+
+// rows whose rstd no wave computes when a pass (prompt) or step of `rows` rows runs the matrix in ranges of K; -1: it runs whole
+extern "C" int stub_rows_without_rstd(int N, int K, int tiles_per_task, int rows, int prompt) {
+    const GemmPlan p = make_gemm_plan(N, K, tiles_per_task);
+    const int ns = prompt ? panel_prompt_split(p, rows) : p.n_split;
+    if (ns <= 1) return -1;
+    const PanelCut cut = panel_cut(p, rows, ns);
+    const GemmPlan q = raw_plan(p);
+    const int per = cut.nw * cut.at, blocks = (q.tasks + per - 1) / per, row_blocks = (rows + 16 * cut.rt - 1) / (16 * cut.rt);
+    std::vector<char> done(rows, 0);
+    for (int fb = 0; fb < blocks; ++fb)
+        for (int rb = 0; rb < row_blocks; ++rb)
+            for (int range = 0; range < ns; ++range)
+                for (int wave = 0; wave < cut.nw; ++wave) {
+                    const RstdShare s = rstd_share(q.tasks, cut.nw, cut.at, row_blocks, fb, rb, range, ns, wave);
+                    for (int r = s.first; r < rows; r += s.step)
+                        for (int i = r; i < r + 4 && i < rows; ++i) done[i] = 1;
+                }
+    int missing = 0;
+    for (char d : done) missing += !d;
+    return missing;
+}

@@ -1,0 +1,50 @@
+"""How the panel GEMM cuts its launches, on the CPU: its host functions (tests/panel_stub.cpp) for devices of several sizes."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2304_04487_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def library(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("panel")
+    obj = str(tmp / "panel.o")
+
+    def run(cmd):
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        return r.stdout
+
+    run([build._hipcc(), "-std=c++17", "-O1", "-fPIC", "-x", "hip", "--offload-arch=gfx950", "--cuda-host-only", "-Wno-unused-result",
+         "-I", build.CSRC, "-c", os.path.join(HERE, "panel_stub.cpp"), "-o", obj])
+    no_code = [f"-Wl,--defsym={w}=0" for w in run(["nm", "-u", obj]).split() if w.startswith("__hip_fatbin")]
+
+    def open_for(units):                        # a library each: the number of units is asked for once
+        out = str(tmp / f"panel_{units}.so")
+        run(["g++", "-shared", "-Wl,-Bsymbolic", "-Wl,--no-undefined", *no_code, "-o", out, obj])
+        lib = ctypes.CDLL(out)
+        lib.stub_compute_units(units)
+        return lib
+    return open_for
+
+
+@pytest.mark.parametrize("units", [256, 128, 64, 32])
+def test_every_row_has_its_rstd(library, units):
+    """in the split-K form the waves of the first kernel share the rows' rstd: all rows, also of a narrow matrix (few waves)
+    with many of them"""
+    lib = library(units)
+    split = 0
+    for d in (512, 768, 1024, 2048, 4096):
+        for width in (16, 64, 128, 192, 224, 256, 512, 1040, 2848):
+            for rows in [*range(49, 2200, 41), 643, 648, 1152, 1281, 1287, 1664, 1801, 2047, 2048, 3000, 4224]:
+                # LM head of a step; gate/up of a step and of a prompt pass; QKV of a prompt pass
+                for shape in ((width, d, 1, rows, 0), (width, d, 2, rows, 0), (width, d, 2, min(rows, 2048), 1), (3 * d, d, 1, min(rows, 2048), 1)):
+                    missing = lib.stub_rows_without_rstd(*shape)
+                    split += missing >= 0
+                    assert missing <= 0, (units, shape, missing)
+    assert split > 1000
