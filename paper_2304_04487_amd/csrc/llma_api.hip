@@ -31,7 +31,8 @@ enum StepKind { STEP_PREFILL = 0, STEP_VERIFY = 1, STEP_GEN = 2, STEP_PROMPTS = 
 
 // what a captured step graph was recorded for: (kind, sequences, rows per sequence, attention chunks, slot, trigger spans)
 typedef std::array<int, 6> GraphKey;
-struct GraphSlot { int seen = 0; hipGraphExec_t exec = nullptr; };
+struct GraphSlot { int seen = 0; uint64_t used = 0; hipGraphExec_t exec = nullptr; };     // used: when last, in run_step calls
+#define GRAPH_SLOTS_MAX 256      // shapes remembered; beyond them the one not used for longest is forgotten
 
 struct llma_ctx {
     llma_model_cfg cfg;
@@ -39,6 +40,7 @@ struct llma_ctx {
     hipStream_t run_st = nullptr;      // where the launchers enqueue: st, or cap_st while capturing
     hipStream_t cap_st = nullptr;      // private stream used only to capture step graphs
     std::map<GraphKey, GraphSlot> graphs;
+    uint64_t graph_clock = 0;
     int *pin = nullptr;                // pinned host memory of steps: HostIo's arrays, then the decoding loop's output counts [2][max_batch]
     HostIo host{};                     // host addresses of the arrays (s.io: the device's)
     int *pin_counts = nullptr, *pin_counts_dev = nullptr;
@@ -684,6 +686,28 @@ static void drop_graphs(llma_ctx *c) {
     c->graphs.clear();
 }
 
+// The slot of a shape.  Prompt passes have a new shape nearly every time (several sequences' above all), so a full map gives up the
+// shape not used for longest: the decoding steps' stay.  (When a full map took no more and ended every replay, the steps of
+// a context that had seen 257 shapes ran eagerly from then on.)
+static GraphSlot &graph_slot(llma_ctx *c, const GraphKey &key) {
+    auto it = c->graphs.find(key);
+    if (it == c->graphs.end()) {
+        if (c->graphs.size() >= GRAPH_SLOTS_MAX) {
+            auto oldest = c->graphs.begin();
+            for (auto g = c->graphs.begin(); g != c->graphs.end(); ++g)
+                if (g->second.used < oldest->second.used) oldest = g;
+            if (oldest->second.exec) {
+                (void)hipStreamSynchronize(c->st);          // (its last launch may be on its way)
+                (void)hipGraphExecDestroy(oldest->second.exec);
+            }
+            c->graphs.erase(oldest);
+        }
+        it = c->graphs.emplace(key, GraphSlot{}).first;
+    }
+    it->second.used = ++c->graph_clock;
+    return it->second;
+}
+
 static int run_step(llma_ctx *c, int kind, int n_seqs, int m, int t_max, int slot) {
     // attention chunks launched: enough for the longest sequence.  A launched chunk streams its K/V
     // blocks before it knows whether it lies past the sequence's end, so the count is rounded up
@@ -695,9 +719,9 @@ static int run_step(llma_ctx *c, int kind, int n_seqs, int m, int t_max, int slo
     if (c->bf16 && n_chunks > c->nc_max) n_chunks = c->nc_max;
     if (kind == STEP_PROMPTS) n_chunks = t_max;                 // row blocks of the attention
     c->run_st = c->st;
-    if (!c->opt_graph || c->opt_timing || c->graphs.size() > 256) return step_body(c, kind, n_seqs, m, n_chunks, slot);
+    if (!c->opt_graph || c->opt_timing) return step_body(c, kind, n_seqs, m, n_chunks, slot);
     const GraphKey key = {kind, n_seqs, m, n_chunks, slot, kind == STEP_GEN ? c->gen_spans : 0};     // every field that shapes a launch or is baked into one
-    GraphSlot &gs = c->graphs[key];
+    GraphSlot &gs = graph_slot(c, key);
     if (gs.exec == nullptr) {
         if (gs.seen++ == 0) return step_body(c, kind, n_seqs, m, n_chunks, slot);   // first time eagerly
         hipGraph_t graph = nullptr;

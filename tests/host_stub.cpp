@@ -17,7 +17,16 @@ static long executed = 0, enqueued = 0;
 static int last_error_in = -1, event_record_in = -1;      // calls until the next injected failure (-1: none)
 static std::vector<int> prompt_T, gemm_rows, gemm_split;
 
-static void enqueue(std::function<void()> f) { queue.push_back(std::move(f)); ++enqueued; }
+struct graph { std::vector<std::function<void()>> work; };
+static graph *recording = nullptr;
+static bool can_capture = false;                          // off: every step runs eagerly
+static int graph_launches = 0, graphs_alive = 0;
+
+static void enqueue(std::function<void()> f) {
+    if (recording) { recording->work.push_back(std::move(f)); return; }
+    queue.push_back(std::move(f));
+    ++enqueued;
+}
 static void run_until(long n) {
     while (executed < n && !queue.empty()) { queue.front()(); queue.pop_front(); ++executed; }
 }
@@ -27,6 +36,9 @@ extern "C" {
 int stub_pending() { return (int)queue.size(); }
 void stub_fail_last_error(int calls) { last_error_in = calls; }
 void stub_fail_event_record(int calls) { event_record_in = calls; }
+void stub_capture(int on) { can_capture = on != 0; }
+int stub_graph_launches() { return graph_launches; }
+int stub_graphs_alive() { return graphs_alive; }                                    // instantiated, not destroyed
 static int take(std::vector<int> &v, int *out, int cap) {
     int n = 0;
     for (; n < (int)v.size() && n < cap; ++n) out[n] = v[n];
@@ -55,12 +67,33 @@ hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { enqueue([=] {
 hipError_t hipStreamSynchronize(hipStream_t) { run_until(enqueued); return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = nullptr; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; }     // every step runs eagerly
-hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *) { return hipErrorNotSupported; }
-hipError_t hipGraphInstantiate(hipGraphExec_t *, hipGraph_t, hipGraphNode_t *, char *, size_t) { return hipErrorNotSupported; }
-hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorNotSupported; }
-hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
-hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
+    if (!can_capture) return hipErrorNotSupported;
+    recording = new graph;
+    return hipSuccess;
+}
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) {
+    *g = (hipGraph_t)recording;
+    recording = nullptr;
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t g, hipGraphNode_t *, char *, size_t) {
+    *x = (hipGraphExec_t) new graph(*(graph *)g);
+    ++graphs_alive;
+    return hipSuccess;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t) {
+    ++graph_launches;
+    for (auto &f : ((graph *)x)->work) enqueue(f);
+    return hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t g) { delete (graph *)g; return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t x) {
+    if (!queue.empty()) abort();                                                    // (it may still be running)
+    delete (graph *)x;
+    --graphs_alive;
+    return hipSuccess;
+}
 hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t) new ev{0}; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { delete (ev *)e; return hipSuccess; }

@@ -74,6 +74,12 @@ class Ctx:
         return self.lib.llma_generate(self.h, 0, i32(*[1] * prompt), prompt, None, offs, 0, 1, k, max_new,
                                       self.out.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), ctypes.byref(n_out), None, None)
 
+    def generate_batch(self, lens, max_new, k):
+        n, total = len(lens), sum(lens)
+        out, n_out = (ctypes.c_int32 * (n * max_new))(), (ctypes.c_int32 * n)()
+        offs = i32(*[sum(lens[:b]) for b in range(n + 1)])
+        return self.lib.llma_generate_batch(self.h, n, i32(*range(n)), i32(*[1] * total), offs, None, None, None, 1, k, max_new, out, n_out, None, None)
+
     def state(self, seq=0):
         t, p = ctypes.c_int32(), ctypes.c_int32()
         assert self.lib.llma_get_state(self.h, seq, ctypes.byref(t), ctypes.byref(p)) == 0
@@ -167,3 +173,36 @@ def test_state_calls_reach_the_next_prompt(ctx):
     assert ctx.lib.llma_reset(ctx.h, 0) == 0
     ctx.prefill(4)
     assert ctx.notes()[0] == [0] and ctx.state() == (3, 1)
+
+
+@pytest.mark.parametrize("ctx", ["bf16"], indirect=True)
+def test_many_shapes_do_not_end_the_replay_of_steps(ctx, monkeypatch):
+    """prompts, shared prompt passes above all, have a shape of their own nearly every time: steps are replayed from their
+    graphs whatever has been seen in between, those captured before and new ones, and the graphs held stay bounded"""
+    lib = ctx.lib
+    wide = Ctx(lib, "bf16", max_batch=16, max_k=4)
+    lib.stub_capture(1)
+    try:
+        def replayed(k):
+            for _ in range(2):                      # seen, captured
+                assert wide.verify([2] * k) == 0
+                assert lib.llma_truncate(wide.h, 0, 19) == 0
+            before = lib.stub_graph_launches()
+            assert wide.verify([2] * k) == 0 and lib.llma_truncate(wide.h, 0, 19) == 0
+            return lib.stub_graph_launches() - before
+
+        wide.prefill(20)
+        assert replayed(2) == 1
+        rng = np.random.RandomState(4)
+        for i in range(400):
+            lens = rng.randint(2, 60, 10 + i % 7).tolist()
+            for _ in range(1 + (i % 3 == 0) * 2):   # (some often enough to be captured)
+                assert wide.generate_batch(lens, 2, 4) == 0
+        assert lib.llma_reset(wide.h, 0) == 0
+        wide.prefill(20)
+        assert replayed(2) == 1 and replayed(3) == 1
+        assert 0 < lib.stub_graphs_alive() <= 256
+    finally:
+        lib.stub_capture(0)
+        lib.llma_destroy(wide.h)
+    assert lib.stub_graphs_alive() == 0
