@@ -2,7 +2,9 @@
 #include <string.h>
 #include <unistd.h>
 
+#include <initializer_list>
 #include <string>
+#include <utility>
 
 #include "../../include/llma.h"
 #include "common.h"
@@ -14,7 +16,9 @@ void llma_set_error_text(const char *text);     // llma_api.hip: text for llma_l
 // memory for a copy of it and the spans' keys.  A call that allocated and freed, and copied with two
 // synchronous calls, spent 35 of its 41 us on that.  So every thread keeps its buffers from one call for the next, up to
 // TRIGGER_KEEP_WORDS of each, until it ends; no state, lock or stream is shared between threads, and nothing
-// of a call's inputs is kept.  Larger calls allocate and free.
+// of a call's inputs is kept.  Larger calls allocate device memory of their own and free it; their inputs pass through the
+// kept pinned buffer half a mebibyte at a time.  300 k / 1 M / 4 M / 20 M tokens 79 / 210 / 620 / 3150 us; with pinned memory of
+// the call's size, which takes longer to get than it saves, 175 / 365 / 750 / 31000, staged in pageable memory 150 / 340 / 1150 / 20000.
 #define TRIGGER_KEEP_WORDS (1 << 18)
 #define RESULT_WORDS 4                          // in front: matched, doc, pos (and the inputs stay 16-byte aligned)
 namespace {
@@ -52,6 +56,34 @@ struct Buffers {
     }
     ~Buffers() { release(); }
 };
+struct Words { const int32_t *at; size_t n; };
+// the lists back to back into device memory, through the two halves of the thread's pinned buffer behind the result: one is on
+// its way while the other is filled
+hipError_t copy_through(const Buffers &b, int *dev, std::initializer_list<Words> lists) {
+    const size_t half = (b.words - RESULT_WORDS) / 2;
+    int *piece = b.host + RESULT_WORDS, *other = piece + half;
+    size_t held = 0;
+    auto flush = [&]() {
+        hipError_t e = hipStreamSynchronize(nullptr);                       // (the other half has left)
+        if (e == hipSuccess) e = hipMemcpyAsync(dev, piece, held * 4, hipMemcpyHostToDevice, nullptr);
+        dev += held;
+        held = 0;
+        std::swap(piece, other);
+        return e;
+    };
+    for (Words w : lists)
+        while (w.n > 0) {
+            const size_t take = w.n < half - held ? w.n : half - held;
+            memcpy(piece + held, w.at, take * 4);
+            held += take;
+            w.at += take;
+            w.n -= take;
+            if (held < half) continue;
+            const hipError_t e = flush();
+            if (e != hipSuccess) return e;
+        }
+    return held > 0 ? flush() : hipSuccess;
+}
 }
 
 static int fail(int code, const std::string &text) {
@@ -75,22 +107,30 @@ extern "C" int llma_find_trigger(const int32_t *y, int32_t y_len, const int32_t 
 
     const size_t n_in = (size_t)y_len + (size_t)ref_len + (size_t)(n_docs + 1), in_words = (n_in + 3) / 4 * 4;
     const size_t need = RESULT_WORDS + in_words + 2 * (size_t)trigger_spans(ref_len);
-    static thread_local Buffers kept;
-    Buffers once;
-    Buffers &b = need <= TRIGGER_KEEP_WORDS ? kept : once;
-    hipError_t e = b.reserve(need);
+    static thread_local Buffers b;
+    const bool large = need > TRIGGER_KEEP_WORDS;
+    int *large_dev = nullptr;
+    hipError_t e = b.reserve(large ? TRIGGER_KEEP_WORDS : need);
+    if (e == hipSuccess && large) e = hipMalloc((void **)&large_dev, need * 4);
     if (e != hipSuccess) {
         (void)hipGetLastError();                // (reported here, not by a later call)
         return fail(LLMA_E_NOMEM, std::string("llma_find_trigger: allocation: ") + hipGetErrorString(e));
     }
-    int *in = b.host + RESULT_WORDS;
-    memcpy(in, y, (size_t)y_len * 4);
-    memcpy(in + y_len, ref, (size_t)ref_len * 4);
-    memcpy(in + y_len + ref_len, doc_offsets, (size_t)(n_docs + 1) * 4);
     b.host[0] = -1;
-    launch_trigger_host(b.host_dev + RESULT_WORDS, b.dev, (int)(in_words / 4), y_len, ref_len, n_docs, n, (unsigned long long *)(b.dev + in_words), b.host_dev, nullptr);
-    e = hipGetLastError();
+    if (!large) {
+        int *in = b.host + RESULT_WORDS;
+        memcpy(in, y, (size_t)y_len * 4);
+        memcpy(in + y_len, ref, (size_t)ref_len * 4);
+        memcpy(in + y_len + ref_len, doc_offsets, (size_t)(n_docs + 1) * 4);
+        launch_trigger_host(b.host_dev + RESULT_WORDS, b.dev, (int)(in_words / 4), y_len, ref_len, n_docs, n, (unsigned long long *)(b.dev + in_words), b.host_dev, nullptr);
+    } else {
+        e = copy_through(b, large_dev, {{y, (size_t)y_len}, {ref, (size_t)ref_len}, {doc_offsets, (size_t)(n_docs + 1)}});
+        if (e == hipSuccess)
+            launch_trigger_plain(large_dev, y_len, large_dev + y_len, large_dev + y_len + ref_len, ref_len, n_docs, n, (unsigned long long *)(large_dev + in_words), b.host_dev, false, nullptr);
+    }
+    if (e == hipSuccess) e = hipGetLastError();
     const hipError_t waited = hipStreamSynchronize(nullptr);        // (the kernels read and write the buffers: also after an error)
+    if (large) (void)hipFree(large_dev);
     if (e == hipSuccess) e = waited;
     if (e != hipSuccess) return fail(LLMA_E_HIP, std::string("llma_find_trigger: ") + hipGetErrorString(e));
     const int found = __atomic_load_n(&b.host[0], __ATOMIC_ACQUIRE);

@@ -6,6 +6,7 @@
 
 #include <deque>
 #include <functional>
+#include <map>
 #include <memory>
 #include <vector>
 
@@ -14,6 +15,12 @@
 
 static std::deque<std::function<void()>> queue;
 static long executed = 0, enqueued = 0;
+static long pinned = 0;
+static std::map<const char *, size_t> pinned_blocks;
+static bool is_pinned(const void *p) {
+    auto it = pinned_blocks.upper_bound((const char *)p);
+    return it != pinned_blocks.begin() && (const char *)p < (--it)->first + it->second;
+}
 static int last_error_in = -1, event_record_in = -1;      // calls until the next injected failure (-1: none)
 static std::vector<int> prompt_T, gemm_rows, gemm_split;
 
@@ -37,6 +44,7 @@ int stub_pending() { return (int)queue.size(); }
 void stub_fail_last_error(int calls) { last_error_in = calls; }
 void stub_fail_event_record(int calls) { event_record_in = calls; }
 void stub_capture(int on) { can_capture = on != 0; }
+long stub_pinned() { return pinned; }                                              // bytes of pinned memory asked for so far
 int stub_graph_launches() { return graph_launches; }
 int stub_graphs_alive() { return graphs_alive; }                                    // instantiated, not destroyed
 static int take(std::vector<int> &v, int *out, int cap) {
@@ -52,11 +60,16 @@ int stub_gemm_split(int *out, int cap) { return take(gemm_split, out, cap); }   
 struct ev { long at; };
 hipError_t hipMalloc(void **p, size_t n) { *p = calloc(n ? n : 1, 1); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void *p) { run_until(enqueued); free(p); return hipSuccess; }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
-hipError_t hipHostFree(void *p) { return hipFree(p); }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+    pinned += (long)n;
+    const hipError_t e = hipMalloc(p, n);
+    pinned_blocks[(const char *)*p] = n;
+    return e;
+}
+hipError_t hipHostFree(void *p) { pinned_blocks.erase((const char *)p); return hipFree(p); }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind kind, hipStream_t) {
-    if (kind == hipMemcpyHostToDevice) {                                            // pageable: staged before the call returns
+    if (kind == hipMemcpyHostToDevice && !is_pinned(s)) {                           // pageable: staged before the call returns
         auto copy = std::make_shared<std::vector<char>>((const char *)s, (const char *)s + n);
         enqueue([=] { memcpy(d, copy->data(), n); });
     } else enqueue([=] { memcpy(d, s, n); });
@@ -64,6 +77,7 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind kind, 
 }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { run_until(enqueued); memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) { enqueue([=] { memset(d, v, n); }); return hipSuccess; }
+hipError_t hipGetDevice(int *dev) { *dev = 0; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { run_until(enqueued); return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = nullptr; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
@@ -150,7 +164,24 @@ void launch_setup_prefill_rows(const StepState &s, const int *, const int *, int
 }
 void launch_advance_T(const StepState &s, int slot, int by, hipStream_t) { enqueue([=] { s.T[slot] += by; }); }
 void launch_trigger_scan(const GenState *, int, int, unsigned long long *, hipStream_t) {}
-void launch_trigger_plain(const int *, int, const int *, const int *, int, int, int, unsigned long long *, int *, bool, hipStream_t) {}
+// (the fake scan matches every reference, at the checksums of its inputs as they lie in device memory)
+static int checksum(const int *p, long n) {
+    unsigned h = 1;
+    for (long i = 0; i < n; ++i) h = h * 31u + (unsigned)p[i];
+    return (int)(h & 0x7fffffffu);
+}
+void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *doc_offsets, int ref_len, int n_docs, int, unsigned long long *part, int *result, bool, hipStream_t) {
+    enqueue([=] {
+        for (int i = 0; i < trigger_spans(ref_len); ++i) part[i] = 0;
+        result[0] = 1;
+        result[1] = checksum(ref, ref_len);
+        result[2] = checksum(y, y_len) ^ checksum(doc_offsets, n_docs + 1);
+    });
+}
+void launch_trigger_host(const int *in, int *dev, int pieces, int y_len, int ref_len, int n_docs, int n, unsigned long long *part, int *result, hipStream_t st) {
+    enqueue([=] { memcpy(dev, in, (size_t)pieces * 16); });
+    launch_trigger_plain(dev, y_len, dev + y_len, dev + y_len + ref_len, ref_len, n_docs, n, part, result, false, st);
+}
 void launch_argmax_accept(const float *, const int *, int, const StepState &s, int n_seqs, int, int max_k, int, const GenState *gen, hipStream_t) {
     enqueue([=] {
         for (int b = 0; b < n_seqs; ++b) {

@@ -1,4 +1,4 @@
-"""The library's host side on the CPU: llma_api.hip compiled for the host alone and linked against tests/host_stub.cpp,
+"""The library's host side on the CPU: llma_api.hip and llma_trigger.hip compiled for the host alone and linked against tests/host_stub.cpp,
 where a stream is a queue that runs when it is waited for and every launcher notes its arguments.  What a GPU cannot
 show reliably: what is still in flight when a call returns, and what the host had told the device by then."""
 import ctypes
@@ -23,7 +23,7 @@ def run(cmd):
 def lib(tmp_path_factory):
     tmp = tmp_path_factory.mktemp("host")
     objs = []
-    for src in (os.path.join(build.CSRC, "llma_api.hip"), os.path.join(HERE, "host_stub.cpp")):
+    for src in (os.path.join(build.CSRC, "llma_api.hip"), os.path.join(build.CSRC, "llma_trigger.hip"), os.path.join(HERE, "host_stub.cpp")):
         objs.append(str(tmp / (os.path.basename(src) + ".o")))
         run([build._hipcc(), "-std=c++17", "-O1", "-fPIC", "-x", "hip", "--offload-arch=gfx950", "--cuda-host-only", "-Wno-unused-result",
              "-I", build.CSRC, "-c", src, "-o", objs[-1]])
@@ -206,3 +206,30 @@ def test_many_shapes_do_not_end_the_replay_of_steps(ctx, monkeypatch):
         lib.stub_capture(0)
         lib.llma_destroy(wide.h)
     assert lib.stub_graphs_alive() == 0
+
+
+def checksum(a):
+    h = 1
+    for v in a.tolist():
+        h = (h * 31 + v) & 0xffffffff
+    return h & 0x7fffffff
+
+
+def find_trigger(lib, seed, y_len, ref_len):
+    rng = np.random.RandomState(seed)
+    y, ref = rng.randint(0, 32000, y_len).astype(np.int32), rng.randint(0, 32000, ref_len).astype(np.int32)
+    offs = np.array([0, ref_len // 3, ref_len], np.int32)
+    doc, pos = ctypes.c_int32(), ctypes.c_int32()
+    p = [a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)) for a in (y, ref, offs)]
+    assert lib.llma_find_trigger(p[0], y_len, p[1], p[2], 2, 1, ctypes.byref(doc), ctypes.byref(pos)) == 1, lib.llma_last_error(None)
+    assert lib.stub_pending() == 0
+    assert (doc.value, pos.value) == (checksum(ref), checksum(y) ^ checksum(offs)), (y_len, ref_len)
+
+
+def test_large_lookups_pin_no_more_than_a_thread_keeps(lib):
+    """a list longer than the kept buffers passes through them in pieces; pinned memory of its size costs more than it saves"""
+    lib.stub_pinned.restype = ctypes.c_long
+    find_trigger(lib, 1, 40, 1000)
+    for i, (y_len, ref_len) in enumerate([(3, 262100), (131069, 131070), (131070, 262140), (262144, 5), (1, 700001), (20, 500)]):
+        find_trigger(lib, 2 + i, y_len, ref_len)
+    assert lib.stub_pinned() <= 3 * (1 << 20)
