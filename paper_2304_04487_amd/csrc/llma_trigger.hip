@@ -22,34 +22,54 @@ void llma_set_error_text(const char *text);     // llma_api.hip: text for llma_l
 #define TRIGGER_KEEP_WORDS (1 << 18)
 #define RESULT_WORDS 4                          // in front: matched, doc, pos (and the inputs stay 16-byte aligned)
 namespace {
+// an allocation's number in this process (never given twice), 0 if p is not the start of one any more
+uint64_t allocation_of(const void *p) {
+    uint64_t id = 0;
+    if (p && hipPointerGetAttribute(&id, HIP_POINTER_ATTRIBUTE_BUFFER_ID, (hipDeviceptr_t)p) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return id;
+}
 struct Buffers {
     int *host = nullptr, *host_dev = nullptr, *dev = nullptr;
+    uint64_t host_id = 0, dev_id = 0;
     size_t words = 0;                           // of either
     int device = -1;
     pid_t owner = 0;
+    // hipDeviceReset frees what the device holds, and its addresses may belong to others by now (0.06 us to ask)
+    bool host_ours() const { return host_id != 0 && allocation_of(host) == host_id; }
+    bool dev_ours() const { return dev_id != 0 && allocation_of(dev) == dev_id; }
     void release() {
         if (!host && !dev) return;
         // (a forked child has no use of its parent's device)
         if (owner == getpid()) {
-            if (host) (void)hipHostFree(host);
-            if (dev) (void)hipFree(dev);
+            if (host_ours()) (void)hipHostFree(host);
+            if (dev_ours()) (void)hipFree(dev);
         }
         host = host_dev = dev = nullptr;
+        host_id = dev_id = 0;
         words = 0;
     }
     hipError_t reserve(size_t need) {
         int current = -1;
         hipError_t e = hipGetDevice(&current);
         if (e != hipSuccess) return e;
-        if (need <= words && current == device && owner == getpid()) return hipSuccess;
+        if (need <= words && current == device && owner == getpid() && host_ours() && dev_ours()) return hipSuccess;
         release();
         size_t n = 4096;
-        while (n < need && n < TRIGGER_KEEP_WORDS) n *= 2;
-        n = n < need ? need : n;
+        while (n < need) n *= 2;
         owner = getpid();
         device = current;
-        if ((e = hipMalloc((void **)&dev, n * 4)) == hipSuccess && (e = hipHostMalloc((void **)&host, n * 4, hipHostMallocMapped | hipHostMallocCoherent)) == hipSuccess)
-            e = hipHostGetDevicePointer((void **)&host_dev, host, 0);
+        if ((e = hipMalloc((void **)&dev, n * 4)) == hipSuccess && (dev_id = allocation_of(dev)) == 0) {
+            (void)hipFree(dev);
+            e = hipErrorNotSupported;
+        }
+        if (e == hipSuccess && (e = hipHostMalloc((void **)&host, n * 4, hipHostMallocMapped | hipHostMallocCoherent)) == hipSuccess && (host_id = allocation_of(host)) == 0) {
+            (void)hipHostFree(host);
+            e = hipErrorNotSupported;
+        }
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&host_dev, host, 0);
         if (e != hipSuccess) { release(); return e; }
         words = n;
         return hipSuccess;

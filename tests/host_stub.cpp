@@ -8,6 +8,7 @@
 #include <functional>
 #include <map>
 #include <memory>
+#include <set>
 #include <vector>
 
 #include "common.h"
@@ -15,6 +16,11 @@
 
 static std::deque<std::function<void()>> queue;
 static long executed = 0, enqueued = 0;
+static std::map<const void *, unsigned> allocations;       // and their numbers
+static unsigned allocations_made = 0;
+static std::set<const void *> lost;                       // to a reset
+static int stale_uses = 0;
+static bool not_ours(const void *p) { return lost.count(p) != 0; }
 static long pinned = 0;
 static std::map<const char *, size_t> pinned_blocks;
 static bool is_pinned(const void *p) {
@@ -58,8 +64,18 @@ int stub_gemm_rows(int *out, int cap) { return take(gemm_rows, out, cap); }     
 int stub_gemm_split(int *out, int cap) { return take(gemm_split, out, cap); }      // and whether it took the lo planes
 
 struct ev { long at; };
-hipError_t hipMalloc(void **p, size_t n) { *p = calloc(n ? n : 1, 1); return *p ? hipSuccess : hipErrorOutOfMemory; }
-hipError_t hipFree(void *p) { run_until(enqueued); free(p); return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) {
+    *p = calloc(n ? n : 1, 1);
+    if (!*p) return hipErrorOutOfMemory;
+    allocations[*p] = ++allocations_made;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+    run_until(enqueued);
+    stale_uses += p && not_ours(p);
+    if (p && !not_ours(p)) { allocations.erase(p); free(p); }
+    return hipSuccess;
+}
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
     pinned += (long)n;
     const hipError_t e = hipMalloc(p, n);
@@ -67,6 +83,20 @@ hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
     return e;
 }
 hipError_t hipHostFree(void *p) { pinned_blocks.erase((const char *)p); return hipFree(p); }
+hipError_t hipPointerGetAttribute(void *data, hipPointer_attribute what, hipDeviceptr_t p) {
+    if (what != HIP_POINTER_ATTRIBUTE_BUFFER_ID || !allocations.count(p)) return hipErrorInvalidValue;
+    *(unsigned *)data = allocations[p];
+    return hipSuccess;
+}
+// The device is reset: what was allocated is gone, or its address already belongs to somebody else (the memory itself is
+// left alone).  Uses and frees of such addresses are counted.
+void stub_device_reset(int reused) {
+    run_until(enqueued);
+    for (auto &a : allocations) lost.insert(a.first);
+    if (!reused) allocations.clear();
+    for (auto &a : allocations) a.second = ++allocations_made;
+}
+int stub_stale_uses() { return stale_uses; }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind kind, hipStream_t) {
     if (kind == hipMemcpyHostToDevice && !is_pinned(s)) {                           // pageable: staged before the call returns
@@ -179,6 +209,7 @@ void launch_trigger_plain(const int *y, int y_len, const int *ref, const int *do
     });
 }
 void launch_trigger_host(const int *in, int *dev, int pieces, int y_len, int ref_len, int n_docs, int n, unsigned long long *part, int *result, hipStream_t st) {
+    stale_uses += not_ours(result) + not_ours(dev);
     enqueue([=] { memcpy(dev, in, (size_t)pieces * 16); });
     launch_trigger_plain(dev, y_len, dev + y_len, dev + y_len + ref_len, ref_len, n_docs, n, part, result, false, st);
 }

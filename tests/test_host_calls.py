@@ -233,3 +233,13 @@ def test_large_lookups_pin_no_more_than_a_thread_keeps(lib):
     for i, (y_len, ref_len) in enumerate([(3, 262100), (131069, 131070), (131070, 262140), (262144, 5), (1, 700001), (20, 500)]):
         find_trigger(lib, 2 + i, y_len, ref_len)
     assert lib.stub_pinned() <= 3 * (1 << 20)
+
+
+@pytest.mark.parametrize("reused", [0, 1])
+def test_kept_buffers_do_not_outlive_a_device_reset(lib, reused):
+    """the caller may reset the device between two lookups: what the thread kept is gone, its addresses may be others'"""
+    find_trigger(lib, 11, 40, 1000)
+    lib.stub_device_reset(reused)
+    find_trigger(lib, 12, 40, 1000)
+    find_trigger(lib, 13, 40, 300000)
+    assert lib.stub_stale_uses() == 0
