@@ -174,12 +174,17 @@ static void timeline_panel(const Shape &sh, const Bufs &b, int rows, float *part
     CK(hipMemcpyFromSymbol(t.data(), HIP_SYMBOL(pn_trace), t.size() * 8));
     auto at = [&](int g, int w, int ch, int sl) { return t[(((size_t)g * 8 + w) * 64 + ch) * 4 + sl]; };
     unsigned long long t0 = ~0ull;
-    int G = 0;
-    for (int g = 0; g < PN_WG; ++g) if (at(g, 0, 63, 0)) { G = g + 1; t0 = std::min(t0, at(g, 0, 63, 0)); }
-    printf("%s, %d rows, %d K ranges: %d workgroups traced, event pair around panel + finishing kernel %.2f us\n", sh.name, rows, a.ksplit, G, ms * 1e3);
+    int G = 0, waves = 0;
+    for (int g = 0; g < PN_WG; ++g)
+        if (at(g, 0, 63, 0)) {
+            ++G;
+            for (int w = 0; w < 8; ++w) if (at(g, w, 63, 0)) { waves = std::max(waves, w + 1); t0 = std::min(t0, at(g, w, 63, 0)); }
+        }
+    printf("%s, %d rows, %d K ranges: %d workgroups of %d waves, event pair around panel + finishing kernel %.2f us\n", sh.name, rows, a.ksplit, G, waves, ms * 1e3);
     std::vector<double> entry, asked, done, mf, bar, nch;
-    for (int g = 0; g < G; ++g)
-        for (int w = 0; w < 8; ++w) {
+    for (int g = 0; g < PN_WG; ++g)
+        for (int w = 0; w < waves; ++w) {
+            if (!at(g, w, 63, 0)) continue;                 // (padding feature blocks leave before the first stamp)
             entry.push_back((at(g, w, 63, 0) - t0) * 0.01); asked.push_back((at(g, w, 63, 1) - at(g, w, 63, 0)) * 0.01);
             done.push_back((at(g, w, 63, 2) - t0) * 0.01);
             int n = 0;
