@@ -24,9 +24,9 @@ def setup():
 @pytest.mark.parametrize("lens,max_seq,k", [
     ((2, 1, 33, 34, 17, 3, 66), 200, 8),                   # one pass of 149 rows
     ((32, 33, 1, 65, 2), 120, 10),                         # blocks that end on a multiple of 32
-    ((100, 30, 72), 100 + 20, 16),                         # passes of 360 rows at most: one of 199
+    ((100, 30, 72), 100 + 20, 16),                         # passes of 480 rows at most: one of 199
     ((900, 41, 1100, 24, 16), 1200, 12),                   # 2048 rows and a remainder of 28 that two sequences share
-    ((700, 690, 680, 90), 760, 12),                        # a sequence of which 22 rows fall into the first pass
+    ((700, 690, 680, 90), 760, 12),                        # 2048 rows, of them 660 of the third sequence, and 108: its last 19 and the fourth's
 ], ids=str)
 def test_shared_prompt_passes(setup, lens, max_seq, k):
     llma, w, om = setup
