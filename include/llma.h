@@ -120,8 +120,12 @@ int llma_set_pending(llma_ctx *ctx, int32_t seq, int32_t token);
 int llma_kv_import(llma_ctx *ctx, int32_t seq, int32_t layer, const void *k, const void *v, int32_t len);
 
 /* --- the three calls of the method ---------------------------------------------------- */
-/* Trigger (paper: Method, the n-gram match step of Algorithm 1).  Stateless; all
- * pointers HOST; the scan itself runs on the current HIP device.
+/* Trigger (paper: Method, the n-gram match step of Algorithm 1).  No call depends on another; all
+ * pointers HOST; the scan itself runs on the current HIP device, on its default stream, which the call
+ * waits for.  The calling thread keeps buffers for its next call, up to 1 MiB of pinned host memory and 1 MiB
+ * of device memory on the device of its last call; they are freed when the thread ends (which waits for the
+ * device) or calls with another device current.  Larger lookups allocate device memory for the call.  The
+ * caller may reset the device between calls.
  *   y[0..y_len): output tokens generated so far.  ref: the documents' tokens, flat;
  *   doc_offsets int32[n_docs+1], non-decreasing, doc j = ref[doc_offsets[j] .. doc_offsets[j+1]).
  * A candidate is (doc, pos) with n <= pos < len(doc) and doc[pos-n..pos) == y[y_len-n..y_len):
@@ -207,8 +211,10 @@ int llma_generate(llma_ctx *ctx, int32_t seq, const int32_t *prompt, int32_t pro
  * Needs n_seqs <= max_batch and prompt length + max_new + k <= max_seq for every sequence.
  * The tokens of a sequence are those the single-sequence call produces for it (bit for bit
  * while n_seqs * (k + 1) <= 48; larger steps run a different GEMM whose sums are taken in
- * another order, so a near-tie of two logits may then resolve differently; bf16 prompts then
- * share passes of up to 2048 rows, their sums as in llma_prefill).
+ * another order, so a near-tie of two logits may then resolve differently.  With larger steps a
+ * bf16 context also feeds the prompts in shared passes of up to 2048 rows, which cut K by the rows
+ * of the pass: K and V of a sequence then depend, in their last bits, on the lengths of the
+ * other prompts of the call, and are not those of an llma_prefill of its own).
  * Errors: INVAL, RANGE; on error before the first launch the context is unchanged. */
 int llma_generate_batch(llma_ctx *ctx, int32_t n_seqs, const int32_t *seqs,
                         const int32_t *prompts, const int32_t *prompt_offsets,

@@ -13,9 +13,9 @@
 // shapes and by absolute key positions, never by the number of rows: row j of a k-row step is
 // bit-identical to the same token processed in a one-row step, in another step or in a short prompt
 // pass.  Steps of more rows share another order, fixed by the shape too (GemmPlan::n_split).  Prompt
-// passes of more than 48 rows cut the K axis by how many rows they have and how many compute units
-// there are (panel_prompt_split), so the K/V of a prefix differ at rounding level between passes of
-// different lengths (logits on top by 3e-5 where the oracle is 1.5e-4 away).
+// passes of more than 48 rows (one sequence's, or several sequences' together) cut the K axis by how many
+// rows they have and how many compute units there are (panel_prompt_split), so the K/V of a prefix differ
+// at rounding level between passes of different lengths (logits on top by 3e-5 where the oracle is 1.5e-4 away).
 #include <stdlib.h>
 
 #include <atomic>
@@ -291,7 +291,8 @@ __device__ __forceinline__ void offset_rows(GemmArgs &a, const GemmPlan &p, int 
 // the K axis; each wave streams its weight blocks from HBM with non-temporal 1 KiB loads, the
 // next batch in flight while the current one feeds the MFMAs; B operands come straight from the
 // tiled activation planes (1 KiB contiguous per k-step and plane, shared through L2 by all
-// workgroups); the waves' partial sums meet in LDS and are added in slice order; the waves share the
+// workgroups); the waves' partial sums meet in LDS and are added in slice order (the 16 slices of QKV and the LM head in
+// groups where tilek_groups says so: the order of launch_gemm_slices, whose sums have to be the same); the waves share the
 // (feature tile, row tile) pairs of the fused epilogue.  The number of K slices depends on the matrix shape only, so
 // the order of every sum is the same for any number of rows and any FT.  With 16 slices and more than one row tile a
 // wave takes two slices one after the other (half the waves, twice the registers).
@@ -499,7 +500,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
             compute(ks, avB, bvB);
             ks += UB;
         }
-        // ---- the slices' partial sums meet in LDS and are added in slice order
+        // ---- the slices' partial sums meet in LDS and are added below, in slice order or in groups of slices
 #pragma unroll
         for (int i = 0; i < AT; ++i)
 #pragma unroll
@@ -771,7 +772,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     const size_t x_start = (size_t)rt0 * KSp * 1024;
     const rsrc_t xh = buffer_of((const char *)a.Xhi + x_start, x_bytes), xl = buffer_of((const char *)a.Xlo + x_start, x_bytes);
 
-    // SLICED: the workgroup's range is a group of a0.slices K slices of the tile-K kernel, each walked from the same k-step on and
+    // SLICED: the workgroup's range is a group of n_slices K slices of the tile-K kernel, each walked from the same k-step on and
     // summed by itself, so that the sums are the same; k-steps past a range read zeros.  (Several slices: of equal, even length,
     // so that a chunk lies in one of them.)
     static_assert(!SLICED || KC == 2, "");

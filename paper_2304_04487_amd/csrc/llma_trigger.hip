@@ -13,10 +13,10 @@
 void llma_set_error_text(const char *text);     // llma_api.hip: text for llma_last_error(NULL)
 
 // What a call needs beside its arguments: pinned host memory that holds [result(4) | y | ref | doc_offsets], and device
-// memory for a copy of it and the spans' keys.  A call that allocated and freed, and copied with two
-// synchronous calls, spent 35 of its 41 us on that.  So every thread keeps its buffers from one call for the next, up to
-// TRIGGER_KEEP_WORDS of each, until it ends; no state, lock or stream is shared between threads, and nothing
-// of a call's inputs is kept.  Larger calls allocate device memory of their own and free it; their inputs pass through the
+// memory for a copy of it and the spans' keys.  A call that allocated and freed, and copied with two synchronous calls, took 41 us
+// where one with buffers of its own takes 18.  So every thread keeps its buffers from one call for the next, up to
+// TRIGGER_KEEP_WORDS of each, until it ends, and nothing of a call's inputs.  No buffer or lock is shared between threads; their
+// launches are, they go to the default stream.  Larger calls allocate device memory of their own and free it; their inputs pass through the
 // kept pinned buffer half a mebibyte at a time.  300 k / 1 M / 4 M / 20 M tokens 79 / 210 / 620 / 3150 us; with pinned memory of
 // the call's size, which takes longer to get than it saves, 175 / 365 / 750 / 31000, staged in pageable memory 150 / 340 / 1150 / 20000.
 #define TRIGGER_KEEP_WORDS (1 << 18)
