@@ -29,8 +29,9 @@ def check(args, n):
 # (output tokens, reference tokens, documents).  One span (4096 positions) or two; lists of 32768 words in one workgroup, and of 32769;
 # 2^18 words with result and keys, the most a thread keeps, and four more; beyond that in pieces of 131070 words: a list that ends with
 # a piece, one that ends a word later, one of many pieces.  Mostly no multiple of four words.
-SIZES = [(1, 1, 1), (3, 5, 2), (700, 4096, 3), (701, 4097, 3), (28600, 4090, 77), (28600, 4090, 78), (300, 20001, 9),
-         (254130, 8000, 5), (254131, 8000, 5), (131070, 131060, 9), (131070, 131061, 9), (262200, 100, 1), (40, 900001, 12), (5, 3, 1)]
+SIZES = [(1, 1, 1), (3, 5, 2), (700, 4096, 3), (701, 4097, 3), (28600, 4090, 77), (28600, 4090, 78), (28601, 4091, 80), (300, 20001, 9),
+         (250000, 12000, 5), (249980, 12100, 7), (254130, 8000, 5), (254131, 8000, 5), (131070, 131060, 9), (131070, 131061, 9),
+         (262200, 100, 1), (40, 900001, 12), (5, 3, 1)]
 
 
 @pytest.mark.parametrize("n", [1, 3])
