@@ -251,8 +251,9 @@ int llma_time_ffn_gemm(llma_ctx *ctx, int32_t rows, int32_t reps, double *mean_u
 /* The same measurement for any weight matrix of a layer and any step size the context admits:
  * which = 0 QKV, 1 attention output, 2 FFN gate/up, 3 FFN down, 4 LM head; rows = 1 ..
  * max_batch * (max_k + 1).  Launches what a step of that many rows launches for the matrix
- * (up to 48 rows the decoding GEMM, above that the panel GEMM in its split-K form together
- * with its finishing kernel).  which = 0 appends K / V rows to sequence slot 0 at position 0
+ * (up to 48 rows the decoding GEMM, or from 17 rows on its K slices over several workgroups and a
+ * finishing kernel; above that the panel GEMM in its split-K form together with its finishing
+ * kernel).  which = 0 appends K / V rows to sequence slot 0 at position 0
  * and every call overwrites the context's activation scratch: llma_reset the context before
  * decoding with it again.  Synchronises the stream. */
 int llma_time_step_gemm(llma_ctx *ctx, int32_t which, int32_t rows, int32_t reps, double *mean_us);
