@@ -250,8 +250,8 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
     // ---- scratch
     const int m_max = g.max_k + 1;
     c->Rmax = g.max_batch * m_max;
-    // (the prompts of a batch share passes: llma_generate_batch)
-    const long prompt_rows = (long)g.max_seq * g.max_batch;
+    // (the prompts of a batch share passes where its steps have more than 48 rows: llma_generate_batch)
+    const long prompt_rows = (long)g.max_seq * (c->Rmax > 48 ? g.max_batch : 1);
     c->Pmax = c->bf16 ? (prompt_rows < PREFILL_ROWS_MAX ? (int)prompt_rows : PREFILL_ROWS_MAX) : PREFILL_ROWS_F32;
     if (c->Rmax < c->Pmax) c->Rmax = c->Pmax;
     const size_t Rp = ((size_t)c->Rmax + 127) / 128 * 128 + 48;  // slack: the GEMMs read whole row tiles / row blocks

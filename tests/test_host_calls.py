@@ -99,6 +99,19 @@ def ctx(lib, request, monkeypatch):
 both_types = pytest.mark.parametrize("ctx", ["fp32", "bf16"], indirect=True)
 
 
+def test_only_contexts_whose_prompts_can_share_passes_hold_their_rows(lib, monkeypatch):
+    """prompts share passes where a step can have more than 48 rows; other contexts need scratch for one sequence's prompt"""
+    monkeypatch.setenv("LLMA_NO_AUTOTUNE", "1")
+    lib.llma_device_bytes.restype = ctypes.c_int64
+    held = []
+    for max_batch in (8, 9, 10):                # 40, 45 and 50 rows
+        c = Ctx(lib, "bf16", max_batch=max_batch, max_k=4)
+        held.append(lib.llma_device_bytes(c.h))
+        lib.llma_destroy(c.h)
+    slot = 3 * 2 * 128 * 128 * 3 + 2 * 48 * 66 * 4 + 1000       # a slot's cache, attention partials and words
+    assert held[1] - held[0] <= slot and held[2] - held[1] > slot
+
+
 @both_types
 def test_calls_run_on_the_stub(ctx):
     ctx.prefill(20)
