@@ -123,6 +123,15 @@ struct EpiIn {
     f32x4 cs01[NT], cs23[NT];  // QKV: (cos, sin) of the lane's four rotary pairs
 };
 
+// QKV: section (q, k, v), head and tile of the head; head_dim is 64 or 128.  (No division: one is a few hundred cycles between
+// the last sum and the kernel's end.)
+struct QkvPlace { int sec, head, j; };
+__device__ __forceinline__ QkvPlace qkv_place(const GemmArgs &a, int task) {
+    const int tps = a.H * a.dh / 16, sh = a.dh == 128 ? 3 : 2;
+    const int sec = (task >= tps) + (task >= 2 * tps), tin = task - sec * tps;
+    return QkvPlace{sec, tin >> sh, tin & ((1 << sh) - 1)};
+}
+
 template <int NT, int EPI>
 __device__ __forceinline__ void epi_prefetch(const GemmArgs &a, const GemmPlan &p, int task, int lane, EpiIn<NT> &in) {
     const int n = lane & 15, g4 = lane >> 4;
@@ -130,17 +139,14 @@ __device__ __forceinline__ void epi_prefetch(const GemmArgs &a, const GemmPlan &
     if (EPI == EPI_RESID) in.gv = *(const f32x4 *)(a.gain + f0);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const int row = t * 16 + n;
-        const bool live = row < a.rows;
+        const int row = t * 16 + n < a.rows ? t * 16 + n : 0;       // (unconditional loads: one under a branch waits for everything in flight)
         if (EPI == EPI_RESID) {
-            in.hv[t] = live ? *(const f32x4 *)(a.out + (size_t)row * p.N + f0) : (f32x4){0.f, 0.f, 0.f, 0.f};
+            in.hv[t] = *(const f32x4 *)(a.out + (size_t)row * p.N + f0);
         } else if (EPI == EPI_QKV) {
-            in.pos[t] = live ? a.row_pos[row] : 0;
-            in.slot[t] = live ? a.row_slot[row] : 0;
-            const int tps = a.H * a.dh / 16, tph = a.dh / 16, half = a.dh / 2;
-            const int j = (task % tps) % tph;
-            const int i0 = 8 * j + (g4 & 1) * 4;
-            const f32x4 *cp = (const f32x4 *)(a.row_cs + ((size_t)(live ? row : 0) * half + i0) * 2);
+            in.pos[t] = a.row_pos[row];
+            in.slot[t] = a.row_slot[row];
+            const int half = a.dh / 2, i0 = 8 * qkv_place(a, task).j + (g4 & 1) * 4;
+            const f32x4 *cp = (const f32x4 *)(a.row_cs + ((size_t)row * half + i0) * 2);
             in.cs01[t] = cp[0];
             in.cs23[t] = cp[1];
         }
@@ -210,9 +216,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
             }
         } else if (EPI == EPI_QKV) {
             // tile rows 0..7 = rotary first halves i, rows 8..15 = their partners i + dh/2
-            const int d = a.H * a.dh, tps = d / 16, tph = a.dh / 16;
-            const int sec = task / tps, tin = task % tps;
-            const int head = tin / tph, j = tin % tph;
+            const int d = a.H * a.dh;
+            const QkvPlace place = qkv_place(a, task);
+            const int sec = place.sec, head = place.head, j = place.j;
             const float rs = live ? rstd_s[row] : 0.f;
             float v[4], o4[4];
 #pragma unroll
@@ -262,6 +268,24 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
     }
 }
 
+// sum of sp[j0 .. j1), in order; j1 - j0 <= chunk, which is the same for all threads
+__device__ __forceinline__ float sum_of_tiles(const float *sp, int j0, int j1, int chunk) {
+    float ss = 0.f;
+    if (chunk <= 2) {                                   // (rows of up to 512 features)
+        if (j0 >= j1) return ss;
+        const float v0 = sp[j0], v1 = sp[j1 - 1];
+        return j1 - j0 == 2 ? v0 + v1 : v0;
+    }
+    for (int j = j0; j < j1; j += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = sp[j + u < j1 ? j + u : j1 - 1];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) ss += j + u < j1 ? v[u] : 0.f;
+    }
+    return ss;
+}
+
 // 16 bytes per lane through a buffer descriptor: base and size are wave-uniform, an offset past the size reads zeros
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 #define BUFFER_NOWHERE 0x40000000u     // past the end of every buffer it is used with (48 rows of at most 2^23 columns: below 1 GiB), also with an offset inside one added
@@ -300,6 +324,11 @@ __device__ __forceinline__ void offset_rows(GemmArgs &a, const GemmPlan &p, int 
 // tilek_ft_default.  Per layer of 7B, back to back: 75 us at one row (405 MB), 80 at 9 (84 before three gate/up pairs
 // shared a workgroup), 98 at 17 (108), 122 at 33 (147).  13B at 33 rows 229 -> 201 us: eight waves instead of four
 // for O and down (28 -> 23, 64 -> 53 us).
+// The chain from a launch's start to its first MFMA and from the last one to its end is what short launches consist of, and a
+// few percent of long ones: epilogue inputs and sums of squares by unconditional loads, the first operands before the live-row
+// count, no division, all slices' sums read from LDS at once.  Back to back at 9 rows: d 512 QKV / O / gate/up / down 4.76 / 3.65 / 4.29 /
+// 5.22 -> 3.83 / 3.30 / 3.72 / 4.87 us, 7B 18.6 / 9.4 / 30.1 / 20.1 -> 18.1 / 9.1 / 29.5 / 19.8 (an empty launch of a replayed graph: 1.6).
+// Stores past the L2 and arguments preloaded into registers changed nothing.
 // A ring of single k-steps with every load unconditional (zeros past the slice) was slower: the blocks of a
 // tile are best requested several in a row (O 10.4 us in ones, 9.1 in fours, 8.7 with the requests past the end left out).
 // ---------------------------------------------------------------------------------------------
@@ -310,7 +339,8 @@ __device__ __forceinline__ void offset_rows(GemmArgs &a, const GemmPlan &p, int 
 // compute unit); 256 with more row tiles, and for three or four gate/up pairs (that matrix always has 8 K slices)
 constexpr int tilek_max_threads(int nt, int tiles_per_task, int ft) { return nt == 1 && (tiles_per_task == 1 || ft < 3) ? 1024 : 512; }
 constexpr int tilek_turn_group(int epi) { return epi == EPI_RESID ? 24 : (epi == EPI_LMHEAD ? 48 : 12); }
-__device__ __forceinline__ int tilek_turn(int group, int len) { return len > 1 ? (group * 7) % len : 0; }
+// (a remainder by a power of two, 7B's slices of K = 4096 and d 512's, without the division: it stands before the kernel's first load)
+__device__ __forceinline__ int tilek_turn(int group, int len) { return len < 2 ? 0 : (len & (len - 1)) == 0 ? (group * 7) & (len - 1) : (group * 7) % len; }
 // SL, K slices per wave, is a constant of the kernel: as a runtime count it cost the matrices of one slice per wave
 // registers (O and down of 13B in launches of 17 rows, mostly one of them live: 123 registers and 28.5 us on average,
 // 94 and 21.2 as a constant)
@@ -379,8 +409,8 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
         if constexpr (W_BY_POINTER) return __builtin_nontemporal_load(wp[i] + (size_t)k * 64);
         else return buffer_load16<true>(wb[i], (unsigned)k * 1024u + w_lane);
     };
-    // One row tile (the usual decoding step): the wave's first weight blocks are requested before
-    // the live-row count is read, which is a round trip to memory of its own.
+    // One row tile (the usual decoding step): the wave's first operands are requested before the live-row count is
+    // known, which is a round trip to memory of its own (0.5 us at d 512).
     u32x4 avA[AT][UB];
     if (NT == 1) {
         const int k_lo = (KSp * wave * SL) >> s_sh, k_hi = (KSp * (wave * SL + 1)) >> s_sh;
@@ -393,15 +423,18 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
                 for (int i = 0; i < AT; ++i) avA[i][u] = load_w(i, k);
             }
         }
-        clamp_rows();
     }
     const unsigned x_bytes = (unsigned)(NT * KSp) * 1024u;
     const rsrc_t xh = buffer_of(a.Xhi, x_bytes), xl = buffer_of(a.Xlo, x_bytes);
-    const int nt_live = (a.rows + 15) >> 4;        // row tiles with at least one live row (uniform)
+    int nt_live = NT;                              // row tiles with at least one live row (uniform)
     unsigned x_lane[NT];
+    auto place_rows = [&]() {
+        nt_live = (a.rows + 15) >> 4;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-        x_lane[t] = t * 16 + (lane & 15) < a.rows ? (unsigned)(t * KSp) * 1024u + (unsigned)xtile_piece(lane, QUADS) * 16u : BUFFER_NOWHERE;
+        for (int t = 0; t < NT; ++t)
+            x_lane[t] = t * 16 + (lane & 15) < a.rows ? (unsigned)(t * KSp) * 1024u + (unsigned)xtile_piece(lane, QUADS) * 16u : BUFFER_NOWHERE;
+    };
+    place_rows();
 
     auto issue = [&](int ks, u32x4 (&av)[AT][UB], u32x4 (&bv)[PL][NT][UB], bool weights = true) {
 #pragma unroll
@@ -443,6 +476,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
     ks1 = (KSp * (slice + 1)) >> s_sh;
     ks0 = ks; turn = k_turn(ks1 - ks0);
     if (ks < ks1) issue(ks, avA, bvA, NT > 1);      // (one row tile: the weights are already on their way)
+    if (NT == 1) { clamp_rows(); place_rows(); }
     // epilogue inputs and rstd while the first batch is in flight
     // (after the sums, wave w finishes the (feature tile, row tile) pairs w, w + W, ...)
     constexpr int UNITS = FT * NT;
@@ -461,16 +495,7 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
             const int r = t * 16 + row;
             float ss = 0.f;
             if (r < a.rows) {
-                const float *sp = a.ssq_in + (size_t)r * a.ssq_tiles;
-                for (int j = j0; j < j1; j += 16) {
-                    float v[16];
-#pragma unroll
-                    for (int u = 0; u < 16; ++u)
-                        if (j + u < j1) v[u] = sp[j + u];
-#pragma unroll
-                    for (int u = 0; u < 16; ++u)
-                        if (j + u < j1) ss += v[u];
-                }
+                ss = sum_of_tiles(a.ssq_in + (size_t)r * a.ssq_tiles, j0, j1, chunk);
             }
 #pragma unroll
             for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
@@ -519,33 +544,36 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
         for (int i = 0; i < TILES; ++i) {
             const f32x4 *const slices = red + ((f * TILES + i) * NT + t) * 64 + lane;
             constexpr int STRIDE = AT * NT * 64;
-            f32x4 v = slices[0];
-            if ((EPI == EPI_QKV || EPI == EPI_LMHEAD) && S == 16) {
-                // in groups (tilek_groups): what one workgroup of the form in slices sums
-                f32x4 r[16];
+            // (8 or 16 slices, all requested before the first is added: in a loop that adds one after the other each waits for its own)
+            f32x4 r[16];
 #pragma unroll
-                for (int w = 0; w < 16; ++w) r[w] = slices[w * STRIDE];
-                const int groups = tilek_groups(p);
+            for (int w = 0; w < 8; ++w) r[w] = slices[w * STRIDE];
+            if (S == 16) {
+#pragma unroll
+                for (int w = 8; w < 16; ++w) r[w] = slices[w * STRIDE];
+                // in groups (tilek_groups): what one workgroup of the form in slices sums
+                const int groups = EPI == EPI_QKV || EPI == EPI_LMHEAD ? tilek_groups(p) : 1;
                 if (groups == 4) {
 #pragma unroll
                     for (int g = 0; g < 16; g += 4) r[g] = ((r[g] + r[g + 1]) + r[g + 2]) + r[g + 3];
-                    v = ((r[0] + r[4]) + r[8]) + r[12];
+                    r[0] = ((r[0] + r[4]) + r[8]) + r[12];
                 } else {
 #pragma unroll
                     for (int w = 1; w < 8; ++w) r[0] += r[w];
                     if (groups == 2) {
 #pragma unroll
                         for (int w = 9; w < 16; ++w) r[8] += r[w];
-                        v = r[0] + r[8];
+                        r[0] += r[8];
                     } else {
 #pragma unroll
                         for (int w = 8; w < 16; ++w) r[0] += r[w];
-                        v = r[0];
                     }
                 }
-            } else
-                for (int w = 1; w < S; ++w) v += slices[w * STRIDE];
-            sum[i][0] = v;
+            } else {
+#pragma unroll
+                for (int w = 1; w < 8; ++w) r[0] += r[w];
+            }
+            sum[i][0] = r[0];
         }
         gemm_epilogue<1, EPI, TILES, QUADS>(at, p, task, lane, sum, rstd_s + 16 * t, in);
     }
@@ -675,16 +703,7 @@ __device__ __forceinline__ void rstd_of_row(const float *__restrict__ ssq, int s
     const int j0 = i * chunk, j1 = (j0 + chunk < ssq_tiles) ? j0 + chunk : ssq_tiles;
     float ss = 0.f;
     if (r < rows) {
-        const float *sp = ssq + (size_t)r * ssq_tiles;
-        for (int j = j0; j < j1; j += 16) {
-            float v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (j + u < j1) v[u] = sp[j + u];
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (j + u < j1) ss += v[u];
-        }
+        ss = sum_of_tiles(ssq + (size_t)r * ssq_tiles, j0, j1, chunk);
     }
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
