@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
@@ -31,6 +33,35 @@ __device__ __forceinline__ void split4(const float v[4], u32x2 &hi, u32x2 &lo) {
         hi[w] = bf16_pair(v[2 * w], v[2 * w + 1]);
         lo[w] = bf16_pair(v[2 * w] - __uint_as_float(hi[w] << 16), v[2 * w + 1] - __uint_as_float(hi[w] & 0xffff0000u));
     }
+}
+// ---- the value of the lane whose number differs in bit OFF (1 .. 32); all 64 lanes of the wave take part.
+// Register moves within the vector unit: __shfl_xor goes through the LDS unit, a round trip of more than a hundred cycles, and reductions
+// are chains of up to six (QKV of d 512 at nine rows 3.83 -> 3.68 us a launch).
+template <int OFF>
+__device__ __forceinline__ uint32_t lane_xor_bits(uint32_t v) {
+    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8 || OFF == 16 || OFF == 32, "");
+    if constexpr (OFF == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);       // [0]: the lower half's values in both halves, [1]: the upper half's
+        return (threadIdx.x & 32) ? r[0] : r[1];
+    } else if constexpr (OFF == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);       // the same for the rows of 16 lanes of each half
+        return (threadIdx.x & 16) ? r[0] : r[1];
+    } else if constexpr (OFF == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false);   // rotate the row of 16 by 8
+    else if constexpr (OFF == 4) {
+        const int m = __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false);                                  // mirror groups of 8 (l ^ 7),
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1b, 0xf, 0xf, false);                                     // then groups of 4 (l ^ 3)
+    } else return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, OFF == 2 ? 0x4e : 0xb1, 0xf, 0xf, false);
+}
+template <int OFF> __device__ __forceinline__ float lane_xor(float v) { return __uint_as_float(lane_xor_bits<OFF>(__float_as_uint(v))); }
+template <int OFF> __device__ __forceinline__ int lane_xor(int v) { return (int)lane_xor_bits<OFF>((uint32_t)v); }
+template <int OFF> __device__ __forceinline__ unsigned long long lane_xor(unsigned long long v) {
+    return (unsigned long long)lane_xor_bits<OFF>((uint32_t)(v >> 32)) << 32 | lane_xor_bits<OFF>((uint32_t)v);
+}
+// f(lane_xor<OFF>) for OFF = FROM, FROM / 2, .., 1: the butterfly over FROM * 2 lanes, f(constant) per step
+template <int FROM, typename F>
+__device__ __forceinline__ void butterfly(F f) {
+    f(std::integral_constant<int, FROM>{});
+    if constexpr (FROM > 1) butterfly<FROM / 2>(f);
 }
 // ---- the 8-bit lo plane of the K/V cache ----------------------------------------------------
 // A cached value x is kept as hi = bf16(x) plus lo = x - hi.  |lo| <= ulp(hi) / 2 = 2^-9 |x| at most, and four

@@ -177,8 +177,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
                 *(u32x2 *)((bf16_t *)a.nx_hi + o) = hi;
                 *(u32x2 *)((bf16_t *)a.nx_lo + o) = lo;
             }
-            ss += __shfl_xor(ss, 16);
-            ss += __shfl_xor(ss, 32);
+            ss += lane_xor<16>(ss);
+            ss += lane_xor<32>(ss);
             if (live && g4 == 0) a.ssq_out[(size_t)row * (p.N / 16) + task] = ss;
         } else if (EPI == EPI_SWIGLU) {
             if (live) {
@@ -204,12 +204,11 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
 #pragma unroll
             for (int r = 1; r < 4; ++r)
                 if (lg[r] > bv) { bv = lg[r]; bi = f0 + r; }
-#pragma unroll
-            for (int sh = 16; sh <= 32; sh <<= 1) {
-                const float ov = __shfl_xor(bv, sh);
-                const int oi = __shfl_xor(bi, sh);
+            auto better = [&](float ov, int oi) {
                 if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-            }
+            };
+            better(lane_xor<16>(bv), lane_xor<16>(bi));
+            better(lane_xor<32>(bv), lane_xor<32>(bi));
             if (g4 == 0 && live) {
                 a.pval[(size_t)row * a.n_part + task] = bv;
                 a.pidx[(size_t)row * a.n_part + task] = bi;
@@ -232,7 +231,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
                                      in.cs23[t][0], in.cs23[t][1], in.cs23[t][2], in.cs23[t][3]};
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float pr = __shfl_xor(v[r], 32);
+                    const float pr = lane_xor<32>(v[r]);
                     o4[r] = (g4 < 2) ? (v[r] * cs[2 * r] - pr * cs[2 * r + 1]) : (v[r] * cs[2 * r] + pr * cs[2 * r + 1]);
                 }
                 const int c0 = (g4 < 2) ? i0 : half + i0;
@@ -497,8 +496,10 @@ __global__ __launch_bounds__((tilek_max_threads(NT, EPI == EPI_SWIGLU ? 2 : 1, F
             if (r < a.rows) {
                 ss = sum_of_tiles(a.ssq_in + (size_t)r * a.ssq_tiles, j0, j1, chunk);
             }
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
+            ss += lane_xor<1>(ss);
+            ss += lane_xor<2>(ss);
+            ss += lane_xor<4>(ss);
+            ss += lane_xor<8>(ss);
             if (i == 0) rstd_s[r] = 1.0f / sqrtf(ss / (float)(a.ssq_tiles * 16) + a.eps);
         }
     }
@@ -705,8 +706,10 @@ __device__ __forceinline__ void rstd_of_row(const float *__restrict__ ssq, int s
     if (r < rows) {
         ss = sum_of_tiles(ssq + (size_t)r * ssq_tiles, j0, j1, chunk);
     }
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
+    ss += lane_xor<1>(ss);
+    ss += lane_xor<2>(ss);
+    ss += lane_xor<4>(ss);
+    ss += lane_xor<8>(ss);
     if (i == 0 && r < rows) rstd[r] = 1.0f / sqrtf(ss / (float)(ssq_tiles * 16) + eps);
 }
 
@@ -1316,8 +1319,8 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
     // every wave publishes (max, sum, O) of a row tile for the merge below
     auto publish = [&](int q, const f32x4 (&oq)[DT]) {
         float l = lrow[q];
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        l += lane_xor<16>(l);
+        l += lane_xor<32>(l);
         if (g == 0) { sm[wave][q * 16 + n] = mrow[q]; sl[wave][q * 16 + n] = l; }
         if (!COMPACT || q * 16 + n < ATTN_COMPACT_ROWS)
 #pragma unroll
@@ -1368,8 +1371,8 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
                     mx = fmaxf(mx, v);
                 }
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = fmaxf(mx, lane_xor<16>(mx));
+            mx = fmaxf(mx, lane_xor<32>(mx));
             float psum = 0.f;
             float p[8];
 #pragma unroll
@@ -1558,8 +1561,8 @@ __global__ __launch_bounds__(256, 2) void attn_walk_bf16_kernel(AttnArgs a) {
                         mx = fmaxf(mx, v);
                     }
                 }
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                mx = fmaxf(mx, lane_xor<16>(mx));
+                mx = fmaxf(mx, lane_xor<32>(mx));
                 float p[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
@@ -1580,8 +1583,8 @@ __global__ __launch_bounds__(256, 2) void attn_walk_bf16_kernel(AttnArgs a) {
                 }
             }
             // publish this wave's (max, sum, O) of the row tile
-            lsum += __shfl_xor(lsum, 16);
-            lsum += __shfl_xor(lsum, 32);
+            lsum += lane_xor<16>(lsum);
+            lsum += lane_xor<32>(lsum);
             if (g == 0) { sm[wave][q * 16 + n] = mrow; sl[wave][q * 16 + n] = lsum; }
             if (q * 16 + n < RS)
 #pragma unroll
@@ -1763,8 +1766,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     mx = fmaxf(mx, v);
                 }
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = fmaxf(mx, lane_xor<16>(mx));
+            mx = fmaxf(mx, lane_xor<32>(mx));
             const float Mn = fmaxf(Mw[q], mx);
             const float s_old = (Mw[q] == LLMA_NEG_INF) ? 0.f : __expf(Mw[q] - Mn);     // (Mn = -inf only if both are)
             float p[8], lsum = 0.f;
@@ -1799,8 +1802,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int q = 0; q < NTQ; ++q) {
         float lsum = Lw[q];
-        lsum += __shfl_xor(lsum, 16);
-        lsum += __shfl_xor(lsum, 32);
+        lsum += lane_xor<16>(lsum);
+        lsum += lane_xor<32>(lsum);
         if (g == 0) { sm[wave][q * 16 + n] = Mw[q]; sl[wave][q * 16 + n] = lsum; }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) *(f32x4 *)&so[wave][q * 16 + n][dt * 16 + 4 * g] = o[q][dt];
@@ -2041,8 +2044,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 sv[q][i] = v;
                 mx = fmaxf(mx, v);
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = fmaxf(mx, lane_xor<16>(mx));
+            mx = fmaxf(mx, lane_xor<32>(mx));
             const float m_new = fmaxf(mrow[q], mx);
             alpha[q] = (mrow[q] == LLMA_NEG_INF) ? 0.f : __expf(mrow[q] - m_new);   // m_new finite then
             float psum = 0.f;
@@ -2080,8 +2083,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int q = 0; q < NTQ; ++q) {
         float l = lrow[q];
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        l += lane_xor<16>(l);
+        l += lane_xor<32>(l);
         if (g == 0) { sm[wave][q * 16 + n] = mrow[q]; sl[wave][q * 16 + n] = l; }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) *(f32x4 *)&so[wave][q * 16 + n][dt * 16 + 4 * g] = o[q][dt];

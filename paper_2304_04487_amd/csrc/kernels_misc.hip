@@ -35,11 +35,10 @@ __device__ __forceinline__ int doc_of(const int *doc_offsets, int n_docs, int p)
 }
 
 __device__ __forceinline__ unsigned long long block_max(unsigned long long best) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        unsigned long long o = __shfl_xor(best, off);
+    butterfly<32>([&](auto off) {
+        const unsigned long long o = lane_xor<off.value>(best);
         best = o > best ? o : best;
-    }
+    });
     __shared__ unsigned long long wbest[4];                     // (256 threads)
     if ((threadIdx.x & 63) == 0) wbest[threadIdx.x >> 6] = best;
     __syncthreads();
@@ -59,20 +58,23 @@ __device__ __forceinline__ unsigned long long scan_span(const int *y, int i, con
     constexpr int U = TRIGGER_SPAN / 256, PROBE = 8, STRIDE = 16;
     __shared__ unsigned short hits_of[4][TRIGGER_SPAN / 4];     // each wave's survivors of the one-token test: p - p_lo, ascending
     unsigned long long best = 0ull;
+    int prev[U];
+    if (p_lo < p_hi) {                                          // (uniform; y's length may still be on its way from memory)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = p_lo + u * 256 + (int)threadIdx.x;
+            prev[u] = ref[p < 1 ? 0 : (p < p_hi ? p - 1 : p_hi - 1)];
+        }
+    }
     if (i >= n && p_lo < p_hi) {                                // uniform
         const int lane = threadIdx.x & 63;
         const auto token_before = [&](int q, int t) { return ref[q - 1 - t > 0 ? q - 1 - t : 0]; };    // (compared only where it exists)
         const auto tail = [&](int t) { return y[i - 1 - t > 0 ? i - 1 - t : 0]; };
         unsigned short *const hit = hits_of[threadIdx.x >> 6];
         int total = 0;
-        int prev[U], want[PROBE];
+        int want[PROBE];
 #pragma unroll
         for (int t = 0; t < PROBE; ++t) want[t] = tail(t);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int p = p_lo + u * 256 + (int)threadIdx.x;
-            prev[u] = ref[p < 1 ? 0 : (p < p_hi ? p - 1 : p_hi - 1)];
-        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int p = p_lo + u * 256 + (int)threadIdx.x;
@@ -107,12 +109,11 @@ __device__ __forceinline__ unsigned long long scan_span(const int *y, int i, con
                 const unsigned long long bound = more ? trigger_key(limit, q) : 0ull;
                 unsigned long long lead = bound;
                 if ((left & (left - 1ull)) != 0ull) {           // (one alone is simply followed)
-#pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) {
-                        const unsigned long long a = __shfl_xor(top, off), b = __shfl_xor(lead, off);
+                    butterfly<32>([&](auto off) {
+                        const unsigned long long a = lane_xor<off.value>(top), b = lane_xor<off.value>(lead);
                         top = a > top ? a : top;
                         lead = b > lead ? b : lead;
-                    }
+                    });
                     if (lead <= top) break;
                     left = __ballot(bound == lead);
                 }
@@ -326,6 +327,8 @@ __global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m
     const int slot = s.batch_slots[b];
     const int T = s.T[slot];
     int keff, tok = s.pending[slot];
+    // (the row's rotary pairs, at most 128 words, are requested with the first loads and stored with the last)
+    const float cs_word = cs[(size_t)(T + j) * 2 * half + ((int)threadIdx.x < 2 * half ? threadIdx.x : 0)];
     if (gp == nullptr) {
         keff = s.keff[b];
         if (j > 0) tok = s.draft[b * max_k + j - 1];
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m
         const int n_out = *G.n_out;
         unsigned long long best = 0ull;
         if (spans == 1) {
-            best = scan_span(G.y, n_out, G.ref, G.doc_offsets, G.n_docs, 0, G.k > 0 && n_out < G.max_new ? G.ref_len : 0, G.n);
+            best = scan_span(G.y, n_out < G.max_new ? n_out : -1, G.ref, G.doc_offsets, G.n_docs, 0, G.k > 0 ? G.ref_len : 0, G.n);   // (n >= 1)
         } else {
             for (int t = threadIdx.x; t < spans; t += 256) {
                 const unsigned long long o = part[(size_t)b * spans + t];
@@ -361,7 +364,7 @@ __global__ __launch_bounds__(256) void setup_step_rows_kernel(StepState s, int m
     tok = j <= keff ? tok : 0;                                    // rows past keff are padding
     const int pos = T + j;
     embed_row<BF16>(e, idx, tok);
-    for (int i = threadIdx.x; i < 2 * half; i += 256) s.row_cs[(size_t)idx * 2 * half + i] = cs[(size_t)pos * 2 * half + i];
+    if ((int)threadIdx.x < 2 * half) s.row_cs[(size_t)idx * 2 * half + threadIdx.x] = cs_word;
     if (threadIdx.x == 0) {
         s.row_tok[idx] = tok;
         s.row_pos[idx] = pos;
@@ -414,56 +417,76 @@ void launch_advance_T(const StepState &s, int slot, int by, hipStream_t st) {
 // o_i == draft_i; the step emits o_0..o_a, the cache keeps the rows of the pending token and
 // of the a accepted drafts (T += a + 1; rows beyond are overwritten by the next step), and
 // o_a becomes the pending token.
-// Bound by latency: a row is 2000 partials (16 KB) at vocabulary 32000, and the decision is a chain of small reads.
-// Sixteen waves take a row each (33 rows: three rounds), 16 partials per lane in flight, requested before the draft
-// count is known; the drafts are compared by 33 lanes at once instead of one thread walking them (that walk was a
-// read per draft, one after the other).  17 rows 23.5 -> 8.3 us, 33 rows 40.8 -> 11.9 us, one row 5.6 -> 4.6 us.
+// Bound by latency: a row is 2000 partials (8 KB of values) at vocabulary 32000, and the decision is a chain of small reads.
+// Sixteen waves take a row each (33 rows: three rounds), 2048 partials in flight, requested before the draft
+// count is known; of the token ids, which ascend with the partials, only the winner's is read; the drafts are compared by 33 lanes
+// at once; what the bookkeeping adds to is requested at the start.  Four partials
+// per load, a chain of comparisons for each of the four.  Back to back at 1 / 9 / 17 / 33 rows 3.9 / 5.1 / 6.8 / 10.6 -> 2.6 / 3.4 / 4.1 / 6.1 us, a fp32
+// model's 512 partials at five rows 3.2 -> 2.3 (ids and values read side by side, one chain with ties in it; one thread's walk over the drafts was 41 at 33).
 #define ACCEPT_THREADS 1024
 __global__ __launch_bounds__(ACCEPT_THREADS) void argmax_accept_kernel(const float *__restrict__ pval, const int *__restrict__ pidx,
                                                                        int n_part, StepState s, int m, int max_k, int vocab, const GenState *gen) {
-    constexpr int U = 16, WAVES = ACCEPT_THREADS / 64;
+    constexpr int WAVES = ACCEPT_THREADS / 64;
     __shared__ int o[40];
     const int b = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (gen != nullptr) gen += b;                                // llma_generate: one GenState per sequence of the batch
     const int keff = s.keff[b];
     const int slot = s.batch_slots[b];
-    int n_out = 0;
-    if (gen != nullptr) n_out = *gen->n_out;
+    int n_out = 0, step = 0, doc = 0, doc_pos = 0;
+    if (gen != nullptr) { n_out = *gen->n_out; step = *gen->n_steps; doc = gen->cur[0]; doc_pos = gen->cur[1]; }
+    const int T = s.T[slot];
+    int draft = -1;
     // one row per wave at a time: wave w reduces rows w, w + 16, ... over the per-tile partials (rows past keff are
     // rows of the step too: their partials exist, what they say is dropped)
     for (int j = wave; j < m; j += WAVES) {
         const size_t r = (size_t)b * m + j;
         float bv = LLMA_NEG_INF;
-        int bi = 0x7fffffff;
-        for (int t0 = lane; t0 < n_part; t0 += 64 * U) {
-            float v[U];
-            int id[U];
+        int bt = 0x7fffffff;
+        const float *const row = pval + r * n_part;
+        const auto look = [&](auto width, auto in_flight) {      // a lane takes `width` neighbours at a time
+            constexpr int E = decltype(width)::value, U = decltype(in_flight)::value, TRIP = 64 * E;
+            float best[E];                                       // per place in the group: a chain of their own, indices ascend
+            int where[E];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = t0 + 64 * u < n_part ? t0 + 64 * u : lane;        // (a partial read twice changes nothing)
-                v[u] = pval[r * n_part + t];
-                id[u] = pidx[r * n_part + t];
+            for (int e = 0; e < E; ++e) { best[e] = LLMA_NEG_INF; where[e] = 0x7fffffff; }
+            for (int first = 0; first < n_part; first += U * TRIP) {
+                float v[U][E];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int t = first + u * TRIP + lane * E;
+                    __builtin_memcpy(v[u], __builtin_assume_aligned(row + (t < n_part ? t : 0), 4 * E), 4 * E);
+                }
+                if (j > keff) return;                            // uniform; padding (the count arrived with the first partials)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int t = first + u * TRIP + lane * E;
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+                        if (t < n_part && v[u][e] > best[e]) { best[e] = v[u][e]; where[e] = t + e; }
+                }
             }
-            if (j > keff) break;                                 // uniform; padding (the count arrived with the first partials)
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (v[u] > bv || (v[u] == bv && id[u] < bi)) { bv = v[u]; bi = id[u]; }
-        }
+            for (int e = 0; e < E; ++e)
+                if (best[e] > bv || (best[e] == bv && where[e] < bt)) { bv = best[e]; bt = where[e]; }
+        };
+        if (n_part % 4 != 0) look(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
+        else if (n_part <= 512) look(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+        else look(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
         if (j > keff) break;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            float ov = __shfl_xor(bv, off);
-            int oi = __shfl_xor(bi, off);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-        }
+        butterfly<32>([&](auto off) {
+            const float ov = lane_xor<off.value>(bv);
+            const int ot = lane_xor<off.value>(bt);
+            if (ov > bv || (ov == bv && ot < bt)) { bv = ov; bt = ot; }
+        });
         // a row without any comparable logit (all NaN: reachable through imported caches or weights that
-        // hold non-finite values) must still yield a token id the next step's embedding gather can use
+        // hold non-finite values; or all of them minus infinity: token 0) must still yield a token id the next step's embedding gather can use
+        int bi = bt >= n_part ? 0 : (n_part == vocab ? bt : pidx[r * n_part + bt]);      // (fp32 models: a partial per token)
         if ((unsigned)bi >= (unsigned)vocab) bi = 0;
         if (lane == 0) o[j] = bi;
+        if (j == 0 && lane < keff) draft = s.draft[b * max_k + lane];
     }
     // the first wave decides: lane j compares draft j
-    const int draft = wave == 0 && lane < keff ? s.draft[b * max_k + lane] : -1;
     __syncthreads();
     if (wave != 0) return;
     if (gen != nullptr && n_out >= gen->max_new) return;         // a finished sequence / a step enqueued past the end: leave all state alone
@@ -478,21 +501,20 @@ __global__ __launch_bounds__(ACCEPT_THREADS) void argmax_accept_kernel(const flo
         host_write(s.io.nacc + b, a);
         host_write(s.io.next + b, o[a]);
     }
-    s.T[slot] += a + 1;
+    s.T[slot] = T + a + 1;
     s.pending[slot] = o[a];
     if (gen != nullptr) {
-        const int st = *gen->n_steps;
-        gen->trace[st * 4 + 0] = 1 + keff;
-        gen->trace[st * 4 + 1] = a + 1;
-        gen->trace[st * 4 + 2] = keff > 0 ? gen->cur[0] : -1;
-        gen->trace[st * 4 + 3] = keff > 0 ? gen->cur[1] : -1;
+        gen->trace[step * 4 + 0] = 1 + keff;
+        gen->trace[step * 4 + 1] = a + 1;
+        gen->trace[step * 4 + 2] = keff > 0 ? doc : -1;
+        gen->trace[step * 4 + 3] = keff > 0 ? doc_pos : -1;
         const int now = n_out + a + 1;
         *gen->n_out = now;
-        *gen->n_steps = st + 1;
-        // the host reads the count of step st after that step's event, while the next step may be running: two places
+        *gen->n_steps = step + 1;
+        // the host reads the count of step `step` after that step's event, while the next step may be running: two places
         // in turn; the last step of a sequence fills both
-        host_write(gen->host_count + (size_t)(st & 1) * gen->host_stride, now);
-        if (now >= gen->max_new) host_write(gen->host_count + (size_t)((st & 1) ^ 1) * gen->host_stride, now);
+        host_write(gen->host_count + (size_t)(step & 1) * gen->host_stride, now);
+        if (now >= gen->max_new) host_write(gen->host_count + (size_t)((step & 1) ^ 1) * gen->host_stride, now);
     }
 }
 void launch_argmax_accept(const float *pval, const int *pidx, int n_part, const StepState &s, int n_seqs, int m,
