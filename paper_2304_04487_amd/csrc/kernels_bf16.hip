@@ -1238,84 +1238,76 @@ __device__ __forceinline__ void loads_stay_above() { asm volatile("" ::: "memory
 // tile of accumulators in registers at a time) and the registers are capped, so that two workgroups
 // fit a compute unit like they do with one or two row tiles (7B, 33 rows over 3500 positions: 38.1 -> 30.8 us).
 #define ATTN_COMPACT_ROWS 36
-template <int DH, int NTQ, bool KVS, bool LIVE, bool COMPACT = false>
+// (Several chunks per workgroup, the next one requested while one is computed, where there are more than fit the chip at once:
+// no gain at 1 .. 33 rows over 2700 and 3500 positions.)
+template <int DH, int NTQ, bool KVS, bool LIVE, bool COMPACT>
 __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4][NTQ * 16], float (&sl)[4][NTQ * 16],
-                                                float (&so)[4][COMPACT ? ATTN_COMPACT_ROWS : NTQ * 16][DH + 4]) {
+                                                 float (&so)[4][COMPACT ? ATTN_COMPACT_ROWS : NTQ * 16][DH + 4]) {
     constexpr int KSTEPS = DH / 32;   // MFMA k-steps of a q.k dot product
     constexpr int DT = DH / 16;       // 16-feature tiles of the head dimension
     constexpr int RQ = NTQ * 16;
     constexpr int OQ = COMPACT ? 1 : NTQ;                      // row tiles of accumulators held at once
 
     const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z / a.n_rblocks, rb = blockIdx.z % a.n_rblocks;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int slot = a.slot_const >= 0 ? a.slot_const : a.batch_slots[b];
     const int m = a.m;
     const int j0 = rb * RQ;                             // first row of this row block
-    const int chunk0 = c * ATTN_CHUNK;
     const int d_model = a.H * DH;
-    const int key0 = chunk0 + wave * 32;
     const size_t head_base = ((size_t)slot * a.H + h) * (size_t)a.max_seq * DH;
     // The sequence length and the live-row count are requested first and used last: both requests
     // are in flight together with the K/V blocks instead of one after the other behind them.
     const int T = a.T[slot];
     const int live_rows = LIVE ? *a.rows_live + 1 : m;
     loads_stay_above();
-    // K and V blocks of the wave's 32 positions: issued before the sequence length is known (any
+    // K and V blocks of the wave's 32 positions: requested before the sequence length is known (any
     // position below max_seq lies inside the cache allocation; unused blocks are simply dropped)
     u32x4 ka[2][KSTEPS], va[DT];
     u32x2 kb[2][KSTEPS], vb[DT];                     // lo planes: one byte per element
+    // query operands of a row tile: they do not depend on the sequence length either.  With more row tiles the
+    // next one's take the registers behind the present one's scores (requested where they are used, each tile waited for its own: 33 rows
+    // over 2700 / 3500 positions 32.2 / 36.0 -> 26.1 / 31.2 us with the combine kernel)
+    u32x4 qh[KSTEPS], ql[KSTEPS];
+    const unsigned q_bytes = (unsigned)((a.n_seqs * m + 15) / 16) * (unsigned)d_model * 32;      // (at most 48 rows of a sequence, or 48 in all: launch_attn_dh)
+    const rsrc_t qhr = buffer_of(a.Qhi, q_bytes), qlr = buffer_of(a.Qlo, q_bytes);
+    auto fetch_q = [&](int q) {
+        const int j = j0 + q * 16 + n;
+        const unsigned at = (unsigned)xtile_off(b * m + (j < m ? j : 0), h * DH + g * 8, d_model / 32, a.quads) * 2;
+#pragma unroll
+        for (int s = 0; s < KSTEPS; ++s) {                  // (a k-step further: the next 1 KiB block)
+            qh[s] = buffer_load16<false>(qhr, at + s * 1024);
+            ql[s] = buffer_load16<false>(qlr, at + s * 1024);
+        }
+    };
     {
-        const bf16_t *kh = (const bf16_t *)a.Khi + head_base; const uint8_t *kl = (const uint8_t *)a.Klo + head_base;
-        const bf16_t *vh = (const bf16_t *)a.Vhi + head_base; const uint8_t *vl = (const uint8_t *)a.Vlo + head_base;
+        const size_t first = head_base + (size_t)(c * ATTN_CHUNK + wave * 32) * DH + lane * 8;
+        const bf16_t *kh = (const bf16_t *)a.Khi + first, *vh = (const bf16_t *)a.Vhi + first;
+        const uint8_t *kl = (const uint8_t *)a.Klo + first, *vl = (const uint8_t *)a.Vlo + first;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int s = 0; s < KSTEPS; ++s) {
-                const size_t off = (size_t)(key0 / 16 + t) * (16 * DH) + s * 512 + lane * 8;
-                ka[t][s] = *(const u32x4 *)(kh + off);
-                if (KVS) kb[t][s] = *(const u32x2 *)(kl + off);
+                ka[t][s] = *(const u32x4 *)(kh + t * (16 * DH) + s * 512);
+                if (KVS) kb[t][s] = *(const u32x2 *)(kl + t * (16 * DH) + s * 512);
             }
+        fetch_q(0);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
-            const size_t off = (size_t)(key0 / 32) * (32 * DH) + dt * 512 + lane * 8;
-            va[dt] = (*(const u32x4 *)(vh + off));
-            if (KVS) vb[dt] = *(const u32x2 *)(vl + off);
+            va[dt] = *(const u32x4 *)(vh + dt * 512);
+            if (KVS) vb[dt] = *(const u32x2 *)(vl + dt * 512);
         }
     }
-    // a single row tile's query operands do not depend on the sequence length either
-    u32x4 qh0[KSTEPS], ql0[KSTEPS];
-    if (NTQ == 1) {
-        const int j = j0 + n;
-        const int r = b * m + (j < m ? j : 0);
-#pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) {
-            const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32, a.quads);
-            qh0[s] = (*(const u32x4 *)((const bf16_t *)a.Qhi + off));
-            ql0[s] = (*(const u32x4 *)((const bf16_t *)a.Qlo + off));
-        }
-    }
-    if (NTQ == 1) loads_stay_above();                   // (with more row tiles the registers are needed elsewhere)
+    loads_stay_above();
     // generation steps: rows past the trigger's draft count are padding (see the GEMM); they are
     // masked like rows past m and a row tile made of them only is skipped
     const int m_live = live_rows < m ? live_rows : m;     // LIVE: rows_live is set
     if (j0 >= m_live) return;
     const int m_blk = (m_live - j0 < RQ) ? m_live - j0 : RQ;   // live rows of this block
     const int kv_len = T + j0 + m_blk;                  // positions the block's last row can see
-    if (chunk0 >= kv_len) return;                       // uniform for the workgroup
-    const bool active = key0 < kv_len;                  // uniform for the wave
 
     float mrow[NTQ], lrow[NTQ];
     f32x4 o[OQ][DT];
-#pragma unroll
-    for (int q = 0; q < NTQ; ++q) {
-        mrow[q] = LLMA_NEG_INF;
-        lrow[q] = 0.f;
-    }
-#pragma unroll
-    for (int q = 0; q < OQ; ++q)
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) o[q][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
     // every wave publishes (max, sum, O) of a row tile for the merge below
     auto publish = [&](int q, const f32x4 (&oq)[DT]) {
         float l = lrow[q];
@@ -1326,75 +1318,78 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) *(f32x4 *)&so[wave][q * 16 + n][dt * 16 + 4 * g] = oq[dt];
     };
+    const int chunk0 = c * ATTN_CHUNK, key0 = chunk0 + wave * 32;
+    if (chunk0 >= kv_len) return;                   // uniform for the workgroup
+    const bool active = key0 < kv_len;              // uniform for the wave
+#pragma unroll
+    for (int q = 0; q < NTQ; ++q) {
+        mrow[q] = LLMA_NEG_INF;
+        lrow[q] = 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < OQ; ++q)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[q][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
     if (COMPACT && !active) {
 #pragma unroll
-        for (int q = 0; q < NTQ; ++q) publish(q, o[0]);         // (zeros)
+        for (int q = 0; q < NTQ; ++q) publish(q, o[0]);     // (zeros)
     }
-
     if (active) {
 #pragma unroll
         for (int q = 0; q < NTQ; ++q) {
             const int oi = COMPACT ? 0 : q;
-            if (LIVE && q > 0 && j0 + q * 16 >= m_live) {           // uniform: no live row in this tile
-                if (COMPACT) publish(q, o[0]);                      // (zeros: o[0] is cleared after every tile)
-                continue;
-            }
+            const bool dead = LIVE && q > 0 && j0 + q * 16 >= m_live;       // uniform: no live row in this tile
             const int j = j0 + q * 16 + n;
-            const bool valid = j < m_live;
-            const int rpos = valid ? T + j : -1;
-            const int r = b * m + (valid ? j : 0);
-            u32x4 qh[KSTEPS], ql[KSTEPS];
-#pragma unroll
-            for (int s = 0; s < KSTEPS; ++s) {
-                if (NTQ == 1) { qh[s] = qh0[s]; ql[s] = ql0[s]; continue; }
-                const size_t off = xtile_off(r, h * DH + s * 32 + g * 8, d_model / 32, a.quads);
-                qh[s] = *(const u32x4 *)((const bf16_t *)a.Qhi + off);
-                ql[s] = *(const u32x4 *)((const bf16_t *)a.Qlo + off);
-            }
+            const int rpos = j < m_live ? T + j : -1;
             float sv[8];
             float mx = LLMA_NEG_INF;
+            if (!dead) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+                for (int t = 0; t < 2; ++t) {
+                    f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int s = 0; s < KSTEPS; ++s) {
-                    acc = mfma16x16x32(ka[t][s], qh[s], acc);
-                    acc = mfma16x16x32(ka[t][s], ql[s], acc);
-                    if (KVS) acc = mfma16x16x32(lo8_operand(kb[t][s]), qh[s], acc);
-                }
+                    for (int s = 0; s < KSTEPS; ++s) {
+                        acc = mfma16x16x32(ka[t][s], qh[s], acc);
+                        acc = mfma16x16x32(ka[t][s], ql[s], acc);
+                        if (KVS) acc = mfma16x16x32(lo8_operand(kb[t][s]), qh[s], acc);
+                    }
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const int key = key0 + t * 16 + 4 * g + r4;
-                    float v = acc[r4] * a.scale;
-                    v = (key > rpos) ? LLMA_NEG_INF : v;
-                    sv[t * 4 + r4] = v;
-                    mx = fmaxf(mx, v);
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        const int key = key0 + t * 16 + 4 * g + r4;
+                        float v = acc[r4] * a.scale;
+                        v = (key > rpos) ? LLMA_NEG_INF : v;
+                        sv[t * 4 + r4] = v;
+                        mx = fmaxf(mx, v);
+                    }
                 }
             }
-            mx = fmaxf(mx, lane_xor<16>(mx));
-            mx = fmaxf(mx, lane_xor<32>(mx));
-            float psum = 0.f;
-            float p[8];
+            if (q < NTQ - 1) fetch_q(q + 1);
+            if (!dead) {
+                mx = fmaxf(mx, lane_xor<16>(mx));
+                mx = fmaxf(mx, lane_xor<32>(mx));
+                float psum = 0.f;
+                float p[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                p[i] = (mx == LLMA_NEG_INF) ? 0.f : __expf(sv[i] - mx);
-                psum += p[i];
-            }
-            lrow[q] = psum;
-            mrow[q] = mx;
-            u32x2 h0, l0, h1, l1;
-            split4(p, h0, l0);
-            split4(p + 4, h1, l1);
-            const u32x4 ph = (u32x4){h0[0], h0[1], h1[0], h1[1]};
-            const u32x4 pl = (u32x4){l0[0], l0[1], l1[0], l1[1]};
+                for (int i = 0; i < 8; ++i) {
+                    p[i] = (mx == LLMA_NEG_INF) ? 0.f : __expf(sv[i] - mx);
+                    psum += p[i];
+                }
+                lrow[q] = psum;
+                mrow[q] = mx;
+                u32x2 h0, l0, h1, l1;
+                split4(p, h0, l0);
+                split4(p + 4, h1, l1);
+                const u32x4 ph = (u32x4){h0[0], h0[1], h1[0], h1[1]};
+                const u32x4 pl = (u32x4){l0[0], l0[1], l1[0], l1[1]};
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                o[oi][dt] = mfma16x16x32(va[dt], ph, o[oi][dt]);
-                o[oi][dt] = mfma16x16x32(va[dt], pl, o[oi][dt]);
-                if (KVS) o[oi][dt] = mfma16x16x32(lo8_operand(vb[dt]), ph, o[oi][dt]);
+                for (int dt = 0; dt < DT; ++dt) {
+                    o[oi][dt] = mfma16x16x32(va[dt], ph, o[oi][dt]);
+                    o[oi][dt] = mfma16x16x32(va[dt], pl, o[oi][dt]);
+                    if (KVS) o[oi][dt] = mfma16x16x32(lo8_operand(vb[dt]), ph, o[oi][dt]);
+                }
             }
             if (COMPACT) {
-                publish(q, o[0]);
+                publish(q, o[0]);                           // (a dead tile: zeros)
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) o[0][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
             }
@@ -1440,8 +1435,8 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
 // LOSKIP (batched steps on caches with hi + lo planes): positions below lo_from[slot] were imported
 // as bf16 values -- their lo planes hold zeros -- so a chunk that lies entirely below it runs the
 // single-plane form of the body: half the K/V bytes, the same sums (the skipped terms are zeros).
-template <int DH, int NTQ, bool KVS, bool LIVE, bool LOSKIP = false, bool COMPACT = false>
-__global__ __launch_bounds__(256, (COMPACT ? 2 : 1)) void attn_bf16_kernel(AttnArgs a) {
+template <int DH, int NTQ, bool KVS, bool LIVE, bool LOSKIP, bool COMPACT>
+__global__ __launch_bounds__(256, 2) void attn_bf16_kernel(AttnArgs a) {
     constexpr int RQ = NTQ * 16;
     __shared__ float sm[4][RQ], sl[4][RQ];
     __shared__ float so[4][COMPACT ? ATTN_COMPACT_ROWS : RQ][DH + 4];
@@ -1842,11 +1837,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // merges the chunk partials of one (row, head): out = sum_c e^{m_c - M} O_c / sum_c e^{m_c - M} l_c,
-// over the chunks that contain positions <= the row's own, in chunk order; writes hi/lo tiled planes.
-// One thread per 4 output features; the partials of 16 chunks are in flight at a time.
-template <int DH, bool QUADS>
-__device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int rq, int r, int h, int d4 /* features 4 d4 .. +3 */) {
-    constexpr int CB = 16;                             // chunks per load batch
+// over the chunks that contain positions <= the row's own; writes hi/lo tiled planes.  A wave per (row, head): groups of DH / 4
+// lanes, four output features per lane; group i takes chunks i, i + PARTS, .. in order, up to sixteen of them in flight, and the groups
+// meet at the end.  Which chunk goes where is a function of its position only.  Bound by the round trips to the partials: with one group per
+// row half of the wave was idle, and every row asked for sixteen partials however few there are.  One row over 200 / 1000 / 2000 / 3500
+// positions of 7B, with the chunk kernel, 7.1 / 10.2 / 13.9 / 25.7 -> 6.3 / 8.7 / 12.7 / 20.6 us, 33 rows 12.2 / 17.8 / 20.8 / 36.0 -> 9.7 / 15.6 / 18.4 / 30.4
+// (of which requesting a row tile's queries early 1.3 .. 5), d 512 6.0 -> 5.2.
+// CB, chunks of a group in flight: 16, less where all launched chunks are fewer (one trip either way: the same sums).
+template <int DH, bool QUADS, int CB>
+__device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int rq, int r, int h) {
+    constexpr int LANES = DH / 4, PARTS = 64 / LANES;
+    const int lane = threadIdx.x & 63, d4 = lane % LANES, part = lane / LANES;
     const int b = r / a.m, j = r % a.m;
     const int slot = a.slot_const >= 0 ? a.slot_const : a.batch_slots[b];
     // live-row count and sequence length: requested before the partials, used after them (one
@@ -1862,7 +1863,7 @@ __device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int rq, int 
     auto fetch = [&](int c0) {
 #pragma unroll
         for (int u = 0; u < CB; ++u) {
-            const int c = (c0 + u < a.n_chunks) ? c0 + u : a.n_chunks - 1;
+            const int c = c0 + u * PARTS + part < a.n_chunks ? c0 + u * PARTS + part : a.n_chunks - 1;
             mv[u] = a.pm[(base + c) * rq + j];
             lv[u] = a.pl[(base + c) * rq + j];
             ov[u] = (*(const f32x4 *)(a.po + ((base + c) * rq + j) * DH + d4 * 4));
@@ -1873,27 +1874,42 @@ __device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int rq, int 
     if (j > live_last) return;                         // padding row of a generation step (its partials are stale: dropped)
     const int pos = T + j;
     const int nc = pos / a.part_span + 1;
-    // running (max, sum, O) over the chunks in chunk order
+    // running (max, sum, O) over the group's chunks
     float M = LLMA_NEG_INF, L = 0.f;
     f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
-    for (int c0 = 0; c0 < nc; c0 += CB) {
+    for (int c0 = 0; c0 < nc; c0 += CB * PARTS) {
         if (c0 > 0) fetch(c0);
         float Mb = M;
 #pragma unroll
-        for (int u = 0; u < CB; ++u)
-            if (c0 + u < nc) Mb = fmaxf(Mb, mv[u]);
+        for (int u = 0; u < CB; ++u) {
+            mv[u] = c0 + u * PARTS + part < nc ? mv[u] : LLMA_NEG_INF;
+            Mb = fmaxf(Mb, mv[u]);
+        }
         const float rs = (M == LLMA_NEG_INF) ? 0.f : __expf(M - Mb);
         L *= rs;
         acc *= rs;
         M = Mb;
 #pragma unroll
-        for (int u = 0; u < CB; ++u)
-            if (c0 + u < nc) {
-                const float w = (mv[u] == LLMA_NEG_INF) ? 0.f : __expf(mv[u] - M);
-                L += w * lv[u];
-                acc += ov[u] * w;
-            }
+        for (int u = 0; u < CB; ++u) {
+            if (c0 + u * PARTS >= nc) break;           // uniform
+            const bool mine = mv[u] != LLMA_NEG_INF;   // (what a chunk past the end holds may be anything)
+            const float w = __expf(mv[u] - M);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = mine ? fmaf(ov[u][e], w, acc[e]) : acc[e];
+            L = mine ? fmaf(w, lv[u], L) : L;
+        }
     }
+    // the groups meet (every lane adds its partner's part to its own; the first group's lanes write)
+    const auto meet = [&](float m1, float l1, const f32x4 &a1) {
+        const float Mn = fmaxf(M, m1);
+        const float s0 = M == LLMA_NEG_INF ? 0.f : __expf(M - Mn), s1 = m1 == LLMA_NEG_INF ? 0.f : __expf(m1 - Mn);
+        L = L * s0 + l1 * s1;
+        acc = acc * s0 + a1 * s1;
+        M = Mn;
+    };
+    if constexpr (PARTS == 4) meet(lane_xor<16>(M), lane_xor<16>(L), (f32x4){lane_xor<16>(acc[0]), lane_xor<16>(acc[1]), lane_xor<16>(acc[2]), lane_xor<16>(acc[3])});
+    meet(lane_xor<32>(M), lane_xor<32>(L), (f32x4){lane_xor<32>(acc[0]), lane_xor<32>(acc[1]), lane_xor<32>(acc[2]), lane_xor<32>(acc[3])});
+    if (part != 0) return;
     float v[4] = {acc[0] / L, acc[1] / L, acc[2] / L, acc[3] / L};
     u32x2 hi, lo;
     split4(v, hi, lo);
@@ -1902,17 +1918,17 @@ __device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int rq, int 
     *(u32x2 *)((bf16_t *)a.out_lo + o) = lo;
 }
 
-template <int DH>
-__global__ void attn_combine_bf16_kernel(AttnArgs a, int rq) { attn_combine_row<DH, false>(a, rq, blockIdx.x, blockIdx.y, threadIdx.x); }
+template <int DH, int CB>
+__global__ __launch_bounds__(64) void attn_combine_bf16_kernel(AttnArgs a, int rq) { attn_combine_row<DH, false, CB>(a, rq, blockIdx.x, blockIdx.y); }
 
 // The same where the planes' pieces go by four rows (more than XTILE_ROWWISE rows): a workgroup takes four rows, one per
 // wave, and writes whole 256-byte pieces of a tile, of which one workgroup per row writes 16 bytes each at a time from four
 // XCDs (a 144-row step wrote 4.5 MB where 2.4 are the result).  7B, 16 sequences of 4096, 144 rows: 10.3 -> 8.6 us.
-template <int DH>
+template <int DH, int CB>
 __global__ __launch_bounds__(256) void attn_combine_quads_bf16_kernel(AttnArgs a, int rq) {
-    const int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), d4 = threadIdx.x & 63;
-    if (r >= a.n_seqs * a.m || d4 >= DH / 4) return;
-    attn_combine_row<DH, true>(a, rq, r, blockIdx.y, d4);
+    const int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (r >= a.n_seqs * a.m) return;
+    attn_combine_row<DH, true, CB>(a, rq, r, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2113,13 +2129,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
+template <int DH, int CB>
+static void launch_combine_cb(const AttnArgs &a, int rq, hipStream_t st) {
+    const int rows = a.n_seqs * a.m;
+    if (a.quads) hipLaunchKernelGGL((attn_combine_quads_bf16_kernel<DH, CB>), dim3((rows + 3) / 4, a.H), dim3(256), 0, st, a, rq);
+    else hipLaunchKernelGGL((attn_combine_bf16_kernel<DH, CB>), dim3(rows, a.H), dim3(64), 0, st, a, rq);
+}
 template <int DH>
 static void launch_combine(const AttnArgs &a, int rq, hipStream_t st) {
-    const int rows = a.n_seqs * a.m;
-    if (a.quads) hipLaunchKernelGGL((attn_combine_quads_bf16_kernel<DH>), dim3((rows + 3) / 4, a.H), dim3(256), 0, st, a, rq);
-    else hipLaunchKernelGGL((attn_combine_bf16_kernel<DH>), dim3(rows, a.H), dim3(DH / 4), 0, st, a, rq);
+    constexpr int PARTS = 256 / DH;
+    if (a.n_chunks <= 4 * PARTS) launch_combine_cb<DH, 4>(a, rq, st);
+    else if (a.n_chunks <= 8 * PARTS) launch_combine_cb<DH, 8>(a, rq, st);
+    else launch_combine_cb<DH, 16>(a, rq, st);
 }
 
+template <int DH, int NTQ, bool KVS>
+static void launch_attn_tiles(const AttnArgs &a, hipStream_t st) {
+    const dim3 grid(a.n_chunks, a.H, a.n_seqs * a.n_rblocks), block(256);
+    constexpr bool FEW = NTQ == 3;                                   // COMPACT where the rows fit it
+    if (a.rows_live != nullptr) {                                    // generation step of one sequence: padding rows known on the device (at most max_k + 1 = 33)
+        hipLaunchKernelGGL((attn_bf16_kernel<DH, NTQ, KVS, true, false, FEW>), grid, block, 0, st, a);
+    } else if (KVS && a.slot_const < 0 && a.lo_from != nullptr) {    // several sequences: their caches may have been imported
+        if (FEW && a.m <= ATTN_COMPACT_ROWS) hipLaunchKernelGGL((attn_bf16_kernel<DH, NTQ, KVS, false, KVS, FEW>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((attn_bf16_kernel<DH, NTQ, KVS, false, KVS, false>), grid, block, 0, st, a);
+    } else {
+        if (FEW && a.m <= ATTN_COMPACT_ROWS) hipLaunchKernelGGL((attn_bf16_kernel<DH, NTQ, KVS, false, false, FEW>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((attn_bf16_kernel<DH, NTQ, KVS, false, false, false>), grid, block, 0, st, a);
+    }
+}
 template <int DH, bool KVS>
 static void launch_attn_dh(const AttnArgs &a0, hipStream_t st) {
     // up to 48 rows per workgroup; longer row lists (prompt processing) are cut into row blocks
@@ -2141,20 +2178,9 @@ static void launch_attn_dh(const AttnArgs &a0, hipStream_t st) {
         launch_combine<DH>(a, a.n_rblocks * ntq * 16, st);
         return;
     }
-    dim3 grid(a.n_chunks, a.H, a.n_seqs * a.n_rblocks);
-    if (a.rows_live != nullptr) {                      // generation step of one sequence: padding rows known on the device
-        if (ntq == 1) hipLaunchKernelGGL((attn_bf16_kernel<DH, 1, KVS, true>), grid, dim3(256), 0, st, a);
-        else if (ntq == 2) hipLaunchKernelGGL((attn_bf16_kernel<DH, 2, KVS, true>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((attn_bf16_kernel<DH, 3, KVS, true, false, true>), grid, dim3(256), 0, st, a);   // (at most max_k + 1 = 33 rows)
-    } else if (KVS && a.slot_const < 0 && a.lo_from != nullptr) {   // several sequences: their caches may have been imported
-        if (ntq == 1) hipLaunchKernelGGL((attn_bf16_kernel<DH, 1, KVS, false, true>), grid, dim3(256), 0, st, a);
-        else if (ntq == 2) hipLaunchKernelGGL((attn_bf16_kernel<DH, 2, KVS, false, true>), grid, dim3(256), 0, st, a);
-        else if (a.m <= ATTN_COMPACT_ROWS) hipLaunchKernelGGL((attn_bf16_kernel<DH, 3, KVS, false, true, true>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((attn_bf16_kernel<DH, 3, KVS, false, true>), grid, dim3(256), 0, st, a);
-    } else if (ntq == 1) hipLaunchKernelGGL((attn_bf16_kernel<DH, 1, KVS, false>), grid, dim3(256), 0, st, a);
-    else if (ntq == 2) hipLaunchKernelGGL((attn_bf16_kernel<DH, 2, KVS, false>), grid, dim3(256), 0, st, a);
-    else if (a.m <= ATTN_COMPACT_ROWS) hipLaunchKernelGGL((attn_bf16_kernel<DH, 3, KVS, false, false, true>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((attn_bf16_kernel<DH, 3, KVS, false>), grid, dim3(256), 0, st, a);
+    if (ntq == 1) launch_attn_tiles<DH, 1, KVS>(a, st);
+    else if (ntq == 2) launch_attn_tiles<DH, 2, KVS>(a, st);
+    else launch_attn_tiles<DH, 3, KVS>(a, st);
     launch_combine<DH>(a, a.n_rblocks * ntq * 16, st);
 }
 
