@@ -993,6 +993,131 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Block GEMM (long prompt passes): like the panel GEMM without a split, but both operands pass through LDS and a wave owns 8 weight tiles x
+// RT / 4 row tiles (2 x 4 waves per workgroup of 16 x RT tiles).  In the panel GEMM a read from LDS feeds two products, which keeps the LDS
+// as busy as the matrix cores (per k-step of nine row tiles 1266 cycles of reads and fills beside 1152 of MFMA) and costs power, the bound of
+// long prompts; here 16 reads feed 64 products (RT 16).  Gate/up of 7B at 2047 rows 536 -> 496 us = 1.38 -> 1.49 PFLOP/s, of which the
+// last round of workgroups leaves a tenth idle.  Which passes take it: block_height.
+// A k-step's (16 + 2 RT) KB come straight into one of three LDS stages.  The groups of a k-step are its row tiles, 16 MFMAs each; the next group's
+// activations are read during the present one, and the next k-step's weights replace the present ones during the last group, tile by
+// tile behind the tile's last product.  The sums are added in the same order as the panel GEMM's: k-step after k-step, hi then lo.
+// ---------------------------------------------------------------------------------------------
+#define BLOCK_STAGES 3
+template <int RT, int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_block_bf16(GemmArgs a0) {
+    constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1, NW = 8, FT = 8, RW = RT / 4, PAIRS = 16 / TILES;
+    constexpr int BLOCKS = 16 + 2 * RT, REQ = BLOCKS / NW;         // 1 KiB blocks per k-step, and how many of them a wave fetches
+    static_assert(RT % 4 == 0 && BLOCKS % NW == 0, "");
+    extern __shared__ u32x4 xs[];                  // [stages][16 weight tiles, then 2 planes x RT][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wf = wave & 1, wr = wave >> 1;       // the wave's eight weight tiles and its row tiles
+    const GemmPlan &p = a0.plan;
+    const int KSp = p.KSp;
+    const int RB = a0.panel_rb;                    // (workgroup order: see the panel GEMM)
+    const int grp = blockIdx.x / (8 * RB), within = blockIdx.x % (8 * RB);
+    const int fb = grp * 8 + (within & 7), rb = within >> 3;
+    if (fb * PAIRS >= p.tasks) return;
+    const int rt0 = rb * RT;
+    const int n_rt_total = (a0.rows + 15) / 16, n_rt = n_rt_total - rt0 < RT ? n_rt_total - rt0 : RT;
+
+    // Descriptors: the block's weight tiles (gate/up: its gate tiles and its up tiles), its part of the two activation planes.  Tiles past the
+    // last one and row tiles past the end lie outside: zeros.
+    const int n_tasks = p.tasks - fb * PAIRS < PAIRS ? p.tasks - fb * PAIRS : PAIRS;
+    const unsigned w_bytes = (unsigned)n_tasks * (unsigned)KSp * 1024u, x_bytes = (unsigned)n_rt * (unsigned)KSp * 1024u;
+    const char *const w0 = (const char *)a0.W + (size_t)fb * PAIRS * KSp * 1024;
+    const rsrc_t wg = buffer_of(w0, w_bytes), wu = buffer_of(w0 + (TILES == 2 ? (size_t)p.tasks * KSp * 1024 : 0), w_bytes);
+    const rsrc_t xh = buffer_of((const char *)a0.Xhi + (size_t)rt0 * KSp * 1024, x_bytes), xl = buffer_of((const char *)a0.Xlo + (size_t)rt0 * KSp * 1024, x_bytes);
+    const unsigned w_lane = (unsigned)lane * 16u, x_lane = (unsigned)xtile_piece(lane, true) * 16u;
+    // block q of a k-step: weight tile q (gate/up: tiles of wave group g in the order four gates, four ups), or piece q - 16 of the activations
+    auto fetch = [&](int k, int stage, int j) {
+        const int q = j * NW + wave;
+        u32x4 *const to = xs + (stage * BLOCKS + q) * 64;
+        const unsigned at = (unsigned)(k < KSp ? k : KSp - 1) * 1024u;       // (requests past the end are unused)
+        if (j < 16 / NW) {                                                   // (constant after unrolling)
+            const int tile = TILES == 2 ? (q >> 3) * 4 + (q & 3) : q;
+            load_to_lds(TILES == 2 && (q & 4) ? wu : wg, w_lane, (unsigned)(tile * KSp) * 1024u + at, to);
+        } else {
+            const int x = q - 16, t = x < RT ? x : x - RT;
+            load_to_lds(x < RT ? xh : xl, x_lane, (unsigned)(t * KSp) * 1024u + at, to);
+        }
+    };
+    f32x4 acc[FT][RW];
+#pragma unroll
+    for (int i = 0; i < FT; ++i)
+#pragma unroll
+        for (int t = 0; t < RW; ++t) acc[i][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int l = 0; l < 2 * REQ; ++l) fetch(l / REQ, l / REQ, l % REQ);
+    u32x4 w[FT], b[2][2];
+    auto read_w = [&](int stage, int i) { w[i] = xs[(stage * BLOCKS + wf * 8 + i) * 64 + lane]; };
+    auto read_x = [&](int stage, int t, u32x4 (&to)[2]) {
+        const u32x4 *const x = xs + (stage * BLOCKS + 16 + wr * RW + t) * 64 + lane;
+        to[0] = x[0];
+        to[1] = x[RT * 64];
+    };
+    wait_loads_and_barrier<REQ>();
+#pragma unroll
+    for (int i = 0; i < FT; ++i) read_w(0, i);
+    read_x(0, 0, b[0]);
+    int stage = 0;
+    auto step = [&](int k, auto parity) {                // b[par]: the first group's operands of this k-step
+        constexpr int par = decltype(parity)::value;
+        const int prev = stage == 0 ? BLOCK_STAGES - 1 : stage - 1, next = stage == BLOCK_STAGES - 1 ? 0 : stage + 1;
+        requests_stay_in_order();
+#pragma unroll
+        for (int t = 0; t < RW; ++t) {
+            const bool last = t == RW - 1;
+            if (!last) {
+                read_x(stage, t + 1, b[(par + t + 1) & 1]);
+            } else {
+                wait_loads_and_barrier<REQ>();           // the next k-step's operands are there; the one after it is on its way
+                read_x(next, 0, b[(par + t + 1) & 1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr int GROUPS = RW > 1 ? RW - 1 : 1;
+#pragma unroll
+            for (int l = 0; l < REQ; ++l)
+                if (l * GROUPS / REQ == t) { fetch(k + 2, prev, l); requests_stay_in_order(); }
+#pragma unroll
+            for (int i = 0; i < FT; ++i) {
+                acc[i][t] = mfma16x16x32(w[i], b[(par + t) & 1][0], acc[i][t]);
+                if (i % 2 == 1) {
+                    acc[i - 1][t] = mfma16x16x32(w[i - 1], b[(par + t) & 1][1], acc[i - 1][t]);
+                    acc[i][t] = mfma16x16x32(w[i], b[(par + t) & 1][1], acc[i][t]);
+                    if (last) { read_w(next, i - 1); read_w(next, i); __builtin_amdgcn_sched_barrier(0); }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        stage = next;
+    };
+    for (int k = 0; k < KSp; k += 2) {                   // (K / 32 is even: launch_panel_epi)
+        step(k, std::integral_constant<int, 0>{});
+        step(k + 1, std::integral_constant<int, RW & 1>{});
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // nothing may still be on its way into LDS when the workgroup ends
+
+    GemmArgs a = a0;
+    const int r0 = (rt0 + wr * RW) * 16;
+    offset_rows(a, p, r0);
+    if (a.rows <= 0) return;
+#pragma unroll
+    for (int f = 0; f < FT / TILES; ++f) {
+        const int task = fb * PAIRS + wf * (FT / TILES) + f;
+        if (task < p.tasks) {
+            EpiIn<RW> in;
+            epi_prefetch<RW, EPI>(a, p, task, lane, in);
+            f32x4 sum[TILES][RW];
+#pragma unroll
+            for (int i = 0; i < TILES; ++i)
+#pragma unroll
+                for (int t = 0; t < RW; ++t) sum[i][t] = acc[i * 4 + f][t];
+            gemm_epilogue<RW, EPI, TILES, true>(a, p, task, lane, sum, a0.rstd_in + r0, in);
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void rstd_rows_kernel(const float *__restrict__ ssq, int ssq_tiles, float eps, float *__restrict__ rstd, int rows) {
     rstd_of_row(ssq, ssq_tiles, eps, rstd, rows, blockIdx.x * 16 + (threadIdx.x >> 4), threadIdx.x & 15);
 }
@@ -1118,6 +1243,37 @@ static void launch_panel_rt(int rt, const GemmArgs &a, hipStream_t st) {
             default: launch_panel_cfg<10, EPI, AT, NW>(a, st); return;
         }
 }
+// Which passes without a split take the block GEMM, and in which height (0: the panel GEMM).  Both are priced alike: a launch's start and end, and its
+// rounds of workgroups, half of a last round's empty places counted (the card's clock rises while compute units idle), times what a
+// workgroup's products take under the power limit: per k-step and pair of weight and row tile 0.0056 us in the panel GEMM (RT 8, 9, 10 of
+// 7B's gate/up: 92 / 103 / 115 us per round), 0.0052 with 12 row tiles and 0.0050 with 16 in blocks (127, 164 us).  The lines between them, us panel / block:
+// gate/up of 7B at 2047 rows 536 / 496, 1919 515 / 485, 1791 465 / 479 (stays), 1535 412 / 385, 1279 338 / 323, 852 251 / 248; QKV at 1919 310 / 294, 2047 325 /
+// 355 (stays), 1279 214 / 200, 852 169 / 155; O and down (16 feature blocks, too few for either height) 98 / 119 .. 151, 272 / 305 .. 375 at 2047.
+static int block_height(const GemmPlan &p, int rows, const PanelCut &cut) {
+    if (p.KSp % 2 != 0 || p.KSp > 65536) return 0;               // (two k-steps per turn; 32-bit offsets inside a block's operands)
+    const int row_tiles = (rows + 15) / 16;
+    auto price = [&](int rt, double step_us, double start) {
+        const double r = (double)panel_feature_blocks(p, 16) * ((row_tiles + rt - 1) / rt) / cu_count(), whole = (double)(long)(r + 0.999999);
+        return start + 0.5 * (r + whole) * p.KSp * step_us;
+    };
+    if (cut.nw * cut.at != 16) return 0;                         // (8 tiles per workgroup: few workgroups as it is)
+    const double in = (16 + 2 * cut.rt) / 44.0, multiply = 0.0056 * 16 * cut.rt;        // (as in panel_cut)
+    double best_us = 0.99 * price(cut.rt, in > multiply ? in : multiply, 15.0);
+    int best = 0;
+    const double b12 = price(12, 0.0052 * 16 * 12, 22.0), b16 = price(16, 0.0050 * 16 * 16, 25.0);
+    if (b12 < best_us) { best = 12; best_us = b12; }
+    if (b16 < best_us) best = 16;
+    return best;
+}
+template <int RT, int EPI>
+static void launch_block_cfg(const GemmArgs &a, hipStream_t st) {
+    GemmArgs a2 = a;
+    a2.panel_rb = (a.rows + 16 * RT - 1) / (16 * RT);
+    const dim3 grid(panel_feature_blocks(a.plan, 16) * a2.panel_rb);
+    static std::atomic<uint64_t> done{0};
+    allow_full_lds((const void *)gemm_block_bf16<RT, EPI>, done);
+    hipLaunchKernelGGL((gemm_block_bf16<RT, EPI>), grid, dim3(512), (size_t)BLOCK_STAGES * (16 + 2 * RT) * 1024, st, a2);
+}
 template <int EPI>
 static void launch_panel_epi(const GemmArgs &a, hipStream_t st) {
     const PanelCut cut = panel_cut(a.plan, a.rows, a.ksplit > 1 ? a.ksplit : 1);
@@ -1129,6 +1285,11 @@ static void launch_panel_epi(const GemmArgs &a, hipStream_t st) {
         else launch_panel_rt<EPI_RAW, 2, 5>(cut.rt, a, st);
         launch_splitk_finish<EPI>(a, st);
         return;
+    }
+    if constexpr (EPI != EPI_LMHEAD) {                           // (the LM head runs in steps only)
+        const int rt = block_height(a.plan, a.rows, cut);
+        if (rt == 16) { launch_block_cfg<16, EPI>(a, st); return; }
+        if (rt == 12) { launch_block_cfg<12, EPI>(a, st); return; }
     }
     if constexpr (EPI != EPI_SWIGLU)
         if (cut.at == 1) { launch_panel_rt<EPI, 1, 8>(cut.rt, a, st); return; }
