@@ -2100,11 +2100,15 @@ __global__ __launch_bounds__(256) void attn_combine_quads_bf16_kernel(AttnArgs a
 // normalised rows go straight to the hi/lo planes -- no partials, no combine kernel.  Row blocks
 // are numbered from the end of the prompt (longest walks start first).  A pass over the prompts of several sequences
 // numbers their blocks one sequence after the other.
-// Bound by the wave's own chain of MFMAs and softmax arithmetic, so two waves per SIMD matter more than anything: the
+// Bound by the wave's own chain of MFMAs and softmax arithmetic -- per 32 positions 96 MFMAs and, counted in issue slots, about as much
+// vector arithmetic -- and by what a compute unit takes in (192 KB per chunk of its two workgroups), so two waves per SIMD matter more than anything: the
 // query rows sit in LDS, and one set of K / V registers is refilled in place (K while the softmax runs, V while the
 // next scores are computed) where two sets took 474 registers and left one wave per SIMD.  A position's lo bytes are
-// widened once for both row tiles.  7B, 2047 + 852 rows: 267 -> 176 us per launch
-// on average; 1535 rows: 174 -> 120.
+// widened once for both row tiles.  Workgroups are numbered heads first, so that the row blocks of a head run on one XCD (ids 8
+// apart, where the heads are a multiple of 8) and find its K and V in that XCD's L2: 7B, 2047 / 1535 / 1023 rows 177 / 104 / 60 -> 136 / 75 / 41 us, 852 rows
+// on top of 2047 141 -> 123, d 512 2047 rows 35 -> 23; then masks only where a row's end lies inside the positions, one fused multiply-add and exp2
+// per probability, and a reference that hardly ever moves: 2047 rows 120, 852 on 2047 121.5.  Half of an XCD's heads at a time (their K and V fit the L2):
+// slower, 79 at 1535.  128 query rows per workgroup and K / V through LDS: 144 at 2047, 96 at 1535, 165 at 852 on 2047 (before the arithmetic changed).
 // ---------------------------------------------------------------------------------------------
 template <int DH, bool KVS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prompt_bf16_kernel(AttnArgs a) {
@@ -2112,8 +2116,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ float sm[4][RQ], sl[4][RQ];
     __shared__ float so[4][RQ][DH + 4];
     static_assert(RQ == PROMPT_BLOCK, "the host counts the row blocks");
-    int rb = gridDim.x - 1 - blockIdx.x;
-    const int h = blockIdx.y;
+    int rb = gridDim.y - 1 - blockIdx.y;
+    const int h = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, g = lane >> 4;
     int slot = a.slot_const, m = a.m, row0 = 0;         // the sequence, its rows, where they start in the pass
@@ -2166,6 +2170,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             if (KVS) vb[dt] = *(const u32x2 *)(vl + off);
         }
     };
+    // Scores are kept as they come out of the products and maxima in powers of two: e^(scale s - max) is one fused multiply-add and one exp2.
+    // A row's reference moves only when a maximum passes it by 2^REBASE (sums of terms up to 2^REBASE lose nothing in fp32): after the
+    // first chunks the accumulators are hardly ever rescaled.
+    constexpr float REBASE = 8.f;
+    const float to_log2 = a.scale * 1.44269504088896341f;
     float mrow[NTQ], lrow[NTQ];
     f32x4 o[NTQ][DT];
 #pragma unroll
@@ -2209,31 +2218,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         fetch_k(c1);
         __builtin_amdgcn_sched_barrier(0);
         u32x4 ph[NTQ], pl[NTQ];
-        float alpha[NTQ];
+        const bool masked = key0 + 31 > T + j0;         // uniform: a row may not see all of these positions
 #pragma unroll
         for (int q = 0; q < NTQ; ++q) {
-            float mx = LLMA_NEG_INF;
+            if (masked)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int key = key0 + (i >> 2) * 16 + 4 * g + (i & 3);
-                float v = sv[q][i] * a.scale;
-                v = (key > rpos[q]) ? LLMA_NEG_INF : v;
-                sv[q][i] = v;
-                mx = fmaxf(mx, v);
-            }
+                for (int i = 0; i < 8; ++i)
+                    if (key0 + (i >> 2) * 16 + 4 * g + (i & 3) > rpos[q]) sv[q][i] = LLMA_NEG_INF;
+            float mx = sv[q][0];
+#pragma unroll
+            for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sv[q][i]);
             mx = fmaxf(mx, lane_xor<16>(mx));
-            mx = fmaxf(mx, lane_xor<32>(mx));
-            const float m_new = fmaxf(mrow[q], mx);
-            alpha[q] = (mrow[q] == LLMA_NEG_INF) ? 0.f : __expf(mrow[q] - m_new);   // m_new finite then
+            mx = fmaxf(mx, lane_xor<32>(mx)) * to_log2;
+            if (__ballot(mx > mrow[q] + REBASE) != 0ull) {          // uniform
+                const float m_new = mx > mrow[q] + REBASE ? mx : mrow[q];
+                const float alpha = m_new == LLMA_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(mrow[q] - m_new);
+                lrow[q] *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) o[q][dt] *= alpha;
+                mrow[q] = m_new;
+            }
+            const float base = mrow[q] == LLMA_NEG_INF ? 0.f : -mrow[q];         // (nothing visible so far: every term is zero)
             float psum = 0.f;
             float p[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                p[i] = (m_new == LLMA_NEG_INF) ? 0.f : __expf(sv[q][i] - m_new);
+                p[i] = __builtin_amdgcn_exp2f(fmaf(sv[q][i], to_log2, base));
                 psum += p[i];
             }
-            lrow[q] = lrow[q] * alpha[q] + psum;        // this lane's 8 keys; lanes are added at the end
-            mrow[q] = m_new;
+            lrow[q] += psum;                            // this lane's 8 keys; lanes are added at the end
             u32x2 h0, l0, h1, l1;
             split4(p, h0, l0);
             split4(p + 4, h1, l1);
@@ -2245,7 +2258,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const u32x4 vlo = KVS ? lo8_operand(vb[dt]) : (u32x4){0u, 0u, 0u, 0u};
 #pragma unroll
             for (int q = 0; q < NTQ; ++q) {
-                o[q][dt] *= alpha[q];
                 o[q][dt] = mfma16x16x32(va[dt], ph[q], o[q][dt]);
                 o[q][dt] = mfma16x16x32(va[dt], pl[q], o[q][dt]);
                 if (KVS) o[q][dt] = mfma16x16x32(vlo, ph[q], o[q][dt]);
@@ -2277,7 +2289,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const float mw = sm[w][j];
-            const float sc = (mw == LLMA_NEG_INF) ? 0.f : __expf(mw - M);
+            const float sc = (mw == LLMA_NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(mw - M);
             acc += *(const f32x4 *)&so[w][j][d4 * 4] * sc;
             L += sl[w][j] * sc;
         }
@@ -2323,7 +2335,8 @@ static void launch_attn_dh(const AttnArgs &a0, hipStream_t st) {
     // up to 48 rows per workgroup; longer row lists (prompt processing) are cut into row blocks
     AttnArgs a = a0;
     if (a.n_seqs == 1 && a.m > 48 && a.slot_const >= 0) {           // prompt pass
-        hipLaunchKernelGGL((attn_prompt_bf16_kernel<DH, KVS>), dim3(a.segs ? a.n_chunks : (a.m + PROMPT_BLOCK - 1) / PROMPT_BLOCK, a.H), dim3(256), 0, st, a);
+        const int blocks = a.segs ? a.n_chunks : (a.m + PROMPT_BLOCK - 1) / PROMPT_BLOCK;
+        hipLaunchKernelGGL((attn_prompt_bf16_kernel<DH, KVS>), dim3(a.H, blocks), dim3(256), 0, st, a);
         return;
     }
     const int ntq = a.m > 32 ? 3 : (a.m + 15) / 16;
