@@ -32,6 +32,7 @@ enum StepKind { STEP_PREFILL = 0, STEP_VERIFY = 1, STEP_GEN = 2, STEP_PROMPTS = 
 // what a captured step graph was recorded for: (kind, sequences, rows per sequence, attention chunks, slot, trigger spans)
 typedef std::array<int, 6> GraphKey;
 struct GraphSlot { int seen = 0; uint64_t used = 0; hipGraphExec_t exec = nullptr; };     // used: when last, in run_step calls
+#define GEN_STAGE_WORDS 16384    // words of a generation's inputs (and results) that pass through pinned memory (more: straight from the caller's)
 #define GRAPH_SLOTS_MAX 256      // shapes remembered; beyond them the one not used for longest is forgotten
 
 struct llma_ctx {
@@ -82,12 +83,16 @@ struct llma_ctx {
 
     StepState s{};
     GenState *gen_dev = nullptr;
-    int *gen_prompt = nullptr, *gen_ref = nullptr, *gen_doc_offsets = nullptr;
+    int *gen_prompt = nullptr;                    // prompts; in a generation the references and document lists behind them
     int *gen_part = nullptr;                      // the trigger's keys, [sequence of the batch][gen_spans] 64-bit words
     int gen_spans = 1;                            // spans the trigger scans per sequence in the current generation
     int *gen_y = nullptr, *gen_trace = nullptr;   // [sequence of the batch][max_new + 64] tokens, x 4 trace words
     int *gen_counters = nullptr;                  // n_out[max_batch], n_steps[max_batch], cur[max_batch][2], prefill base
-    int cap_prompt = 0, cap_ref = 0, cap_part = 0, cap_docs = 0, cap_y = 0, cap_trace = 0;
+    // s.T, s.pending, lo_from, s.batch_slots, gen_counters and gen_dev lie in one allocation, in this order, so that a generation
+    // sends them in one copy; pin_block: pinned memory of the same layout.  pin_stage: a generation's inputs and results on their way
+    int *block = nullptr, *pin_block = nullptr, *pin_stage = nullptr;
+    size_t block_words = 0, block_states = 0;     // all of it; the words before gen_dev
+    int cap_prompt = 0, cap_part = 0, cap_y = 0, cap_trace = 0;
 
     // what the host knows about every slot; the device's copies (s.T, s.pending, lo_from) are brought up to date by the
     // next verification step, which carries them, or by sync_state before anything else reads them
@@ -309,9 +314,16 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
     ALLOC(c, s.row_slot, Rp * 4);
     ALLOC(c, s.row_cs, Rp * dh * 4);
     HIP_TRY(c, hipMemsetAsync(s.row_cs, 0, Rp * dh * 4, c->st));
-    ALLOC(c, s.T, g.max_batch * 4);
-    ALLOC(c, s.pending, g.max_batch * 4);
-    ALLOC(c, s.batch_slots, g.max_batch * 4);
+    {
+        const size_t B = g.max_batch;
+        c->block_states = (8 * B + 4 + 1) / 2 * 2;                // (GenState holds pointers: eight-byte aligned)
+        c->block_words = c->block_states + sizeof(GenState) / 4 * B;
+        static_assert(sizeof(GenState) % 8 == 0, "");
+        ALLOC(c, c->block, c->block_words * 4);
+        s.T = c->block; s.pending = c->block + B; c->lo_from = c->block + 2 * B; s.batch_slots = c->block + 3 * B;
+        c->gen_counters = c->block + 4 * B;
+        c->gen_dev = (GenState *)(c->block + c->block_states);
+    }
     ALLOC(c, s.keff, g.max_batch * 4);
     ALLOC(c, s.draft, (size_t)g.max_batch * (g.max_k + 1) * 4);
     HIP_TRY(c, hipMemsetAsync(s.T, 0, g.max_batch * 4, c->st));
@@ -319,14 +331,11 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
     HIP_TRY(c, hipMemsetAsync(s.keff, 0, g.max_batch * 4, c->st));
     HIP_TRY(c, hipMemsetAsync(s.row_pos, 0, Rp * 4, c->st));
     HIP_TRY(c, hipMemsetAsync(s.row_slot, 0, Rp * 4, c->st));
-    ALLOC(c, c->gen_dev, sizeof(GenState) * g.max_batch);
-    ALLOC(c, c->gen_counters, (size_t)(4 * g.max_batch + 4) * 4);
     c->T_host.assign(g.max_batch, 0);
     c->pending_host.assign(g.max_batch, -1);
     c->stale.assign(g.max_batch, 0);
     c->lo_from_host.assign(g.max_batch, 0);
     c->imp_len.assign((size_t)g.max_batch * g.n_layers, -1);
-    ALLOC(c, c->lo_from, g.max_batch * 4);
     HIP_TRY(c, hipMemsetAsync(c->lo_from, 0, g.max_batch * 4, c->st));
     s.lo_from = c->lo_from;
     HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_st, hipStreamNonBlocking));
@@ -334,6 +343,9 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
         const size_t B = g.max_batch, sizes[9] = {B, B, B, B, B, B * (g.max_k + 1), B, B, B * m_max};
         size_t words = 2 * B;
         for (size_t n : sizes) words += n;
+        words = (words + 3) / 4 * 4;
+        const size_t block_at = words;
+        words += (c->block_words + 3) / 4 * 4 + GEN_STAGE_WORDS;
         HIP_TRY(c, hipHostMalloc((void **)&c->pin, words * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent));
         memset(c->pin, 0, words * sizeof(int));
         int *dev = nullptr;
@@ -344,6 +356,8 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
         for (int i = 0; i < 9; at += sizes[i], ++i) { *h[i] = c->pin + at; *d[i] = dev + at; }
         c->pin_counts = c->pin + at;
         c->pin_counts_dev = dev + at;
+        c->pin_block = c->pin + block_at;
+        c->pin_stage = c->pin_block + (c->block_words + 3) / 4 * 4;
     }
     HIP_TRY(c, hipEventCreateWithFlags(&c->cnt_ev[0], hipEventDisableTiming));
     HIP_TRY(c, hipEventCreateWithFlags(&c->cnt_ev[1], hipEventDisableTiming));
@@ -839,11 +853,8 @@ static int check_tokens(llma_ctx *c, const int32_t *t, int n, const char *who) {
     return LLMA_OK;
 }
 
-// feeds gen_prompt[0..n_feed) in chunks on top of the slot's cache; rows only write KV, no LM head
-static int prefill_rows(llma_ctx *c, int seq, int n_feed) {
-    // the chunk's tokens are gen_prompt[T - base ..]: base = T at the start of the prompt
-    HIP_TRY(c, hipMemcpyAsync(c->gen_counters + 4 * c->cfg.max_batch, &c->T_host[seq], 4, hipMemcpyHostToDevice, c->st));
-    HIP_TRY(c, hipStreamSynchronize(c->st));
+// feeds gen_prompt[T - base .. ) in chunks on top of the slot's cache, n_feed rows in all (the device knows T and base); rows only write KV, no LM head
+static int prefill_passes(llma_ctx *c, int seq, int n_feed) {
     for (int off = 0; off < n_feed; off += c->Pmax) {
         const int m = n_feed - off < c->Pmax ? n_feed - off : c->Pmax;
         int rc = run_step(c, STEP_PREFILL, 1, m, c->T_host[seq], seq);
@@ -851,6 +862,15 @@ static int prefill_rows(llma_ctx *c, int seq, int n_feed) {
         c->T_host[seq] += m;
     }
     return LLMA_OK;
+}
+// the same with the prompt's first token at gen_prompt[tok0]
+static int prefill_rows(llma_ctx *c, int seq, int n_feed, int tok0 = 0) {
+    int rc = sync_state(c, seq);
+    if (rc) return rc;
+    const int base = c->T_host[seq] - tok0;
+    HIP_TRY(c, hipMemcpyAsync(c->gen_counters + 4 * c->cfg.max_batch, &base, 4, hipMemcpyHostToDevice, c->st));
+    HIP_TRY(c, hipStreamSynchronize(c->st));
+    return prefill_passes(c, seq, n_feed);
 }
 
 static int ensure_cap(llma_ctx *c, int **buf, int *cap, int need);
@@ -1054,18 +1074,6 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
     hipStream_t st = c->st;
     const int ystride = max_new + 64;                       // per-sequence output / trace rows on the device
     const bool together = c->bf16 && n_seqs > 1 && n_seqs * (k + 1) > 48;      // (the prompts, see below)
-    if ((rc = ensure_cap(c, &c->gen_prompt, &c->cap_prompt, together ? total_prompt : max_prompt))) return rc;
-    if ((rc = ensure_cap(c, &c->gen_ref, &c->cap_ref, total_ref))) return rc;
-    // spans the trigger scans per sequence: enough for the longest reference, a power of two (few distinct launch shapes)
-    int max_ref = 0, spans = 1;
-    for (int b = 0; b < n_seqs; ++b) max_ref = ref_start[b + 1] - ref_start[b] > max_ref ? ref_start[b + 1] - ref_start[b] : max_ref;
-    while (spans < trigger_spans(max_ref)) spans *= 2;
-    c->gen_spans = spans;
-    if ((rc = ensure_cap(c, &c->gen_part, &c->cap_part, 2 * n_seqs * spans))) return rc;
-    if ((rc = ensure_cap(c, &c->gen_doc_offsets, &c->cap_docs, docs_start[n_seqs] + n_seqs))) return rc;
-    if ((rc = ensure_cap(c, &c->gen_y, &c->cap_y, n_seqs * ystride))) return rc;
-    if ((rc = ensure_cap(c, &c->gen_trace, &c->cap_trace, 4 * n_seqs * ystride))) return rc;
-    if (total_ref) HIP_TRY(c, hipMemcpyAsync(c->gen_ref, refs, (size_t)total_ref * 4, hipMemcpyHostToDevice, st));
     // device document lists: every sequence gets one (a sequence without reference: the single entry 0)
     std::vector<int> dof_host, dof_at(n_seqs);
     for (int b = 0; b < n_seqs; ++b) {
@@ -1074,42 +1082,71 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
         if (nd > 0) dof_host.insert(dof_host.end(), doc_offsets + docs_start[b], doc_offsets + docs_start[b] + nd + 1);
         else dof_host.push_back(0);
     }
-    HIP_TRY(c, hipMemcpyAsync(c->gen_doc_offsets, dof_host.data(), dof_host.size() * 4, hipMemcpyHostToDevice, st));
-    HIP_TRY(c, hipMemsetAsync(c->gen_counters, 0, (size_t)(4 * g.max_batch + 4) * 4, st));
-    std::vector<GenState> G(n_seqs);
-    int *const cnt_out = c->gen_counters, *const cnt_steps = c->gen_counters + g.max_batch, *const cnt_cur = c->gen_counters + 2 * g.max_batch;
-    for (int b = 0; b < n_seqs; ++b) {
-        const int nd = n_docs ? n_docs[b] : 0, rlen = ref_start[b + 1] - ref_start[b];
-        GenState &s = G[b];
-        s.y = c->gen_y + (size_t)b * ystride; s.trace = c->gen_trace + (size_t)4 * b * ystride;
-        s.n_out = cnt_out + b; s.n_steps = cnt_steps + b; s.cur = cnt_cur + 2 * b;
-        s.host_count = c->pin_counts_dev + b; s.host_stride = g.max_batch;
-        s.ref = c->gen_ref + ref_start[b]; s.doc_offsets = c->gen_doc_offsets + dof_at[b];
-        s.ref_len = rlen; s.n_docs = nd; s.n = n; s.k = k; s.max_new = max_new; s.prompt = c->gen_prompt;
-    }
-    HIP_TRY(c, hipMemcpyAsync(c->gen_dev, G.data(), sizeof(GenState) * n_seqs, hipMemcpyHostToDevice, st));
-    HIP_TRY(c, hipStreamSynchronize(st));     // the host staging buffers may go out of scope / change
-    memset(c->pin_counts, 0, (size_t)2 * g.max_batch * sizeof(int));    // (written by the accept kernels directly: not before the wait)
+    // [prompts | references | document lists] on the device
+    const size_t ref_at = ((size_t)total_prompt + 3) / 4 * 4, docs_at = ref_at + ((size_t)total_ref + 3) / 4 * 4, in_words = docs_at + dof_host.size();
+    if (in_words > 0x5fffffff) return fail(c, LLMA_E_RANGE, "llma_generate: %zu words of input", in_words);
+    if ((rc = ensure_cap(c, &c->gen_prompt, &c->cap_prompt, (int)in_words))) return rc;
+    // spans the trigger scans per sequence: enough for the longest reference, a power of two (few distinct launch shapes)
+    int max_ref = 0, spans = 1;
+    for (int b = 0; b < n_seqs; ++b) max_ref = ref_start[b + 1] - ref_start[b] > max_ref ? ref_start[b + 1] - ref_start[b] : max_ref;
+    while (spans < trigger_spans(max_ref)) spans *= 2;
+    c->gen_spans = spans;
+    if ((rc = ensure_cap(c, &c->gen_part, &c->cap_part, 2 * n_seqs * spans))) return rc;
+    if ((rc = ensure_cap(c, &c->gen_y, &c->cap_y, n_seqs * ystride))) return rc;
+    if ((rc = ensure_cap(c, &c->gen_trace, &c->cap_trace, 4 * n_seqs * ystride))) return rc;
 
-    // ---- x: reset each slot, feed prompt[0..len-2], prompt[len-1] becomes the pending token
-    // Together where the steps have more than 48 rows: those of fewer rows give every sequence the same bits as a call of its
-    // own, which its prompt in a pass of another length would not.
-    std::vector<int> T0(n_seqs);
-    if (together) HIP_TRY(c, hipMemcpyAsync(c->gen_prompt, prompts, (size_t)total_prompt * 4, hipMemcpyHostToDevice, st));
-    for (int b = 0; b < n_seqs; ++b) {
-        const int seq = seqs[b], plen = prompt_offsets[b + 1] - prompt_offsets[b];
-        const int32_t *prompt = prompts + prompt_offsets[b];
-        if (!together) HIP_TRY(c, hipMemcpyAsync(c->gen_prompt, prompt, (size_t)plen * 4, hipMemcpyHostToDevice, st));
-        c->T_host[seq] = 0;
-        c->pending_host[seq] = prompt[plen - 1];
-        c->lo_from_host[seq] = 0;
-        forget_imports(c, seq);
-        if ((rc = push_state(c, seq))) return rc;
-        if (together) continue;
-        if ((rc = prefill_rows(c, seq, plen - 1))) return rc;
-        HIP_TRY(c, hipStreamSynchronize(st));                   // gen_prompt is reused by the next sequence
+    // Everything the device has to know goes there in two copies out of pinned memory, which nothing on the device reads or writes now (every call
+    // is waited for, failed ones too), and nobody waits for them: ten pageable copies and four waits took 60 us of a call.
+    int *const cnt_out = c->gen_counters, *const cnt_steps = c->gen_counters + g.max_batch, *const cnt_cur = c->gen_counters + 2 * g.max_batch;
+    for (int b = 0; b < n_seqs; ++b) {                      // x: reset each slot; prompt[len-1] becomes the pending token
+        c->T_host[seqs[b]] = 0;
+        c->pending_host[seqs[b]] = prompts[prompt_offsets[b + 1] - 1];
+        c->lo_from_host[seqs[b]] = 0;
+        forget_imports(c, seqs[b]);
     }
-    if (together && (rc = prefill_together(c, n_seqs, seqs, prompt_offsets))) return rc;
+    {
+        int *const w = c->pin_block;
+        const size_t B = g.max_batch;
+        std::copy(c->T_host.begin(), c->T_host.end(), w);
+        std::copy(c->pending_host.begin(), c->pending_host.end(), w + B);
+        std::copy(c->lo_from_host.begin(), c->lo_from_host.end(), w + 2 * B);
+        std::copy(seqs, seqs + n_seqs, w + 3 * B);
+        std::fill(w + 3 * B + n_seqs, w + c->block_states, 0);
+        for (int b = 0; b < n_seqs; ++b) {
+            GenState s{};
+            s.y = c->gen_y + (size_t)b * ystride; s.trace = c->gen_trace + (size_t)4 * b * ystride;
+            s.n_out = cnt_out + b; s.n_steps = cnt_steps + b; s.cur = cnt_cur + 2 * b;
+            s.host_count = c->pin_counts_dev + b; s.host_stride = g.max_batch;
+            s.ref = c->gen_prompt + ref_at + ref_start[b]; s.doc_offsets = c->gen_prompt + docs_at + dof_at[b];
+            s.ref_len = ref_start[b + 1] - ref_start[b]; s.n_docs = n_docs ? n_docs[b] : 0; s.n = n; s.k = k; s.max_new = max_new; s.prompt = c->gen_prompt;
+            memcpy(w + c->block_states + sizeof(GenState) / 4 * b, &s, sizeof s);
+        }
+    }
+    memset(c->pin_counts, 0, (size_t)2 * g.max_batch * sizeof(int));
+    std::vector<int> T0(n_seqs);
+    auto prepare = [&]() -> int {
+        HIP_TRY(c, hipMemcpyAsync(c->block, c->pin_block, (c->block_states + sizeof(GenState) / 4 * n_seqs) * 4, hipMemcpyHostToDevice, st));
+        std::fill(c->stale.begin(), c->stale.end(), 0);
+        if (in_words <= GEN_STAGE_WORDS) {
+            memcpy(c->pin_stage, prompts, (size_t)total_prompt * 4);
+            if (total_ref) memcpy(c->pin_stage + ref_at, refs, (size_t)total_ref * 4);
+            memcpy(c->pin_stage + docs_at, dof_host.data(), dof_host.size() * 4);
+            HIP_TRY(c, hipMemcpyAsync(c->gen_prompt, c->pin_stage, in_words * 4, hipMemcpyHostToDevice, st));
+        } else {
+            HIP_TRY(c, hipMemcpyAsync(c->gen_prompt, prompts, (size_t)total_prompt * 4, hipMemcpyHostToDevice, st));
+            if (total_ref) HIP_TRY(c, hipMemcpyAsync(c->gen_prompt + ref_at, refs, (size_t)total_ref * 4, hipMemcpyHostToDevice, st));
+            HIP_TRY(c, hipMemcpyAsync(c->gen_prompt + docs_at, dof_host.data(), dof_host.size() * 4, hipMemcpyHostToDevice, st));
+            HIP_TRY(c, hipStreamSynchronize(st));           // (the caller's memory)
+        }
+        // prompt[0 .. len-2] of every sequence.  Together where the steps have more than 48 rows: those of fewer rows give every
+        // sequence the same bits as a call of its own, which its prompt in a pass of another length would not.
+        if (n_seqs == 1) return prefill_passes(c, seqs[0], total_prompt - 1);
+        if (together) return prefill_together(c, n_seqs, seqs, prompt_offsets);
+        for (int b = 0; b < n_seqs; ++b)
+            if (int r = prefill_rows(c, seqs[b], prompt_offsets[b + 1] - prompt_offsets[b] - 1, prompt_offsets[b])) return r;
+        return LLMA_OK;
+    };
+    if ((rc = prepare())) return drained(c, rc);
     for (int b = 0; b < n_seqs; ++b) T0[b] = c->T_host[seqs[b]];
 
     // ---- the decoding loop: trigger -> rows -> forward -> accept, all on the device, all sequences of
@@ -1118,7 +1155,10 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
     //      the output counts back to know when to stop, and it does so one step late: step s+1 is
     //      already enqueued when the counts of step s are awaited, so the GPU never waits for the host.
     const int m = k + 1;
-    HIP_TRY(c, hipMemcpyAsync(c->s.batch_slots, seqs, (size_t)n_seqs * 4, hipMemcpyHostToDevice, st));
+    if (n_seqs > 1) {                                       // (prompt passes leave a slot of their own there; one sequence's is the same)
+        const hipError_t e = hipMemcpyAsync(c->s.batch_slots, c->pin_block + 3 * g.max_batch, (size_t)n_seqs * 4, hipMemcpyHostToDevice, st);
+        if (e != hipSuccess) return drained(c, fail(c, LLMA_E_HIP, "llma_generate: %s", hipGetErrorString(e)));
+    }
     std::vector<int> produced(n_seqs, 0);
     int steps = 0, enq = 0;
     auto enqueue = [&]() -> int {
@@ -1150,20 +1190,29 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
         return r;
     };
     if ((rc = decode())) return drained(c, rc);
-    HIP_TRY(c, hipStreamSynchronize(st));                       // drains the step that ran ahead
-    std::vector<int> nst(n_seqs);
-    HIP_TRY(c, hipMemcpyAsync(nst.data(), cnt_steps, (size_t)n_seqs * 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipStreamSynchronize(st));
+    // results: the counters and pending tokens in one copy, tokens and traces in one each, one wait (which also drains the step that ran ahead)
+    const size_t y_words = (size_t)n_seqs * ystride;
+    const bool staged = 5 * y_words <= GEN_STAGE_WORDS;
+    std::vector<int> pageable(staged ? 0 : 5 * y_words);
+    int *const y_host = staged ? c->pin_stage : pageable.data(), *const trace_host = y_host + y_words;
+    auto fetch = [&]() -> int {
+        HIP_TRY(c, hipMemcpyAsync(c->pin_block, c->block, c->block_states * 4, hipMemcpyDeviceToHost, st));
+        HIP_TRY(c, hipMemcpyAsync(y_host, c->gen_y, y_words * 4, hipMemcpyDeviceToHost, st));
+        if (trace) HIP_TRY(c, hipMemcpyAsync(trace_host, c->gen_trace, 4 * y_words * 4, hipMemcpyDeviceToHost, st));
+        HIP_TRY(c, hipStreamSynchronize(st));
+        return LLMA_OK;
+    };
+    if ((rc = fetch())) return drained(c, rc);
     for (int b = 0; b < n_seqs; ++b) {
-        const int seq = seqs[b];
+        const int seq = seqs[b], took = c->pin_block[4 * g.max_batch + g.max_batch + b];
+        if (took < 1 || took > max_new) return fail(c, LLMA_E_HIP, "llma_generate: device step count of sequence %d is %d", b, took);
         c->T_host[seq] = T0[b] + produced[b];
-        HIP_TRY(c, hipMemcpyAsync(out_tokens + (size_t)b * max_new, c->gen_y + (size_t)b * ystride, (size_t)max_new * 4, hipMemcpyDeviceToHost, st));
-        if (trace) HIP_TRY(c, hipMemcpyAsync(trace + (size_t)b * max_new, c->gen_trace + (size_t)4 * b * ystride, (size_t)nst[b] * sizeof(llma_step_rec), hipMemcpyDeviceToHost, st));
-        HIP_TRY(c, hipMemcpyAsync(&c->pending_host[seq], c->s.pending + seq, 4, hipMemcpyDeviceToHost, st));
+        c->pending_host[seq] = c->pin_block[g.max_batch + seq];
+        memcpy(out_tokens + (size_t)b * max_new, y_host + (size_t)b * ystride, (size_t)max_new * 4);
+        if (trace) memcpy(trace + (size_t)b * max_new, trace_host + (size_t)4 * b * ystride, (size_t)took * sizeof(llma_step_rec));
         n_out[b] = produced[b];
-        if (n_steps) n_steps[b] = nst[b];
+        if (n_steps) n_steps[b] = took;
     }
-    HIP_TRY(c, hipStreamSynchronize(st));
     return LLMA_OK;
 }
 
