@@ -1384,6 +1384,40 @@ GemmPlan make_gemm_plan(int N, int K, int tiles_per_task) {
 // sequence length) arrives.
 __device__ __forceinline__ void loads_stay_above() { asm volatile("" ::: "memory"); }
 
+// ---- softmax arithmetic of the attention kernels.  Scores stay as they come out of the products; row maxima (and everything that is
+// exchanged about them) are powers of two, so a probability is one fused multiply-add and one exp2.
+#define LOG2E 1.44269504088896341f
+// e^(scale s) / 2^m; m = -inf (nothing visible so far): the score is -inf too, and the result zero
+__device__ __forceinline__ float attn_exp(float s, float to_log2, float m) {
+    return __builtin_amdgcn_exp2f(fmaf(s, to_log2, m == LLMA_NEG_INF ? 0.f : -m));
+}
+// a lane's scores of eight positions, first .. first + 3 and first + 16 .. first + 19, and of its row: the largest over the lanes of the row
+// (32 positions).  masked (uniform): positions past the row's own are taken out first
+__device__ __forceinline__ float attn_mask_max(float (&sv)[8], bool masked, int first, int row_pos) {
+    if (masked)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sv[i] = first + (i >> 2) * 16 + (i & 3) > row_pos ? LLMA_NEG_INF : sv[i];
+    float mx = sv[0];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sv[i]);
+    mx = fmaxf(mx, lane_xor<16>(mx));
+    return fmaxf(mx, lane_xor<32>(mx));
+}
+// Running (reference, sum, O) of a row: the reference moves only when a maximum passes it by 2^ATTN_REBASE (sums of terms up to that lose
+// nothing in fp32), so after the first positions the accumulators are hardly ever rescaled.  A row's decision is its own: rows beside it
+// that move make it multiply by one.
+#define ATTN_REBASE 8.f
+template <int DT>
+__device__ __forceinline__ void attn_rebase(float mx, float &m, float &l, f32x4 (&o)[DT]) {
+    if (__ballot(mx > m + ATTN_REBASE) == 0ull) return;             // uniform
+    const float m_new = mx > m + ATTN_REBASE ? mx : m;
+    const float alpha = m_new == LLMA_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+    l *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt] *= alpha;
+    m = m_new;
+}
+
 // =============================================================================================
 // causal attention of m <= 16*NTQ query rows of one sequence over its KV cache
 // =============================================================================================
@@ -1467,6 +1501,7 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
     const int m_blk = (m_live - j0 < RQ) ? m_live - j0 : RQ;   // live rows of this block
     const int kv_len = T + j0 + m_blk;                  // positions the block's last row can see
 
+    const float to_log2 = a.scale * LOG2E;              // scores stay as the products leave them, maxima are powers of two (see attn_exp)
     float mrow[NTQ], lrow[NTQ];
     f32x4 o[OQ][DT];
     // every wave publishes (max, sum, O) of a row tile for the merge below
@@ -1482,6 +1517,7 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
     const int chunk0 = c * ATTN_CHUNK, key0 = chunk0 + wave * 32;
     if (chunk0 >= kv_len) return;                   // uniform for the workgroup
     const bool active = key0 < kv_len;              // uniform for the wave
+    const bool masked = key0 + 31 > T + j0;         // uniform: some row may not see all of these positions
 #pragma unroll
     for (int q = 0; q < NTQ; ++q) {
         mrow[q] = LLMA_NEG_INF;
@@ -1515,24 +1551,17 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
                         if (KVS) acc = mfma16x16x32(lo8_operand(kb[t][s]), qh[s], acc);
                     }
 #pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        const int key = key0 + t * 16 + 4 * g + r4;
-                        float v = acc[r4] * a.scale;
-                        v = (key > rpos) ? LLMA_NEG_INF : v;
-                        sv[t * 4 + r4] = v;
-                        mx = fmaxf(mx, v);
-                    }
+                    for (int r4 = 0; r4 < 4; ++r4) sv[t * 4 + r4] = acc[r4];
                 }
             }
             if (q < NTQ - 1) fetch_q(q + 1);
             if (!dead) {
-                mx = fmaxf(mx, lane_xor<16>(mx));
-                mx = fmaxf(mx, lane_xor<32>(mx));
+                mx = attn_mask_max(sv, masked, key0 + 4 * g, rpos) * to_log2;
                 float psum = 0.f;
                 float p[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    p[i] = (mx == LLMA_NEG_INF) ? 0.f : __expf(sv[i] - mx);
+                    p[i] = attn_exp(sv[i], to_log2, mx);
                     psum += p[i];
                 }
                 lrow[q] = psum;
@@ -1574,7 +1603,7 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const float mw = sm[w][j];
-            const float sc = (mw == LLMA_NEG_INF) ? 0.f : __expf(mw - M);
+            const float sc = (mw == LLMA_NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(mw - M);
             acc += *(const f32x4 *)&so[w][j][d4 * 4] * sc;
         }
         *(f32x4 *)(a.po + (pbase + j) * DH + d4 * 4) = acc;
@@ -1586,7 +1615,7 @@ __device__ __forceinline__ void attn_chunk_body(const AttnArgs &a, float (&sm)[4
         float L = 0.f;
         for (int w = 0; w < 4; ++w) {
             float mw = sm[w][j];
-            L += (mw == LLMA_NEG_INF) ? 0.f : sl[w][j] * __expf(mw - M);
+            L += (mw == LLMA_NEG_INF) ? 0.f : sl[w][j] * __builtin_amdgcn_exp2f(mw - M);
         }
         a.pm[pbase + j] = M;
         a.pl[pbase + j] = L;
@@ -1652,6 +1681,7 @@ __global__ __launch_bounds__(256, 2) void attn_walk_bf16_kernel(AttnArgs a) {
     const bf16_t *kh = (const bf16_t *)a.Khi + head_base; const uint8_t *kl = (const uint8_t *)a.Klo + head_base;
     const bf16_t *vh = (const bf16_t *)a.Vhi + head_base; const uint8_t *vl = (const uint8_t *)a.Vlo + head_base;
 
+    const float to_log2 = a.scale * LOG2E;
     f32x4 acc_run[OWN];
     float M_run[OWN];
 #pragma unroll
@@ -1661,6 +1691,7 @@ __global__ __launch_bounds__(256, 2) void attn_walk_bf16_kernel(AttnArgs a) {
         const int key0 = c * ATTN_CHUNK + wave * 32;
         const bool active = key0 < kv_len;                           // uniform for the wave
         const bool use_lo = KVS && c >= c_lo;                        // uniform for the workgroup
+        const bool masked = key0 + 31 > T + j0;                      // uniform: some row may not see all of these positions
         u32x4 ka[2][KSTEPS], va[DT];
         u32x2 kb[2][KSTEPS], vb[DT];                     // lo planes: one byte per element
         if (active) {
@@ -1698,7 +1729,6 @@ __global__ __launch_bounds__(256, 2) void attn_walk_bf16_kernel(AttnArgs a) {
                     ql[s] = *(const u32x4 *)((const bf16_t *)a.Qlo + off);
                 }
                 float sv[8];
-                float mx = LLMA_NEG_INF;
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -1709,20 +1739,13 @@ __global__ __launch_bounds__(256, 2) void attn_walk_bf16_kernel(AttnArgs a) {
                         if (KVS && use_lo) acc = mfma16x16x32(lo8_operand(kb[t][s]), qh[s], acc);
                     }
 #pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        const int key = key0 + t * 16 + 4 * g + r4;
-                        float v = acc[r4] * a.scale;
-                        v = (key > rpos) ? LLMA_NEG_INF : v;
-                        sv[t * 4 + r4] = v;
-                        mx = fmaxf(mx, v);
-                    }
+                    for (int r4 = 0; r4 < 4; ++r4) sv[t * 4 + r4] = acc[r4];
                 }
-                mx = fmaxf(mx, lane_xor<16>(mx));
-                mx = fmaxf(mx, lane_xor<32>(mx));
+                const float mx = attn_mask_max(sv, masked, key0 + 4 * g, rpos) * to_log2;
                 float p[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    p[i] = (mx == LLMA_NEG_INF) ? 0.f : __expf(sv[i] - mx);
+                    p[i] = attn_exp(sv[i], to_log2, mx);
                     lsum += p[i];
                 }
                 mrow = mx;
@@ -1761,12 +1784,12 @@ __global__ __launch_bounds__(256, 2) void attn_walk_bf16_kernel(AttnArgs a) {
 #pragma unroll
                     for (int w = 0; w < 4; ++w) {
                         const float mw = sm[w][j];
-                        const float sc = (mw == LLMA_NEG_INF) ? 0.f : __expf(mw - Mc);
+                        const float sc = (mw == LLMA_NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(mw - Mc);
                         accc += *(const f32x4 *)&so[w][j][d4 * 4] * sc;
                     }
                     const float Mn = fmaxf(M_run[i], Mc);
-                    const float s_run = (M_run[i] == LLMA_NEG_INF) ? 0.f : __expf(M_run[i] - Mn);
-                    acc_run[i] = acc_run[i] * s_run + accc * __expf(Mc - Mn);
+                    const float s_run = (M_run[i] == LLMA_NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(M_run[i] - Mn);
+                    acc_run[i] = acc_run[i] * s_run + accc * __builtin_amdgcn_exp2f(Mc - Mn);
                     M_run[i] = Mn;
                 }
             }
@@ -1779,11 +1802,11 @@ __global__ __launch_bounds__(256, 2) void attn_walk_bf16_kernel(AttnArgs a) {
                 float Lc = 0.f;
                 for (int w = 0; w < 4; ++w) {
                     const float mw = sm[w][j];
-                    Lc += (mw == LLMA_NEG_INF) ? 0.f : sl[w][j] * __expf(mw - Mc);
+                    Lc += (mw == LLMA_NEG_INF) ? 0.f : sl[w][j] * __builtin_amdgcn_exp2f(mw - Mc);
                 }
                 const float Mn = fmaxf(M_row, Mc);
-                const float s_run = (M_row == LLMA_NEG_INF) ? 0.f : __expf(M_row - Mn);
-                L_row = L_row * s_run + Lc * __expf(Mc - Mn);
+                const float s_run = (M_row == LLMA_NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(M_row - Mn);
+                L_row = L_row * s_run + Lc * __builtin_amdgcn_exp2f(Mc - Mn);
                 M_row = Mn;
             }
         }
@@ -1866,8 +1889,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
     }
     if (QLDS) __syncthreads();
+    const float to_log2 = a.scale * LOG2E;
     f32x4 o[NTQ][DT];
-    float Mw[NTQ], Lw[NTQ];                                          // row n's running max; the lane's share of its running sum
+    float Mw[NTQ], Lw[NTQ];                                          // row n's reference (see ATTN_REBASE); the lane's share of its running sum
 #pragma unroll
     for (int q = 0; q < NTQ; ++q) {
         Mw[q] = LLMA_NEG_INF; Lw[q] = 0.f;
@@ -1880,6 +1904,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         constexpr bool LO = decltype(lo_tag)::value;
         const int key0 = c * ATTN_CHUNK + wave * 32;
         if (key0 >= kv_len) return;                                  // uniform for the wave: no row sees these positions
+        const bool masked = key0 + 31 > T + j0;                      // uniform: some row may not see all of them
         u32x4 ka[2][KSTEPS], va[DT];
         u32x2 kb[2][KSTEPS], vb[DT];                     // lo planes: one byte per element
 #pragma unroll
@@ -1901,7 +1926,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int q = 0; q < NTQ; ++q) {
             if (j0 + q * 16 >= m) continue;                          // a row tile past the block's rows (uniform)
             float sv[8];
-            float mx = LLMA_NEG_INF;
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -1914,26 +1938,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     if (LO) acc = mfma16x16x32(lo8_operand(kb[t][s]), q_hi, acc);
                 }
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const int key = key0 + t * 16 + 4 * g + r4;
-                    float v = acc[r4] * a.scale;
-                    v = (key > rpos[q]) ? LLMA_NEG_INF : v;
-                    sv[t * 4 + r4] = v;
-                    mx = fmaxf(mx, v);
-                }
+                for (int r4 = 0; r4 < 4; ++r4) sv[t * 4 + r4] = acc[r4];
             }
-            mx = fmaxf(mx, lane_xor<16>(mx));
-            mx = fmaxf(mx, lane_xor<32>(mx));
-            const float Mn = fmaxf(Mw[q], mx);
-            const float s_old = (Mw[q] == LLMA_NEG_INF) ? 0.f : __expf(Mw[q] - Mn);     // (Mn = -inf only if both are)
+            attn_rebase(attn_mask_max(sv, masked, key0 + 4 * g, rpos[q]) * to_log2, Mw[q], Lw[q], o[q]);
             float p[8], lsum = 0.f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                p[i] = (Mn == LLMA_NEG_INF) ? 0.f : __expf(sv[i] - Mn);
+                p[i] = attn_exp(sv[i], to_log2, Mw[q]);
                 lsum += p[i];
             }
-            Lw[q] = Lw[q] * s_old + lsum;
-            Mw[q] = Mn;
+            Lw[q] += lsum;
             u32x2 h0, l0, h1, l1;
             split4(p, h0, l0);
             split4(p + 4, h1, l1);
@@ -1941,7 +1955,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const u32x4 pl = (u32x4){l0[0], l0[1], l1[0], l1[1]};
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
-                f32x4 od = o[q][dt] * s_old;
+                f32x4 od = o[q][dt];
                 od = mfma16x16x32(va[dt], ph, od);
                 od = mfma16x16x32(va[dt], pl, od);
                 if (LO) od = mfma16x16x32(lo8_operand(vb[dt]), ph, od);
@@ -1978,7 +1992,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
                 const float mw = sm[w][j];
-                const float sc = (mw == LLMA_NEG_INF) ? 0.f : __expf(mw - Mc);
+                const float sc = (mw == LLMA_NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(mw - Mc);
                 accc += *(const f32x4 *)&so[w][j][d4 * 4] * sc;
             }
             *(f32x4 *)(a.po + (pbase + j) * DH + d4 * 4) = accc;
@@ -1990,14 +2004,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int w = 0; w < 4; ++w) Mc = fmaxf(Mc, sm[w][j]);
         for (int w = 0; w < 4; ++w) {
             const float mw = sm[w][j];
-            Lc += (mw == LLMA_NEG_INF) ? 0.f : sl[w][j] * __expf(mw - Mc);
+            Lc += (mw == LLMA_NEG_INF) ? 0.f : sl[w][j] * __builtin_amdgcn_exp2f(mw - Mc);
         }
         a.pm[pbase + j] = Mc;
         a.pl[pbase + j] = Lc;
     }
 }
 
-// merges the chunk partials of one (row, head): out = sum_c e^{m_c - M} O_c / sum_c e^{m_c - M} l_c,
+// merges the chunk partials of one (row, head): out = sum_c 2^{m_c - M} O_c / sum_c 2^{m_c - M} l_c,
 // over the chunks that contain positions <= the row's own; writes hi/lo tiled planes.  A wave per (row, head): groups of DH / 4
 // lanes, four output features per lane; group i takes chunks i, i + PARTS, .. in order, up to sixteen of them in flight, and the groups
 // meet at the end.  Which chunk goes where is a function of its position only.  Bound by the round trips to the partials: with one group per
@@ -2046,7 +2060,7 @@ __device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int rq, int 
             mv[u] = c0 + u * PARTS + part < nc ? mv[u] : LLMA_NEG_INF;
             Mb = fmaxf(Mb, mv[u]);
         }
-        const float rs = (M == LLMA_NEG_INF) ? 0.f : __expf(M - Mb);
+        const float rs = (M == LLMA_NEG_INF) ? 0.f : __builtin_amdgcn_exp2f(M - Mb);
         L *= rs;
         acc *= rs;
         M = Mb;
@@ -2054,7 +2068,7 @@ __device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int rq, int 
         for (int u = 0; u < CB; ++u) {
             if (c0 + u * PARTS >= nc) break;           // uniform
             const bool mine = mv[u] != LLMA_NEG_INF;   // (what a chunk past the end holds may be anything)
-            const float w = __expf(mv[u] - M);
+            const float w = __builtin_amdgcn_exp2f(mv[u] - M);
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] = mine ? fmaf(ov[u][e], w, acc[e]) : acc[e];
             L = mine ? fmaf(w, lv[u], L) : L;
@@ -2063,7 +2077,7 @@ __device__ __forceinline__ void attn_combine_row(const AttnArgs &a, int rq, int 
     // the groups meet (every lane adds its partner's part to its own; the first group's lanes write)
     const auto meet = [&](float m1, float l1, const f32x4 &a1) {
         const float Mn = fmaxf(M, m1);
-        const float s0 = M == LLMA_NEG_INF ? 0.f : __expf(M - Mn), s1 = m1 == LLMA_NEG_INF ? 0.f : __expf(m1 - Mn);
+        const float s0 = M == LLMA_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(M - Mn), s1 = m1 == LLMA_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(m1 - Mn);
         L = L * s0 + l1 * s1;
         acc = acc * s0 + a1 * s1;
         M = Mn;
@@ -2170,11 +2184,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             if (KVS) vb[dt] = *(const u32x2 *)(vl + off);
         }
     };
-    // Scores are kept as they come out of the products and maxima in powers of two: e^(scale s - max) is one fused multiply-add and one exp2.
-    // A row's reference moves only when a maximum passes it by 2^REBASE (sums of terms up to 2^REBASE lose nothing in fp32): after the
-    // first chunks the accumulators are hardly ever rescaled.
-    constexpr float REBASE = 8.f;
-    const float to_log2 = a.scale * 1.44269504088896341f;
+    const float to_log2 = a.scale * LOG2E;
     float mrow[NTQ], lrow[NTQ];
     f32x4 o[NTQ][DT];
 #pragma unroll
@@ -2221,29 +2231,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const bool masked = key0 + 31 > T + j0;         // uniform: a row may not see all of these positions
 #pragma unroll
         for (int q = 0; q < NTQ; ++q) {
-            if (masked)
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (key0 + (i >> 2) * 16 + 4 * g + (i & 3) > rpos[q]) sv[q][i] = LLMA_NEG_INF;
-            float mx = sv[q][0];
-#pragma unroll
-            for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sv[q][i]);
-            mx = fmaxf(mx, lane_xor<16>(mx));
-            mx = fmaxf(mx, lane_xor<32>(mx)) * to_log2;
-            if (__ballot(mx > mrow[q] + REBASE) != 0ull) {          // uniform
-                const float m_new = mx > mrow[q] + REBASE ? mx : mrow[q];
-                const float alpha = m_new == LLMA_NEG_INF ? 0.f : __builtin_amdgcn_exp2f(mrow[q] - m_new);
-                lrow[q] *= alpha;
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) o[q][dt] *= alpha;
-                mrow[q] = m_new;
-            }
-            const float base = mrow[q] == LLMA_NEG_INF ? 0.f : -mrow[q];         // (nothing visible so far: every term is zero)
+            attn_rebase(attn_mask_max(sv[q], masked, key0 + 4 * g, rpos[q]) * to_log2, mrow[q], lrow[q], o[q]);
             float psum = 0.f;
             float p[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                p[i] = __builtin_amdgcn_exp2f(fmaf(sv[q][i], to_log2, base));
+                p[i] = attn_exp(sv[q][i], to_log2, mrow[q]);
                 psum += p[i];
             }
             lrow[q] += psum;                            // this lane's 8 keys; lanes are added at the end
