@@ -723,7 +723,8 @@ __host__ __device__ __forceinline__ RstdShare rstd_share(int tasks, int nw, int 
 
 #define PANEL_KC 2          // k-steps per LDS chunk
 #define PANEL_TURN 8        // k-steps of weights in registers; the K axis is cut into ranges of whole turns of this ring
-#define PANEL_RT_MAX 10     // row tiles per workgroup: 4 .. 10
+#define PANEL_RT_MAX 10     // row tiles per workgroup: 4 .. 10,
+#define PANEL_RT_SPLIT 12   // and up to 12 where the K axis is split, six waves take 12 weight tiles, and one row block then holds all rows
 #define PANEL_STAGES 3      // chunks of activations in LDS: one in use, the others on their way
 #ifndef PN_TRACE
 #define PN_TRACE(slot, chunk)   // (timeline probe of the one-off microbenchmarks; nothing in the library build)
@@ -1183,7 +1184,9 @@ static GemmPlan raw_plan(const GemmPlan &p) {
 // kernel, 5 us, and its partial sums once written and once read at 4 TB/s.
 // So many workgroups as there are compute units is what counts: 12 weight tiles instead of 16 for gate/up of 7B (1376 tiles in two ranges)
 // 48.5 -> 43.8 us at 54 rows, 61.3 -> 57.6 at 144, for QKV (768 in four) 32.5 -> 30.3 and 41.8 -> 40.2; 10 for down of 13B (320 in eight)
-// 39.4 -> 34.2 at 54; 8 for O and down of 7B: 17.0 -> 15.9, 33.6 -> 27.4.  189 prompt rows: splits of 2 .. 8, 2.01 -> 0.98 ms for
+// 39.4 -> 34.2 at 54; 8 for O and down of 7B: 17.0 -> 15.9, 33.6 -> 27.4.  11 and 12 row tiles where one row block then holds all rows and
+// the weights are read once: gate/up at 176 / 189 rows 76.5 / 78.3 (unsplit, two row blocks) -> 65.3 / 69.0 (two blocks of 11 or 12 at 340 .. 376: 108 -> 119 .. 127, not taken;
+// nor five or seven waves of that height, nor QKV of 13B in three ranges: 1 .. 5 % slower, hence the surcharge).  189 prompt rows: splits of 2 .. 8, 2.01 -> 0.98 ms for
 // four layers; from 1535 rows on nothing is split.
 struct PanelCut { int rt, nw, at; double us; };
 static PanelCut panel_cut(const GemmPlan &p, int rows, int ns) {
@@ -1192,10 +1195,12 @@ static PanelCut panel_cut(const GemmPlan &p, int rows, int ns) {
     PanelCut best{0, 0, 0, 0.0};
     auto consider = [&](int nw, int at) {
         const int pt = nw * at;
-        for (int rt = 4; rt <= (at == 1 ? 5 : PANEL_RT_MAX); ++rt) {
+        for (int rt = 4; rt <= (at == 1 ? 5 : (ns > 1 && nw == 6 && row_tiles <= PANEL_RT_SPLIT ? PANEL_RT_SPLIT : PANEL_RT_MAX)); ++rt) {
+            const bool tall = rt > PANEL_RT_MAX;
+            if (tall && rt < row_tiles) continue;
             const long groups = (long)panel_feature_blocks(q, pt) * ((row_tiles + rt - 1) / rt) * ns, rounds = (groups + cu_count() - 1) / cu_count();
             const double in = (pt + 2 * rt) / 44.0, multiply = 0.0056 * pt * rt;
-            const double us = (double)rounds * (5.0 + (double)((turns + ns - 1) / ns) * PANEL_TURN * (in > multiply ? in : multiply));
+            const double us = (tall ? 1.06 : 1.0) * (double)rounds * (5.0 + (double)((turns + ns - 1) / ns) * PANEL_TURN * (in > multiply ? in : multiply));
             if (best.rt == 0 || us <= best.us) best = PanelCut{rt, nw, at, us};        // (ties: fewer, taller row blocks stream the weights less often)
         }
     };
@@ -1240,8 +1245,12 @@ static void launch_panel_rt(int rt, const GemmArgs &a, hipStream_t st) {
             case 7: launch_panel_cfg<7, EPI, AT, NW>(a, st); return;
             case 8: launch_panel_cfg<8, EPI, AT, NW>(a, st); return;
             case 9: launch_panel_cfg<9, EPI, AT, NW>(a, st); return;
-            default: launch_panel_cfg<10, EPI, AT, NW>(a, st); return;
+            case 10: launch_panel_cfg<10, EPI, AT, NW>(a, st); return;
         }
+    if constexpr (AT > 1 && NW == 6 && EPI == EPI_RAW) {
+        if (rt == 11) launch_panel_cfg<11, EPI, AT, NW>(a, st);
+        else launch_panel_cfg<12, EPI, AT, NW>(a, st);
+    }
 }
 // Which passes without a split take the block GEMM, and in which height (0: the panel GEMM).  Both are priced alike: a launch's start and end, and its
 // rounds of workgroups, half of a last round's empty places counted (the card's clock rises while compute units idle), times what a
