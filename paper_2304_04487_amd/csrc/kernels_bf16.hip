@@ -1005,6 +1005,18 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
 // tile behind the tile's last product.  The sums are added in the same order as the panel GEMM's: k-step after k-step, hi then lo.
 // ---------------------------------------------------------------------------------------------
 #define BLOCK_STAGES 3
+// The blocks of a k-step: its 16 weight tiles (gate/up: four gates, four ups per wave group), then the row tiles of the activations' hi plane and of the
+// lo plane.  Which of the workgroup's n_tasks tiles (pairs) or n_rt row tiles a block holds: places past the last one take the last weight tile's and the
+// first row tile's operands, whose sums are not stored.  The tile goes into the load's scalar offset, which a descriptor's size need not
+// bound: only tiles that exist may be asked for.
+__host__ __device__ __forceinline__ int block_weight_tile(int q, int tiles_per_task, int n_tasks) {
+    const int tile = tiles_per_task == 2 ? (q >> 3) * 4 + (q & 3) : q;
+    return tile < n_tasks ? tile : n_tasks - 1;
+}
+__host__ __device__ __forceinline__ int block_row_tile(int x, int rt, int n_rt) {
+    const int t = x < rt ? x : x - rt;
+    return t < n_rt ? t : 0;
+}
 template <int RT, int EPI>
 __global__ __launch_bounds__(512, 2) void gemm_block_bf16(GemmArgs a0) {
     constexpr int TILES = (EPI == EPI_SWIGLU) ? 2 : 1, NW = 8, FT = 8, RW = RT / 4, PAIRS = 16 / TILES;
@@ -1022,25 +1034,22 @@ __global__ __launch_bounds__(512, 2) void gemm_block_bf16(GemmArgs a0) {
     const int rt0 = rb * RT;
     const int n_rt_total = (a0.rows + 15) / 16, n_rt = n_rt_total - rt0 < RT ? n_rt_total - rt0 : RT;
 
-    // Descriptors: the block's weight tiles (gate/up: its gate tiles and its up tiles), its part of the two activation planes.  Tiles past the
-    // last one and row tiles past the end lie outside: zeros.
+    // Descriptors: the block's weight tiles (gate/up: its gate tiles and its up tiles), its part of the two activation planes.
     const int n_tasks = p.tasks - fb * PAIRS < PAIRS ? p.tasks - fb * PAIRS : PAIRS;
     const unsigned w_bytes = (unsigned)n_tasks * (unsigned)KSp * 1024u, x_bytes = (unsigned)n_rt * (unsigned)KSp * 1024u;
     const char *const w0 = (const char *)a0.W + (size_t)fb * PAIRS * KSp * 1024;
     const rsrc_t wg = buffer_of(w0, w_bytes), wu = buffer_of(w0 + (TILES == 2 ? (size_t)p.tasks * KSp * 1024 : 0), w_bytes);
     const rsrc_t xh = buffer_of((const char *)a0.Xhi + (size_t)rt0 * KSp * 1024, x_bytes), xl = buffer_of((const char *)a0.Xlo + (size_t)rt0 * KSp * 1024, x_bytes);
     const unsigned w_lane = (unsigned)lane * 16u, x_lane = (unsigned)xtile_piece(lane, true) * 16u;
-    // block q of a k-step: weight tile q (gate/up: tiles of wave group g in the order four gates, four ups), or piece q - 16 of the activations
-    auto fetch = [&](int k, int stage, int j) {
+    auto fetch = [&](int k, int stage, int j) {                              // block q of a k-step
         const int q = j * NW + wave;
         u32x4 *const to = xs + (stage * BLOCKS + q) * 64;
-        const unsigned at = (unsigned)(k < KSp ? k : KSp - 1) * 1024u;       // (requests past the end are unused)
+        const unsigned at = (unsigned)(k < KSp ? k : KSp - 1) * 1024u;       // (requests past the end of K are unused)
         if (j < 16 / NW) {                                                   // (constant after unrolling)
-            const int tile = TILES == 2 ? (q >> 3) * 4 + (q & 3) : q;
-            load_to_lds(TILES == 2 && (q & 4) ? wu : wg, w_lane, (unsigned)(tile * KSp) * 1024u + at, to);
+            load_to_lds(TILES == 2 && (q & 4) ? wu : wg, w_lane, (unsigned)(block_weight_tile(q, TILES, n_tasks) * KSp) * 1024u + at, to);
         } else {
-            const int x = q - 16, t = x < RT ? x : x - RT;
-            load_to_lds(x < RT ? xh : xl, x_lane, (unsigned)(t * KSp) * 1024u + at, to);
+            const int x = q - 16;
+            load_to_lds(x < RT ? xh : xl, x_lane, (unsigned)(block_row_tile(x, RT, n_rt) * KSp) * 1024u + at, to);
         }
     };
     f32x4 acc[FT][RW];

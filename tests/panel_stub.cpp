@@ -40,3 +40,21 @@ extern "C" int stub_rows_without_rstd(int N, int K, int tiles_per_task, int rows
     for (char d : done) missing += !d;
     return missing;
 }
+
+// a prompt pass of `rows` rows: height of the block GEMM's row blocks for this matrix (0: it runs in the panel GEMM), and into *outside the tiles that its
+// workgroups ask for and that the matrix or the pass does not have
+extern "C" int stub_block_tiles_outside(int N, int K, int tiles_per_task, int rows, int *outside) {
+    const GemmPlan p = make_gemm_plan(N, K, tiles_per_task);
+    *outside = 0;
+    if (panel_prompt_split(p, rows) > 1) return 0;
+    const int rt = block_height(p, rows, panel_cut(p, rows, 1));
+    if (rt == 0) return 0;
+    const int pairs = 16 / tiles_per_task, row_tiles = (rows + 15) / 16;
+    for (int task0 = 0; task0 < p.tasks; task0 += pairs)
+        for (int rt0 = 0; rt0 < row_tiles; rt0 += rt)
+            for (int q = 0; q < 16 + 2 * rt; ++q) {
+                const int n_tasks = p.tasks - task0 < pairs ? p.tasks - task0 : pairs, n_rt = row_tiles - rt0 < rt ? row_tiles - rt0 : rt;
+                *outside += q < 16 ? task0 + block_weight_tile(q, tiles_per_task, n_tasks) >= p.tasks : rt0 + block_row_tile(q - 16, rt, n_rt) >= row_tiles;
+            }
+    return rt;
+}

@@ -48,3 +48,22 @@ def test_every_row_has_its_rstd(library, units):
                     split += missing >= 0
                     assert missing <= 0, (units, shape, missing)
     assert split > 1000
+
+
+SHAPES = [(d, f) for d, f in ((512, 1408), (4096, 11008), (5120, 13824), (4096, 11088), (1040 * 2, 5632))]
+
+
+@pytest.mark.parametrize("units", [256, 128, 64, 32])
+def test_block_gemm_reads_tiles_that_exist(library, units):
+    """every weight and row tile that the block GEMM's workgroups fetch belongs to the matrix and to the pass: ragged last feature blocks and
+    last row blocks of QKV, O, gate/up and down"""
+    lib = library(units)
+    taken, outside = {12: 0, 16: 0}, ctypes.c_int()
+    for d, f in SHAPES:
+        for rows in range(49, 2049, 13):
+            for shape in ((3 * d, d, 1), (d, d, 1), (f, d, 2), (d, f, 1)):
+                rt = lib.stub_block_tiles_outside(*shape, rows, ctypes.byref(outside))
+                assert outside.value == 0, (units, shape, rows, rt, outside.value)
+                if rt:
+                    taken[rt] += 1
+    assert min(taken.values()) > 50
