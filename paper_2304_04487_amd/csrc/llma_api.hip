@@ -69,7 +69,8 @@ struct llma_ctx {
     void *xhi = nullptr, *xlo = nullptr, *q = nullptr, *q_lo = nullptr, *att_hi = nullptr, *att_lo = nullptr, *act_hi = nullptr, *act_lo = nullptr;
     float *po = nullptr, *pm = nullptr, *pl = nullptr;
     int *gen_segs = nullptr;           // PromptSeg[] of the pass over several sequences' prompts
-    int cap_segs = 0, n_segs = 0;      // n_segs: set while such a pass is enqueued, else 0
+    size_t cap_segs = 0;
+    int n_segs = 0;                    // set while such a pass is enqueued, else 0
     const int *rows_live = nullptr;    // set per step: device count of live rows - 1 (generation, one sequence) or null
     float *part = nullptr;             // partial sums of launches that cut K over workgroups (contexts whose steps or passes can exceed 16 rows)
     int nc_max = 0;
@@ -92,7 +93,7 @@ struct llma_ctx {
     // sends them in one copy; pin_block: pinned memory of the same layout.  pin_stage: a generation's inputs and results on their way
     int *block = nullptr, *pin_block = nullptr, *pin_stage = nullptr;
     size_t block_words = 0, block_states = 0;     // all of it; the words before gen_dev
-    int cap_prompt = 0, cap_part = 0, cap_y = 0, cap_trace = 0;
+    size_t cap_prompt = 0, cap_part = 0, cap_y = 0, cap_trace = 0;      // words
 
     // what the host knows about every slot; the device's copies (s.T, s.pending, lo_from) are brought up to date by the
     // next verification step, which carries them, or by sync_state before anything else reads them
@@ -873,7 +874,7 @@ static int prefill_rows(llma_ctx *c, int seq, int n_feed, int tok0 = 0) {
     return prefill_passes(c, seq, n_feed);
 }
 
-static int ensure_cap(llma_ctx *c, int **buf, int *cap, int need);
+static int ensure_cap(llma_ctx *c, int **buf, size_t *cap, size_t need);
 // The prompts of several sequences (reset slots; gen_prompt holds all of them, sequence b's from offsets[b] on) in passes of up to
 // Pmax rows, sequence after sequence: the weights go through the chip once per pass instead of once per sequence, and a
 // pass fills it.  Six prompts of 166..230 tokens and the first step's
@@ -909,7 +910,7 @@ static int prefill_together(llma_ctx *c, int n_seqs, const int32_t *seqs, const 
             }
             continue;
         }
-        int rc = ensure_cap(c, &c->gen_segs, &c->cap_segs, (int)(segs.size() * sizeof(PromptSeg) / sizeof(int)));
+        int rc = ensure_cap(c, &c->gen_segs, &c->cap_segs, segs.size() * sizeof(PromptSeg) / sizeof(int));
         if (rc) return rc;
         HIP_TRY(c, hipMemcpyAsync(c->gen_segs, segs.data(), segs.size() * sizeof(PromptSeg), hipMemcpyHostToDevice, c->st));
         HIP_TRY(c, hipStreamSynchronize(c->st));                // (the list is written anew for the next pass)
@@ -924,12 +925,12 @@ static int prefill_together(llma_ctx *c, int n_seqs, const int32_t *seqs, const 
     return LLMA_OK;
 }
 
-static int ensure_cap(llma_ctx *c, int **buf, int *cap, int need) {
+static int ensure_cap(llma_ctx *c, int **buf, size_t *cap, size_t need) {
     if (need <= *cap) return LLMA_OK;
     drop_graphs(c);                                   // captured launches hold the old pointer
     if (*buf) { dev_free_one(c, *buf); *buf = nullptr; *cap = 0; }
-    int ncap = need + need / 2 + 64;
-    ALLOC(c, *buf, (size_t)ncap * 4);
+    const size_t ncap = need + need / 2 + 64;
+    ALLOC(c, *buf, ncap * 4);
     *cap = ncap;
     return LLMA_OK;
 }
@@ -1042,7 +1043,6 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
     int rc;
     // per sequence: where its reference tokens and its document list start in the concatenated inputs
     std::vector<int> ref_start(n_seqs + 1, 0), docs_start(n_seqs + 1, 0);
-    int max_prompt = 0;
     for (int b = 0; b < n_seqs; ++b) {
         if ((rc = check_slot(c, seqs[b], "llma_generate"))) return rc;
         for (int b2 = 0; b2 < b; ++b2)
@@ -1051,7 +1051,6 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
         if (plen < 1) return fail(c, LLMA_E_INVAL, "llma_generate: sequence %d has an empty prompt", b);
         if ((long)plen + max_new + k > g.max_seq)
             return fail(c, LLMA_E_RANGE, "llma_generate: prompt %d + max_new %d + k %d > max_seq %d", plen, max_new, k, g.max_seq);
-        max_prompt = plen > max_prompt ? plen : max_prompt;
         const int nd = n_docs ? n_docs[b] : 0;
         if (nd < 0 || (nd > 0 && !doc_offsets)) return fail(c, LLMA_E_INVAL, "llma_generate: bad documents");
         int rlen = 0;
@@ -1084,16 +1083,15 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
     }
     // [prompts | references | document lists] on the device
     const size_t ref_at = ((size_t)total_prompt + 3) / 4 * 4, docs_at = ref_at + ((size_t)total_ref + 3) / 4 * 4, in_words = docs_at + dof_host.size();
-    if (in_words > 0x5fffffff) return fail(c, LLMA_E_RANGE, "llma_generate: %zu words of input", in_words);
-    if ((rc = ensure_cap(c, &c->gen_prompt, &c->cap_prompt, (int)in_words))) return rc;
+    if ((rc = ensure_cap(c, &c->gen_prompt, &c->cap_prompt, in_words))) return rc;
     // spans the trigger scans per sequence: enough for the longest reference, a power of two (few distinct launch shapes)
     int max_ref = 0, spans = 1;
     for (int b = 0; b < n_seqs; ++b) max_ref = ref_start[b + 1] - ref_start[b] > max_ref ? ref_start[b + 1] - ref_start[b] : max_ref;
     while (spans < trigger_spans(max_ref)) spans *= 2;
     c->gen_spans = spans;
-    if ((rc = ensure_cap(c, &c->gen_part, &c->cap_part, 2 * n_seqs * spans))) return rc;
-    if ((rc = ensure_cap(c, &c->gen_y, &c->cap_y, n_seqs * ystride))) return rc;
-    if ((rc = ensure_cap(c, &c->gen_trace, &c->cap_trace, 4 * n_seqs * ystride))) return rc;
+    if ((rc = ensure_cap(c, &c->gen_part, &c->cap_part, (size_t)2 * n_seqs * spans))) return rc;
+    if ((rc = ensure_cap(c, &c->gen_y, &c->cap_y, (size_t)n_seqs * ystride))) return rc;
+    if ((rc = ensure_cap(c, &c->gen_trace, &c->cap_trace, (size_t)4 * n_seqs * ystride))) return rc;
 
     // Everything the device has to know goes there in two copies out of pinned memory, which nothing on the device reads or writes now (every call
     // is waited for, failed ones too), and nobody waits for them: ten pageable copies and four waits took 60 us of a call.

@@ -22,6 +22,7 @@ static std::set<const void *> lost;                       // to a reset
 static int stale_uses = 0;
 static bool not_ours(const void *p) { return lost.count(p) != 0; }
 static long pinned = 0;
+static size_t alloc_limit = ~(size_t)0, refused = 0;       // larger allocations fail; the last one that did
 static std::map<const char *, size_t> pinned_blocks;
 static bool is_pinned(const void *p) {
     auto it = pinned_blocks.upper_bound((const char *)p);
@@ -64,7 +65,10 @@ int stub_gemm_rows(int *out, int cap) { return take(gemm_rows, out, cap); }     
 int stub_gemm_split(int *out, int cap) { return take(gemm_split, out, cap); }      // and whether it took the lo planes
 
 struct ev { long at; };
+void stub_alloc_limit(long bytes) { alloc_limit = bytes < 0 ? ~(size_t)0 : (size_t)bytes; }
+unsigned long stub_refused() { return refused; }
 hipError_t hipMalloc(void **p, size_t n) {
+    if (n > alloc_limit) { refused = n; *p = nullptr; return hipErrorOutOfMemory; }
     *p = calloc(n ? n : 1, 1);
     if (!*p) return hipErrorOutOfMemory;
     allocations[*p] = ++allocations_made;

@@ -221,6 +221,25 @@ def test_many_shapes_do_not_end_the_replay_of_steps(ctx, monkeypatch):
     assert lib.stub_graphs_alive() == 0
 
 
+@both_types
+def test_input_lists_beyond_2_gib_get_memory_of_their_size(ctx):
+    """prompts, references and document lists of a generation share one allocation: its size does not wrap around (the list is all zeros, so the host
+    holds no memory for it either; nothing of this size is given to it here)"""
+    lib, words = ctx.lib, 1_450_000_000
+    ref = np.zeros(words, np.int32)
+    lib.stub_refused.restype = ctypes.c_ulong
+    out, n_out = np.zeros(4, np.int32), ctypes.c_int32()
+    p = [a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)) for a in (ref, out)]
+    lib.stub_alloc_limit(ctypes.c_long(1 << 32))
+    try:
+        rc = lib.llma_generate(ctx.h, 0, i32(1, 2), 2, p[0], i32(0, words), 1, 1, 2, 4, p[1], ctypes.byref(n_out), None, None)
+    finally:
+        lib.stub_alloc_limit(ctypes.c_long(-1))
+    assert rc == llma.LLMA_E_NOMEM
+    assert 4 * words <= lib.stub_refused() <= 8 * words
+    assert ctx.generate(9) == 0 and ctx.out.tolist() == [7] * 9
+
+
 def checksum(a):
     h = 1
     for v in a.tolist():
