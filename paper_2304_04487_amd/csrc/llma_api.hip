@@ -1188,28 +1188,40 @@ extern "C" int llma_generate_batch(llma_ctx *c, int32_t n_seqs, const int32_t *s
         return r;
     };
     if ((rc = decode())) return drained(c, rc);
-    // results: the counters and pending tokens in one copy, tokens and traces in one each, one wait (which also drains the step that ran ahead)
+    // results: the counters and pending tokens in one copy, tokens and traces in one each, one wait (which also drains the step that ran ahead).  Where
+    // they are more than the stage holds, the counters first, and then what the steps produced straight to the caller.
     const size_t y_words = (size_t)n_seqs * ystride;
-    const bool staged = 5 * y_words <= GEN_STAGE_WORDS;
-    std::vector<int> pageable(staged ? 0 : 5 * y_words);
-    int *const y_host = staged ? c->pin_stage : pageable.data(), *const trace_host = y_host + y_words;
+    const bool staged = (trace ? 5 : 1) * y_words <= GEN_STAGE_WORDS;
+    int *const y_host = c->pin_stage, *const trace_host = y_host + y_words;
+    const int *const took = c->pin_block + 5 * (size_t)g.max_batch;
     auto fetch = [&]() -> int {
         HIP_TRY(c, hipMemcpyAsync(c->pin_block, c->block, c->block_states * 4, hipMemcpyDeviceToHost, st));
-        HIP_TRY(c, hipMemcpyAsync(y_host, c->gen_y, y_words * 4, hipMemcpyDeviceToHost, st));
-        if (trace) HIP_TRY(c, hipMemcpyAsync(trace_host, c->gen_trace, 4 * y_words * 4, hipMemcpyDeviceToHost, st));
+        if (staged) {
+            HIP_TRY(c, hipMemcpyAsync(y_host, c->gen_y, y_words * 4, hipMemcpyDeviceToHost, st));
+            if (trace) HIP_TRY(c, hipMemcpyAsync(trace_host, c->gen_trace, 4 * y_words * 4, hipMemcpyDeviceToHost, st));
+        }
+        HIP_TRY(c, hipStreamSynchronize(st));
+        for (int b = 0; b < n_seqs; ++b)
+            if (took[b] < 1 || took[b] > max_new) return fail(c, LLMA_E_HIP, "llma_generate: device step count of sequence %d is %d", b, took[b]);
+        if (staged) return LLMA_OK;
+        for (int b = 0; b < n_seqs; ++b) {
+            HIP_TRY(c, hipMemcpyAsync(out_tokens + (size_t)b * max_new, c->gen_y + (size_t)b * ystride, (size_t)max_new * 4, hipMemcpyDeviceToHost, st));
+            if (trace) HIP_TRY(c, hipMemcpyAsync(trace + (size_t)b * max_new, c->gen_trace + (size_t)4 * b * ystride, (size_t)took[b] * sizeof(llma_step_rec), hipMemcpyDeviceToHost, st));
+        }
         HIP_TRY(c, hipStreamSynchronize(st));
         return LLMA_OK;
     };
     if ((rc = fetch())) return drained(c, rc);
     for (int b = 0; b < n_seqs; ++b) {
-        const int seq = seqs[b], took = c->pin_block[4 * g.max_batch + g.max_batch + b];
-        if (took < 1 || took > max_new) return fail(c, LLMA_E_HIP, "llma_generate: device step count of sequence %d is %d", b, took);
+        const int seq = seqs[b];
         c->T_host[seq] = T0[b] + produced[b];
         c->pending_host[seq] = c->pin_block[g.max_batch + seq];
-        memcpy(out_tokens + (size_t)b * max_new, y_host + (size_t)b * ystride, (size_t)max_new * 4);
-        if (trace) memcpy(trace + (size_t)b * max_new, trace_host + (size_t)4 * b * ystride, (size_t)took * sizeof(llma_step_rec));
+        if (staged) {
+            memcpy(out_tokens + (size_t)b * max_new, y_host + (size_t)b * ystride, (size_t)max_new * 4);
+            if (trace) memcpy(trace + (size_t)b * max_new, trace_host + (size_t)4 * b * ystride, (size_t)took[b] * sizeof(llma_step_rec));
+        }
         n_out[b] = produced[b];
-        if (n_steps) n_steps[b] = took;
+        if (n_steps) n_steps[b] = took[b];
     }
     return LLMA_OK;
 }

@@ -21,7 +21,7 @@ static unsigned allocations_made = 0;
 static std::set<const void *> lost;                       // to a reset
 static int stale_uses = 0;
 static bool not_ours(const void *p) { return lost.count(p) != 0; }
-static long pinned = 0;
+static long pinned = 0, fetched = 0;
 static size_t alloc_limit = ~(size_t)0, refused = 0;       // larger allocations fail; the last one that did
 static std::map<const char *, size_t> pinned_blocks;
 static bool is_pinned(const void *p) {
@@ -67,6 +67,7 @@ int stub_gemm_split(int *out, int cap) { return take(gemm_split, out, cap); }   
 struct ev { long at; };
 void stub_alloc_limit(long bytes) { alloc_limit = bytes < 0 ? ~(size_t)0 : (size_t)bytes; }
 unsigned long stub_refused() { return refused; }
+long stub_fetched() { const long n = fetched; fetched = 0; return n; }              // bytes copied to the host since the last look
 hipError_t hipMalloc(void **p, size_t n) {
     if (n > alloc_limit) { refused = n; *p = nullptr; return hipErrorOutOfMemory; }
     *p = calloc(n ? n : 1, 1);
@@ -103,6 +104,7 @@ void stub_device_reset(int reused) {
 int stub_stale_uses() { return stale_uses; }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind kind, hipStream_t) {
+    if (kind == hipMemcpyDeviceToHost) fetched += (long)n;
     if (kind == hipMemcpyHostToDevice && !is_pinned(s)) {                           // pageable: staged before the call returns
         auto copy = std::make_shared<std::vector<char>>((const char *)s, (const char *)s + n);
         enqueue([=] { memcpy(d, copy->data(), n); });

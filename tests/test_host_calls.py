@@ -41,11 +41,11 @@ def i32(*values):
 class Ctx:
     """a context of zero weights on the stubbed runtime"""
 
-    def __init__(self, lib, dtype, n_layers=3, max_batch=2, max_k=4):
+    def __init__(self, lib, dtype, n_layers=3, max_batch=2, max_k=4, max_seq=128):
         self.lib, self.L = lib, n_layers
         bf16 = dtype == "bf16"
         d, F, V = 128, 256, 64
-        cfg = llma.ModelCfgC(n_layers, d, 2, 64, F, V, 128, max_batch, max_k, llma.LLMA_DTYPE_BF16 if bf16 else llma.LLMA_DTYPE_F32, 1, 1e-6, 1e4)
+        cfg = llma.ModelCfgC(n_layers, d, 2, 64, F, V, max_seq, max_batch, max_k, llma.LLMA_DTYPE_BF16 if bf16 else llma.LLMA_DTYPE_F32, 1, 1e-6, 1e4)
         self.keep = np.zeros(2 * F * d + 3 * d * d + 2 * V * d, np.float32)
         p = self.keep.ctypes.data
         per = (ctypes.c_void_p * n_layers)(*[p] * n_layers)
@@ -238,6 +238,29 @@ def test_input_lists_beyond_2_gib_get_memory_of_their_size(ctx):
     assert rc == llma.LLMA_E_NOMEM
     assert 4 * words <= lib.stub_refused() <= 8 * words
     assert ctx.generate(9) == 0 and ctx.out.tolist() == [7] * 9
+
+
+@pytest.mark.parametrize("max_new", [3212, 3213, 16320, 16321, 40000])
+def test_long_results_come_as_they_are(lib, monkeypatch, max_new):
+    """results of more than the 16384 words that pass through pinned memory go straight to the caller: the tokens, and of the trace
+    the steps that were taken"""
+    monkeypatch.setenv("LLMA_NO_AUTOTUNE", "1")
+    lib.stub_fetched.restype = ctypes.c_long
+    c = Ctx(lib, "fp32", n_layers=1, max_seq=max_new + 16)
+    try:
+        offs, n_out, steps = i32(0, 0), ctypes.c_int32(), ctypes.c_int32()
+        for with_trace in (False, True):
+            out, trace = np.full(max_new, -1, np.int32), np.full((max_new, 4), -2, np.int32)
+            p = [a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)) for a in (out, trace)]
+            lib.stub_fetched()
+            assert lib.llma_generate(c.h, 0, i32(*[1] * 8), 8, None, offs, 0, 1, 2, max_new, p[0], ctypes.byref(n_out), p[1] if with_trace else None, ctypes.byref(steps)) == 0
+            words = max_new + 4 * steps.value * with_trace
+            assert (out == 7).all() and n_out.value == steps.value == max_new and c.state() == (7 + max_new, 7)
+            assert (trace == ([1, 1, -1, -1] if with_trace else -2)).all()
+            if (max_new + 64) * (5 if with_trace else 1) > 16384:
+                assert lib.stub_fetched() <= 4 * words + 128            # (and the slots' words)
+    finally:
+        lib.llma_destroy(c.h)
 
 
 def checksum(a):
