@@ -1242,23 +1242,27 @@ static void launch_panel_cfg(const GemmArgs &a, hipStream_t st) {
     allow_full_lds((const void *)gemm_panel_bf16<RT, EPI, AT, NW>, done);
     hipLaunchKernelGGL((gemm_panel_bf16<RT, EPI, AT, NW>), grid, block, lds, st, a2);
 }
+// (any height is carried out: beyond the tallest form of these waves in that one)
 template <int EPI, int AT, int NW>
 static void launch_panel_rt(int rt, const GemmArgs &a, hipStream_t st) {
-    switch (rt) {
-        case 4: launch_panel_cfg<4, EPI, AT, NW>(a, st); return;
-        case 5: launch_panel_cfg<5, EPI, AT, NW>(a, st); return;
-    }
-    if constexpr (AT > 1)
+    if (rt <= 4) { launch_panel_cfg<4, EPI, AT, NW>(a, st); return; }
+    if constexpr (AT == 1) {
+        launch_panel_cfg<5, EPI, AT, NW>(a, st);
+    } else {
+        if constexpr (NW == 6 && EPI == EPI_RAW)
+            if (rt > PANEL_RT_MAX) {
+                if (rt == 11) launch_panel_cfg<11, EPI, AT, NW>(a, st);
+                else launch_panel_cfg<12, EPI, AT, NW>(a, st);
+                return;
+            }
         switch (rt) {
-            case 6: launch_panel_cfg<6, EPI, AT, NW>(a, st); return;
-            case 7: launch_panel_cfg<7, EPI, AT, NW>(a, st); return;
-            case 8: launch_panel_cfg<8, EPI, AT, NW>(a, st); return;
-            case 9: launch_panel_cfg<9, EPI, AT, NW>(a, st); return;
-            case 10: launch_panel_cfg<10, EPI, AT, NW>(a, st); return;
+            case 5: launch_panel_cfg<5, EPI, AT, NW>(a, st); break;
+            case 6: launch_panel_cfg<6, EPI, AT, NW>(a, st); break;
+            case 7: launch_panel_cfg<7, EPI, AT, NW>(a, st); break;
+            case 8: launch_panel_cfg<8, EPI, AT, NW>(a, st); break;
+            case 9: launch_panel_cfg<9, EPI, AT, NW>(a, st); break;
+            default: launch_panel_cfg<10, EPI, AT, NW>(a, st); break;
         }
-    if constexpr (AT > 1 && NW == 6 && EPI == EPI_RAW) {
-        if (rt == 11) launch_panel_cfg<11, EPI, AT, NW>(a, st);
-        else launch_panel_cfg<12, EPI, AT, NW>(a, st);
     }
 }
 // Which passes without a split take the block GEMM, and in which height (0: the panel GEMM).  Both are priced alike: a launch's start and end, and its

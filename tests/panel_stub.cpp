@@ -8,9 +8,18 @@ extern "C" hipError_t hipGetDevice(int *dev) { *dev = 0; return hipSuccess; }
 extern "C" hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) { p->multiProcessorCount = compute_units; return hipSuccess; }
 
 extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
-extern "C" hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { return hipErrorNotSupported; }
-extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
-extern "C" hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { return hipSuccess; }
+static int launches = 0;
+static dim3 launch_grid, launch_block;
+static size_t launch_lds;
+extern "C" hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { ++launches; return hipSuccess; }
+extern "C" hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t) {
+    launch_grid = grid; launch_block = block; launch_lds = lds;
+    return hipSuccess;
+}
+extern "C" hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *st) {
+    *grid = launch_grid; *block = launch_block; *lds = launch_lds; *st = nullptr;
+    return hipSuccess;
+}
 extern "C" void **__hipRegisterFatBinary(const void *) { return nullptr; }
 extern "C" void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
 extern "C" void __hipUnregisterFatBinary(void **) {}
@@ -57,4 +66,22 @@ extern "C" int stub_block_tiles_outside(int N, int K, int tiles_per_task, int ro
                 *outside += q < 16 ? task0 + block_weight_tile(q, tiles_per_task, n_tasks) >= p.tasks : rt0 + block_row_tile(q - 16, rt, n_rt) >= row_tiles;
             }
     return rt;
+}
+
+// a split launch of the panel GEMM over `rows` rows in row blocks of rt tiles: how many row tiles its grid covers (0: nothing was launched)
+template <int AT, int NW>
+static int panel_covers(int N, int K, int rows, int rt) {
+    GemmArgs a{};
+    a.plan = make_gemm_plan(N, K, 1);
+    a.rows = rows;
+    a.ksplit = 2;
+    launches = 0;
+    launch_panel_rt<EPI_RAW, AT, NW>(rt, a, nullptr);
+    if (launches == 0) return 0;
+    const int height = (int)(launch_lds / ((size_t)PANEL_STAGES * 2 * PANEL_KC * 1024));
+    return (int)launch_grid.x / panel_feature_blocks(a.plan, AT * NW) * height;
+}
+extern "C" int stub_panel_covers(int at, int nw, int N, int K, int rows, int rt) {
+    if (at == 1) return panel_covers<1, 8>(N, K, rows, rt);
+    return nw == 8 ? panel_covers<2, 8>(N, K, rows, rt) : (nw == 7 ? panel_covers<2, 7>(N, K, rows, rt) : (nw == 6 ? panel_covers<2, 6>(N, K, rows, rt) : panel_covers<2, 5>(N, K, rows, rt)));
 }

@@ -67,3 +67,12 @@ def test_block_gemm_reads_tiles_that_exist(library, units):
                 if rt:
                     taken[rt] += 1
     assert min(taken.values()) > 50
+
+
+@pytest.mark.parametrize("at,nw", [(1, 8), (2, 8), (2, 7), (2, 6), (2, 5)])
+def test_any_height_of_row_blocks_is_launched(library, at, nw):
+    """a cut of a height that some form does not have runs in another one: the finishing kernel would add what the last launch left otherwise"""
+    lib = library(256)
+    for rt in range(4, 20):
+        for rows in (49, 160, 161, 192, 193, 400):
+            assert lib.stub_panel_covers(at, nw, 4096, 4096, rows, rt) >= (rows + 15) // 16, (rt, rows)
