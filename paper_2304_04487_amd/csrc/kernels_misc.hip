@@ -479,8 +479,16 @@ __global__ __launch_bounds__(ACCEPT_THREADS) void argmax_accept_kernel(const flo
             const int ot = lane_xor<off.value>(bt);
             if (ov > bv || (ov == bv && ot < bt)) { bv = ov; bt = ot; }
         });
+        if (bt >= n_part) {                                      // (uniform) nothing above minus infinity: the first that is it
+            for (int t = lane; t < n_part && bt >= n_part; t += 64)
+                if (row[t] == LLMA_NEG_INF) bt = t;
+            butterfly<32>([&](auto off) {
+                const int ot = lane_xor<off.value>(bt);
+                bt = ot < bt ? ot : bt;
+            });
+        }
         // a row without any comparable logit (all NaN: reachable through imported caches or weights that
-        // hold non-finite values; or all of them minus infinity: token 0) must still yield a token id the next step's embedding gather can use
+        // hold non-finite values) must still yield a token id the next step's embedding gather can use
         int bi = bt >= n_part ? 0 : (n_part == vocab ? bt : pidx[r * n_part + bt]);      // (fp32 models: a partial per token)
         if ((unsigned)bi >= (unsigned)vocab) bi = 0;
         if (lane == 0) o[j] = bi;

@@ -52,3 +52,29 @@ def test_rows_without_a_comparable_logit_give_token_0(dtype, vocab):
     assert np.isnan(ctx.logits(4)).all()
     assert (acc, nxt, list(emitted)) == (2, 0, [0, 0, 0])
     ctx.close()
+
+
+@pytest.mark.parametrize("vocab,first", [(515, 0), (515, 7), (515, 514), (2052, 3), (2052, 700), (2052, 2051)])
+def test_minus_infinity_beside_nan(vocab, first):
+    """the largest comparable logit is the arg max also where it is minus infinity: the first one of them, behind tokens whose logit is NaN"""
+    def head(value):
+        def make_head(h):
+            h = np.zeros_like(h)
+            h[:first, 0] = np.nan
+            h[first:, 0] = value
+            return h
+        return make_head
+    prompt = synth.uniform_tokens(3, 1, 20, vocab)
+    for value in (1.0, None):
+        if value is None:
+            value = -np.inf * sign              # the logits' sign is that of the row's first feature
+        cfg, ctx = make("fp32", vocab, head(value))
+        ctx.prefill(prompt)
+        acc, nxt, emitted = ctx.verify_step([])
+        logits = ctx.logits(1)[0]
+        assert np.isnan(logits[:first]).all()
+        sign = np.sign(logits[first])
+        assert sign != 0
+        ctx.close()
+    assert (logits[first:] == -np.inf).all()
+    assert (acc, nxt, list(emitted)) == (0, first, [first])
