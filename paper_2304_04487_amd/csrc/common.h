@@ -151,6 +151,8 @@ struct GemmPlan {
                      //   only -- every tile's sum is the same whatever the value -- so it may be tuned per device
     int tk_waves;    //   and K slices (= waves, or half as many waves taking two slices each): fixes the order of the sums
     int n_split;     // panel kernel, batched steps: ranges the K axis is cut into (1 = no split)
+    int block_rt;    // passes without a split: row tiles per block of the block GEMM (12, 16) or 0, the panel GEMM; -1: as block_height prices
+                     //   them.  Work division only, like tk_ft
 };
 
 // Groups of consecutive K slices that are summed before the groups are added (1: one slice after the other).  16 slices of equal,

@@ -1273,6 +1273,7 @@ static void launch_panel_rt(int rt, const GemmArgs &a, hipStream_t st) {
 // 355 (stays), 1279 214 / 200, 852 169 / 155; O and down (16 feature blocks, too few for either height) 98 / 119 .. 151, 272 / 305 .. 375 at 2047.
 static int block_height(const GemmPlan &p, int rows, const PanelCut &cut) {
     if (p.KSp % 2 != 0 || p.KSp > 65536) return 0;               // (two k-steps per turn; 32-bit offsets inside a block's operands)
+    if (p.block_rt >= 0) return p.block_rt;
     const int row_tiles = (rows + 15) / 16;
     auto price = [&](int rt, double step_us, double start) {
         const double r = (double)panel_feature_blocks(p, 16) * ((row_tiles + rt - 1) / rt) / cu_count(), whole = (double)(long)(r + 0.999999);
@@ -1397,6 +1398,7 @@ GemmPlan make_gemm_plan(int N, int K, int tiles_per_task) {
     ns = ns < 2 ? 2 : (ns > 8 ? 8 : ns);
     const int turns = (p.KSp + PANEL_TURN - 1) / PANEL_TURN;
     p.n_split = ns < turns ? ns : (turns > 0 ? turns : 1);
+    p.block_rt = -1;
     return p;
 }
 

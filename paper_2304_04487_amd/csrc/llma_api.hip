@@ -200,6 +200,11 @@ static int create_impl(llma_ctx *c, const llma_weights *w) {
         c->plan_gu = make_gemm_plan(F, d, 2);
         c->plan_down = make_gemm_plan(d, F, 1);
         c->plan_lm = make_gemm_plan(V, d, 1);
+        if (const char *forced = getenv("LLMA_BLOCK_ROWS")) {     // tests: long prompt passes in blocks of 12 or 16 row tiles, or (0) none
+            const int rt = atoi(forced);
+            if (rt == 0 || rt == 12 || rt == 16)
+                for (GemmPlan *p : {&c->plan_qkv, &c->plan_o, &c->plan_gu, &c->plan_down}) p->block_rt = rt;
+        }
     }
     // ---- weights
     ALLOC(c, c->embed, (size_t)V * d * es);
