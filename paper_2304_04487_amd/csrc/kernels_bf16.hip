@@ -1265,25 +1265,41 @@ static void launch_panel_rt(int rt, const GemmArgs &a, hipStream_t st) {
         }
     }
 }
-// Which passes without a split take the block GEMM, and in which height (0: the panel GEMM).  Both are priced alike: a launch's start and end, and its
-// rounds of workgroups, half of a last round's empty places counted (the card's clock rises while compute units idle), times what a
-// workgroup's products take under the power limit: per k-step and pair of weight and row tile 0.0056 us in the panel GEMM (RT 8, 9, 10 of
-// 7B's gate/up: 92 / 103 / 115 us per round), 0.0052 with 12 row tiles and 0.0050 with 16 in blocks (127, 164 us).  The lines between them, us panel / block:
-// gate/up of 7B at 2047 rows 536 / 496, 1919 515 / 485, 1791 465 / 479 (stays), 1535 412 / 385, 1279 338 / 323, 852 251 / 248; QKV at 1919 310 / 294, 2047 325 /
-// 355 (stays), 1279 214 / 200, 852 169 / 155; O and down (16 feature blocks, too few for either height) 98 / 119 .. 151, 272 / 305 .. 375 at 2047.
+// Rounds of workgroups, one per compute unit, on the busiest XCD -- feature blocks of 16 weight tiles go round the eight of them, a block's row
+// blocks stay on one -- and the share of all compute units that the last of them keeps busy.
+struct Rounds { int n; double last; };
+static Rounds panel_rounds(const GemmPlan &p, int row_blocks) {
+    const int per = 16 / p.tiles_per_task, blocks = (p.tasks + per - 1) / per, units = cu_count() / 8 > 0 ? cu_count() / 8 : 1;
+    auto on = [&](int xcd) { return (blocks + 7 - xcd) / 8 * row_blocks; };
+    Rounds r{(on(0) + units - 1) / units, 0.0};
+    for (int x = 0; x < 8; ++x) r.last += on(x) > units * (r.n - 1) ? (double)(on(x) - units * (r.n - 1)) / (8 * units) : 0.0;
+    return r;
+}
+// Which passes without a split take the block GEMM, and in which height (0: the panel GEMM).  Both are priced alike, in us per pair of weight and row tile:
+// a k-step takes what the matrix cores do under the card's power limit (0.0056 with seven row tiles in the panel GEMM, where fewer
+// wait for operands; 0.0052 / 0.00505 in blocks of 12 / 16), in the last round down to two thirds of it, as compute units idle and the
+// clock rises; every round ends with its epilogue, which nothing overlaps (gate/up writes half the outputs); 5 us to start and end.
+// Fitted to 978 launches in each form inside prompt passes of 320 .. 2048 rows (every 16 or 32, the forms in turn; d 512, 2048, 3072, 7B and 13B): error
+// 2.4 % rms, largely the same for both forms of a case.  With 3 % to be gained none of them is slower than in the panel GEMM, nor are
+// those of four shapes that were not fitted (d 1600, 2560, 6144, 8192); the model before (launches back to back, the chip as a whole) took 84 of them to blocks that were
+// 1 .. 15 % slower.  us panel / 12 / 16: gate/up of 7B 431 rows 143 / 236 / 164, 847 247 / 261 / 322, 1327 375 / 383 / 482 (stay), 1536 425 / 401 / 487,
+// 2048 564 / 536 / 513; of 13B 512 219 / 295 / 202, 1103 453 / 463 / 591, 1792 709 / 781 / 795 (stay), 1711 705 / 642 / 787; QKV of 7B 911 166 / 156 / 192, 1679
+// 281 / 298 / 357 (stays), 1920 320 / 304 / 368; of 13B 847 229 / 321 / 239 (stays), 1024 258 / 332 / 240, 2048 512 / 538 / 474; O of 13B 1664 174 / 177 / 216 (stays),
+// 1792 190 / 182 / 214, 2016 201 / 317 / 229 (stays).  O and down of 7B (16 feature blocks) stay: 98 .. 114 / 120 .. 138 / 152 .. 170 and 230 .. 263 / 292 .. 305 / 373 .. 379.
 static int block_height(const GemmPlan &p, int rows, const PanelCut &cut) {
     if (p.KSp % 2 != 0 || p.KSp > 65536) return 0;               // (two k-steps per turn; 32-bit offsets inside a block's operands)
     if (p.block_rt >= 0) return p.block_rt;
-    const int row_tiles = (rows + 15) / 16;
-    auto price = [&](int rt, double step_us, double start) {
-        const double r = (double)panel_feature_blocks(p, 16) * ((row_tiles + rt - 1) / rt) / cu_count(), whole = (double)(long)(r + 0.999999);
-        return start + 0.5 * (r + whole) * p.KSp * step_us;
-    };
     if (cut.nw * cut.at != 16) return 0;                         // (8 tiles per workgroup: few workgroups as it is)
-    const double in = (16 + 2 * cut.rt) / 44.0, multiply = 0.0056 * 16 * cut.rt;        // (as in panel_cut)
-    double best_us = 0.99 * price(cut.rt, in > multiply ? in : multiply, 15.0);
+    const int row_tiles = (rows + 15) / 16;
+    auto price = [&](int rt, double step_us) {
+        const Rounds r = panel_rounds(p, (row_tiles + rt - 1) / rt);
+        return 5.0 + 16.0 * rt * (p.KSp * step_us * (r.n - 1 + 0.66 + 0.34 * r.last) + (p.tiles_per_task == 2 ? 0.03 : 0.13) * r.n);
+    };
+    static const double panel_us[] = {0.0067, 0.0061, 0.0057, 0.0056, 0.0055, 0.0055, 0.0055};      // 4 .. 10 row tiles
+    static_assert(sizeof panel_us / sizeof *panel_us == PANEL_RT_MAX - 3, "");
+    double best_us = 0.97 * price(cut.rt, panel_us[cut.rt - 4]);
     int best = 0;
-    const double b12 = price(12, 0.0052 * 16 * 12, 22.0), b16 = price(16, 0.0050 * 16 * 16, 25.0);
+    const double b12 = price(12, 0.0052), b16 = price(16, 0.00505);
     if (b12 < best_us) { best = 12; best_us = b12; }
     if (b16 < best_us) best = 16;
     return best;

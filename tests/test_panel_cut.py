@@ -76,3 +76,25 @@ def test_any_height_of_row_blocks_is_launched(library, at, nw):
     for rt in range(4, 20):
         for rows in (49, 160, 161, 192, 193, 400):
             assert lib.stub_panel_covers(at, nw, 4096, 4096, rows, rt) >= (rows + 15) // 16, (rt, rows)
+
+
+# us of one launch inside prompt passes on 256 compute units, the forms in turn: ((N, K, tiles per task), rows): panel, blocks of 12, of 16
+QKV_7B, QKV_13B, O_13B, GU_7B, GU_13B = (12288, 4096, 1), (15360, 5120, 1), (5120, 5120, 1), (11008, 4096, 2), (13824, 5120, 2)
+MEASURED = [
+    (GU_7B, 335, 126.2, 128.1, 163.7), (GU_7B, 431, 143.1, 236.4, 164.0), (GU_7B, 847, 247.2, 260.8, 321.5), (GU_7B, 1327, 375.5, 382.7, 482.1),
+    (GU_7B, 1536, 425.2, 401.4, 486.5), (GU_7B, 2048, 564.2, 535.9, 513.3), (QKV_7B, 911, 165.8, 156.1, 192.3), (QKV_7B, 1280, 213.9, 276.8, 199.0),
+    (QKV_7B, 1679, 281.5, 297.6, 357.1), (QKV_7B, 1920, 319.7, 303.8, 368.4), (QKV_7B, 2048, 331.9, 422.6, 371.6), (GU_13B, 416, 193.4, 291.1, 201.9),
+    (GU_13B, 512, 218.8, 294.6, 201.5), (GU_13B, 1103, 453.4, 463.0, 591.2), (GU_13B, 1711, 705.2, 641.7, 787.5), (GU_13B, 1792, 709.4, 781.2, 794.6),
+    (GU_13B, 2016, 802.9, 814.7, 833.0), (QKV_13B, 768, 199.4, 186.1, 222.3), (QKV_13B, 847, 229.1, 321.5, 238.9), (QKV_13B, 1024, 258.2, 331.7, 240.4),
+    (QKV_13B, 1327, 341.1, 354.8, 436.3), (QKV_13B, 2048, 512.5, 537.5, 473.5), (O_13B, 1664, 173.6, 177.0, 215.7), (O_13B, 2016, 201.1, 316.5, 229.3),
+    ((9216, 3072, 1), 1216, 144.4, 204.1, 148.4), ((9216, 3072, 1), 1951, 219.1, 229.1, 281.7), ((8192, 2048, 2), 1024, 105.2, 133.0, 96.4),
+]
+
+
+@pytest.mark.parametrize("shape,rows,panel,b12,b16", MEASURED)
+def test_blocks_where_they_are_faster(library, shape, rows, panel, b12, b16):
+    """the rule never takes a form that was measured slower than the panel GEMM, and takes one that was 5 % faster"""
+    times = {0: panel, 12: b12, 16: b16}
+    chosen = times[library(256).stub_block_tiles_outside(*shape, rows, ctypes.byref(ctypes.c_int()))]
+    assert chosen <= panel
+    assert chosen <= 1.05 * min(times.values())
