@@ -24,25 +24,27 @@ void launch_kv_import_f32(const void *k, const void *v, void *kc, void *vc, int 
                        (const float *)k, (const float *)v, (float *)kc, (float *)vc, H, len, dh, max_seq);
 }
 
-// A workgroup per output feature (SwiGLU: the gate and the up row; QKV: the two features of a rotary pair) and eight rows,
-// two rows per wavefront; lanes take four consecutive elements of the reduction axis each, butterfly reduction across the
+// A wave takes one output feature (SwiGLU: the gate and the up row; QKV: the two features of a rotary pair) and NR rows; lanes take four
+// consecutive elements of the reduction axis each, butterfly reduction across the
 // wavefront.  RMSNorm runs inside: the wave sees every element of its rows anyway, so it adds their squares and scales the sums
-// (W (x g)) rstd at the end; RoPE and the cache append run in the epilogue.  Latency-bound at the shapes it is used for
-// (d 128, five rows; an empty launch of a replayed graph takes 1.6 us): the chain from the arguments to the last store is kept
+// (W (x g)) rstd at the end; RoPE and the cache append run in the epilogue.
+// Small launches (d 128, five rows; an empty launch of a replayed graph takes 1.6 us) are bound by latency: the chain from the arguments to the last store is kept
 // short.  All loads of a pass over 512 elements and everything the epilogue reads are in flight together; lanes exchange by
-// register moves; and with all eight rows in one wave the butterflies were the longest part.  Back to back at 1 / 5 / 9 rows, us:
+// register moves; and with all eight rows in one wave the butterflies were the longest part, so a wave takes two, four waves of a workgroup the
+// same feature.  Back to back at 1 / 5 / 9 rows, us:
 // QKV 3.1 / 4.5 / 5.6 -> 2.4 / 2.8 / 2.8, O 2.6 / 3.5 / 4.1 -> 2.0 / 2.1 / 2.2, gate/up 3.1 / 4.5 / 5.6 -> 2.4 / 2.8 / 3.0.
-#define F32_WAVE_ROWS 2
-#define F32_GROUP_ROWS 8
-template <int EPI, bool VEC>
-__global__ __launch_bounds__(64 * F32_GROUP_ROWS / F32_WAVE_ROWS) void gemm_f32_kernel(GemmArgs a) {
-    constexpr int NR = F32_WAVE_ROWS, E = VEC ? 4 : 1;
+// Large ones are bound by what the waves load, of which the weights come again for every NR rows: four or eight rows in a wave, one wave per
+// workgroup (f32_rows_per_wave).
+#define F32_WAVES(NR) ((NR) == 2 ? 4 : 1)
+template <int EPI, bool VEC, int NR>
+__global__ __launch_bounds__(64 * F32_WAVES(NR)) void gemm_f32_kernel(GemmArgs a) {
+    constexpr int E = VEC ? 4 : 1;
     constexpr bool PAIR = EPI == EPI_SWIGLU || EPI == EPI_QKV, NORM = EPI != EPI_RESID;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // QKV: grid (i, head, 3 sections x row groups); the workgroup's features are i and i + dh/2 of the head
     const int n = blockIdx.x, half = a.dh / 2, d = a.H * a.dh;
     const int sec = EPI == EPI_QKV ? blockIdx.z % 3 : 0, head = EPI == EPI_QKV ? blockIdx.y : 0, i = n;
-    const int r0 = (int)(EPI == EPI_QKV ? blockIdx.z / 3 : blockIdx.y) * F32_GROUP_ROWS + wave * NR;
+    const int r0 = (int)(EPI == EPI_QKV ? blockIdx.z / 3 : blockIdx.y) * (F32_WAVES(NR) * NR) + wave * NR;
     const int K = a.K, nr = a.rows - r0 < NR ? a.rows - r0 : NR;
     if (nr <= 0) return;
     const size_t f0 = EPI == EPI_QKV ? (size_t)sec * d + head * a.dh + i : n, f1 = EPI == EPI_QKV ? f0 + half : (size_t)n + a.N;
@@ -83,29 +85,33 @@ __global__ __launch_bounds__(64 * F32_GROUP_ROWS / F32_WAVE_ROWS) void gemm_f32_
             if (!(h ? in1 : in0)) break;
 #pragma unroll
             for (int r = 0; r < NR; ++r)
+                if (NR <= 2 || r < nr)                          // (uniform)
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const float xv = x[h][r][e], xg = NORM ? xv * g[h][e] : xv;
-                    if (NORM) ss[r] = fmaf(xv, xv, ss[r]);
-                    acc[r] = fmaf(w0[h][e], xg, acc[r]);
-                    if (PAIR) acc1[r] = fmaf(w1[h][e], xg, acc1[r]);
-                }
+                    for (int e = 0; e < E; ++e) {
+                        const float xv = x[h][r][e], xg = NORM ? xv * g[h][e] : xv;
+                        if (NORM) ss[r] = fmaf(xv, xv, ss[r]);
+                        acc[r] = fmaf(w0[h][e], xg, acc[r]);
+                        if (PAIR) acc1[r] = fmaf(w1[h][e], xg, acc1[r]);
+                    }
         }
     }
     // every lane ends with all sums; lane r finishes row r
     butterfly<32>([&](auto off) {
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            acc[r] += lane_xor<off.value>(acc[r]);
-            if (PAIR) acc1[r] += lane_xor<off.value>(acc1[r]);
-            if (NORM) ss[r] += lane_xor<off.value>(ss[r]);
-        }
+        for (int r = 0; r < NR; ++r)
+            if (NR <= 2 || r < nr) {                            // (uniform)
+                acc[r] += lane_xor<off.value>(acc[r]);
+                if (PAIR) acc1[r] += lane_xor<off.value>(acc1[r]);
+                if (NORM) ss[r] += lane_xor<off.value>(ss[r]);
+            }
     });
     if (lane >= nr) return;
-    float v0 = lane ? acc[1] : acc[0], v1 = lane ? acc1[1] : acc1[0];
-    static_assert(NR == 2, "");
+    float v0 = acc[0], v1 = acc1[0], s2 = ss[0];
+#pragma unroll
+    for (int r = 1; r < NR; ++r)
+        if (lane == r) { v0 = acc[r]; v1 = acc1[r]; s2 = ss[r]; }
     if (NORM) {
-        const float rstd = 1.0f / sqrtf((lane ? ss[1] : ss[0]) / (float)K + a.eps);
+        const float rstd = 1.0f / sqrtf(s2 / (float)K + a.eps);
         v0 *= rstd;
         v1 *= rstd;
     }
@@ -126,13 +132,29 @@ __global__ __launch_bounds__(64 * F32_GROUP_ROWS / F32_WAVE_ROWS) void gemm_f32_
         dst[i + half] = o1;
     }
 }
+template <int EPI, int NR>
+static void launch_gemm_f32_rows(const GemmArgs &a, hipStream_t st) {
+    constexpr int WAVES = F32_WAVES(NR);
+    const int waves = (a.rows + NR - 1) / NR, groups = (waves + WAVES - 1) / WAVES;
+    const dim3 grid = EPI == EPI_QKV ? dim3(a.dh / 2, a.H, 3 * groups) : dim3(a.N, groups);
+    const dim3 block(64 * (groups > 1 ? WAVES : waves));
+    if (a.K % 4 == 0) hipLaunchKernelGGL((gemm_f32_kernel<EPI, true, NR>), grid, block, 0, st, a);       // (rows and gains start at multiples of 16 bytes)
+    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, false, NR>), grid, block, 0, st, a);
+}
+// Rows per wave: work division only, every sum is the same.  Two up to 48 M products; from there on as many as there are, up to eight.  us with 2 / 4 / 8 rows (8
+// are the kernel of before the split): d 512 gate/up, 16 rows (34 M products) 10.2 / 8.7 / 9.5; d 1024 QKV 9 rows (28 M) 8.4 / 7.9 / 9.5, 16 (50 M) 11.1 / 10.4 / 10.9,
+// 48 26.5 / 21.2 / 21.3; down 9 rows (38 M) 9.6 / 9.9 / 13.2, 48 36.0 / 30.4 / 29.6; d 2048 QKV 4 / 8 / 48 rows 17.4 / 15.4 / 19.1, 26.9 / 21.9 / 21.0,
+// 107 / 89 / 69, gate/up 48 rows 271 / 237 / 175; d 4096 QKV 4 / 5 / 48 rows 61 / 49 / 58, 78 / 75 / 60, 431 / 357 / 270, O 4 / 48 23 / 18 / 28, 169 / 147 / 130.
+static int f32_rows_per_wave(const GemmArgs &a) {
+    const double products = (double)a.rows * a.N * a.K * (a.epi == EPI_SWIGLU ? 2 : 1);
+    return a.rows <= 2 || products < 48e6 ? 2 : (a.rows <= 4 ? 4 : 8);
+}
 template <int EPI>
 static void launch_gemm_f32_epi(const GemmArgs &a, hipStream_t st) {
-    const int groups = (a.rows + F32_GROUP_ROWS - 1) / F32_GROUP_ROWS, waves = (a.rows + F32_WAVE_ROWS - 1) / F32_WAVE_ROWS;
-    const dim3 grid = EPI == EPI_QKV ? dim3(a.dh / 2, a.H, 3 * groups) : dim3(a.N, groups);
-    const dim3 block(64 * (groups > 1 ? F32_GROUP_ROWS / F32_WAVE_ROWS : waves));
-    if (a.K % 4 == 0) hipLaunchKernelGGL((gemm_f32_kernel<EPI, true>), grid, block, 0, st, a);       // (rows and gains start at multiples of 16 bytes)
-    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, false>), grid, block, 0, st, a);
+    const int nr = f32_rows_per_wave(a);
+    if (nr == 2) launch_gemm_f32_rows<EPI, 2>(a, st);
+    else if (nr == 4) launch_gemm_f32_rows<EPI, 4>(a, st);
+    else launch_gemm_f32_rows<EPI, 8>(a, st);
 }
 void launch_gemm_f32(const GemmArgs &a, hipStream_t st) {
     switch (a.epi) {

@@ -1,4 +1,4 @@
-// The panel GEMM's host side on the CPU: kernels_bf16.hip compiled for the host alone, on a device whose number of
+// The GEMMs' host side on the CPU: kernels_bf16.hip and kernels_f32.hip compiled for the host alone, on a device whose number of
 // compute units the caller sets.
 #include <hip/hip_runtime.h>
 
@@ -25,6 +25,7 @@ extern "C" void __hipRegisterFunction(void **, const void *, char *, const char 
 extern "C" void __hipUnregisterFatBinary(void **) {}
 
 #include "kernels_bf16.hip"
+#include "kernels_f32.hip"
 
 #include <vector>
 
@@ -84,4 +85,10 @@ static int panel_covers(int N, int K, int rows, int rt) {
 extern "C" int stub_panel_covers(int at, int nw, int N, int K, int rows, int rt) {
     if (at == 1) return panel_covers<1, 8>(N, K, rows, rt);
     return nw == 8 ? panel_covers<2, 8>(N, K, rows, rt) : (nw == 7 ? panel_covers<2, 7>(N, K, rows, rt) : (nw == 6 ? panel_covers<2, 6>(N, K, rows, rt) : panel_covers<2, 5>(N, K, rows, rt)));
+}
+
+extern "C" int stub_f32_rows_per_wave(int N, int K, int epi, int rows) {
+    GemmArgs a{};
+    a.N = N; a.K = K; a.epi = epi; a.rows = rows;
+    return f32_rows_per_wave(a);
 }

@@ -1,4 +1,4 @@
-"""How the panel GEMM cuts its launches, on the CPU: its host functions (tests/panel_stub.cpp) for devices of several sizes."""
+"""How the panel, block and fp32 GEMMs cut their launches, on the CPU: their host functions (tests/panel_stub.cpp) for devices of several sizes."""
 import ctypes
 import os
 import subprocess
@@ -98,3 +98,21 @@ def test_blocks_where_they_are_faster(library, shape, rows, panel, b12, b16):
     chosen = times[library(256).stub_block_tiles_outside(*shape, rows, ctypes.byref(ctypes.c_int()))]
     assert chosen <= panel
     assert chosen <= 1.05 * min(times.values())
+
+
+# us of one fp32 launch: (N, K, epilogue), rows: the kernel with eight rows per wave of before the split; 2, 4, 8 rows per wave now
+RESID, SWIGLU, LMHEAD, QKV = 1, 2, 3, 4
+MEASURED_F32 = [
+    ((384, 128, QKV), 5, 4.6, 2.8, 3.5, 4.2), ((1536, 512, QKV), 16, 7.9, 6.1, 6.0, 6.8), ((2048, 512, SWIGLU), 16, 11.9, 10.2, 8.7, 9.5), ((512, 2048, RESID), 48, 12.0, 11.6, 10.4, 11.1),
+    ((3072, 1024, QKV), 9, 10.1, 8.4, 7.9, 9.5), ((3072, 1024, QKV), 48, 23.9, 26.5, 21.2, 21.3), ((4096, 1024, SWIGLU), 48, 51.1, 60.2, 47.5, 45.1), ((1024, 4096, RESID), 5, 12.2, 8.3, 9.2, 11.4),
+    ((1024, 4096, RESID), 48, 30.9, 36.0, 30.4, 29.6), ((6144, 2048, QKV), 4, 19.4, 17.4, 15.4, 19.1), ((6144, 2048, QKV), 8, 21.7, 26.9, 21.9, 21.0), ((6144, 2048, QKV), 48, 70.8, 106.5, 88.7, 69.0),
+    ((2048, 2048, RESID), 5, 11.5, 8.5, 9.2, 10.8), ((2048, 2048, RESID), 48, 31.7, 39.1, 32.6, 30.8), ((8192, 2048, SWIGLU), 2, 39.0, 27.0, 30.0, 39.0), ((8192, 2048, SWIGLU), 33, 142.0, 203.0, 177.6, 139.7),
+    ((8000, 2048, LMHEAD), 33, 116.2, 153.0, 121.1, 113.8), ((12288, 4096, QKV), 5, 60.0, 77.8, 75.0, 60.0), ((12288, 4096, QKV), 48, 272.4, 430.6, 356.9, 269.8),
+    ((11008, 4096, SWIGLU), 4, 97.0, 107.0, 86.0, 98.0), ((11008, 4096, SWIGLU), 24, 334.8, 506.5, 500.5, 336.3), ((4096, 11008, RESID), 2, 73.0, 41.0, 48.0, 74.0), ((4096, 11008, RESID), 24, 195.4, 243.7, 215.2, 197.3),
+]
+
+
+@pytest.mark.parametrize("shape,rows,before,two,four,eight", MEASURED_F32)
+def test_fp32_rows_per_wave(library, shape, rows, before, two, four, eight):
+    """the form taken is no slower than eight rows per wave were, from the smallest models to the widest"""
+    assert {2: two, 4: four, 8: eight}[library(256).stub_f32_rows_per_wave(*shape, rows)] <= 1.015 * before
