@@ -1160,6 +1160,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_finish_bf16(GemmArgs a0) {
         f32x4 v[8];                                             // (at most 8 ranges; all requested before the first is added)
 #pragma unroll
         for (int s = 0; s < 8; ++s) v[s] = part[((s < a0.ksplit ? s : 0) * stride + tile) * 64 + lane];
+        requests_stay_in_order();                               // (left alone, the compiler waits for two after two of them, and requests the epilogue's inputs last)
 #pragma unroll
         for (int s = 1; s < 8; ++s)
             if (s < a0.ksplit) v[0] += v[s];
