@@ -267,7 +267,17 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, const GemmPlan 
     }
 }
 
-// sum of sp[j0 .. j1), in order; j1 - j0 <= chunk, which is the same for all threads
+// adds sp[j .. j + U) below j1 to ss, in order: U loads in flight
+template <int U>
+__device__ __forceinline__ void add_tiles(const float *sp, int j, int j1, float &ss) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = sp[j + u < j1 ? j + u : j1 - 1];
+#pragma unroll
+    for (int u = 0; u < U; ++u) ss += j + u < j1 ? v[u] : 0.f;
+}
+// sum of sp[j0 .. j1), in order; j1 - j0 <= chunk, which is the same for all threads; j1 >= 1.  Loads are unconditional (see epi_prefetch) and as many as there
+// are, rounded up to fours, at most sixteen at a time: always sixteen, QKV of d 1024 / 2048 (4 / 8 to add) took 9.2 / 16.4 us at 48 rows instead of 7.5 / 14.1
 __device__ __forceinline__ float sum_of_tiles(const float *sp, int j0, int j1, int chunk) {
     float ss = 0.f;
     if (chunk <= 2) {                                   // (rows of up to 512 features)
@@ -275,13 +285,11 @@ __device__ __forceinline__ float sum_of_tiles(const float *sp, int j0, int j1, i
         const float v0 = sp[j0], v1 = sp[j1 - 1];
         return j1 - j0 == 2 ? v0 + v1 : v0;
     }
-    for (int j = j0; j < j1; j += 16) {
-        float v[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = sp[j + u < j1 ? j + u : j1 - 1];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) ss += j + u < j1 ? v[u] : 0.f;
-    }
+    int j = j0, left = chunk;
+    for (; left > 12; j += 16, left -= 16) add_tiles<16>(sp, j, j1, ss);
+    if (left > 8) add_tiles<12>(sp, j, j1, ss);
+    else if (left > 4) add_tiles<8>(sp, j, j1, ss);
+    else if (left > 0) add_tiles<4>(sp, j, j1, ss);
     return ss;
 }
 
