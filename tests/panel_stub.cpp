@@ -87,6 +87,13 @@ extern "C" int stub_panel_covers(int at, int nw, int N, int K, int rows, int rt)
     return nw == 8 ? panel_covers<2, 8>(N, K, rows, rt) : (nw == 7 ? panel_covers<2, 7>(N, K, rows, rt) : (nw == 6 ? panel_covers<2, 6>(N, K, rows, rt) : panel_covers<2, 5>(N, K, rows, rt)));
 }
 
+// row tiles per workgroup of a split launch: a step's (ranges by the matrix alone) or a prompt pass's (by its rows); 0: it runs whole
+extern "C" int stub_split_height(int N, int K, int tiles_per_task, int rows, int prompt) {
+    const GemmPlan p = make_gemm_plan(N, K, tiles_per_task);
+    const int ns = prompt ? panel_prompt_split(p, rows) : p.n_split;
+    return ns > 1 ? panel_cut(p, rows, ns).rt : 0;
+}
+
 extern "C" int stub_f32_rows_per_wave(int N, int K, int epi, int rows) {
     GemmArgs a{};
     a.N = N; a.K = K; a.epi = epi; a.rows = rows;

@@ -116,3 +116,23 @@ MEASURED_F32 = [
 def test_fp32_rows_per_wave(library, shape, rows, before, two, four, eight):
     """the form taken is no slower than eight rows per wave were, from the smallest models to the widest"""
     assert {2: two, 4: four, 8: eight}[library(256).stub_f32_rows_per_wave(*shape, rows)] <= 1.015 * before
+
+
+def test_forms_that_the_gpu_tests_are_about(library):
+    """on 256 compute units: what tests/test_gpu_tall_panels.py, test_gpu_prompt_blocks.py and test_gpu_f32_kernels.py say that their launches take"""
+    lib, outside = library(256), ctypes.c_int()
+    for rows in (161, 175, 176, 177, 192):
+        assert lib.stub_split_height(*GU_7B, rows, 1) == (rows + 15) // 16, rows
+    assert all(lib.stub_split_height(*GU_7B, rows, 1) <= 10 for rows in (160, 193))
+    assert all(lib.stub_split_height(*QKV_7B, rows, 0) == (rows + 15) // 16 for rows in (161, 176, 177, 192))       # (steps; see kernels_bf16.hip)
+    height = lambda shape, rows: lib.stub_block_tiles_outside(*shape, rows, ctypes.byref(outside))
+    assert [height((8192, 2048, 2), rows) for rows in (2047, 2033)] == [16, 16]
+    assert [height((6144, 2048, 1), rows) for rows in (1905, 1889)] == [12, 12]
+    for shape in ((6336, 2112, 1), (2112, 2112, 1), (2112, 2112, 2)):                       # unsplit: LLMA_BLOCK_ROWS applies
+        assert all(lib.stub_split_height(*shape, rows, 1) == 0 for rows in (2047, 1905, 1889, 1500)), shape
+    rows_per_wave = lambda shape: [lib.stub_f32_rows_per_wave(*shape, rows) for rows in (2, 3, 4, 5, 12, 17, 33)]
+    assert rows_per_wave((6144, 2048, QKV)) == [2, 2, 4, 8, 8, 8, 8]
+    assert rows_per_wave((2048, 2048, RESID)) == [2, 2, 2, 2, 8, 8, 8]
+    assert rows_per_wave((6002, 2048, SWIGLU)) == [2, 4, 4, 8, 8, 8, 8]
+    assert rows_per_wave((2048, 6002, RESID)) == [2, 2, 4, 8, 8, 8, 8]
+    assert rows_per_wave((8000, 2048, LMHEAD)) == [2, 4, 4, 8, 8, 8, 8]
