@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_panel_bf16(GemmArgs a0) {
 // Block GEMM (long prompt passes): like the panel GEMM without a split, but both operands pass through LDS and a wave owns 8 weight tiles x
 // RT / 4 row tiles (2 x 4 waves per workgroup of 16 x RT tiles).  In the panel GEMM a read from LDS feeds two products, which keeps the LDS
 // as busy as the matrix cores (per k-step of nine row tiles 1266 cycles of reads and fills beside 1152 of MFMA) and costs power, the bound of
-// long prompts; here 16 reads feed 64 products (RT 16).  Gate/up of 7B at 2047 rows 536 -> 496 us = 1.38 -> 1.49 PFLOP/s, of which the
+// long prompts; here 16 reads feed 64 products (RT 16).  Gate/up of 7B at 2047 rows, inside a pass, 544 -> 507 us = 1.36 -> 1.46 PFLOP/s, of which the
 // last round of workgroups leaves a tenth idle.  Which passes take it: block_height.
 // A k-step's (16 + 2 RT) KB come straight into one of three LDS stages.  The groups of a k-step are its row tiles, 16 MFMAs each; the next group's
 // activations are read during the present one, and the next k-step's weights replace the present ones during the last group, tile by
@@ -1203,9 +1203,11 @@ static GemmPlan raw_plan(const GemmPlan &p) {
 // So many workgroups as there are compute units is what counts: 12 weight tiles instead of 16 for gate/up of 7B (1376 tiles in two ranges)
 // 48.5 -> 43.8 us at 54 rows, 61.3 -> 57.6 at 144, for QKV (768 in four) 32.5 -> 30.3 and 41.8 -> 40.2; 10 for down of 13B (320 in eight)
 // 39.4 -> 34.2 at 54; 8 for O and down of 7B: 17.0 -> 15.9, 33.6 -> 27.4.  11 and 12 row tiles where one row block then holds all rows and
-// the weights are read once: gate/up at 176 / 189 rows 76.5 / 78.3 (unsplit, two row blocks) -> 65.3 / 69.0 (two blocks of 11 or 12 at 340 .. 376: 108 -> 119 .. 127, not taken;
-// nor five or seven waves of that height, nor QKV of 13B in three ranges: 1 .. 5 % slower, hence the surcharge).  189 prompt rows: splits of 2 .. 8, 2.01 -> 0.98 ms for
-// four layers; from 1535 rows on nothing is split.
+// the weights are read once: gate/up of 7B at 176 / 189 rows 76.5 / 78.3 (unsplit, two row blocks) -> 65.3 / 69.5, the one matrix of 7B, 13B and d 512 whose prompt passes
+// take them; steps of 161 .. 192 rows, whose ranges are the matrix's own, do in most: at 161 / 177 rows QKV of 7B 50.4 / 51.4 -> 43.6 / 45.7, of 13B 64.4 / 65.5 ->
+// 58.2 / 61.5, of d 2048 26.8 / 27.0 -> 25.2 / 26.3, down of 13B 60.0 / 61.2 -> 56.6 / 60.4, of d 6144 81 / 84 -> 69 / 72 (O of 13B 34.9 / 35.6 -> 33.4 / 35.7).  Not
+// two blocks of 11 or 12 (340 .. 376 rows: 108 -> 119 .. 127), nor five or seven waves of that height, nor prompts' QKV of 13B in three ranges: 1 .. 5 % slower, hence the
+// surcharge.  189 prompt rows: splits of 2 .. 8, 2.01 -> 0.98 ms for four layers; from 1535 rows on nothing is split.
 struct PanelCut { int rt, nw, at; double us; };
 static PanelCut panel_cut(const GemmPlan &p, int rows, int ns) {
     const int row_tiles = (rows + 15) / 16, turns = (p.KSp + PANEL_TURN - 1) / PANEL_TURN;

@@ -162,7 +162,7 @@ static int check_cfg(const llma_model_cfg *g) {
     if (g->dtype == LLMA_DTYPE_BF16) {
         if (g->d_model % 32 || g->d_ffn % 32 || g->vocab % 16)
             return fail(nullptr, LLMA_E_INVAL, "bf16 needs d_model %% 32 == 0, d_ffn %% 32 == 0, vocab %% 16 == 0");
-        if (g->d_model > 1 << 23 || g->d_ffn > 1 << 23)       // 32-bit offsets inside a row block's activations (160 rows x 2^23 x 2 bytes)
+        if (g->d_model > 1 << 23 || g->d_ffn > 1 << 23)       // 32-bit offsets inside a row block's activations (192 rows x 2^23 x 2 bytes; the block GEMM takes up to 2^21 columns)
             return fail(nullptr, LLMA_E_INVAL, "bf16 needs d_model and d_ffn <= 2^23");
         if (g->head_dim != 64 && g->head_dim != 128) return fail(nullptr, LLMA_E_INVAL, "bf16 needs head_dim 64 or 128");
     } else if (g->dtype == LLMA_DTYPE_F32) {
